@@ -169,13 +169,22 @@ struct StackIO {
     const SharedMap *shared;    // decoded-share step: ragged units (see model.h), else nullptr
 };
 
+// what the kernel in front of a fused norm leaves for it, and what the GEMM behind it reads (m_tiles row tiles)
+NormOut norm_out(const Model &m, char *base, const Plan &pl, const float *gain, int m_tiles) {
+    const int span = ssq_span(m_tiles);
+    return NormOut{(u16 *)(base + pl.xa), (float *)(base + pl.ssq), gain, m.cfg.d_model / span, m.counters, span};
+}
+NormIn norm_in(const Model &m, char *base, const Plan &pl, int m_tiles) {
+    return NormIn{(float *)(base + pl.ssq), m.cfg.d_model / ssq_span(m_tiles), m.cfg.rms_eps};
+}
+
 Workspace workspace(const Model &m, char *base, const Plan &pl) {
     return Workspace{(float *)(base + pl.part), pl.part_bytes, m.ksplit_reduce ? m.counters + 1024 : nullptr};
 }
 
 int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackIO &io, hipStream_t s) {
     const odb_config &cfg = m.cfg;
-    float *h = (float *)(base + pl.h), *ssq = (float *)(base + pl.ssq);
+    float *h = (float *)(base + pl.h);
     u16 *xa = (u16 *)(base + pl.xa), *q = (u16 *)(base + pl.q), *kf = (u16 *)(base + pl.kf),
         *vf = (u16 *)(base + pl.vf), *ao = (u16 *)(base + pl.ao), *act = (u16 *)(base + pl.act);
     const int d = cfg.d_model, H = cfg.n_heads, dh = cfg.head_dim, F = cfg.d_ff;
@@ -186,10 +195,9 @@ int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackI
     const size_t spec_off = sm ? (size_t)sm->batch * H * ru(sm->bp, 32) * dh : 0;
     const size_t seq_elems = (size_t)H * c.lmax32 * dh;
     const int fresh32 = ru(io.rm.rpu_pad, 32);
-    const int n_ssq = d / 16;
     const Workspace ws = workspace(m, base, pl);
     unsigned *status = m.counters;
-    const NormIn ni = io.fused_norm ? NormIn{ssq, n_ssq, cfg.rms_eps} : NormIn{nullptr, 0, 0.f};
+    const NormIn ni = io.fused_norm ? norm_in(m, base, pl, mt) : NormIn{nullptr, 0, 0.f};
 
     for (int l = 0; l < cfg.n_layers; l++) {
         LayerPtrs w = layer_ptrs(m, l);
@@ -246,8 +254,8 @@ int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackI
         }
         // the residual epilogues prepare the norm that follows them
         const float *g_after_mlp = l + 1 < cfg.n_layers ? m.g1 + (size_t)(l + 1) * d : m.gf;
-        NormOut no_attn = io.fused_norm ? NormOut{xa, ssq, w.g2, n_ssq, status} : NormOut{nullptr, nullptr, nullptr, 0, nullptr};
-        NormOut no_mlp = io.fused_norm ? NormOut{xa, ssq, g_after_mlp, n_ssq, status} : NormOut{nullptr, nullptr, nullptr, 0, nullptr};
+        NormOut no_attn = io.fused_norm ? norm_out(m, base, pl, w.g2, mt) : NormOut{};
+        NormOut no_mlp = io.fused_norm ? norm_out(m, base, pl, g_after_mlp, mt) : NormOut{};
         {
             ProfScope ps(m, ODB_K_GEMM_O, s);
             launch_gemm_resid(ao, w.o, GemmShape{mt, d / 16, d / 32}, h, d, no_attn, ws, s);
@@ -284,7 +292,7 @@ int run_head(Model &m, char *base, const Plan &pl, RowMap rm, int skip, bool fus
         lm_mt = rm.units * rm.rpu_pad / 16;
         rpu_pad = rm.rpu_pad;
         valid = rm.valid;
-        ni = NormIn{(float *)(base + pl.ssq), cfg.d_model / 16, cfg.rms_eps};
+        ni = norm_in(m, base, pl, lm_mt);
     } else {
         lm_mt = (rows + 15) / 16;
         rpu_pad = valid = rpu_out;
@@ -324,8 +332,7 @@ int prefill_impl(odb_model *mh, odb_cache *ch, const int32_t *tokens, int L, int
     RowMap rm{c.batch, lp, L};
     c.length = L;
     char *base = (char *)m.scratch;
-    launch_embed(m, tokens, rm, (float *)(base + pl.h),
-                 NormOut{(u16 *)(base + pl.xa), (float *)(base + pl.ssq), m.g1, m.cfg.d_model / 16, m.counters}, s);
+    launch_embed(m, tokens, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), s);
     StackIO io{rm, 0, true, 0, 0, 0, 1, true};
     rc = run_stack(m, c, base, pl, io, s);
     if (rc) return rc;
@@ -381,8 +388,7 @@ int step_impl(odb_model *mh, const odb_cache *ch, const int32_t *drafts, int blo
         base = (char *)m.scratch;
     }
     RowMap rm{units, bp, b};
-    launch_embed(m, drafts, rm, (float *)(base + pl.h),
-                 NormOut{(u16 *)(base + pl.xa), (float *)(base + pl.ssq), m.g1, cfg.d_model / 16, m.counters}, s);
+    launch_embed(m, drafts, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), s);
     if (b % 32)   // slots of padded keys must hold finite values: they meet zero probabilities in the P*V product
         launch_fill_f32((float *)(base + pl.vf), 0.f, (size_t)units * bp32 * cfg.d_model / 2, s);
     StackIO io{rm, block_off, false, block_off, block_off + b, b, S, true};
@@ -666,7 +672,7 @@ static int step_shared_impl(odb_model *mh, const odb_cache *ch, const int32_t *d
     launch_shared_setup(drafts, sm, block_off, cfg.mask_id, n_masked, conf, argmax, unmask, m.counters, s);
     // rows are embedded through the token-per-row table: every row is its own unit of one
     launch_embed(m, sm.rowtok, RowMap{rows_pad, 1, 1}, (float *)(base + pl.h),
-                 NormOut{(u16 *)(base + pl.xa), (float *)(base + pl.ssq), m.g1, cfg.d_model / 16, m.counters}, s);
+                 norm_out(m, base, pl, m.g1, rows_pad / 16), s);
     // slots of padded keys must hold finite values: they meet zero probabilities in the P*V product
     launch_fill_f32((float *)(base + pl.vf), 0.f, (size_t)fresh_rows * cfg.d_model / 2, s);
     RowMap rm{c.batch, sm.bp, b};
@@ -676,7 +682,7 @@ static int step_shared_impl(odb_model *mh, const odb_cache *ch, const int32_t *d
     // final norm (fused) + LM head on all rows, then the per-unit finish
     u16 *xa = (u16 *)(base + pl.xa);
     const Workspace ws = workspace(m, base, pl);
-    const NormIn ni{(float *)(base + pl.ssq), cfg.d_model / 16, cfg.rms_eps};
+    const NormIn ni = norm_in(m, base, pl, rows_pad / 16);
     const GemmShape sh{rows_pad / 16, cfg.vocab / 16, cfg.d_model / 32};
     if (logits) {
         launch_gemm_store(xa, m.w[PK_LM], sh, ni, logits, 1, rows_pad, rows_pad, cfg.vocab, ws, s);

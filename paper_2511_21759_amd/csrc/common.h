@@ -68,6 +68,18 @@ __device__ inline uint32_t pack2_inrange(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, f16x2_t));
 }
 
+// Four operand elements, saturating (a NaN becomes -65504), round to nearest even: four clamps and two packed conversions.
+__device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
+    uint2 v;
+    v.x = pack2_inrange(__builtin_amdgcn_fmed3f(a, -65504.f, 65504.f), __builtin_amdgcn_fmed3f(b, -65504.f, 65504.f));
+    v.y = pack2_inrange(__builtin_amdgcn_fmed3f(c, -65504.f, 65504.f), __builtin_amdgcn_fmed3f(d, -65504.f, 65504.f));
+    return v;
+}
+// The test of note_saturation without its branch, for epilogues that collect it over their tiles and report once.
+__device__ __forceinline__ bool out_of_f16(float a, float b, float c, float d) {
+    return !(fmaxf(fmaxf(fabsf(a), fabsf(b)), fmaxf(fabsf(c), fabsf(d))) <= 65504.f);
+}
+
 __device__ inline frag_t ld_frag(const u16 *p) {
     return *reinterpret_cast<const frag_t *>(p);
 }

@@ -146,11 +146,11 @@ static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
     g.n_blocks = (sh.N_tiles + 4 * WN - 1) / (4 * WN);
     static std::once_flag attr_once;        // once per instantiation: the ring needs more than the default 64 KiB
     std::call_once(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_big_kernel<WN, Epi, 8, MBT>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, big_smem_bytes(WN));
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_big_kernel<WN, Epi, MBT>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, big_smem_bytes(WN, MBT));
     });
     dim3 grid(8 * g.m_blocks * ((g.n_blocks + 7) / 8));
-    gemm_big_kernel<WN, Epi, 8, MBT><<<grid, 64 * 8, big_smem_bytes(WN), s>>>(g, e);
+    gemm_big_kernel<WN, Epi, MBT><<<grid, 512, big_smem_bytes(WN, MBT), s>>>(g, e);
 }
 
 // Block shape for the LDS-ring kernel - MBT 16-row tiles by 64 * WN columns - or wn = 0 when the tile kernel
@@ -164,13 +164,14 @@ static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
 // (256 blocks of 128 x 192 instead of 192 of 256 x 128: 83 -> 69 us), every wide projection at 640 rows (five row
 // blocks that fit exactly: refresh 14.7 -> 13.0 ms), the 256-row step (7.6 -> 7.2 ms).
 struct BigChoice { int mbt, wn; };
-static BigChoice big_choice(GemmShape sh) {
+static BigChoice big_choice(GemmShape sh, bool may_192 = true) {
     BigChoice best{16, 0};
     if (sh.M_tiles < 12 || sh.N_tiles < 32) return best;     // (192 rows fill three quarters of a 256-row block)
     const double rel16[5] = {0, 0, 0.68, 0.87, 1.0}, rel8[5] = {0, 0, 0.46, 0.60, 0.66};
     double best_cost = 0;
     for (int mbt = 16; mbt >= 8; mbt -= 8)
         for (int wn = 4; wn >= 2; wn--) {
+            if (wn == 3 && !may_192) continue;
             const int blocks = ((sh.M_tiles + mbt - 1) / mbt) * ((sh.N_tiles + 4 * wn - 1) / (4 * wn));
             const int rounds = (blocks + kStreamWGs - 1) / kStreamWGs;
             const double useful = (sh.M_tiles / (double)mbt) * (sh.N_tiles / (4.0 * wn)) / ((double)rounds * kStreamWGs);
@@ -183,24 +184,25 @@ static BigChoice big_choice(GemmShape sh) {
         }
     return best;
 }
-static int big_width(GemmShape sh) { return big_choice(sh).wn; }
-static bool use_big(GemmShape sh) { return big_width(sh) != 0; }
+static bool use_big(GemmShape sh, bool may_192 = true) { return big_choice(sh, may_192).wn != 0; }
 
 template <class Epi>
 static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
-    const BigChoice c = big_choice(sh);
-    if (c.mbt == 8) {
-        switch (c.wn) {
-            case 2: launch_big_wn<2, Epi, 8>(a, w, sh, ni, e, s); break;
-            case 3: launch_big_wn<3, Epi, 8>(a, w, sh, ni, e, s); break;
-            default: launch_big_wn<4, Epi, 8>(a, w, sh, ni, e, s); break;
+    constexpr bool may_192 = !is_resid<Epi>::value;
+    const BigChoice c = big_choice(sh, may_192);
+    if constexpr (may_192) {
+        if (c.wn == 3) {
+            if (c.mbt == 8) launch_big_wn<3, Epi, 8>(a, w, sh, ni, e, s);
+            else launch_big_wn<3, Epi, 16>(a, w, sh, ni, e, s);
+            return;
         }
-        return;
     }
-    switch (c.wn) {
-        case 2: launch_big_wn<2>(a, w, sh, ni, e, s); break;
-        case 3: launch_big_wn<3>(a, w, sh, ni, e, s); break;
-        default: launch_big_wn<4>(a, w, sh, ni, e, s); break;
+    if (c.wn == 2) {
+        if (c.mbt == 8) launch_big_wn<2, Epi, 8>(a, w, sh, ni, e, s);
+        else launch_big_wn<2, Epi, 16>(a, w, sh, ni, e, s);
+    } else {
+        if (c.mbt == 8) launch_big_wn<4, Epi, 8>(a, w, sh, ni, e, s);
+        else launch_big_wn<4, Epi, 16>(a, w, sh, ni, e, s);
     }
 }
 
@@ -236,7 +238,8 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
     else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
     // (128-row blocks only for the O projection: at 1024 rows 256 blocks of 128 x 128 take 57 us against 64 us for the
     // tile kernel and its reduction pass; the down projection, three times as long in K, measured 4 % slower that way)
-    else if (use_big(sh) && (big_choice(sh).mbt == 16 || sh.K_tiles <= sh.N_tiles))
+    // (no 192-column blocks here: N is a multiple of 256, and the sums of squares are left per 64 columns)
+    else if (use_big(sh, false) && (big_choice(sh, false).mbt == 16 || sh.K_tiles <= sh.N_tiles))
         launch_big(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
     else launch_tile(a, w, sh, NormIn{nullptr, 0, 0.f}, e, ws, true, s);
 }
@@ -265,7 +268,7 @@ static int lm_ng(int n_tiles, int m_tiles) {
 // Beyond 128 rows the LM head of a long vocabulary always runs on the LDS-ring kernel, 256 columns wide where no other width is chosen
 // (129..191 rows leave part of a 256-row block empty, and still measure 283 us against 427 us on the tile kernel:
 // the vocabulary is long enough to be bound by the weight stream either way)
-static int lm_big_width(GemmShape sh) { const int wn = big_width(sh); return wn || sh.N_tiles < 32 ? wn : 4; }
+static int lm_big_width(GemmShape sh) { const int wn = big_choice(sh).wn; return wn || sh.N_tiles < 32 ? wn : 4; }
 // From 33 to 128 rows the LM head runs on the tile kernel with four n-tiles per wave (see launch_gemm_lmstats)
 constexpr int kLmTileNGW = 4;
 static bool lm_tile(int m_tiles) { return m_tiles > 2 && m_tiles <= 8; }

@@ -4,12 +4,9 @@
 //
 // A workgroup of eight waves computes a 256 x (64 WN) block of C over all of K, WN = 4, 3 or 2 (256, 192 or
 // 128 columns: the narrower blocks exist for shapes whose count of 256-wide blocks fills the compute units
-// badly), or with MBT = 8 a 128 x (64 WN) block (each wave half as many row tiles; the description below is
-// for 256 rows).  Per k-tile it needs sixteen 1 KiB tiles of A and 4 WN of W; they are copied from global memory straight into LDS
-// (global_load ... lds, no registers in between) into a ring of four stages, three k-tiles ahead of
-// the MFMAs, so one barrier per k-tile is the only synchronisation.  The waves form a 2 x 4 grid,
-// each owning 8 x WN output tiles: per k-tile a wave reads 8 + WN operand tiles from LDS for 8 WN MFMAs,
-// one k-tile ahead into a second register set, so LDS traffic and MFMAs overlap within a wave.
+// badly), or with MBT = 8 a 128 x (64 WN) block (each wave half as many row tiles).  Per k-tile it needs MBT 1 KiB
+// tiles of A and 4 WN of W; they are copied from global memory straight into LDS (global_load ... lds, no registers in
+// between) into a ring of stages.  The waves form a 2 x 4 grid, each owning MBT/2 x WN output tiles.
 // Operand bytes per flop are half those of the 128-row tile kernel, which is what matters here:
 // a re-read that misses the 4 MiB L2 of an XCD is served at HBM-like bandwidth (about 7 TB/s measured
 // on MI355X, against 22 TB/s for L2 hits), so the ids of the workgroups are also mapped to blocks
@@ -20,11 +17,16 @@
 
 namespace odb {
 
-// ring stages for a block 64 * WN columns wide (16 + 4 WN KiB of a 32 KiB slot per stage).  Four for every
-// width: three and five measured within 3 % of it on the same GPU (differences between GPUs of the pool are larger).
-constexpr int big_stages(int) { return 4; }
-constexpr int big_stage_bytes(int) { return 32 * 1024; }       // every width uses 32 KiB slots (narrower slots measured slower)
-constexpr int big_smem_bytes(int wn) { return big_stages(wn) * big_stage_bytes(wn) + 8 * 1024 + 256 * 4; }   // ring, per-wave scratch, row scales
+// k-tiles per stage and stages in the ring: one barrier interval covers a stage.  A 256-row block has 24 or 32 MFMAs per
+// wave and k-tile, enough to hide the operand reads of the other group of waves; a 128-row block has 8 to 16, so its
+// stages are two k-tiles deep (measured on the loop alone at K = 4096: 128 x 128 blocks 43.3 -> 37.1 us at 1024 x 4096,
+// 128 x 192 blocks 56.1 -> 52.4 us at 256 x 24576; 256 x 256 blocks equal).
+constexpr int big_kp(int mbt) { return mbt == 8 ? 2 : 1; }
+constexpr int big_stages(int mbt) { return mbt == 8 ? 3 : 4; }
+constexpr int big_stage_tiles(int wn, int mbt) { return big_kp(mbt) * (mbt + 4 * wn); }
+constexpr int big_smem_bytes(int wn, int mbt) { return big_stages(mbt) * big_stage_tiles(wn, mbt) * 1024 + 256 * 4; }   // ring, row scales
+// per-wave scratch of the epilogues, in the ring's place once the k-loop is over
+constexpr int kBigScratch = 4096;
 
 struct BigArgs {
     const u16 *A, *W;
@@ -35,24 +37,189 @@ struct BigArgs {
     float eps, inv_d;
 };
 
-// NWV = 4 (four waves of 128 x 32 WN columns each, accumulators in the AGPR half of the register file) halves the
-// LDS reads per MFMA but measured 20 % slower than eight waves on MI355X; only NWV = 8 is instantiated.
+// ---- epilogues of a wave's MW x WT output tiles ------------------------------------------------------------------
+// A wave's tiles are finished row of tiles by row of tiles; what a row reads from global memory (the residual, the RoPE
+// table) is requested while the row before it is worked on, index arithmetic is done once per row and column of tiles,
+// and values beyond the binary16 range are collected and reported once.  (One tile at a time, each waiting for its own
+// loads, this tail was 15 of the 103 us of the QKV projection at 1024 rows.)
+// mtw, ntw: the wave's first row tile and n-tile; rstd: row scales of the wave's rows; scr: kBigScratch bytes of LDS.
+template <int MW, int WT>
+__device__ __forceinline__ void big_epilogue(const EpiQKV &e, f32x4 (&acc)[MW][WT], int mtw, int ntw, const BigArgs &g,
+                                             const float *rstd, char *scr, int lane) {
+    const QkvOut &o = e.o;
+    const int mi = lane & 15, gq = lane >> 4;
+    int sec[WT], hd[WT], p0[WT];
+#pragma unroll
+    for (int j = 0; j < WT; j++) {
+        const int nt = ntw + j < g.NT ? ntw + j : g.NT - 1;
+        sec[j] = o.fd_d.quot(nt);
+        const int rt = nt - sec[j] * (o.d >> 4);
+        hd[j] = o.fd_dh.quot(rt);
+        p0[j] = (rt - hd[j] * (o.dh >> 4)) * 16;
+    }
+    struct Row { int unit, tu; bool spec; f32x4 cs[WT]; };         // cs: (cos, sin) of the lane's two channel pairs
+    auto fetch = [&](int m) __attribute__((always_inline)) {
+        Row r;
+        const int mt = mtw + m < g.MT_total ? mtw + m : g.MT_total - 1;
+        r.spec = o.split_tile > 0 && mt >= o.split_tile;
+        const int tpu = pick(r.spec, o.tiles_per_unit_b, o.tiles_per_unit), mtu = pick(r.spec, mt - o.split_tile, mt);
+        r.unit = pick(r.spec, o.fd_tpu_b, o.fd_tpu).quot(mtu);
+        r.tu = mtu - r.unit * tpu;
+        const int pos = o.rowpos ? o.rowpos[mt * 16 + mi] : o.pos_off + r.tu * 16 + mi;
+        const float *tab = o.rope + (size_t)pos * o.dh + 4 * gq;
+#pragma unroll
+        for (int j = 0; j < WT; j++) r.cs[j] = sec[j] < 2 ? *reinterpret_cast<const f32x4 *>(tab + p0[j]) : f32x4{0.f, 0.f, 0.f, 0.f};
+        return r;
+    };
+    bool bad = false;
+    Row next = fetch(0);
+#pragma unroll
+    for (int m = 0; m < MW; m++) {
+        const Row r = next;
+        if (m + 1 < MW) next = fetch(m + 1);
+        const int mt = mtw + m;
+        if (mt >= g.MT_total) break;
+        const float rs = rstd[m * 16 + mi];
+        const f32x4 rs4 = *reinterpret_cast<const f32x4 *>(rstd + m * 16 + 4 * gq);
+        u16 *kdst = pick(r.spec, o.k_b, o.k) + r.unit * pick(r.spec, o.k_b_unit_stride, o.k_unit_stride) + (size_t)r.tu * (o.dh / 32) * kTileElems;
+        u16 *vdst = pick(r.spec, o.v_b, o.v) + r.unit * pick(r.spec, o.v_b_unit_stride, o.v_unit_stride) +
+                    (size_t)(r.tu >> 1) * (o.dh / 16) * kTileElems + lane * 8 + 4 * (r.tu & 1);
+        const size_t khs = pick(r.spec, o.k_b_head_stride, o.k_head_stride), vhs = pick(r.spec, o.v_b_head_stride, o.v_head_stride);
+        // V goes out transposed: lane (gq, ni) takes rows 4 gq .. 4 gq + 3 of column ni, through the wave's scratch
+        f32x4 (*tr)[64] = reinterpret_cast<f32x4 (*)[64]>(scr);
+#pragma unroll
+        for (int j = 0; j < WT; j++)
+            if (sec[j] == 2) tr[j][lane] = acc[m][j];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // stores before the transposed reads
+#pragma unroll
+        for (int j = 0; j < WT; j++) {
+            if (ntw + j >= g.NT) break;
+            if (sec[j] < 2) {
+                const f32x4 c = acc[m][j] * rs, cs = r.cs[j];
+                const float y0 = c[0] * cs[0] - c[1] * cs[1], y1 = c[1] * cs[0] + c[0] * cs[1];
+                const float y2 = c[2] * cs[2] - c[3] * cs[3], y3 = c[3] * cs[2] + c[2] * cs[3];
+                u16 *dst = (sec[j] == 0 ? o.q + ((size_t)hd[j] * e.mt_total + mt) * (o.dh / 32) * kTileElems : kdst + hd[j] * khs) +
+                           (p0[j] >> 5) * kTileElems;
+                const int kk = (p0[j] & 16) + 4 * gq;
+                bad |= out_of_f16(y0, y1, y2, y3);
+                st_f16x4(dst + ((kk >> 3) * 16 + mi) * 8 + (kk & 7), y0, y1, y2, y3);
+            } else {
+                const float *base = reinterpret_cast<const float *>(&tr[j][0]) + ((mi >> 2) * 16 + 4 * gq) * 4 + (mi & 3);
+                const float y0 = base[0] * rs4[0], y1 = base[4] * rs4[1], y2 = base[8] * rs4[2], y3 = base[12] * rs4[3];
+                bad |= out_of_f16(y0, y1, y2, y3);
+                st_f16x4(vdst + hd[j] * vhs + (p0[j] >> 4) * kTileElems, y0, y1, y2, y3);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // reads before the next row's stores
+    }
+    if (bad && o.status) atomicOr(o.status, kStatusSaturated);
+}
+
+template <int MW, int WT>
+__device__ __forceinline__ void big_epilogue(const EpiSwiGLU &e, f32x4 (&acc)[MW][WT], int mtw, int ntw, const BigArgs &g,
+                                             const float *rstd, char *, int lane) {
+    const int mi = lane & 15, gq = lane >> 4;
+    u16 *dst[WT];
+#pragma unroll
+    for (int j = 0; j < WT; j++) {
+        const int ch = (ntw + j) * 8 + 2 * gq, kk = ch & 31;      // channel of the lane's first (gate, up) pair
+        dst[j] = e.act + ((size_t)((ntw + j) >> 2) * e.mt_total + mtw) * kTileElems + ((kk >> 3) * 16 + mi) * 8 + (kk & 7);
+    }
+    bool bad = false;
+#pragma unroll
+    for (int m = 0; m < MW; m++) {
+        if (mtw + m >= g.MT_total) break;
+        const float rs = rstd[m * 16 + mi];
+#pragma unroll
+        for (int j = 0; j < WT; j++) {
+            if (ntw + j >= g.NT) break;
+            const f32x4 c = acc[m][j] * rs;
+            const float y0 = EpiSwiGLU::act2(c[0], c[1]), y1 = EpiSwiGLU::act2(c[2], c[3]);
+            bad |= out_of_f16(y0, y1, 0.f, 0.f);
+            *reinterpret_cast<uint32_t *>(dst[j] + m * kTileElems) = pack4(y0, y1, 0.f, 0.f).x;
+        }
+    }
+    if (bad && e.status) atomicOr(e.status, kStatusSaturated);
+}
+
+// (N is a multiple of 256 here, and WN = 4 or 2: the wave's columns are one partial sum of squares, or half of one)
+template <int MW, int WT>
+__device__ __forceinline__ void big_epilogue(const EpiResid &e, f32x4 (&acc)[MW][WT], int mtw, int ntw, const BigArgs &g,
+                                             const float *, char *scr, int lane) {
+    const NormOut &no = e.no;
+    const int mi = lane & 15, gq = lane >> 4;
+    float *s_q = reinterpret_cast<float *>(scr);
+    f32x4 gn[WT], hv[WT];
+    float *hp = e.h + (size_t)(mtw * 16 + mi) * e.ld + ntw * 16 + 4 * gq;
+    u16 *xp[WT];
+#pragma unroll
+    for (int j = 0; j < WT; j++) {
+        gn[j] = no.hb ? *reinterpret_cast<const f32x4 *>(no.gain + (ntw + j) * 16 + 4 * gq) : f32x4{0.f, 0.f, 0.f, 0.f};
+        const int kk = ((ntw + j) & 1) * 16 + 4 * gq;
+        xp[j] = no.hb + ((size_t)((ntw + j) >> 1) * e.mt_total + mtw) * kTileElems + ((kk >> 3) * 16 + mi) * 8 + (kk & 7);
+    }
+    auto fetch = [&](int m) __attribute__((always_inline)) {
+        const int mt = mtw + m < g.MT_total ? mtw + m : g.MT_total - 1;
+        const float *p = e.h + (size_t)(mt * 16 + mi) * e.ld + ntw * 16 + 4 * gq;
+#pragma unroll
+        for (int j = 0; j < WT; j++) hv[j] = *reinterpret_cast<const f32x4 *>(p + j * 16);
+    };
+    bool bad = false;
+    fetch(0);
+#pragma unroll
+    for (int m = 0; m < MW; m++) {
+        f32x4 v[WT];
+#pragma unroll
+        for (int j = 0; j < WT; j++) v[j] = hv[j] + acc[m][j];
+        if (mtw + m >= g.MT_total) break;
+        if (m + 1 < MW) fetch(m + 1);
+        float q = 0.f;
+#pragma unroll
+        for (int j = 0; j < WT; j++) {
+            *reinterpret_cast<f32x4 *>(hp + (size_t)m * 16 * e.ld + j * 16) = v[j];
+            if (no.hb) {
+                const f32x4 y = v[j] * gn[j];
+                bad |= out_of_f16(y[0], y[1], y[2], y[3]);
+                st_f16x4(xp[j] + m * kTileElems, y[0], y[1], y[2], y[3]);
+                q += v[j][0] * v[j][0] + v[j][1] * v[j][1] + v[j][2] * v[j][2] + v[j][3] * v[j][3];
+            }
+        }
+        if (no.hb) {
+            q = EpiResid::over_row(q);
+            if (lane < 16) {
+                if constexpr (WT == 4) no.ssq[(size_t)((mtw + m) * 16 + lane) * no.n_ssq + (ntw >> 2)] = q;
+                else s_q[m * 16 + lane] = q;
+            }
+        }
+    }
+    if (bad && no.status) atomicOr(no.status, kStatusSaturated);
+}
+
+template <int MW, int WT>
+__device__ __forceinline__ void big_epilogue(const EpiStore &e, f32x4 (&acc)[MW][WT], int mtw, int ntw, const BigArgs &g,
+                                             const float *rstd, char *, int lane) {
+#pragma unroll
+    for (int m = 0; m < MW; m++)
+#pragma unroll
+        for (int j = 0; j < WT; j++)
+            if (mtw + m < g.MT_total && ntw + j < g.NT) e(mtw + m, ntw + j, acc[m][j] * rstd[m * 16 + (lane & 15)], lane, 0);
+}
+
 // MBT: 16-row tiles per block, 16 (256 rows) or 8 (128 rows: twice the blocks for shapes that leave compute
 // units idle otherwise; per flop it needs 1.4 x the operand bytes of the 256-row block).
-template <int WN, class Epi, int NWV = 8, int MBT = 16>
-__global__ __launch_bounds__(64 * NWV) void gemm_big_kernel(BigArgs g, Epi epi) {
+template <int WN, class Epi, int MBT = 16>
+__global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
     static_assert(WN >= 2 && WN <= 4, "block width in units of 64 columns");
-    static_assert(NWV == 8 || NWV == 4, "waves per workgroup");
     static_assert(MBT == 16 || MBT == 8, "rows per block");
-    constexpr int CW = NWV / 2;                 // waves side by side; two rows of them
-    constexpr int WT = 4 * WN / CW;             // 16-column tiles per wave
+    static_assert(!is_resid<Epi>::value || WN != 3, "partial sums of squares cover 64 columns");
+    constexpr int CW = 4;                       // waves side by side; two rows of them
+    constexpr int WT = WN;                      // 16-column tiles per wave
     constexpr int MW = MBT / 2;                 // 16-row tiles per wave
+    constexpr int NS = big_stages(MBT), KP = big_kp(MBT), TK = MBT + 4 * WN, ST = KP * TK;     // tiles per k-tile, per stage
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int NS = big_stages(WN);
-    typedef frag_t stage_t[32][64];                                          // tiles 0..15: A, 16..16+4*WN-1: W
+    typedef frag_t stage_t[ST][64];                                          // per k-tile: MBT tiles of A, then 4 WN of W
     stage_t *ring = reinterpret_cast<stage_t *>(smem);
-    f32x4 (*scr)[64] = reinterpret_cast<f32x4 (*)[64]>(smem + NS * big_stage_bytes(WN));   // [waves][64]
-    float *s_rstd = reinterpret_cast<float *>(smem + NS * big_stage_bytes(WN) + 8 * 1024);
+    float *s_rstd = reinterpret_cast<float *>(smem + NS * ST * 1024);
 
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave index, scalar
     const int wm = w / CW, wn = w % CW;                  // position of the wave in the 2 x CW grid
@@ -64,11 +231,11 @@ __global__ __launch_bounds__(64 * NWV) void gemm_big_kernel(BigArgs g, Epi epi) 
     if (nb >= g.n_blocks) return;
     const int mt0 = mb * MBT, nt0 = nb * 4 * WN;
 
-    // the first half of the waves copies the MBT tiles of A into every stage, the second half the 4 WN of W
+    // the first half of the waves copies the MBT tiles of A of every k-tile, the second half the 4 WN of W
     constexpr int PA = MBT / CW, PW = 4 * WN / CW, PMAX = PA > PW ? PA : PW;
     const u16 *src[PMAX];
     size_t kstride;
-    const int per = w < CW ? PA : PW, slot0 = w < CW ? PA * w : 16 + (w - CW) * PW;
+    const int per = w < CW ? PA : PW, slot0 = w < CW ? PA * w : MBT + (w - CW) * PW;
     if (w < CW) {
 #pragma unroll
         for (int i = 0; i < PMAX; i++) {
@@ -88,63 +255,42 @@ __global__ __launch_bounds__(64 * NWV) void gemm_big_kernel(BigArgs g, Epi epi) 
     }
     // (the tile addresses are wave-uniform, so they live in scalar registers; a lane adds its 16 bytes)
     const unsigned lane_off = lane * 16;
-    auto issue = [&](int slot, int k) __attribute__((always_inline)) {
+    auto issue = [&](int slot, int s) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < PMAX; i++)
-            if (i < per)
-                __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(
-                                                     reinterpret_cast<const char *>(src[i] + (size_t)k * kstride) + lane_off),
-                                                 (__attribute__((address_space(3))) void *)(&ring[slot][slot0 + i][0]),
-                                                 16, 0, 0);
+        for (int q = 0; q < KP; q++)
+#pragma unroll
+            for (int i = 0; i < PMAX; i++)
+                if (i < per)
+                    __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(
+                                                         reinterpret_cast<const char *>(src[i] + (size_t)(s * KP + q) * kstride) + lane_off),
+                                                     (__attribute__((address_space(3))) void *)(&ring[slot][q * TK + slot0 + i][0]),
+                                                     16, 0, 0);
     };
 
-    const int nk = g.KT;
+    const int ns = g.KT / KP;                   // stages (K is a multiple of 256: k-tiles come in eights)
 #pragma unroll
     for (int j = 0; j < NS - 1; j++)
-        if (j < nk) issue(j, j);
+        if (j < ns) issue(j, j);
 
-    // Row scales of the fused RMSNorm, 256 / NWV rows per wave in rounds of 16.  A row's partial sums (up to 256)
-    // are one 16-byte load per lane, the loads of 16 rows are in flight together (behind the ring's first
-    // stages), and the 64 lane-sums of each row are added through the still unused last slot of the
-    // ring: written rotated by the row number, so that the transposed gather is free of bank conflicts.
-    if (g.ssq) {
-        // (32 KiB from the start of the last slot: for the narrower blocks this runs on into the per-wave
-        // scratch behind the ring, which is not in use yet, and ends before the row scales)
-        static_assert(big_stage_bytes(WN) + 8 * 1024 >= NWV * 16 * 64 * 4, "room for the row-scale scratch");
-        constexpr int RW = MBT * 16 / NWV;      // rows per wave
-        float *tmp = reinterpret_cast<float *>(&ring[NS - 1][0][0]) + w * (16 * 64);
-        const int si = 4 * lane, sic = si < g.n_ssq - 4 ? si : g.n_ssq - 4;
-#pragma unroll
-        for (int half = 0; half < RW / 16; half++) {
-            f32x4 sv[16];
-            const float *rp[16];
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-                int row = mt0 * 16 + w * RW + half * 16 + r;
-                row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
-                rp[r] = g.ssq + (size_t)row * g.n_ssq;
-                sv[r] = *reinterpret_cast<const f32x4 *>(rp[r] + sic);
+    // row scales of the fused RMSNorm: two (256 rows) or four threads per row, behind the ring's first copies
+    {
+        constexpr int TR = 512 / (MBT * 16);
+        const int r = threadIdx.x / TR, part = threadIdx.x % TR;
+        float t = 1.f;
+        if (g.ssq) {
+            int row = mt0 * 16 + r;
+            row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
+            const float *p = g.ssq + (size_t)row * g.n_ssq;
+            t = 0.f;
+            for (int i = part * 4; i < g.n_ssq; i += TR * 4) {          // n_ssq is a multiple of 4
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(p + i);
+                t += (v[0] + v[1]) + (v[2] + v[3]);
             }
 #pragma unroll
-            for (int r = 0; r < 16; r++) {
-                float part = si < g.n_ssq ? (sv[r][0] + sv[r][1]) + (sv[r][2] + sv[r][3]) : 0.f;
-                for (int i0 = 256; i0 < g.n_ssq; i0 += 256) {       // rows wider than 4096 only
-                    const int i = i0 + si, ic = i < g.n_ssq - 4 ? i : g.n_ssq - 4;
-                    f32x4 v = *reinterpret_cast<const f32x4 *>(rp[r] + ic);
-                    part += i < g.n_ssq ? (v[0] + v[1]) + (v[2] + v[3]) : 0.f;
-                }
-                tmp[r * 64 + ((lane + r) & 63)] = part;
-            }
-            const int rr = lane & 15, p0 = (lane >> 4) * 16;
-            float t = 0.f;
-#pragma unroll
-            for (int u = 0; u < 16; u++) t += tmp[rr * 64 + ((p0 + u + rr) & 63)];
-            t += __shfl_xor(t, 16);
-            t += __shfl_xor(t, 32);
-            if (lane < 16) s_rstd[w * RW + half * 16 + lane] = 1.0f / sqrtf(t * g.inv_d + g.eps);
+            for (int o = 1; o < TR; o <<= 1) t += __shfl_xor(t, o);
+            t = 1.0f / sqrtf(t * g.inv_d + g.eps);
         }
-    } else {
-        for (int r = lane; r < MBT * 16 / NWV; r += 64) s_rstd[w * (MBT * 16 / NWV) + r] = 1.0f;
+        if (part == 0) s_rstd[r] = t;
     }
 
     f32x4 acc[MW][WT];
@@ -153,76 +299,53 @@ __global__ __launch_bounds__(64 * NWV) void gemm_big_kernel(BigArgs g, Epi epi) 
 #pragma unroll
         for (int j = 0; j < WT; j++) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Software pipeline over the k-tiles.  In iteration k a wave first fetches the operand tiles of stage
-    // k+1 from LDS into the second register set and then issues the MFMAs of stage k, so the LDS reads of
-    // all waves run under the MFMAs instead of in a phase of their own after each barrier.  Stage k+NS-1
-    // is requested from global memory in iteration k, into the slot whose tiles fed the MFMAs of k-1.
-    static_assert(NS >= 3 && (NS - 2) * PMAX <= 16, "slot arithmetic and counted waits below");
-    frag_t a[2][MW], b[2][WT];
-    auto fetch = [&](auto P, int k) __attribute__((always_inline)) {
-        constexpr int p = decltype(P)::value;
-        const stage_t &st = ring[k % NS];
-#pragma unroll
-        for (int j = 0; j < WT; j++) b[p][j] = st[16 + wn * WT + j][lane];
-#pragma unroll
-        for (int m = 0; m < MW; m++) a[p][m] = st[wm * MW + m][lane];
+    // Two groups of four waves (the two rows of the wave grid; waves w and w + 4 share a SIMD) work in opposite phases:
+    // while one issues the MFMAs of a stage, the other reads its operands of that stage (or the next) from LDS and
+    // requests the copies of a later one, and the barrier between two phases swaps them.  LDS reads, copies and MFMAs
+    // of different waves overlap; in one wave they do not: the same loop with reads of stage s + 1 spread between the
+    // MFMAs of stage s in every wave, all eight in step, took 366 us where this one takes 318 (gate/up at 2048 rows;
+    // the MFMAs alone take 220 us there, at the clock the chip holds under them).
+    // Phases: group 0 reads stage s in phase 2s and multiplies it in 2s + 1, group 1 one phase later.  Stage s + NS - 1
+    // goes into the slot of stage s - 1, whose last reads (group 1, phase 2s - 1) were complete before the barrier
+    // in front of phase 2s; its copies have landed when both groups have waited for them, before phase 2(s + NS - 1).
+    static_assert(NS >= 3, "slot arithmetic");
+    frag_t a[KP][MW], b[KP][WT];
+    auto wait_stage = [&](bool more) __attribute__((always_inline)) {       // all but the latest NS - 2 stages have landed
+        if (!more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else if (PA == PW || w < CW) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KP * PA * (NS - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KP * PW * (NS - 2)) : "memory");
     };
-    auto mfmas = [&](auto P) __attribute__((always_inline)) {
-        constexpr int p = decltype(P)::value;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the first stages have landed (and the row sums, behind them)
+    __syncthreads();
+    if (wm == 1) __builtin_amdgcn_s_barrier();
+    for (int s = 0, slot = 0; s < ns; s++) {
+        const stage_t &st = ring[slot];
 #pragma unroll
-        for (int m = 0; m < MW; m++)
+        for (int q = 0; q < KP; q++) {
 #pragma unroll
-            for (int j = 0; j < WT; j++) acc[m][j] = mfma16(b[p][j], a[p][m], acc[m][j]);
-    };
-    // a k-tile that has a successor
-    auto step = [&](auto P, int k) __attribute__((always_inline)) {
-        constexpr int p = decltype(P)::value;
-        // stage k+1 has landed once every wave's copies of it are done (those of stages k+2 .. k+NS-2 may be in flight)
-        if (k + NS - 2 <= nk - 1) {          // steady state: the copies of NS - 3 later stages stay in flight
-            if (PA == PW || w < CW) wait_vmcnt(PA * (NS - 3));
-            else wait_vmcnt(PW * (NS - 3));
-        } else {
-            wait_vmcnt(per * (nk - 1 - (k + 1)));
+            for (int j = 0; j < WT; j++) b[q][j] = st[q * TK + MBT + wn * WT + j][lane];
+#pragma unroll
+            for (int m = 0; m < MW; m++) a[q][m] = st[q * TK + wm * MW + m][lane];
         }
+        const bool more = s + NS - 1 < ns;
+        if (more) issue(slot == 0 ? NS - 1 : slot - 1, s + NS - 1);
+        slot = slot == NS - 1 ? 0 : slot + 1;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (wm == 1) wait_stage(more);
         __builtin_amdgcn_s_barrier();
-        if (k + NS - 1 < nk) issue((k + NS - 1) % NS, k + NS - 1);
-        if constexpr (WN == 4 && NWV == 8 && MBT == 16) {
-            // widest block: every register is taken, the reads of stage k+1 go ahead of the MFMAs of stage k
-            // (measured 5 % faster than the interleaved order, which needs more live registers)
-            fetch(std::integral_constant<int, 1 - p>{}, k + 1);
-            mfmas(P);
-        } else {
-            // The MFMAs of stage k come first in program order and the LDS reads of stage k+1 are spread
-            // between them: the wait for this stage's operands (read during the previous k-tile) then sits
-            // in front of the first MFMA, before any new read is issued, and the new reads complete under
-            // the MFMAs instead of being waited for ahead of them (2 % faster at 192 columns).
-            mfmas(P);
-            fetch(std::integral_constant<int, 1 - p>{}, k + 1);
-            constexpr int NR = MW + WT, NM = MW * WT, MPR = NM / NR;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < NR; i++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, MPR, 0);       // MPR MFMAs
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);         // one LDS read
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, NM - NR * MPR, 0);
-        }
-    };
-    // stage 0 has landed (everything issued so far has: the row-scale loads came after the ring's)
-    wait_vmcnt(g.ssq ? 0 : per * ((nk < NS - 1 ? nk : NS - 1) - 1));
-    __syncthreads();            // also orders the row-scale scratch before stage 3 reuses its slot
-    fetch(std::integral_constant<int, 0>{}, 0);
-    int k = 0;
-    for (; k + 2 <= nk - 1; k += 2) {      // (no branch around a step's MFMAs: the accumulators keep their registers)
-        step(std::integral_constant<int, 0>{}, k);
-        step(std::integral_constant<int, 1>{}, k + 1);
+        for (int q = 0; q < KP; q++)
+#pragma unroll
+            for (int m = 0; m < MW; m++)
+#pragma unroll
+                for (int j = 0; j < WT; j++) acc[m][j] = mfma16(b[q][j], a[q][m], acc[m][j]);
+        if (wm == 0) wait_stage(more);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
     }
-    if (k < nk - 1) {
-        step(std::integral_constant<int, 0>{}, k);
-        mfmas(std::integral_constant<int, 1>{});
-    } else {
-        mfmas(std::integral_constant<int, 0>{});
-    }
-    __syncthreads();            // the ring is reused below; also publishes s_rstd
+    if (wm == 0) __builtin_amdgcn_s_barrier();
+    __syncthreads();            // the ring is reused below
 
     if constexpr (is_row_stats<Epi>::value) {
         // softmax statistics per row over this workgroup's columns: lane-local, across the four lane
@@ -265,7 +388,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_big_kernel(BigArgs g, Epi epi) 
             }
         }
         __syncthreads();
-        for (int r = threadIdx.x; r < MBT * 16; r += 64 * NWV) {
+        for (int r = threadIdx.x; r < MBT * 16; r += 512) {
             const int row = mt0 * 16 + r;
             float rm = st_m[r], rs = st_s[r];
             int ra = st_a[r];
@@ -279,30 +402,18 @@ __global__ __launch_bounds__(64 * NWV) void gemm_big_kernel(BigArgs g, Epi epi) 
             }
         }
     } else {
-#pragma unroll
-        for (int m = 0; m < MW; m++)
-#pragma unroll
-            for (int j = 0; j < WT; j++) {
-                const int mt = mt0 + wm * MW + m, nt = nt0 + wn * WT + j;
-                if (mt < g.MT_total && nt < g.NT) {
-                    const float *rsd = s_rstd + (wm * MW + m) * 16;
-                    f32x4 c;
-                    if (!epi.transposed(nt)) {
-                        c = acc[m][j] * rsd[lane & 15];
-                    } else {
-                        // lane (g, ni) gets rows 4g..4g+3 of column ni: through this wave's LDS scratch
-                        const int ni = lane & 15, gq = lane >> 4;
-                        scr[w][lane] = acc[m][j];
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // store before the transposed reads
-                        const float *base = reinterpret_cast<const float *>(&scr[w][0]);
-#pragma unroll
-                        for (int r = 0; r < 4; r++)
-                            c[r] = base[((ni >> 2) * 16 + 4 * gq + r) * 4 + (ni & 3)] * rsd[4 * gq + r];
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // reads before the next tile's store
-                    }
-                    epi(mt, nt, c, lane, 0);
+        big_epilogue<MW, WT>(epi, acc, mt0 + wm * MW, nt0 + wn * WT, g, s_rstd + wm * MW * 16, smem + w * kBigScratch, lane);
+        if constexpr (is_resid<Epi>::value && WT == 2) {
+            if (epi.no.hb) {        // two waves side by side make one partial sum of 64 columns
+                __syncthreads();
+                for (int i = threadIdx.x; i < 2 * MBT * 16; i += 512) {
+                    const int r = i % (MBT * 16), c = i / (MBT * 16), row = mt0 * 16 + r, wr = r / (MW * 16), rr = r % (MW * 16);
+                    const float *q0 = reinterpret_cast<const float *>(smem + (wr * CW + 2 * c) * kBigScratch);
+                    const float *q1 = reinterpret_cast<const float *>(smem + (wr * CW + 2 * c + 1) * kBigScratch);
+                    if (row < g.MT_total * 16) epi.no.ssq[(size_t)row * epi.no.n_ssq + nb * 2 + c] = q0[rr] + q1[rr];
                 }
             }
+        }
     }
 }
 

@@ -242,12 +242,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
 // Default:    lane l holds C[row = 16*mt + (l&15)][col = 16*nt + 4*(l>>4) + r], r = 0..3.
 // Transposed: lane l holds C[row = 16*mt + 4*(l>>4) + r][col = 16*nt + (l&15)].
 
-__device__ inline void st_f16x4(u16 *p, float a, float b, float c, float d) {
-    uint2 v;
-    v.x = pack2(a, b);
-    v.y = pack2(c, d);
-    *reinterpret_cast<uint2 *>(p) = v;
-}
+__device__ inline void st_f16x4(u16 *p, float a, float b, float c, float d) { *reinterpret_cast<uint2 *>(p) = pack4(a, b, c, d); }
 
 // (by-value pick: `c ? x : y` on two struct members is an lvalue conditional, which the compiler turns into a
 // select of addresses and then parks the members on the stack)
@@ -316,22 +311,27 @@ struct EpiResid {
         return p;
     }
     __device__ void operator()(int mt, int nt, f32x4 c, int lane, int) const { apply(mt, nt, c, lane, preload(mt, nt, lane)); }
-    __device__ void apply(int mt, int nt, f32x4 c, int lane, const ResidPre &pre) const {
+    // h += c and the next norm's input for one output tile; returns the lane's sum of squares over its four columns
+    __device__ float put(int mt, int nt, f32x4 c, int lane, const ResidPre &pre) const {
         const int mi = lane & 15, g = lane >> 4, row = mt * 16 + mi, col = nt * 16 + 4 * g;
         float *p = h + (size_t)row * ld + col;
         f32x4 v = pre.hv + c;
         *reinterpret_cast<f32x4 *>(p) = v;
-        if (no.hb) {
-            const int kk = (nt & 1) * 16 + 4 * g;
-            const f32x4 y = v * pre.gn;
-            note_saturation(no.status, y[0], y[1], y[2], y[3]);
-            st_f16x4(no.hb + ((size_t)(nt >> 1) * mt_total + mt) * kTileElems + ((kk >> 3) * 16 + mi) * 8 + (kk & 7),
-                     y[0], y[1], y[2], y[3]);
-            float q = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-            q += __shfl_xor(q, 16);
-            q += __shfl_xor(q, 32);
-            if (g == 0) no.ssq[(size_t)row * no.n_ssq + nt] = q;
-        }
+        if (!no.hb) return 0.f;
+        const int kk = (nt & 1) * 16 + 4 * g;
+        const f32x4 y = v * pre.gn;
+        note_saturation(no.status, y[0], y[1], y[2], y[3]);
+        *reinterpret_cast<uint2 *>(no.hb + ((size_t)(nt >> 1) * mt_total + mt) * kTileElems + ((kk >> 3) * 16 + mi) * 8 + (kk & 7)) =
+            pack4(y[0], y[1], y[2], y[3]);
+        return v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    }
+    __device__ static float over_row(float q) {         // sum over the four lanes of a row
+        q += __shfl_xor(q, 16);
+        return q + __shfl_xor(q, 32);
+    }
+    __device__ void apply(int mt, int nt, f32x4 c, int lane, const ResidPre &pre) const {
+        const float q = over_row(put(mt, nt, c, lane, pre));
+        if (no.hb && lane < 16) no.ssq[(size_t)(mt * 16 + lane) * no.n_ssq + nt] = q;
     }
 };
 
@@ -345,13 +345,13 @@ struct EpiSwiGLU {
     unsigned *status;
     __device__ bool transposed(int) const { return false; }
     __device__ void finish(int, int, int, int) const {}
+    // silu(gate) * up with the hardware exponential and reciprocal (each good to 1 ulp; the result is rounded to
+    // binary16 next): the exact division and exponential are some forty instructions per pair in the kernel's tail
+    __device__ static float act2(float gate, float up) { return gate * __builtin_amdgcn_rcpf(1.0f + __expf(-gate)) * up; }
     __device__ void operator()(int mt, int nt, f32x4 c, int lane, int) const {
         const int mi = lane & 15, g = lane >> 4;
         const int j = nt * 8 + 2 * g;                         // channel of the first (gate, up) pair
-        // silu(gate) * up with the hardware exponential and reciprocal (each good to 1 ulp; the result is rounded to
-        // binary16 next): the exact division and exponential are some forty instructions per pair in the kernel's tail
-        float y0 = c[0] * __builtin_amdgcn_rcpf(1.0f + __expf(-c[0])) * c[1];
-        float y1 = c[2] * __builtin_amdgcn_rcpf(1.0f + __expf(-c[2])) * c[3];
+        const float y0 = act2(c[0], c[1]), y1 = act2(c[2], c[3]);
         const int kk = j & 31;
         note_saturation(status, y0, y1, 0.f, 0.f);
         u16 *dst = act + ((size_t)(j >> 5) * mt_total + mt) * kTileElems + ((kk >> 3) * 16 + mi) * 8 + (kk & 7);

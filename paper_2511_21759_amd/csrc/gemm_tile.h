@@ -33,6 +33,8 @@ struct TileLMStats {
 
 template <class Epi> struct is_row_stats { static constexpr bool value = false; };
 template <> struct is_row_stats<TileLMStats> { static constexpr bool value = true; };
+template <class Epi> struct is_resid { static constexpr bool value = false; };
+template <> struct is_resid<EpiResid> { static constexpr bool value = true; };
 
 
 __device__ __forceinline__ void merge_stat(float &m, float &s, int &a, float om, float os, int oa) {
@@ -241,6 +243,29 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
             }
         }
     } else {
+        if constexpr (is_resid<Epi>::value && NGW == 2) {
+            if (epi.no.hb && epi.no.span == 64) {
+                // (N is a multiple of 256 here, so every n-tile of the workgroup exists)
+                float *s_q = reinterpret_cast<float *>(smem);               // the A slots are free now: [8 waves][128 rows]
+#pragma unroll
+                for (int m = 0; m < 8; m++) {
+                    const int mt = mt0 + m;
+                    if (mt >= g.MT_total) break;
+                    float q = 0.f;
+#pragma unroll
+                    for (int j = 0; j < NGW; j++)
+                        q += epi.put(mt, nt0 + j, acc[m][j] * s_rstd[m * 16 + (lane & 15)], lane, epi.preload(mt, nt0 + j, lane));
+                    q = EpiResid::over_row(q);
+                    if (lane < 16) s_q[w * 128 + m * 16 + lane] = q;
+                }
+                __syncthreads();
+                for (int i = threadIdx.x; i < 4 * 128; i += 64 * NW) {
+                    const int r = i & 127, c4 = i >> 7, row = mt0 * 16 + r;     // 64 columns = two waves
+                    if (row < g.MT_total * 16) epi.no.ssq[(size_t)row * epi.no.n_ssq + nb * 4 + c4] = s_q[2 * c4 * 128 + r] + s_q[(2 * c4 + 1) * 128 + r];
+                }
+                return;
+            }
+        }
 #pragma unroll
         for (int m = 0; m < 8; m++)
 #pragma unroll
@@ -343,6 +368,20 @@ __global__ __launch_bounds__(512) void tile_epilogue_kernel(TileArgs g, Epi epi)
         }
 #pragma unroll
         for (int r = 0; r < 4; r++) c[r] *= s_rstd[4 * gq + r];
+    }
+    if constexpr (is_resid<Epi>::value) {
+        if (epi.no.hb && epi.no.span == 64) {       // the sums of four n-tiles (four waves) make one partial sum
+            __shared__ float s_q[8][16];
+            const float q = EpiResid::over_row(epi.put(mt, nt, c, lane, pre));
+            if (lane < 16) s_q[w][lane] = q;
+            __syncthreads();
+            if (threadIdx.x < 32) {
+                const int r = threadIdx.x & 15, c4 = threadIdx.x >> 4;
+                epi.no.ssq[(size_t)(mt * 16 + r) * epi.no.n_ssq + blockIdx.x * 2 + c4] =
+                    (s_q[4 * c4][r] + s_q[4 * c4 + 1][r]) + (s_q[4 * c4 + 2][r] + s_q[4 * c4 + 3][r]);
+            }
+            return;
+        }
     }
     epi_apply(epi, mt, nt, c, lane, 0, pre);
 }

@@ -64,8 +64,12 @@ void launch_cache_read(const Cache &c, int layer, int kv, int batch_index, int p
 // sums of x^2 over the row; output rows are scaled by 1/sqrt(sum/d + eps) (ssq == nullptr: off).
 // NormOut: the residual epilogue also emits that pair for the next norm (hb == nullptr: off);
 // status: the model's status word, where a value beyond the binary16 range is reported (may be nullptr).
+// A partial sum covers ssq_span columns: 16 (one n-tile) up to 128 rows, where the kernels that write them give
+// neighbouring n-tiles to different workgroups; 64 above, where a workgroup of a GEMM reads the sums of 128 or 256 rows
+// before its first block is done (256 KiB of 16-column sums at d = 4096, as much as eight k-tiles of its operands).
+constexpr int ssq_span(int m_tiles) { return m_tiles > 8 ? 64 : 16; }
 struct NormIn { const float *ssq; int n_ssq; float eps; };
-struct NormOut { u16 *hb; float *ssq; const float *gain; int n_ssq; unsigned *status; };
+struct NormOut { u16 *hb; float *ssq; const float *gain; int n_ssq; unsigned *status; int span; };
 
 // ---- rows.hip ---------------------------------------------------------------
 // Row bookkeeping.  Rows are grouped in "units" (a draft in the step, a

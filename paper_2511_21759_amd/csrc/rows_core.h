@@ -33,7 +33,13 @@ __device__ __forceinline__ void embed_row(int r, const u16 *embed, const int32_t
             float q = 0.f;
 #pragma unroll
             for (int j = 0; j < 16; j++) q += x[j] * x[j];
-            no.ssq[(size_t)r * no.n_ssq + nt] = q;
+            if (no.span == 64) {            // four n-tiles per partial sum: four neighbouring lanes (d is a multiple of 256)
+                q += __shfl_xor(q, 1);
+                q += __shfl_xor(q, 2);
+                if ((nt & 3) == 0) no.ssq[(size_t)r * no.n_ssq + (nt >> 2)] = q;
+            } else {
+                no.ssq[(size_t)r * no.n_ssq + nt] = q;
+            }
             const float *gn = no.gain + nt * 16;
 #pragma unroll
             for (int half = 0; half < 2; half++) {

@@ -1,0 +1,42 @@
+"""GPU parity of the GEMM kernels beyond 128 rows at shapes where their row blocks end raggedly: 128- and 256-row blocks
+of the LDS-ring kernel, the tile kernel with and without its K split, and the partial sums of squares of 64 columns that
+all of them leave for the next RMSNorm.  Element by element against the oracle, with the bars of test_gpu_parity."""
+import pytest
+
+from paper_2511_21759_amd import workloads as W
+from test_gpu_parity import Pair, run_prefill_case, run_step_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = dict(n_layers=2, d_model=1024, n_heads=8, head_dim=128, d_ff=3072, vocab=4096, rope_base=10000.0,
+             rms_eps=1e-5, mask_id=4095)
+
+
+@pytest.fixture(scope="module")
+def mid():
+    p = Pair(SHAPE)
+    yield p
+    p.close()
+
+
+@pytest.mark.parametrize("Bn,P,R", [
+    (1, 100, 33),      # 9 row tiles: the first count with 64-column partial sums
+    (2, 90, 50),       # 18 row tiles: two row blocks of 128, the second almost empty
+    (1, 420, 227),     # 647 rows: 41 row tiles, one beyond five blocks of 128
+    (3, 140, 193),     # three sequences of an odd length, 63 row tiles
+    (1, 700, 303),     # 1003 rows
+])
+def test_refresh_with_ragged_row_blocks(mid, Bn, P, R):
+    wl = W.decode_workload(mid.shape, P, R, 16, 1, 500 + P, batch=Bn)
+    run_prefill_case(mid, wl.tokens, wl.resp_off, "%d x %d" % (Bn, P + R))
+
+
+@pytest.mark.parametrize("Bn,b,S", [
+    (1, 16, 9),        # 144 step rows
+    (1, 23, 17),       # 34 row tiles, padded rows inside every draft
+    (2, 64, 8),        # 1024 step rows
+])
+def test_step_with_ragged_row_blocks(mid, Bn, b, S):
+    wl = W.decode_workload(mid.shape, 70, 90, b, S, 600 + b, batch=Bn)
+    cache, oc = run_prefill_case(mid, wl.tokens, wl.resp_off, "step set-up")
+    run_step_case(mid, cache, oc, wl.drafts, wl.block_off, 0.9, "%d x %d x %d" % (Bn, S, b))
