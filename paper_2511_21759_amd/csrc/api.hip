@@ -332,7 +332,7 @@ int prefill_impl(odb_model *mh, odb_cache *ch, const int32_t *tokens, int L, int
     RowMap rm{c.batch, lp, L};
     c.length = L;
     char *base = (char *)m.scratch;
-    launch_embed(m, tokens, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), s);
+    launch_embed(m, tokens, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), nullptr, 0, s);
     StackIO io{rm, 0, true, 0, 0, 0, 1, true};
     rc = run_stack(m, c, base, pl, io, s);
     if (rc) return rc;
@@ -388,9 +388,9 @@ int step_impl(odb_model *mh, const odb_cache *ch, const int32_t *drafts, int blo
         base = (char *)m.scratch;
     }
     RowMap rm{units, bp, b};
-    launch_embed(m, drafts, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), s);
-    if (b % 32)   // slots of padded keys must hold finite values: they meet zero probabilities in the P*V product
-        launch_fill_f32((float *)(base + pl.vf), 0.f, (size_t)units * bp32 * cfg.d_model / 2, s);
+    // (slots of padded keys must hold finite values: they meet zero probabilities in the P*V product)
+    launch_embed(m, drafts, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), base + pl.vf,
+                 b % 32 ? (size_t)units * bp32 * cfg.d_model * 2 : 0, s);
     StackIO io{rm, block_off, false, block_off, block_off + b, b, S, true};
     int rc = run_stack(m, c, base, pl, io, s);
     if (rc) return rc;
@@ -671,10 +671,9 @@ static int step_shared_impl(odb_model *mh, const odb_cache *ch, const int32_t *d
     sm.dmask = (unsigned long long *)t;
     launch_shared_setup(drafts, sm, block_off, cfg.mask_id, n_masked, conf, argmax, unmask, m.counters, s);
     // rows are embedded through the token-per-row table: every row is its own unit of one
-    launch_embed(m, sm.rowtok, RowMap{rows_pad, 1, 1}, (float *)(base + pl.h),
-                 norm_out(m, base, pl, m.g1, rows_pad / 16), s);
-    // slots of padded keys must hold finite values: they meet zero probabilities in the P*V product
-    launch_fill_f32((float *)(base + pl.vf), 0.f, (size_t)fresh_rows * cfg.d_model / 2, s);
+    // (slots of padded keys must hold finite values: they meet zero probabilities in the P*V product)
+    launch_embed(m, sm.rowtok, RowMap{rows_pad, 1, 1}, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16),
+                 base + pl.vf, (size_t)fresh_rows * cfg.d_model * 2, s);
     RowMap rm{c.batch, sm.bp, b};
     StackIO io{rm, block_off, false, block_off, block_off + b, b, 1, true, &sm};
     rc = run_stack(m, c, base, pl, io, s);

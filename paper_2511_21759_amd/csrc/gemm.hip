@@ -1,15 +1,15 @@
 // Stand-alone launches of the weight-streaming GEMM (see gemm_core.h).
 #include <mutex>
 
-#include "gemm_big.h"
+#include "gemm_slab.h"
 
 namespace odb {
 
-template <int MT, int NG, int PF, class Epi, int WKT = WK, bool IL = false>
-__global__ __launch_bounds__(64 * WKT) void gemm_stream_kernel(GemmArgs g, Epi epi) {
+template <int MT, int NG, int PF, class Epi, bool IL = false>
+__global__ __launch_bounds__(64 * WK) void gemm_stream_kernel(GemmArgs g, Epi epi) {
     __shared__ __attribute__((aligned(16))) char smem[kGemmSmemBytes];
     frag_t wb[PF][NG];
-    gemm_wg<MT, NG, PF, Epi, WKT, IL>(g, epi, blockIdx.x, gridDim.x, blockIdx.y * MT, wb, smem);
+    gemm_wg<MT, NG, PF, Epi, IL>(g, epi, blockIdx.x, gridDim.x, blockIdx.y * MT, wb, smem);
 }
 
 constexpr int kStreamWGs = 256;      // one workgroup per compute unit
@@ -41,17 +41,19 @@ __global__ __launch_bounds__(64 * WK) void gemm_stream_ksplit_kernel(GemmArgs g,
     gs.W += (size_t)ks * kl * kTileElems;
     const size_t slice = (size_t)g.MT_total * g.NT * 256;
     frag_t wb[PF][NG];
-    gemm_wg<MT, NG, PF, EpiPartial, WK, false>(gs, EpiPartial{partial + ks * slice, g.NT}, nb, nblocks, 0, wb, smem);
+    const int mt0 = blockIdx.y * MT, mt1 = mt0 + MT < g.MT_total ? mt0 + MT : g.MT_total;
+    gemm_wg<MT, NG, PF, EpiPartial, false>(gs, EpiPartial{partial + ks * slice, g.NT}, nb, nblocks, mt0, wb, smem);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's partial sums have been written
     __syncthreads();
-    if (threadIdx.x == 0) s_old = __hip_atomic_fetch_add(arrive + nb, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    arrive += blockIdx.y * nblocks + nb;
+    if (threadIdx.x == 0) s_old = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_old != KS - 1) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int n_lo = (int)((unsigned)nb * (unsigned)g.NT / (unsigned)nblocks), n_hi = (int)((unsigned)(nb + 1) * (unsigned)g.NT / (unsigned)nblocks);
     const int nn = n_hi - n_lo;
-    for (int t = wv; t < g.MT_total * nn; t += WK) {
-        const int mt = t / nn, nt = n_lo + t % nn;
+    for (int t = wv; t < (mt1 - mt0) * nn; t += WK) {
+        const int mt = mt0 + t / nn, nt = n_lo + t % nn;
         const float *q = partial + ((size_t)mt * g.NT + nt) * 256 + lane;
         const auto pre = epi_preload(epi, mt, nt, lane);
         f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -61,23 +63,29 @@ __global__ __launch_bounds__(64 * WK) void gemm_stream_ksplit_kernel(GemmArgs g,
                 c[r] += __hip_atomic_load(q + s * slice + r * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         epi_apply(epi, mt, nt, c, lane, 0, pre);
     }
-    if (threadIdx.x == 0) __hip_atomic_store(arrive + nb, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 constexpr int kSplitKS = 4, kSplitNG = 4, kSplitPF = 4;      // (2 x 2 n-tiles, rings of 2, 6 and 8 measured slower)
+static bool ksplit_fits(GemmShape sh, int nblocks, Workspace ws) {       // nblocks: blocks of rows and n-tiles
+    return ws.arrive && nblocks * kSplitKS <= kStreamWGs && nblocks <= 1024 &&
+           (size_t)kSplitKS * sh.M_tiles * sh.N_tiles * 1024 <= ws.partial_bytes;
+}
 // shapes the K-split kernel takes: up to 96 rows without a fused norm, n-blocks x KS workgroups within the chip,
 // k-slices that the waves and the ring divide, room for the partial sums
 static bool ksplit_ok(GemmShape sh, Workspace ws) {
-    const int nblocks = (sh.N_tiles + kSplitNG - 1) / kSplitNG;
-    return sh.M_tiles <= 6 && ws.arrive && nblocks * kSplitKS <= kStreamWGs && nblocks <= 1024 &&
-           sh.K_tiles % (kSplitKS * WK * kSplitPF) == 0 &&
-           (size_t)kSplitKS * sh.M_tiles * sh.N_tiles * 1024 <= ws.partial_bytes;
+    return sh.M_tiles <= 6 && sh.K_tiles % (kSplitKS * WK * kSplitPF) == 0 &&
+           ksplit_fits(sh, (sh.N_tiles + kSplitNG - 1) / kSplitNG, ws);
 }
-template <class Epi>
-static void launch_stream_ksplit(const u16 *a, const u16 *w, GemmShape sh, Epi e, Workspace ws, hipStream_t s) {
+static GemmArgs ksplit_args(const u16 *a, const u16 *w, GemmShape sh) {
     GemmArgs g;
     g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
     g.ssq = nullptr; g.n_ssq = 0; g.eps = 0.f; g.inv_d = 0.f; g.k_len = 0; g.k_rot = kKRot;
+    return g;
+}
+template <class Epi>
+static void launch_stream_ksplit(const u16 *a, const u16 *w, GemmShape sh, Epi e, Workspace ws, hipStream_t s) {
+    const GemmArgs g = ksplit_args(a, w, sh);
     const int nblocks = (sh.N_tiles + kSplitNG - 1) / kSplitNG;
     const dim3 grid(nblocks * kSplitKS);
     if (sh.M_tiles <= 2) gemm_stream_ksplit_kernel<2, kSplitNG, kSplitPF, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
@@ -85,21 +93,58 @@ static void launch_stream_ksplit(const u16 *a, const u16 *w, GemmShape sh, Epi e
     else gemm_stream_ksplit_kernel<6, kSplitNG, 2, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
 }
 
+// The same kernel for narrow models (N up to 2048) from 33 to 128 rows: blocks of 64 rows and one, two or four n-tiles, so
+// that four k-slices of every block make up to 256 workgroups, and as many ring stages as a wave has k-tiles where that is two
+// or three.  At d = 1024, d_ff = 3072 and 128 rows it replaces the tile kernel on 32 and 64 workgroups and its merge pass:
+// O 6.7 + 3.7, down 9.0 + 3.7 us before (blocks of all 128 rows and one n-tile: 7.4 and 9.7 us).
+static int ksplit_narrow_ng(GemmShape sh, Workspace ws) {
+    if (sh.M_tiles <= 2 || sh.M_tiles > 8 || sh.K_tiles % (kSplitKS * WK) != 0) return 0;
+    const int rb = (sh.M_tiles + 3) / 4, ng = sh.N_tiles <= 64 ? rb : sh.N_tiles <= 128 ? 2 * rb : 0;
+    return ng && ksplit_fits(sh, (sh.N_tiles + ng - 1) / ng * rb, ws) ? ng : 0;
+}
+template <int NG, class Epi>
+static void launch_ksplit_narrow(const u16 *a, const u16 *w, GemmShape sh, Epi e, Workspace ws, hipStream_t s) {
+    const GemmArgs g = ksplit_args(a, w, sh);
+    const dim3 grid((sh.N_tiles + NG - 1) / NG * kSplitKS, (sh.M_tiles + 3) / 4);
+    const int kw = sh.K_tiles / (kSplitKS * WK);
+    if (kw % 3 == 0) gemm_stream_ksplit_kernel<4, NG, 3, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    else if (kw % 2 == 0) gemm_stream_ksplit_kernel<4, NG, 2, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    else gemm_stream_ksplit_kernel<4, NG, 1, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+}
+
 // The persistent streaming kernel for up to 128 rows: MT row tiles per wave (2, 4, 6 or 8: 32-row steps),
-// NG n-tiles per group, a PF-deep ring, WKT waves (four when the accumulators need the 512-register budget).
+// NG n-tiles per group, a PF-deep ring.
 // The per-projection choices below are the fastest measured on MI355X; K_tiles that the ring depth does not
 // divide fall back to a ring of one.
-template <int MT, int NG, int PF, int WKT, bool IL, class Epi>
+template <int MT, int NG, int PF, bool IL, class Epi>
 static void launch_stream(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
     GemmArgs g;
     g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
     g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
     g.k_len = 0; g.k_rot = kKRot;
-    const int kw = sh.K_tiles / WKT;                // K_tiles is a multiple of 8 (checked at model creation)
+    const int kw = sh.K_tiles / WK;                // K_tiles is a multiple of 8 (checked at model creation)
     const int groups = (sh.N_tiles + NG - 1) / NG;
-    dim3 grid(groups < kStreamWGs ? groups : kStreamWGs, 1);
-    if (kw % PF == 0) gemm_stream_kernel<MT, NG, PF, Epi, WKT, IL><<<grid, 64 * WKT, 0, s>>>(g, e);
-    else gemm_stream_kernel<MT, NG, 1, Epi, WKT, IL><<<grid, 64 * WKT, 0, s>>>(g, e);
+    dim3 grid(groups < kStreamWGs ? groups : kStreamWGs, (sh.M_tiles + MT - 1) / MT);
+    if (kw % PF == 0) gemm_stream_kernel<MT, NG, PF, Epi, IL><<<grid, 64 * WK, 0, s>>>(g, e);
+    else gemm_stream_kernel<MT, NG, 1, Epi, IL><<<grid, 64 * WK, 0, s>>>(g, e);
+}
+
+// Narrow models: a projection whose n-tiles give fewer than 256 groups of the usual width takes smaller groups, the
+// smallest that still fit one per compute unit (the groups below were picked for N = 12288 and 24576; at d = 1024 they
+// leave three quarters of the chip idle: QKV of 128 rows 14.9 us and gate/up 17.9 us on 64 workgroups).  `widest` is
+// the usual group, `has3` whether a group of three exists beside one and two.
+static int stream_ng(int n_tiles, int widest, bool has3) {
+    if (n_tiles <= kStreamWGs) return 1;
+    if (n_tiles <= 2 * kStreamWGs) return 2;
+    if (has3 && n_tiles <= 3 * kStreamWGs) return 3;
+    return widest;
+}
+template <int NG, int PF, class Epi>
+static void stream_by_rows(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
+    if (sh.M_tiles <= 2) launch_stream<2, NG, PF, true>(a, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 4) launch_stream<4, NG, PF, true>(a, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 6) launch_stream<6, NG, PF, true>(a, w, sh, ni, e, s);
+    else launch_stream<8, NG, PF, true>(a, w, sh, ni, e, s);
 }
 
 // workgroup shapes of the tile kernel: (waves, n-tiles per wave, ring depth)
@@ -162,11 +207,13 @@ static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
 // ragged last block counts by its real rows); below 70 % for every shape the 128-row tile kernel wins
 // (measured at 640 rows).  The 128-row blocks serve shapes that would leave compute units idle: QKV at 512 rows
 // (256 blocks of 128 x 192 instead of 192 of 256 x 128: 83 -> 69 us), every wide projection at 640 rows (five row
-// blocks that fit exactly: refresh 14.7 -> 13.0 ms), the 256-row step (7.6 -> 7.2 ms).
+// blocks that fit exactly: refresh 14.7 -> 13.0 ms), the 256-row step (7.6 -> 7.2 ms).  144 to 176 rows count as 192: both
+// kernels run two row blocks for them, gate/up at 160 rows takes 73.9 us on the tile kernel and 65 us in 128 x 192 blocks.
 struct BigChoice { int mbt, wn; };
 static BigChoice big_choice(GemmShape sh, bool may_192 = true) {
     BigChoice best{16, 0};
-    if (sh.M_tiles < 12 || sh.N_tiles < 32) return best;     // (192 rows fill three quarters of a 256-row block)
+    if (sh.M_tiles <= 8 || sh.N_tiles < 32) return best;
+    const double m_tiles = sh.M_tiles < 12 ? 12 : sh.M_tiles;     // (see above)
     const double rel16[5] = {0, 0, 0.68, 0.87, 1.0}, rel8[5] = {0, 0, 0.46, 0.60, 0.66};
     double best_cost = 0;
     for (int mbt = 16; mbt >= 8; mbt -= 8)
@@ -174,7 +221,7 @@ static BigChoice big_choice(GemmShape sh, bool may_192 = true) {
             if (wn == 3 && !may_192) continue;
             const int blocks = ((sh.M_tiles + mbt - 1) / mbt) * ((sh.N_tiles + 4 * wn - 1) / (4 * wn));
             const int rounds = (blocks + kStreamWGs - 1) / kStreamWGs;
-            const double useful = (sh.M_tiles / (double)mbt) * (sh.N_tiles / (4.0 * wn)) / ((double)rounds * kStreamWGs);
+            const double useful = (m_tiles / (double)mbt) * (sh.N_tiles / (4.0 * wn)) / ((double)rounds * kStreamWGs);
             const double cost = rounds * (mbt == 16 ? rel16[wn] : rel8[wn]);
             // (a 128-row shape has to promise 5 % over the best 256-row one: the unit times are measurements)
             if (useful >= 0.7 && (best.wn == 0 || cost < best_cost * (mbt == 8 && best.mbt == 16 ? 0.95 : 1.0) - 1e-9)) {
@@ -206,17 +253,39 @@ static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi 
     }
 }
 
+// The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles.
+template <int NTB, class Epi>
+static void launch_slab(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
+    SlabArgs g;
+    g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
+    g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
+    static std::once_flag attr_once;
+    std::call_once(attr_once, [] {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_slab_kernel<NTB, Epi>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, slab_smem_bytes(NTB));
+    });
+    gemm_slab_kernel<NTB, Epi><<<dim3((g.NT + NTB - 1) / NTB, (g.MT_total + 7) / 8), 512, slab_smem_bytes(NTB), s>>>(g, e);
+}
+
 void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOut out, Workspace ws, hipStream_t s) {
     EpiQKV e{out, sh.M_tiles};
     // (Up to 96 rows a ring of ONE stage is the fastest since the weight tiles are loaded non-temporally - 2048 waves
     // with one group of tiles each in flight keep the HBM stream full, and fewer outstanding weight loads per
     // compute unit leave the activation loads less to queue behind: 1.9 % per step at 32 rows for this and the
-    // gate/up projection together, 1.5 % at 64 rows, 0.5 % at 96; the 128-row gate/up keeps its four waves and deeper ring.)
-    if (sh.M_tiles <= 2) launch_stream<2, 3, 1, 8, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, 8, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
-    else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, 8, true>(xa, w, sh, ni, e, s);          // 65..96 rows
-    // (128 rows: eight waves and a ring of one fit 256 registers - 36.5 -> 35.3 us against four waves with a ring of four)
-    else if (sh.M_tiles <= 8) launch_stream<8, 3, 1, 8, false>(xa, w, sh, ni, e, s);
+    // gate/up projection together, 1.5 % at 64 rows, 0.5 % at 96.)
+    const int ng = stream_ng(sh.N_tiles, 3, false);
+    // (a narrow model's 97 to 128 rows: blocks of 32 rows and three n-tiles read 160 instead of 288 KB per compute unit at
+    // d = 1024: 10.4 -> 7.2 us; gate/up below: 64 rows and three n-tiles, 10.9 -> 8.5 us)
+    if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 1) launch_stream<2, 3, 4, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 2) stream_by_rows<2, 2>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 2) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
+    else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);          // 65..96 rows
+    else if (sh.M_tiles <= 8) launch_slab<3>(xa, w, sh, ni, e, s);
+    // two row blocks on 130 to 256 compute units: 44 us at 160 to 256 rows of the 8B shape, against 54 to 58 us on the tile
+    // kernel and its merge pass and 50 us in 192 blocks of 128 x 128
+    else if (sh.M_tiles <= 16 && sh.N_tiles > 384 && sh.N_tiles <= 768) launch_slab<6>(xa, w, sh, ni, e, s);
     else if (use_big(sh)) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }
@@ -234,8 +303,13 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
     // reads, with a separate pass that adds the partial sums.  From 2048 rows the 256 x 128 blocks of the 256-row
     // kernel fill the chip (8 x 32 blocks for N = 4096).
     const bool long_k = sh.K_tiles > sh.N_tiles;
-    if (sh.M_tiles <= 6 && (long_k || sh.M_tiles > 2) && ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
-    else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
+    if (const int ng = ksplit_narrow_ng(sh, ws)) {
+        if (ng == 1) launch_ksplit_narrow<1>(a, w, sh, e, ws, s);
+        else if (ng == 2) launch_ksplit_narrow<2>(a, w, sh, e, ws, s);
+        else launch_ksplit_narrow<4>(a, w, sh, e, ws, s);
+    }
+    else if (sh.M_tiles <= 6 && (long_k || sh.M_tiles > 2) && ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
+    else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
     // (128-row blocks only for the O projection: at 1024 rows 256 blocks of 128 x 128 take 57 us against 64 us for the
     // tile kernel and its reduction pass; the down projection, three times as long in K, measured 4 % slower that way)
     // (no 192-column blocks here: N is a multiple of 256, and the sums of squares are left per 64 columns)
@@ -246,10 +320,15 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
 void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u16 *act, unsigned *status, Workspace ws,
                         hipStream_t s) {
     EpiSwiGLU e{act, sh.M_tiles, status};
-    if (sh.M_tiles <= 2) launch_stream<2, 6, 1, 8, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 4) launch_stream<4, 6, 1, 8, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 6) launch_stream<6, 6, 1, 8, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8) launch_stream<8, 6, 2, 4, true>(xa, w, sh, ni, e, s);
+    const int ng = stream_ng(sh.N_tiles, 6, true);
+    if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 2) launch_stream<4, 3, 2, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 2) stream_by_rows<2, 2>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 3) stream_by_rows<3, 1>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 2) launch_stream<2, 6, 1, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 4) launch_stream<4, 6, 1, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 6) launch_stream<6, 6, 1, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8) launch_slab<6>(xa, w, sh, ni, e, s);
     else if (use_big(sh)) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }
@@ -269,11 +348,12 @@ static int lm_ng(int n_tiles, int m_tiles) {
 // (129..191 rows leave part of a 256-row block empty, and still measure 283 us against 427 us on the tile kernel:
 // the vocabulary is long enough to be bound by the weight stream either way)
 static int lm_big_width(GemmShape sh) { const int wn = big_choice(sh).wn; return wn || sh.N_tiles < 32 ? wn : 4; }
-// From 33 to 128 rows the LM head runs on the tile kernel with four n-tiles per wave (see launch_gemm_lmstats)
-constexpr int kLmTileNGW = 4;
-static bool lm_tile(int m_tiles) { return m_tiles > 2 && m_tiles <= 8; }
+// From 33 to 128 rows the LM head runs on the LDS-ring kernel as one row block, 64 * lm_one_wn columns wide: the widest block
+// that makes no more than a round of workgroups shorter (see launch_gemm_lmstats).
+static bool lm_one_block(int m_tiles) { return m_tiles > 2 && m_tiles <= 8; }
+static int lm_one_wn(int n_tiles) { return n_tiles <= 8 * kStreamWGs ? 2 : n_tiles <= 16 * kStreamWGs ? 4 : 8; }
 int lm_stats_parts(int n_tiles, int m_tiles) {
-    if (lm_tile(m_tiles)) return (n_tiles + 8 * kLmTileNGW - 1) / (8 * kLmTileNGW);
+    if (lm_one_block(m_tiles)) return (n_tiles + 4 * lm_one_wn(n_tiles) - 1) / (4 * lm_one_wn(n_tiles));
     if (m_tiles <= 8) {
         const int ng = lm_ng(n_tiles, m_tiles);
         const int groups = (n_tiles + ng - 1) / ng;
@@ -287,21 +367,22 @@ int lm_stats_parts(int n_tiles, int m_tiles) {
 void launch_gemm_lmstats(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, float *stats, Workspace ws,
                          hipStream_t s) {
     const int parts = lm_stats_parts(sh.N_tiles, sh.M_tiles);
-    if (sh.M_tiles <= 2 && lm_ng(sh.N_tiles, sh.M_tiles) == 4) launch_stream<2, 4, 4, 8, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
-    else if (sh.M_tiles <= 2) launch_stream<2, kLmNG, 4, 8, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
-    else if (lm_tile(sh.M_tiles)) {
+    if (sh.M_tiles <= 2 && lm_ng(sh.N_tiles, sh.M_tiles) == 4) launch_stream<2, 4, 4, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
+    else if (sh.M_tiles <= 2) launch_stream<2, kLmNG, 4, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
+    else if (lm_one_block(sh.M_tiles)) {
         // 33..128 rows.  A streaming workgroup reads all activation rows once per group of six n-tiles, and with 31
         // n-tiles per workgroup that is five to six times [rows x d] through each compute unit's vector-memory path,
-        // more than its weights: at 128 rows the kernel was bound by that path (244 us, 4.2 TB/s).  The tile kernel
-        // shares the activation slab between eight waves through LDS, so with four n-tiles per wave a workgroup reads
-        // the activations once for 32 n-tiles; the vocabulary gives 247 such workgroups, one round on the chip:
-        // 167 us at 128 rows (6.2 TB/s), and the finishing kernel merges 247 partials per row instead of 1536.
-        TileArgs g;
-        g.A = xa; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
-        g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
-        g.partial = nullptr; g.KS = 1;
-        g.n_blocks = parts;
-        gemm_tile_kernel<8, kLmTileNGW, 4, TileLMStats, true><<<dim3(g.n_blocks, 1), 512, 0, s>>>(g, TileLMStats{stats, parts});
+        // more than its weights: at 128 rows the kernel was bound by that path (244 us, 4.2 TB/s).  A block of 512
+        // columns reads the activations once for 32 n-tiles; a vocabulary of 126464 gives 247 such workgroups, one round
+        // on the chip.  With the weights copied through the LDS ring it takes 170 us at 96 rows and 168 at 128, against 191
+        // and 174 us on the tile kernel, which loads them into registers four k-tiles ahead.  A vocabulary of 32000 is 63 such
+        // blocks (42.7 us at d = 1024 and 128 rows) and 250 of 128 columns.
+        const TileLMStats e{stats, parts};
+        switch (lm_one_wn(sh.N_tiles)) {
+            case 2: launch_big_wn<2, TileLMStats, 8>(xa, w, sh, ni, e, s); break;
+            case 4: launch_big_wn<4, TileLMStats, 8>(xa, w, sh, ni, e, s); break;
+            default: launch_big_wn<8, TileLMStats, 8>(xa, w, sh, ni, e, s);
+        }
     }
     else if (use_big(sh)) launch_big(xa, w, sh, ni, TileLMStats{stats, parts}, s);
     else if (lm_big_width(sh)) launch_big_wn<4>(xa, w, sh, ni, TileLMStats{stats, parts}, s);
@@ -310,9 +391,9 @@ void launch_gemm_lmstats(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, f
 void launch_gemm_store(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, float *out, int units, int rpu_pad,
                        int valid, int ld, Workspace ws, hipStream_t s) {
     EpiStore e{out, units, rpu_pad, valid, ld};
-    if (sh.M_tiles <= 2) launch_stream<2, 3, 8, 8, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 4) launch_stream<4, 3, 4, 8, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8) launch_stream<8, 3, 2, 8, false>(xa, w, sh, ni, e, s);
+    if (sh.M_tiles <= 2) launch_stream<2, 3, 8, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 4) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8) launch_stream<8, 3, 2, false>(xa, w, sh, ni, e, s);
     else if (use_big(sh)) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, false, s);
 }

@@ -21,9 +21,9 @@ namespace odb {
 // wave and k-tile, enough to hide the operand reads of the other group of waves; a 128-row block has 8 to 16, so its
 // stages are two k-tiles deep (measured on the loop alone at K = 4096: 128 x 128 blocks 43.3 -> 37.1 us at 1024 x 4096,
 // 128 x 192 blocks 56.1 -> 52.4 us at 256 x 24576; 256 x 256 blocks equal).
-constexpr int big_kp(int mbt) { return mbt == 8 ? 2 : 1; }
+constexpr int big_kp(int wn, int mbt) { return mbt == 8 && wn <= 4 ? 2 : 1; }
 constexpr int big_stages(int mbt) { return mbt == 8 ? 3 : 4; }
-constexpr int big_stage_tiles(int wn, int mbt) { return big_kp(mbt) * (mbt + 4 * wn); }
+constexpr int big_stage_tiles(int wn, int mbt) { return big_kp(wn, mbt) * (mbt + 4 * wn); }
 constexpr int big_smem_bytes(int wn, int mbt) { return big_stages(mbt) * big_stage_tiles(wn, mbt) * 1024 + 256 * 4; }   // ring, row scales
 // per-wave scratch of the epilogues, in the ring's place once the k-loop is over
 constexpr int kBigScratch = 4096;
@@ -206,16 +206,17 @@ __device__ __forceinline__ void big_epilogue(const EpiStore &e, f32x4 (&acc)[MW]
 }
 
 // MBT: 16-row tiles per block, 16 (256 rows) or 8 (128 rows: twice the blocks for shapes that leave compute
-// units idle otherwise; per flop it needs 1.4 x the operand bytes of the 256-row block).
+// units idle otherwise; per flop it needs 1.4 x the operand bytes of the 256-row block).  WN = 8: a single block of 128 rows
+// against 512 columns, for the LM head at 33 to 128 rows; W is then read once, non-temporally.
 template <int WN, class Epi, int MBT = 16>
 __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
-    static_assert(WN >= 2 && WN <= 4, "block width in units of 64 columns");
+    static_assert((WN >= 2 && WN <= 4) || (WN == 8 && MBT == 8), "block width in units of 64 columns");
     static_assert(MBT == 16 || MBT == 8, "rows per block");
     static_assert(!is_resid<Epi>::value || WN != 3, "partial sums of squares cover 64 columns");
     constexpr int CW = 4;                       // waves side by side; two rows of them
     constexpr int WT = WN;                      // 16-column tiles per wave
     constexpr int MW = MBT / 2;                 // 16-row tiles per wave
-    constexpr int NS = big_stages(MBT), KP = big_kp(MBT), TK = MBT + 4 * WN, ST = KP * TK;     // tiles per k-tile, per stage
+    constexpr int NS = big_stages(MBT), KP = big_kp(WN, MBT), TK = MBT + 4 * WN, ST = KP * TK;     // tiles per k-tile, per stage
     extern __shared__ __attribute__((aligned(16))) char smem[];
     typedef frag_t stage_t[ST][64];                                          // per k-tile: MBT tiles of A, then 4 WN of W
     stage_t *ring = reinterpret_cast<stage_t *>(smem);
@@ -260,11 +261,12 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
         for (int q = 0; q < KP; q++)
 #pragma unroll
             for (int i = 0; i < PMAX; i++)
-                if (i < per)
-                    __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(
-                                                         reinterpret_cast<const char *>(src[i] + (size_t)(s * KP + q) * kstride) + lane_off),
-                                                     (__attribute__((address_space(3))) void *)(&ring[slot][q * TK + slot0 + i][0]),
-                                                     16, 0, 0);
+                if (i < per) {
+                    const void *from = reinterpret_cast<const char *>(src[i] + (size_t)(s * KP + q) * kstride) + lane_off;
+                    auto *to = (__attribute__((address_space(3))) void *)(&ring[slot][q * TK + slot0 + i][0]);
+                    if (WN == 8 && w >= CW) __builtin_amdgcn_global_load_lds(from, to, 16, 0, 2);
+                    else __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+                }
     };
 
     const int ns = g.KT / KP;                   // stages (K is a multiple of 256: k-tiles come in eights)

@@ -11,10 +11,8 @@
 // next, so the HBM stream never drains.  The eight K-slices of an output tile
 // are added through LDS in a fixed order, so results do not depend on scheduling.
 //
-// Variants (template parameters of gemm_wg): WKT waves per workgroup (8, or 4 when 48
-// accumulator tiles per wave need the 512-register budget of one wave per SIMD), and
-// IL, which hands the k-tiles to the waves round-robin instead of in contiguous
-// slices, so that the workgroup as a whole reads WKT KiB of contiguous weights per step
+// Variant (template parameter of gemm_wg): IL hands the k-tiles to the waves round-robin instead of in contiguous
+// slices, so that the workgroup as a whole reads eight KiB of contiguous weights per step
 // (measured 5 % faster on the wide gate/up stream, slightly slower on the down projection).
 //
 // The epilogues fuse what follows each projection in the transformer block:
@@ -46,10 +44,8 @@ struct GemmArgs {
 };
 
 // m-tiles per reduction pass: at most six 1 KiB tiles per wave go through LDS at a time
-// (with four waves twice as many: the buffer holds WK * 6 tiles)
-constexpr int gemm_mc(int mt, int ng, int wkt = WK) {
-    return wkt == 4 && mt == 8 ? (ng >= 6 ? 2 : (ng >= 3 ? 4 : 8))
-                               : (ng >= 4 ? 1 : (ng >= 3 ? 2 : (mt < 4 ? mt : (mt % 4 == 0 ? 4 : 3))));
+constexpr int gemm_mc(int mt, int ng) {
+    return (ng >= 4 ? 1 : (ng >= 3 ? 2 : ng == 2 ? (mt == 6 ? 3 : 2) : (mt < 4 ? mt : (mt % 4 == 0 ? 4 : 3))));
 }
 
 constexpr int kGemmSmemBytes = WK * 6 * 1024 + 8 * 16 * 4;    // LDS one workgroup needs (red + row scales)
@@ -67,12 +63,12 @@ __device__ __forceinline__ void epi_apply(Epi &epi, int mt, int nt, f32x4 c, int
 // The epilogue is called as epi(mt, nt, c, lane, slot): slot numbers the (m-chunk, tile) pairs that
 // this wave serves, the same in every group of n-tiles, so a stateful epilogue can keep one
 // accumulator per slot; epi.finish(mt, part, lane, slot) follows once per slot at the end.
-template <int MT, int NG, int PF, class Epi, int WKT = WK, bool IL = false>
+template <int MT, int NG, int PF, class Epi, bool IL = false>
 __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int nwg, int mt0,
                                         frag_t (&wb)[PF][NG], char *smem) {
-    constexpr int MC = gemm_mc(MT, NG, WKT);                // m-tiles reduced per pass through LDS (<= 48 KiB)
-    constexpr int SPW = (MC * NG + WKT - 1) / WKT;          // reduced tiles a wave serves per m-chunk
-    static_assert(MT % MC == 0 && MC * NG * WKT <= 6 * WK && MT <= 8 && WKT <= WK, "m chunking");
+    constexpr int MC = gemm_mc(MT, NG);                // m-tiles reduced per pass through LDS (<= 48 KiB)
+    constexpr int SPW = (MC * NG + WK - 1) / WK;          // reduced tiles a wave serves per m-chunk
+    static_assert(MT % MC == 0 && MC * NG * WK <= 6 * WK && MT <= 8, "m chunking");
     f32x4 (*red)[MC * NG][64] = reinterpret_cast<f32x4 (*)[MC * NG][64]>(smem);
     float *s_rstd = reinterpret_cast<float *>(smem + WK * 6 * 1024);
 
@@ -80,9 +76,9 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
     const int n_lo = (int)((unsigned)wg * (unsigned)g.NT / (unsigned)nwg);      // (32-bit: wg * NT stays far below 2^32)
     const int n_hi = (int)((unsigned)(wg + 1) * (unsigned)g.NT / (unsigned)nwg);
     if (n_lo >= n_hi) return;
-    const int KW = (g.k_len ? g.k_len : g.KT) / WKT;
+    const int KW = (g.k_len ? g.k_len : g.KT) / WK;
     const int ngroups = (n_hi - n_lo + NG - 1) / NG;
-    const int k0 = IL ? wk : wk * KW, kst = IL ? WKT : 1;      // first k-tile of this wave and its stride
+    const int k0 = IL ? wk : wk * KW, kst = IL ? WK : 1;      // first k-tile of this wave and its stride
 
     const u16 *wbase = g.W + (size_t)k0 * kTileElems + lane * 8;
     const u16 *ap[MT];
@@ -112,7 +108,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
     // load per lane; the loads of all RPW rows of this wave are issued back to back and BEFORE the
     // first stage, so that waiting for them does not wait for the weight stream (loads return in
     // order), and they are only reduced after the ring has been filled.
-    constexpr int RPW = MT * 16 / WKT;                      // rows per wave
+    constexpr int RPW = MT * 16 / WK;                      // rows per wave
     float q[RPW];
     f32x4 sv[RPW];
     const int si = 4 * lane, sic = si < g.n_ssq - 4 ? si : g.n_ssq - 4;     // n_ssq is a multiple of 16
@@ -121,7 +117,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
         q[j] = 0.f;
         sv[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (g.ssq) {
-            int row = mt0 * 16 + wk + j * WKT;
+            int row = mt0 * 16 + wk + j * WK;
             row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
             const float *p = g.ssq + (size_t)row * g.n_ssq;
             for (int i0 = 256; i0 < g.n_ssq; i0 += 256) {   // rows wider than 4096 only
@@ -141,7 +137,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
         // (RP: RPW rounded up to a power of two - six row tiles over eight waves give twelve rows per wave;
         // the lanes of the rows beyond RPW add stale scratch and are dropped)
         constexpr int RP = RPW <= 1 ? 1 : RPW <= 2 ? 2 : RPW <= 4 ? 4 : RPW <= 8 ? 8 : RPW <= 16 ? 16 : RPW <= 32 ? 32 : 64;
-        static_assert(RPW <= 64 && WKT * RP * 65 * 4 <= WK * 6 * 1024, "rows per wave");
+        static_assert(RPW <= 64 && WK * RP * 65 * 4 <= WK * 6 * 1024, "rows per wave");
         float *tmp = reinterpret_cast<float *>(smem) + wk * (RP * 65);
 #pragma unroll
         for (int j = 0; j < RPW; j++)
@@ -152,10 +148,10 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
         for (int i = 0; i < RP; i++) t += tmp[row * 65 + part * RP + i];
 #pragma unroll
         for (int o = RP; o < 64; o <<= 1) t += __shfl_xor(t, o);
-        if (lane < RPW) s_rstd[wk + lane * WKT] = 1.0f / sqrtf(t * g.inv_d + g.eps);
+        if (lane < RPW) s_rstd[wk + lane * WK] = 1.0f / sqrtf(t * g.inv_d + g.eps);
         __syncthreads();                        // the buffer is reused by the K reduction below
     } else if (lane < RPW) {
-        s_rstd[wk + lane * WKT] = 1.0f;
+        s_rstd[wk + lane * WK] = 1.0f;
     }
 
     for (int grp = 0; grp < ngroups; grp++) {
@@ -185,7 +181,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
             decltype(epi_preload(epi, 0, 0, 0)) pre[SPW];
 #pragma unroll
             for (int u = 0; u < SPW; u++) {
-                const int t = wk + u * WKT, m = t / NG, n = t % NG;
+                const int t = wk + u * WK, m = t / NG, n = t % NG;
                 const int mt = mt0 + mc + m, nt = n_lo + grp * NG + n;
                 if (t < MC * NG && mt < g.MT_total && nt < n_hi) pre[u] = epi_preload(epi, mt, nt, lane);
             }
@@ -196,7 +192,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < SPW; u++) {
-                const int t = wk + u * WKT;
+                const int t = wk + u * WK;
                 if (t >= MC * NG) break;
                 const int m = t / NG, n = t % NG;
                 const int mt = mt0 + mc + m, nt = n_lo + grp * NG + n;
@@ -205,7 +201,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
                     if (!epi.transposed(nt)) {
                         c = red[0][t][lane];
 #pragma unroll
-                        for (int w = 1; w < WKT; w++) c += red[w][t][lane];
+                        for (int w = 1; w < WK; w++) c += red[w][t][lane];
                         c *= s_rstd[(mc + m) * 16 + (lane & 15)];
                     } else {
                         // hand lane (g, ni) the four rows 4g..4g+3 of column ni instead of four columns of one row
@@ -217,7 +213,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
                             const int src = ((ni >> 2) * 16 + 4 * gq + r) * 4 + (ni & 3);
                             float v = base[src];
 #pragma unroll
-                            for (int w = 1; w < WKT; w++) v += base[w * stride + src];
+                            for (int w = 1; w < WK; w++) v += base[w * stride + src];
                             c[r] = v * s_rstd[(mc + m) * 16 + 4 * gq + r];
                         }
                     }
@@ -232,7 +228,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
     for (int mc = 0; mc < MT; mc += MC)
 #pragma unroll
         for (int u = 0; u < SPW; u++) {
-            const int t = wk + u * WKT;         // a tile this wave served in every group
+            const int t = wk + u * WK;         // a tile this wave served in every group
             if (t < MC * NG && mt0 + mc + t / NG < g.MT_total)
                 epi.finish(mt0 + mc + t / NG, wg * NG + t % NG, lane, (mc / MC) * SPW + u);
         }

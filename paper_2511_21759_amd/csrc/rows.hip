@@ -5,15 +5,16 @@
 namespace odb {
 
 __global__ void embed_kernel(const u16 *embed, const int32_t *tokens, RowMap rm, int d, int vocab, float *h,
-                             NormOut no, int mt_total) {
+                             NormOut no, int mt_total, f32x4 *zero, int n_zero) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     embed_row(blockIdx.x, embed, tokens, rm, d, vocab, h, no, mt_total);
 }
 
-void launch_embed(const Model &m, const int32_t *tokens, RowMap rm, float *h, NormOut no, hipStream_t s) {
+void launch_embed(const Model &m, const int32_t *tokens, RowMap rm, float *h, NormOut no, void *zero, size_t zero_bytes, hipStream_t s) {
     int rows = rm.units * rm.rpu_pad;
     int threads = m.cfg.d_model / 16 < 256 ? 64 : 256;
     embed_kernel<<<dim3(rows), threads, 0, s>>>(m.w[PK_EMBED], tokens, rm, m.cfg.d_model, m.cfg.vocab, h, no,
-                                                rows / 16);
+                                                rows / 16, (f32x4 *)zero, (int)(zero_bytes / 16));
 }
 
 __device__ inline float wave_sum(float v) {

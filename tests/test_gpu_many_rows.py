@@ -40,3 +40,27 @@ def test_step_with_ragged_row_blocks(mid, Bn, b, S):
     wl = W.decode_workload(mid.shape, 70, 90, b, S, 600 + b, batch=Bn)
     cache, oc = run_prefill_case(mid, wl.tokens, wl.resp_off, "step set-up")
     run_step_case(mid, cache, oc, wl.drafts, wl.block_off, 0.9, "%d x %d x %d" % (Bn, S, b))
+
+
+# ---- dispatch by width: 33 to 256 rows of models between the tiny and the 8B width -------------------------------------
+
+def _width(d, f, layers=1):
+    return dict(n_layers=layers, d_model=d, n_heads=d // 128, head_dim=128, d_ff=f, vocab=2048, rope_base=10000.0,
+                rms_eps=1e-5, mask_id=2047)
+
+
+@pytest.mark.parametrize("d,f,rows", [
+    (1024, 3072, [(3, 16), (4, 16), (5, 16), (7, 16), (4, 32)]),   # K split over 64-row blocks, one and two n-tiles per group
+    (1024, 5120, [(1, 16), (5, 16), (8, 16)]),                     # gate/up in groups of three
+    (2048, 2048, [(3, 16), (7, 16)]),                              # K split with two and four n-tiles per block
+    (2816, 6400, [(7, 16), (4, 32), (9, 16), (16, 16)]),           # all rows through LDS; from 9 row tiles two row blocks for QKV
+])
+def test_step_by_width(d, f, rows):
+    p = Pair(_width(d, f))
+    try:
+        for S, b in rows:
+            wl = W.decode_workload(p.shape, 40, 40, b, S, 700 + S)
+            cache, oc = run_prefill_case(p, wl.tokens, wl.resp_off, "set-up at d = %d" % d)
+            run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "d = %d, %d x %d" % (d, S, b))
+    finally:
+        p.close()
