@@ -131,8 +131,10 @@ def _check(rc: int) -> None:
 
 
 def _stream() -> int:
+    # the handle of torch.cuda.current_stream() without building the Stream object (a call of the jump controller is
+    # bound by its host side: 15.3 us a call, of which the kernel takes 7)
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev_i32(t):
@@ -330,15 +332,15 @@ def odb_speculative_jump(model: int, drafts, conf, argmax, unmask, cand_pos, can
     """drafts/argmax int32, conf f32, unmask uint8: CUDA tensors [B, S, b], S = 4 or 8; cand_pos/cand_tok int32 [B, 4]
     -> (chosen int32 [B], new_drafts int32 [B, n_next, b], new_cand_pos int32 [B, 4], new_cand_tok int32 [B, 4])."""
     import torch
-    B, S, b = drafts.shape
-    want = {"drafts": (drafts, torch.int32, (B, S, b)), "conf": (conf, torch.float32, (B, S, b)),
-            "argmax": (argmax, torch.int32, (B, S, b)), "unmask": (unmask, torch.uint8, (B, S, b)),
-            "cand_pos": (cand_pos, torch.int32, (B, 4)), "cand_tok": (cand_tok, torch.int32, (B, 4))}
-    for name, (t, dt, shp) in want.items():
-        if t.dtype != dt or tuple(t.shape) != shp or not t.is_contiguous() or not t.is_cuda:
-            raise TypeError("%s must be a contiguous CUDA tensor of dtype %s and shape %s" % (name, dt, shp))
-    chosen = torch.empty((B,), dtype=torch.int32, device=drafts.device)
-    new_drafts = torch.empty((B, max(int(n_next), 1), b), dtype=torch.int32, device=drafts.device)
+    B, S, b = shape = drafts.shape
+    i32 = torch.int32
+    for name, t, dt, shp in (("drafts", drafts, i32, shape), ("conf", conf, torch.float32, shape), ("argmax", argmax, i32, shape),
+                             ("unmask", unmask, torch.uint8, shape), ("cand_pos", cand_pos, i32, (B, 4)),
+                             ("cand_tok", cand_tok, i32, (B, 4))):
+        if t.dtype is not dt or t.shape != shp or not t.is_contiguous() or not t.is_cuda:
+            raise TypeError("%s must be a contiguous CUDA tensor of dtype %s and shape %s" % (name, dt, tuple(shp)))
+    chosen = drafts.new_empty((B,))
+    new_drafts = drafts.new_empty((B, max(int(n_next), 1), b))
     new_pos, new_tok = torch.empty_like(cand_pos), torch.empty_like(cand_tok)
     _check(lib().odb_speculative_jump(model, drafts.data_ptr(), conf.data_ptr(), argmax.data_ptr(), unmask.data_ptr(),
                                       cand_pos.data_ptr(), cand_tok.data_ptr(), B, b, S, n_next, chosen.data_ptr(),
