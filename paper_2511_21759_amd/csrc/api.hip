@@ -51,7 +51,9 @@ void dev_free(const Model &m, void *p) {
 }
 
 constexpr int kCounters = 1 << 12;     // status word and arrival counters
-constexpr size_t kPartialBytes = 32u << 20;   // K-split partial sums of the tile GEMM
+// Room for the K-split partial sums: 32 MiB, and with more rows four slices of a [rows, d] projection up to 96 MiB (three slices
+// of 1264 rows at d = 4096 are 62 MB).
+constexpr size_t kPartialBytes = 32u << 20, kPartialMax = 96u << 20, kPartialByRows = ~(size_t)0;
 
 // byte offsets of the per-call buffers inside the scratch area of a call
 struct Plan {
@@ -61,8 +63,12 @@ struct Plan {
 
 // part_bytes: room for K-split partial sums (the GEMM launchers split K only as far as it allows)
 Plan make_plan(const odb_config &c, int rows_pad, int fresh_rows, int lm_rows_pad, bool need_stats, size_t extra_bytes = 0,
-               size_t part_bytes = kPartialBytes) {
+               size_t part_bytes = kPartialByRows) {
     Plan p;
+    if (part_bytes == kPartialByRows) {
+        const size_t four = (size_t)rows_pad * c.d_model * 16;
+        part_bytes = four < kPartialBytes ? kPartialBytes : four < kPartialMax ? four : kPartialMax;
+    }
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     size_t d = c.d_model;

@@ -29,9 +29,13 @@ constexpr int kKRot = 7;
 // device-coherent accesses, ordered by a wait for the stores' completion before the counter is touched; cache-wide
 // fences (a release / acquire pair) were measured to stall the weight streams of every workgroup on the chip
 // (108 us instead of 20 us in a traffic model of this kernel).  The counter is back at zero when the kernel ends.
-template <int MT, int NG, int PF, int KS, class Epi>
-__global__ __launch_bounds__(64 * WK) void gemm_stream_ksplit_kernel(GemmArgs g, Epi epi, float *partial, unsigned *arrive) {
+// (RB: blockIdx.y numbers blocks of MT row tiles.  SPAN64: sums of squares over 64 columns, NormOut::span; with NG = 4 and N a
+// multiple of 64 a block is one such sum.)
+template <int MT, int NG, int PF, int KS, bool RB = false, bool SPAN64 = false>
+__global__ __launch_bounds__(64 * WK) void gemm_stream_ksplit_kernel(GemmArgs g, EpiResid epi, float *partial, unsigned *arrive) {
     __shared__ __attribute__((aligned(16))) char smem[kGemmSmemBytes];
+    static_assert(!SPAN64 || NG == 4, "one sum per block");
+    float *s_q = reinterpret_cast<float *>(smem);            // (SPAN64) [MT * NG][16], in the finishing workgroup
     __shared__ unsigned s_old;
     const int ks = blockIdx.x % KS, nb = blockIdx.x / KS, nblocks = gridDim.x / KS;
     const int kl = g.KT / KS;
@@ -41,11 +45,11 @@ __global__ __launch_bounds__(64 * WK) void gemm_stream_ksplit_kernel(GemmArgs g,
     gs.W += (size_t)ks * kl * kTileElems;
     const size_t slice = (size_t)g.MT_total * g.NT * 256;
     frag_t wb[PF][NG];
-    const int mt0 = blockIdx.y * MT, mt1 = mt0 + MT < g.MT_total ? mt0 + MT : g.MT_total;
+    const int mt0 = RB ? blockIdx.y * MT : 0, mt1 = RB && mt0 + MT < g.MT_total ? mt0 + MT : g.MT_total;
     gemm_wg<MT, NG, PF, EpiPartial, false>(gs, EpiPartial{partial + ks * slice, g.NT}, nb, nblocks, mt0, wb, smem);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's partial sums have been written
     __syncthreads();
-    arrive += blockIdx.y * nblocks + nb;
+    arrive += RB ? blockIdx.y * nblocks + nb : nb;
     if (threadIdx.x == 0) s_old = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_old != KS - 1) return;
@@ -61,7 +65,19 @@ __global__ __launch_bounds__(64 * WK) void gemm_stream_ksplit_kernel(GemmArgs g,
 #pragma unroll
             for (int r = 0; r < 4; r++)
                 c[r] += __hip_atomic_load(q + s * slice + r * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        epi_apply(epi, mt, nt, c, lane, 0, pre);
+        if constexpr (SPAN64) {                     // the block's four n-tiles make one partial sum of squares
+            const float sq = EpiResid::over_row(epi.put(mt, nt, c, lane, pre));
+            if (lane < 16) s_q[t * 16 + lane] = sq;
+        } else {
+            epi_apply(epi, mt, nt, c, lane, 0, pre);
+        }
+    }
+    if constexpr (SPAN64) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < (mt1 - mt0) * 16; i += 64 * WK) {
+            const float *p = s_q + (i >> 4) * 64 + (i & 15);
+            epi.no.ssq[(size_t)(mt0 * 16 + i) * epi.no.n_ssq + nb] = (p[0] + p[16]) + (p[32] + p[48]);
+        }
     }
     if (threadIdx.x == 0) __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -83,33 +99,33 @@ static GemmArgs ksplit_args(const u16 *a, const u16 *w, GemmShape sh) {
     g.ssq = nullptr; g.n_ssq = 0; g.eps = 0.f; g.inv_d = 0.f; g.k_len = 0; g.k_rot = kKRot;
     return g;
 }
-template <class Epi>
-static void launch_stream_ksplit(const u16 *a, const u16 *w, GemmShape sh, Epi e, Workspace ws, hipStream_t s) {
+static void launch_stream_ksplit(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, Workspace ws, hipStream_t s) {
     const GemmArgs g = ksplit_args(a, w, sh);
     const int nblocks = (sh.N_tiles + kSplitNG - 1) / kSplitNG;
     const dim3 grid(nblocks * kSplitKS);
-    if (sh.M_tiles <= 2) gemm_stream_ksplit_kernel<2, kSplitNG, kSplitPF, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else if (sh.M_tiles <= 4) gemm_stream_ksplit_kernel<4, kSplitNG, 4, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else gemm_stream_ksplit_kernel<6, kSplitNG, 2, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    if (sh.M_tiles <= 2) gemm_stream_ksplit_kernel<2, kSplitNG, kSplitPF, kSplitKS><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    else if (sh.M_tiles <= 4) gemm_stream_ksplit_kernel<4, kSplitNG, 4, kSplitKS><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    else gemm_stream_ksplit_kernel<6, kSplitNG, 2, kSplitKS><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
 }
 
-// The same kernel for narrow models (N up to 2048) from 33 to 128 rows: blocks of 64 rows and one, two or four n-tiles, so
+// The same kernel for narrow models (N up to 2048 from 33 to 128 rows, up to 1024 from 129 to 256): blocks of 64 rows and one, two or four n-tiles, so
 // that four k-slices of every block make up to 256 workgroups, and as many ring stages as a wave has k-tiles where that is two
 // or three.  At d = 1024, d_ff = 3072 and 128 rows it replaces the tile kernel on 32 and 64 workgroups and its merge pass:
-// O 6.7 + 3.7, down 9.0 + 3.7 us before (blocks of all 128 rows and one n-tile: 7.4 and 9.7 us).
+// O 6.7 + 3.7, down 9.0 + 3.7 us before, 7.3 and 8.5 now (blocks of all 128 rows and one n-tile: 7.4 and 9.7 us); at 192 rows
+// 7.6 + 4.4 and 11.6 + 4.4 before, 9.3 and 11.7 now.
 static int ksplit_narrow_ng(GemmShape sh, Workspace ws) {
-    if (sh.M_tiles <= 2 || sh.M_tiles > 8 || sh.K_tiles % (kSplitKS * WK) != 0) return 0;
-    const int rb = (sh.M_tiles + 3) / 4, ng = sh.N_tiles <= 64 ? rb : sh.N_tiles <= 128 ? 2 * rb : 0;
+    if (sh.M_tiles <= 2 || sh.M_tiles > 16 || sh.K_tiles % (kSplitKS * WK) != 0) return 0;
+    const int rb = (sh.M_tiles + 3) / 4, ng = sh.N_tiles <= 64 ? (rb <= 2 ? rb : 4) : sh.N_tiles <= 128 && rb <= 2 ? 2 * rb : 0;
     return ng && ksplit_fits(sh, (sh.N_tiles + ng - 1) / ng * rb, ws) ? ng : 0;
 }
-template <int NG, class Epi>
-static void launch_ksplit_narrow(const u16 *a, const u16 *w, GemmShape sh, Epi e, Workspace ws, hipStream_t s) {
+template <int NG, bool SPAN64 = false>
+static void launch_ksplit_narrow(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, Workspace ws, hipStream_t s) {
     const GemmArgs g = ksplit_args(a, w, sh);
     const dim3 grid((sh.N_tiles + NG - 1) / NG * kSplitKS, (sh.M_tiles + 3) / 4);
     const int kw = sh.K_tiles / (kSplitKS * WK);
-    if (kw % 3 == 0) gemm_stream_ksplit_kernel<4, NG, 3, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else if (kw % 2 == 0) gemm_stream_ksplit_kernel<4, NG, 2, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else gemm_stream_ksplit_kernel<4, NG, 1, kSplitKS, Epi><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    if (kw % 3 == 0) gemm_stream_ksplit_kernel<4, NG, 3, kSplitKS, true, SPAN64><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    else if (kw % 2 == 0) gemm_stream_ksplit_kernel<4, NG, 2, kSplitKS, true, SPAN64><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    else gemm_stream_ksplit_kernel<4, NG, 1, kSplitKS, true, SPAN64><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
 }
 
 // The persistent streaming kernel for up to 128 rows: MT row tiles per wave (2, 4, 6 or 8: 32-row steps),
@@ -148,8 +164,26 @@ static void stream_by_rows(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, 
 }
 
 // workgroup shapes of the tile kernel: (waves, n-tiles per wave, ring depth)
-struct TileCfg { int nw, ngw, max_wgs; };
-static TileCfg tile_cfg(int m_tiles) { return m_tiles > 8 ? TileCfg{8, 2, 256} : TileCfg{8, 1, 256}; }
+struct TileCfg { int nw, ngw; };
+static TileCfg tile_cfg(int m_tiles) { return m_tiles > 8 ? TileCfg{8, 2} : TileCfg{8, 1}; }
+
+// K slices of the tile kernel: fewest microseconds by a model of its two launches.  A compute unit takes in about 52 GB/s
+// of operands, one block and k-tile being 8 + per_wg KiB, so a launch takes as long as its fullest compute unit has blocks
+// and k-tiles; every slice costs 8 bytes per output (written and read once more, at about 5 TB/s), and the epilogue runs in a
+// second launch (5 us) or, unsplit, on the few compute units that own a block (6 us).
+// (Slices need not divide K.  640 rows of the 8B shape are 80 blocks: three slices on 240 workgroups instead of two on 160.)
+static int tile_slices(GemmShape sh, int blocks, int per_wg, Workspace ws) {
+    const double t_tile = (8 + per_wg) * 1024 / 52e3, t_slice = (double)sh.M_tiles * sh.N_tiles * 256 * 8 / 5e6;
+    int best = 1;
+    double best_us = 0;
+    for (int ks = 1; ks <= 16; ks++) {
+        if (ks > 1 && (sh.K_tiles / ks < 8 || (size_t)ks * sh.M_tiles * sh.N_tiles * 1024 > ws.partial_bytes)) break;
+        const int rounds = (blocks * ks + kStreamWGs - 1) / kStreamWGs;
+        const double us = rounds * ((double)sh.K_tiles / ks) * t_tile + (ks > 1 ? ks * t_slice + 5.0 : 6.0);
+        if (ks == 1 || us < best_us) { best = ks; best_us = us; }
+    }
+    return best;
+}
 
 template <class Epi>
 static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, Workspace ws, bool may_split,
@@ -162,10 +196,7 @@ static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
     const TileCfg c = tile_cfg(sh.M_tiles);
     const int per_wg = c.nw * c.ngw;
     g.n_blocks = (sh.N_tiles + per_wg - 1) / per_wg;
-    int ks = 1;
-    while (may_split && g.n_blocks * m_blocks * ks * 2 <= c.max_wgs && sh.K_tiles % (ks * 2) == 0 &&
-           sh.K_tiles / (ks * 2) >= 8 && (size_t)(ks * 2) * sh.M_tiles * sh.N_tiles * 1024 <= ws.partial_bytes)
-        ks *= 2;
+    const int ks = may_split ? tile_slices(sh, g.n_blocks * m_blocks, per_wg, ws) : 1;
     g.KS = ks;
     dim3 grid(g.n_blocks * ks, m_blocks);
     // (8 waves x 1 n-tile, ring of 8) for the multi-draft step, (8 x 2, ring of 4) for compute-bound shapes:
@@ -275,8 +306,10 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     // gate/up projection together, 1.5 % at 64 rows, 0.5 % at 96.)
     const int ng = stream_ng(sh.N_tiles, 3, false);
     // (a narrow model's 97 to 128 rows: blocks of 32 rows and three n-tiles read 160 instead of 288 KB per compute unit at
-    // d = 1024: 10.4 -> 7.2 us; gate/up below: 64 rows and three n-tiles, 10.9 -> 8.5 us)
+    // d = 1024: 10.4 -> 7.2 us; gate/up below: 64 rows and three n-tiles, 10.9 -> 8.5 us.  129 to 256 rows: blocks of 64 rows,
+    // QKV 22.7 -> 9.8 us and gate/up 22.9 -> 10.6 us at 192 rows against the split tile kernel and its merge pass)
     if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 1) launch_stream<2, 3, 4, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles > 8 && sh.M_tiles <= 16 && ng == 1) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 2) stream_by_rows<2, 2>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
@@ -306,6 +339,7 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
     if (const int ng = ksplit_narrow_ng(sh, ws)) {
         if (ng == 1) launch_ksplit_narrow<1>(a, w, sh, e, ws, s);
         else if (ng == 2) launch_ksplit_narrow<2>(a, w, sh, e, ws, s);
+        else if (no.span == 64) launch_ksplit_narrow<4, true>(a, w, sh, e, ws, s);
         else launch_ksplit_narrow<4>(a, w, sh, e, ws, s);
     }
     else if (sh.M_tiles <= 6 && (long_k || sh.M_tiles > 2) && ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
@@ -322,6 +356,8 @@ void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u1
     EpiSwiGLU e{act, sh.M_tiles, status};
     const int ng = stream_ng(sh.N_tiles, 6, true);
     if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 2) launch_stream<4, 3, 2, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles > 8 && sh.M_tiles <= 16 && ng == 2) launch_stream<4, 6, 2, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles > 8 && sh.M_tiles <= 16 && ng == 1) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 2) stream_by_rows<2, 2>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 3) stream_by_rows<3, 1>(xa, w, sh, ni, e, s);

@@ -335,7 +335,11 @@ __global__ __launch_bounds__(512) void tile_epilogue_kernel(TileArgs g, Epi epi)
         };
         switch (g.KS) {
             case 2: sum(std::integral_constant<int, 2>{}); break;
+            case 3: sum(std::integral_constant<int, 3>{}); break;
             case 4: sum(std::integral_constant<int, 4>{}); break;
+            case 5: sum(std::integral_constant<int, 5>{}); break;
+            case 6: sum(std::integral_constant<int, 6>{}); break;
+            case 7: sum(std::integral_constant<int, 7>{}); break;
             case 8: sum(std::integral_constant<int, 8>{}); break;
             case 16: sum(std::integral_constant<int, 16>{}); break;
             default:
@@ -359,7 +363,11 @@ __global__ __launch_bounds__(512) void tile_epilogue_kernel(TileArgs g, Epi epi)
         };
         switch (g.KS) {
             case 2: sum(std::integral_constant<int, 2>{}); break;
+            case 3: sum(std::integral_constant<int, 3>{}); break;
             case 4: sum(std::integral_constant<int, 4>{}); break;
+            case 5: sum(std::integral_constant<int, 5>{}); break;
+            case 6: sum(std::integral_constant<int, 6>{}); break;
+            case 7: sum(std::integral_constant<int, 7>{}); break;
             case 8: sum(std::integral_constant<int, 8>{}); break;
             default:
                 for (int s = 0; s < g.KS; s++)

@@ -64,3 +64,40 @@ def test_step_by_width(d, f, rows):
             run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "d = %d, %d x %d" % (d, S, b))
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("heads,b,S", [
+    (8, 32, 8),        # 16 row tiles of one sequence: one row tile per workgroup, not the many-row kernel
+    (32, 32, 5),       # 320 one-tile items: two row tiles per workgroup
+    (32, 64, 8),       # 128 rows per workgroup pay again
+    (2, 16, 20),       # single-tile units, few heads that no XCD mapping takes
+])
+def test_step_attention_by_size(heads, b, S):
+    """The three ways to share the attention of a step out, at the sizes between them."""
+    p = Pair(dict(_width(heads * 128, 512), vocab=512, mask_id=511))
+    try:
+        wl = W.decode_workload(p.shape, 150, 100, b, S, 900 + S)
+        cache, oc = run_prefill_case(p, wl.tokens, wl.resp_off, "set-up with %d heads" % heads)
+        run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "%d heads, %d x %d" % (heads, S, b))
+    finally:
+        p.close()
+
+
+@pytest.mark.parametrize("rows", [(9, 16), (3, 64), (13, 16), (8, 32)])
+def test_narrow_step_beyond_128_rows(mid, rows):
+    """129 to 256 rows at d = 1024: row blocks of 64 in the streaming kernels, 64-column sums from the K-split kernel."""
+    S, b = rows
+    wl = W.decode_workload(mid.shape, 60, 90, b, S, 950 + S)
+    cache, oc = run_prefill_case(mid, wl.tokens, wl.resp_off, "set-up")
+    run_step_case(mid, cache, oc, wl.drafts, wl.block_off, 0.9, "%d x %d" % (S, b))
+
+
+@pytest.mark.parametrize("L", [300, 600])
+def test_refresh_with_slices_that_do_not_divide_k(L):
+    """Five and three K slices of the tile kernel at row-block counts that leave a power of two with idle compute units."""
+    p = Pair(dict(_width(4096, 512), vocab=512, mask_id=511))
+    try:
+        wl = W.decode_workload(p.shape, L - 40, 40, 16, 1, 990, batch=1)
+        run_prefill_case(p, wl.tokens, wl.resp_off, "%d positions" % L)
+    finally:
+        p.close()
