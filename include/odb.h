@@ -174,7 +174,8 @@ int odb_model_status(odb_model *m);
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
  * kernels and same results as odb_block_step, but every intermediate buffer lives in a fixed
  * area of ODB_STATIC_SCRATCH_BYTES bytes that is part of the loaded library (one per GPU,
- * held until the process ends); the call itself allocates and frees nothing.
+ * held until the process ends; 32 MiB beside it take the partial sums of split projections, so
+ * that they are added in the order of odb_block_step); the call itself allocates and frees nothing.
  * A step whose rows need more than that area is rejected with ODB_E_UNSUPPORTED before
  * anything is launched (at the 8B shape of the paper's models, d = 4096, d_ff = 12288,
  * vocab = 126464, the area holds steps of up to 128 rows).  All models on one GPU share the

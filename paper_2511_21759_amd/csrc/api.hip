@@ -89,6 +89,18 @@ Plan make_plan(const odb_config &c, int rows_pad, int fresh_rows, int lm_rows_pa
     return p;
 }
 
+// The LM head of 33..176 rows writes its statistics per 8 or 16 n-tiles where its vocabulary is short, per 32 (from 129 rows 16)
+// where it is long.  What a call in the fixed area is said to need counts the long blocks: the others' surplus (at most 0.3 MB)
+// comes out of the 1 MiB that the rule adds to the buffers, so that whether a call fits does not hang on the block's width.
+size_t lm_stats_excess(const odb_config &c, int rows_pad) {
+    const int m_tiles = rows_pad / 16, nt = c.vocab / 16;
+    if (m_tiles <= 2 || m_tiles > 11 || (m_tiles > 8 && nt < 32)) return 0;
+    const int parts = lm_stats_parts(nt, m_tiles), wide = m_tiles <= 8 ? (nt + 31) / 32 : (nt + 15) / 16;
+    if (parts <= wide) return 0;
+    const size_t row = (size_t)rows_pad * 12, over = align_up(row * parts, 256) - align_up(row * wide, 256);
+    return over < (1u << 20) ? over : 1u << 20;
+}
+
 int ensure_scratch(Model &m, size_t bytes, hipStream_t s) {
     if (bytes <= m.scratch_bytes) return ODB_OK;
     HIP_TRY(hipStreamSynchronize(s));
@@ -358,8 +370,7 @@ int static_scratch_ptr(int device, char **out);      // defined behind the array
 // scratch_base == nullptr: the model's own scratch, grown on demand.  Otherwise the call runs in the given area of
 // scratch_bytes bytes and allocates nothing.
 int step_impl(odb_model *mh, const odb_cache *ch, const int32_t *drafts, int block_off, int b, int S, float tau,
-              float *conf, int32_t *argmax, uint8_t *unmask, float *logits, void *stream, char *scratch_base = nullptr,
-              size_t scratch_bytes = 0) {
+              float *conf, int32_t *argmax, uint8_t *unmask, float *logits, void *stream, char *scratch_base = nullptr) {
     if (!mh || !ch || !drafts) return fail(ODB_E_INVALID_ARG, "block_step: NULL handle or drafts");
     Model &m = mh->m;
     const Cache &c = ch->c;
@@ -377,18 +388,19 @@ int step_impl(odb_model *mh, const odb_cache *ch, const int32_t *drafts, int blo
     const int bp = ru(b, 16), bp32 = ru(b, 32), units = c.batch * S, rows_pad = units * bp;
     Plan pl;
     char *base;
+    // What the call needs beside K-split partial sums decides whether the fixed area holds it.  A call that it holds gets the same
+    // room for partial sums there as in the model's own scratch: their number of slices, and with it the order of the
+    // additions, follows from that room, and both entry points promise the same results.
+    const size_t need = make_plan(cfg, rows_pad, units * bp32, rows_pad, true, 0, 0).total + (1u << 20) - lm_stats_excess(cfg, rows_pad);
+    const size_t part = need <= kStaticScratchBytes ? kPartialBytes : kPartialByRows;
     if (scratch_base) {
-        // everything but the K-split partial sums first; they get what is left of the fixed area (the GEMM launchers
-        // split K only as far as the room allows), at most what the growing scratch would give them
-        pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, true, 0, 0);
-        if (pl.total + (1u << 20) > scratch_bytes)
+        if (need > kStaticScratchBytes)
             return fail(ODB_E_UNSUPPORTED, "block_step_static: %d rows of this model need %zu bytes of scratch, the fixed "
-                        "area holds %zu", rows_pad, pl.total + (1u << 20), scratch_bytes);
-        size_t part = (scratch_bytes - pl.total) / 256 * 256;
-        pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, true, 0, part < kPartialBytes ? part : kPartialBytes);
+                        "area holds %zu", rows_pad, need, kStaticScratchBytes);
+        pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, true, 0, part);
         base = scratch_base;
     } else {
-        pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, logits == nullptr);
+        pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, logits == nullptr, 0, part);
         int rc = ensure_scratch(m, pl.total, s);
         if (rc) return rc;
         base = (char *)m.scratch;
@@ -1022,8 +1034,7 @@ int odb_block_step_static(odb_model *m, const odb_cache *c, const int32_t *draft
     char *base = nullptr;
     int rc = static_scratch_ptr(m->m.device, &base);      // a table look-up after model creation
     if (rc) return rc;
-    return step_impl(m, c, drafts_dev, block_off, b, S, tau, conf_dev, argmax_dev, unmask_dev, nullptr, stream, base,
-                     kStaticScratchBytes);
+    return step_impl(m, c, drafts_dev, block_off, b, S, tau, conf_dev, argmax_dev, unmask_dev, nullptr, stream, base);
 }
 
 }  // extern "C"
@@ -1032,7 +1043,8 @@ int odb_block_step_static(odb_model *m, const odb_cache *c, const int32_t *draft
 // Device memory that exists without any allocation call: every GPU the library runs on holds its own copy of
 // this array at its own address.  In host code the name `scratch` is only a handle for hipGetSymbolAddress;
 // the address it yields (per device, with that device current) is what kernels and copies are given.
-static __device__ __align__(256) unsigned char scratch[ODB_STATIC_SCRATCH_BYTES];
+// (Behind the area itself, room for the K-split partial sums.)
+static __device__ __align__(256) unsigned char scratch[ODB_STATIC_SCRATCH_BYTES + kPartialBytes];
 
 namespace {
 int static_scratch_ptr(int device, char **out) {

@@ -101,3 +101,26 @@ def test_refresh_with_slices_that_do_not_divide_k(L):
         run_prefill_case(p, wl.tokens, wl.resp_off, "%d positions" % L)
     finally:
         p.close()
+
+
+# ---- the fixed scratch area: the same bits as the growing one, up to its limit ------------------------------------------
+
+@pytest.mark.parametrize("d,f,vocab,b,S", [
+    (1024, 117248, 32768, 16, 8),      # exactly at the limit with LM statistics per 32 n-tiles; they are written per 8
+    (1536, 6144, 4096, 32, 11),        # 352 rows: more K slices than the rest of the area would hold
+])
+def test_static_scratch_step_adds_in_the_same_order(d, f, vocab, b, S):
+    import numpy as np
+    from paper_2511_21759_amd import binding as B
+    from test_zz_no_alloc import compare, cuda_i32
+    shape = dict(_width(d, f), vocab=vocab, mask_id=vocab - 1)
+    model = B.odb_model_create(shape)
+    try:
+        B.odb_model_init_random(model, W.WEIGHT_SEED, W.WEIGHT_STD)
+        wl = W.decode_workload(shape, 40, 90, b, S, 700 + S)
+        cache = B.odb_cache_create(model, 1, wl.tokens.shape[1])
+        B.odb_prefill(model, cache, cuda_i32(wl.tokens), wl.resp_off)
+        compare(model, cache, np.ascontiguousarray(wl.drafts), wl.block_off, 0.9, "d %d, d_ff %d, %d rows" % (d, f, b * S))
+        B.odb_cache_destroy(cache)
+    finally:
+        B.odb_model_destroy(model)
