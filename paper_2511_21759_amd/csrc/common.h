@@ -49,9 +49,14 @@ __device__ inline u16 f2h(float x) {           // binary16, round to nearest eve
 // beyond the binary16 range (or a NaN) is reported instead: bit kStatusSaturated of the model's status word is set
 // and odb_model_status turns it into an error.  Rare path: one compare per four values otherwise.
 constexpr unsigned kStatusSharedOverflow = 2u, kStatusSaturated = 4u;
+// (the maximum that hands a NaN on: fmaxf returns its other operand, and one NaN beside three finite values would pass)
+__device__ __forceinline__ bool out_of_f16(float a, float b, float c, float d) {
+    const float m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(a), fabsf(b)),
+                                                  __builtin_elementwise_maximum(fabsf(c), fabsf(d)));
+    return !(m <= 65504.f);
+}
 __device__ __forceinline__ void note_saturation(unsigned *status, float a, float b, float c, float d) {
-    const float m = fmaxf(fmaxf(fabsf(a), fabsf(b)), fmaxf(fabsf(c), fabsf(d)));
-    if (status && !(m <= 65504.f)) atomicOr(status, kStatusSaturated);
+    if (status && out_of_f16(a, b, c, d)) atomicOr(status, kStatusSaturated);
 }
 __device__ inline float h2f(u16 b) {
     return (float)__builtin_bit_cast(_Float16, b);
@@ -74,10 +79,6 @@ __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
     v.x = pack2_inrange(__builtin_amdgcn_fmed3f(a, -65504.f, 65504.f), __builtin_amdgcn_fmed3f(b, -65504.f, 65504.f));
     v.y = pack2_inrange(__builtin_amdgcn_fmed3f(c, -65504.f, 65504.f), __builtin_amdgcn_fmed3f(d, -65504.f, 65504.f));
     return v;
-}
-// The test of note_saturation without its branch, for epilogues that collect it over their tiles and report once.
-__device__ __forceinline__ bool out_of_f16(float a, float b, float c, float d) {
-    return !(fmaxf(fmaxf(fabsf(a), fabsf(b)), fmaxf(fabsf(c), fabsf(d))) <= 65504.f);
 }
 
 __device__ inline frag_t ld_frag(const u16 *p) {

@@ -846,6 +846,45 @@ def test_out_of_range_activations_are_reported_not_clamped_in_silence(tiny):
         p.close()
 
 
+@pytest.mark.parametrize("tensor,layer", [("G1", 0), ("G2", 0), ("G1", 1), ("GF", 0)])
+def test_one_nan_among_finite_activations_is_reported(tensor, layer):
+    """One NaN element in a gain makes one channel of the next norm's input NaN, beside finite neighbours.  Every kernel
+    that writes such an input has to report it: the embedding, and the residual epilogues of the streaming (16 rows),
+    K-split (48, 128), tile (144) and LDS-ring (640 rows) kernels, and the compacting norm of a refresh."""
+    shape = dict(n_layers=2, d_model=2048, n_heads=16, head_dim=128, d_ff=2048, vocab=512, rope_base=10000.0,
+                 rms_eps=1e-5, mask_id=511)
+    m = B.odb_model_create(shape)
+    try:
+        B.odb_model_init_random(m, W.WEIGHT_SEED, W.WEIGHT_STD)
+        # embeddings of deviation 64: what the stand-in for the NaN (-65504) adds further on stays within the range
+        rng = np.random.default_rng(3)
+        emb = rng.normal(0, 64, 512 * 2048).astype(np.float32).view(np.uint32)
+        B.odb_model_set_tensor(m, B.T_EMBED, 0, (emb >> 16).astype(np.uint16))
+        wl = W.decode_workload(shape, 300, 90, 16, 40, 43)
+        cache = B.odb_cache_create(m, 1, 390)
+        tok, drafts = cuda_i32(wl.tokens), cuda_i32(wl.drafts)
+        tid = getattr(B, "T_" + tensor)
+        clean, bad = np.full(2048, 0x3F80, np.uint16), np.full(2048, 0x3F80, np.uint16)
+        bad[5] = 0x7FC0
+        for S in (1, 3, 8, 9, 40, 0):
+            def call():
+                if S == 0:
+                    B.odb_prefill(m, cache, tok, wl.resp_off)
+                else:
+                    B.odb_block_step(m, cache, drafts[:, :S].contiguous(), wl.block_off, 0.9)
+            B.odb_prefill(m, cache, tok, wl.resp_off)
+            call()
+            B.odb_model_status(m)
+            B.odb_model_set_tensor(m, tid, layer, bad)
+            call()
+            with pytest.raises(B.OdbError, match="binary16"):
+                B.odb_model_status(m)
+            B.odb_model_set_tensor(m, tid, layer, clean)
+        B.odb_cache_destroy(cache)
+    finally:
+        B.odb_model_destroy(m)
+
+
 # ------------------------------------------------------------------ options, allocator
 
 def test_k_split_switch_routes_to_the_kernels_without_an_exchange():
