@@ -90,15 +90,16 @@ Plan make_plan(const odb_config &c, int rows_pad, int fresh_rows, int lm_rows_pa
 }
 
 // The LM head of 33..176 rows writes its statistics per 8 or 16 n-tiles where its vocabulary is short, per 32 (from 129 rows 16)
-// where it is long.  What a call in the fixed area is said to need counts the long blocks: the others' surplus (at most 0.3 MB)
-// comes out of the 1 MiB that the rule adds to the buffers, so that whether a call fits does not hang on the block's width.
+// where it is long.  What a call in the fixed area is said to need counts the long blocks, so that whether a call fits does not
+// hang on the block's width: the others' surplus comes out of the 1 MiB that the rule adds to the buffers.  It is at most
+// 0.3 MB up to 128 rows (vocabularies up to 32768) and 0.55 MB up to 176 rows (narrow blocks up to 65536 only).
 size_t lm_stats_excess(const odb_config &c, int rows_pad) {
     const int m_tiles = rows_pad / 16, nt = c.vocab / 16;
     if (m_tiles <= 2 || m_tiles > 11 || (m_tiles > 8 && nt < 32)) return 0;
     const int parts = lm_stats_parts(nt, m_tiles), wide = m_tiles <= 8 ? (nt + 31) / 32 : (nt + 15) / 16;
     if (parts <= wide) return 0;
-    const size_t row = (size_t)rows_pad * 12, over = align_up(row * parts, 256) - align_up(row * wide, 256);
-    return over < (1u << 20) ? over : 1u << 20;
+    const size_t row = (size_t)rows_pad * 12;
+    return align_up(row * parts, 256) - align_up(row * wide, 256);
 }
 
 int ensure_scratch(Model &m, size_t bytes, hipStream_t s) {

@@ -265,10 +265,8 @@ static BigChoice big_choice(GemmShape sh, bool may_192 = true) {
 static bool use_big(GemmShape sh, bool may_192 = true) { return big_choice(sh, may_192).wn != 0; }
 
 template <class Epi>
-static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
-    constexpr bool may_192 = !is_resid<Epi>::value;
-    const BigChoice c = big_choice(sh, may_192);
-    if constexpr (may_192) {
+static void launch_big_as(BigChoice c, const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
+    if constexpr (!is_resid<Epi>::value) {
         if (c.wn == 3) {
             if (c.mbt == 8) launch_big_wn<3, Epi, 8>(a, w, sh, ni, e, s);
             else launch_big_wn<3, Epi, 16>(a, w, sh, ni, e, s);
@@ -282,6 +280,10 @@ static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi 
         if (c.mbt == 8) launch_big_wn<4, Epi, 8>(a, w, sh, ni, e, s);
         else launch_big_wn<4, Epi, 16>(a, w, sh, ni, e, s);
     }
+}
+template <class Epi>
+static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
+    launch_big_as(big_choice(sh, !is_resid<Epi>::value), a, w, sh, ni, e, s);
 }
 
 // The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles.
@@ -383,7 +385,13 @@ static int lm_ng(int n_tiles, int m_tiles) {
 // Beyond 128 rows the LM head of a long vocabulary always runs on the LDS-ring kernel, 256 columns wide where no other width is chosen
 // (129..191 rows leave part of a 256-row block empty, and still measure 283 us against 427 us on the tile kernel:
 // the vocabulary is long enough to be bound by the weight stream either way)
-static int lm_big_width(GemmShape sh) { const int wn = big_choice(sh).wn; return wn || sh.N_tiles < 32 ? wn : 4; }
+// At 144 to 176 rows blocks narrower than that serve vocabularies whose 256-column blocks leave compute units idle, up to 65536;
+// beyond, their statistics (twice as many, over 1 MiB) would not fit the room that lm_stats_excess counts on.
+static BigChoice lm_big(GemmShape sh) {
+    const BigChoice c = big_choice(sh);
+    if (sh.N_tiles < 32 || (c.wn && (sh.M_tiles >= 12 || sh.N_tiles <= 16 * kStreamWGs))) return c;
+    return BigChoice{16, 4};
+}
 // From 33 to 128 rows the LM head runs on the LDS-ring kernel as one row block, 64 * lm_one_wn columns wide: the widest block
 // that makes no more than a round of workgroups shorter (see launch_gemm_lmstats).
 static bool lm_one_block(int m_tiles) { return m_tiles > 2 && m_tiles <= 8; }
@@ -395,7 +403,7 @@ int lm_stats_parts(int n_tiles, int m_tiles) {
         const int groups = (n_tiles + ng - 1) / ng;
         return (groups < kStreamWGs ? groups : kStreamWGs) * ng;
     }
-    if (const int wn = lm_big_width(GemmShape{m_tiles, n_tiles, 0})) return (n_tiles + 4 * wn - 1) / (4 * wn);
+    if (const int wn = lm_big(GemmShape{m_tiles, n_tiles, 0}).wn) return (n_tiles + 4 * wn - 1) / (4 * wn);
     const TileCfg c = tile_cfg(m_tiles);
     return (n_tiles + c.nw * c.ngw - 1) / (c.nw * c.ngw);
 }
@@ -420,8 +428,7 @@ void launch_gemm_lmstats(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, f
             default: launch_big_wn<8, TileLMStats, 8>(xa, w, sh, ni, e, s);
         }
     }
-    else if (use_big(sh)) launch_big(xa, w, sh, ni, TileLMStats{stats, parts}, s);
-    else if (lm_big_width(sh)) launch_big_wn<4>(xa, w, sh, ni, TileLMStats{stats, parts}, s);
+    else if (lm_big(sh).wn) launch_big_as(lm_big(sh), xa, w, sh, ni, TileLMStats{stats, parts}, s);
     else launch_tile(xa, w, sh, ni, TileLMStats{stats, parts}, ws, false, s);
 }
 void launch_gemm_store(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, float *out, int units, int rpu_pad,

@@ -108,6 +108,7 @@ def test_refresh_with_slices_that_do_not_divide_k(L):
 @pytest.mark.parametrize("d,f,vocab,b,S", [
     (1024, 117248, 32768, 16, 8),      # exactly at the limit with LM statistics per 32 n-tiles; they are written per 8
     (1536, 6144, 4096, 32, 11),        # 352 rows: more K slices than the rest of the area would hold
+    (1024, 79104, 160000, 16, 11),     # 176 rows at the limit with LM statistics per 16 n-tiles, none narrower
 ])
 def test_static_scratch_step_adds_in_the_same_order(d, f, vocab, b, S):
     import numpy as np
