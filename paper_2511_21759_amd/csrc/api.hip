@@ -40,8 +40,9 @@ void *dev_alloc(const Model &m, size_t bytes) {
     if (bytes == 0) bytes = 256;
     if (m.has_alloc) return m.alloc.alloc(bytes, m.alloc.user);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
-    return p;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();        // reported by the NULL, not by the next launch that is checked
+    return nullptr;
 }
 
 void dev_free(const Model &m, void *p) {
@@ -62,8 +63,8 @@ struct Plan {
 };
 
 // part_bytes: room for K-split partial sums (the GEMM launchers split K only as far as it allows)
-Plan make_plan(const odb_config &c, int rows_pad, int fresh_rows, int lm_rows_pad, bool need_stats, size_t extra_bytes = 0,
-               size_t part_bytes = kPartialByRows) {
+Plan make_plan(const odb_config &c, int rows_pad, int fresh_rows, int lm_rows_pad, bool need_stats, size_t extra_bytes,
+               size_t part_bytes) {
     Plan p;
     if (part_bytes == kPartialByRows) {
         const size_t four = (size_t)rows_pad * c.d_model * 16;
@@ -115,6 +116,21 @@ int ensure_scratch(Model &m, size_t bytes, hipStream_t s) {
     HIP_TRY(hipMemsetAsync(m.scratch, 0, want, s));
     HIP_TRY(hipStreamSynchronize(s));
     return ODB_OK;
+}
+
+// Plans a call's buffers - make(room for partial sums) - and sees to it that the scratch area holds them.  Room beyond 32 MiB
+// only makes a call faster: where it cannot be allocated the model does without from then on (its projections are split
+// into fewer slices, whose sums are added in another order).
+template <class F>
+int plan_scratch(Model &m, F make, Plan &pl, hipStream_t s) {
+    pl = make(m.least_partials ? kPartialBytes : kPartialByRows);
+    int rc = ensure_scratch(m, pl.total, s);
+    if (rc == ODB_E_NOMEM && pl.part_bytes > kPartialBytes) {
+        m.least_partials = true;
+        pl = make(kPartialBytes);
+        rc = ensure_scratch(m, pl.total, s);
+    }
+    return rc;
 }
 
 int check_config(const odb_config *c) {
@@ -345,8 +361,8 @@ int prefill_impl(odb_model *mh, odb_cache *ch, const int32_t *tokens, int L, int
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(m.device));
     const int lp = ru(L, 16), rows_pad = c.batch * lp, lm_rows = c.batch * (L - resp_off);
-    Plan pl = make_plan(m.cfg, rows_pad, 0, ru(lm_rows, 16), logits == nullptr);
-    int rc = ensure_scratch(m, pl.total, s);
+    Plan pl;
+    int rc = plan_scratch(m, [&](size_t room) { return make_plan(m.cfg, rows_pad, 0, ru(lm_rows, 16), logits == nullptr, 0, room); }, pl, s);
     if (rc) return rc;
     RowMap rm{c.batch, lp, L};
     c.length = L;
@@ -401,8 +417,9 @@ int step_impl(odb_model *mh, const odb_cache *ch, const int32_t *drafts, int blo
         pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, true, 0, part);
         base = scratch_base;
     } else {
-        pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, logits == nullptr, 0, part);
-        int rc = ensure_scratch(m, pl.total, s);
+        int rc = plan_scratch(m, [&](size_t room) {
+            return make_plan(cfg, rows_pad, units * bp32, rows_pad, logits == nullptr, 0, part == kPartialBytes ? part : room);
+        }, pl, s);
         if (rc) return rc;
         base = (char *)m.scratch;
     }
@@ -679,8 +696,10 @@ static int step_shared_impl(odb_model *mh, const odb_cache *ch, const int32_t *d
     const int fresh_rows = c.batch * (ru(sm.bp, 32) + ru(sm.mp, 32));
     const size_t tables = align_up((size_t)rows_pad * 4, 256) * 3 + align_up((size_t)c.batch * 4, 256) +
                           align_up((size_t)c.batch * 8, 256);
-    Plan pl = make_plan(cfg, rows_pad, fresh_rows, rows_pad, logits == nullptr, tables);
-    int rc = ensure_scratch(m, pl.total, s);
+    Plan pl;
+    int rc = plan_scratch(m, [&](size_t room) {
+        return make_plan(cfg, rows_pad, fresh_rows, rows_pad, logits == nullptr, tables, room);
+    }, pl, s);
     if (rc) return rc;
     char *base = (char *)m.scratch, *t = base + pl.extra;
     sm.rowtok = (int32_t *)t; t += align_up((size_t)rows_pad * 4, 256);

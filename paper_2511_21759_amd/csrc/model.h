@@ -32,6 +32,7 @@ struct Model {
     // scratch, grown on demand (see api.hip)
     void *scratch;
     size_t scratch_bytes;
+    bool least_partials;       // no more room for K-split partial sums than every call has (see plan_scratch)
     unsigned *counters;        // [0] status word (kStatus* bits), [1024..2048) arrival counters of the K-split GEMM
     bool ksplit_reduce;        // the K-split streaming GEMM with its in-kernel reduction may be used (ODB_OPT_KSPLIT_REDUCE)
     int n_cu;

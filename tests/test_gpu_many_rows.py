@@ -125,3 +125,41 @@ def test_static_scratch_step_adds_in_the_same_order(d, f, vocab, b, S):
         B.odb_cache_destroy(cache)
     finally:
         B.odb_model_destroy(model)
+
+
+def test_scratch_that_cannot_grow_past_the_least_room():
+    """A refresh of 1300 positions would take 86 MB for partial sums; with memory for 32 MiB of them it runs all the same, and so
+    do the calls behind it."""
+    import numpy as np
+    import torch
+    from paper_2511_21759_amd import binding as B
+    shape = dict(_width(4096, 512), vocab=512, mask_id=511)
+    wl = W.decode_workload(shape, 1200, 100, 16, 3, 77)
+    tok, dr = (torch.from_numpy(np.ascontiguousarray(x, np.int32)).cuda() for x in (wl.tokens, wl.drafts))
+    out = []
+    for limit in (None, 120 << 20):
+        model = B.odb_model_create(shape)
+        B.odb_model_init_random(model, W.WEIGHT_SEED, W.WEIGHT_STD)
+        cache = B.odb_cache_create(model, 1, 1300)
+        whole, refused = torch.empty, []
+        if limit:
+            def empty(n, **kw):
+                if isinstance(n, int) and n > limit:
+                    refused.append(n)
+                    raise RuntimeError("out of memory")
+                return whole(n, **kw)
+            torch.empty = empty
+        try:
+            a = [t.clone() for t in B.odb_prefill(model, cache, tok, wl.resp_off)]
+            n_refused = len(refused)
+            a += [t.clone() for t in B.odb_block_step(model, cache, dr, wl.block_off, 0.9)]
+            B.odb_prefill(model, cache, tok, wl.resp_off)
+            B.odb_model_status(model)
+            assert len(refused) == n_refused == (1 if limit else 0), "asked once, not on every call"
+        finally:
+            torch.empty = whole
+            B.odb_cache_destroy(cache)
+            B.odb_model_destroy(model)
+        out.append(a)
+    for i in (0, 2):
+        assert torch.allclose(torch.log(out[0][i]), torch.log(out[1][i]), atol=2e-2)
