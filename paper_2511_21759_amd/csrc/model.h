@@ -78,7 +78,7 @@ struct NormOut { u16 *hb; float *ssq; const float *gain; int n_ssq; unsigned *st
 // `valid` are real.
 struct RowMap { int units, rpu_pad, valid; };
 // h = E[token] (fp32); with a NormOut also hb = bf16(h * gain) and the partial sums of squares.  Clears zero_bytes (a
-// multiple of 16, below 2^35) at `zero` on the way: a step's fresh V, which a launch of its own would clear in 2 to 5 us
+// multiple of 16) at `zero` on the way: a step's fresh V, which a launch of its own would clear in 2 to 5 us
 void launch_embed(const Model &m, const int32_t *tokens, RowMap rm, float *h, NormOut no, void *zero, size_t zero_bytes, hipStream_t s);
 // xa = bf16(rmsnorm(h) * gain) in tile-major [d/32][mt_total][512]; if `compact`, destination
 // row j = u*(valid-skip) + (i-skip) for source row (u, i >= skip), else the same row.

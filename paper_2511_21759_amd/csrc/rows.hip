@@ -5,8 +5,8 @@
 namespace odb {
 
 __global__ void embed_kernel(const u16 *embed, const int32_t *tokens, RowMap rm, int d, int vocab, float *h,
-                             NormOut no, int mt_total, f32x4 *zero, int n_zero) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                             NormOut no, int mt_total, f32x4 *zero, size_t n_zero) {
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += (size_t)gridDim.x * blockDim.x) zero[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     embed_row(blockIdx.x, embed, tokens, rm, d, vocab, h, no, mt_total);
 }
 
@@ -14,7 +14,7 @@ void launch_embed(const Model &m, const int32_t *tokens, RowMap rm, float *h, No
     int rows = rm.units * rm.rpu_pad;
     int threads = m.cfg.d_model / 16 < 256 ? 64 : 256;
     embed_kernel<<<dim3(rows), threads, 0, s>>>(m.w[PK_EMBED], tokens, rm, m.cfg.d_model, m.cfg.vocab, h, no,
-                                                rows / 16, (f32x4 *)zero, (int)(zero_bytes / 16));
+                                                rows / 16, (f32x4 *)zero, zero_bytes / 16);
 }
 
 __device__ inline float wave_sum(float v) {
