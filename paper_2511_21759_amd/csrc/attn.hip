@@ -2,6 +2,7 @@
 #include <mutex>
 
 #include "attn_rows.h"
+#include "choose.h"
 
 namespace odb {
 
@@ -53,36 +54,19 @@ void launch_attention(AttnArgs a, hipStream_t s) {
         launch_split<1, 8, true>(a, sc, a.mt_total, s);
         return;
     }
-    // Three ways to share the work out: one row tile per workgroup of eight waves, two row tiles of a unit per workgroup of four
-    // (a K/V tile fetched from L2 then serves 32 rows), or the many-row kernel (it serves 128 or 256 rows, but a wave walks
-    // over all keys).  The fewest microseconds by what they measured at heads of 128 channels, n = 32-key tiles and
-    // r = workgroups per compute unit:
-    //   one tile   8 heads, 8 x 32 rows, n = 19: 8.4 us (many-row: 20.4); 32 heads, 4 x 32 rows, n = 16: 8.6 (two tiles: 10.5),
-    //              8 x 32 rows: 17.4, n = 94: 49.6 (steps only: a refresh gains nothing, r = 2.4, n = 10: 17.3, r = 8, n = 32: 72)
-    //   two tiles  32 heads, 8 x 32 rows, n = 16: 12.2, n = 94: 40.5; refreshes r = 1.25, n = 10: 15.5, r = 1.7, n = 54: 40,
-    //              r = 2.5, n = 20: 31.4, r = 4, n = 32: 55
-    //   many rows  8 x 32 rows, n = 16: 19.1, n = 94: 79.5; refreshes n = 10: 13.2, n = 20: 22.6, n = 32: 35, n = 54: 47
-    const int tiles_per_seq = a.units_per_seq * a.tiles_per_unit, seqs = a.units / a.units_per_seq;
-    const double n = (a.L + 31) / 32;
-    const int items1 = a.units * a.tiles_per_unit, items2 = a.units * ((a.tiles_per_unit + 1) / 2);
-    const double r1 = items1 * a.H / 256.0, r2 = items2 * a.H / 256.0;
-    const double t1 = a.fresh == 0 ? 1e30 : 5.0 + (r1 <= 1.0 ? 0.22 * n : r1 * (2.0 + 0.22 * n));
-    const double t2 = (a.fresh > 0 ? 5.0 : 8.0) + (r2 < 1.0 ? 1.0 : r2) * (2.5 + 0.36 * n);
-    const int wgs4 = seqs * ((tiles_per_seq + 7) / 8) * a.H, wgs8 = seqs * ((tiles_per_seq + 15) / 16) * a.H;
-    // (256 rows per workgroup when that still gives every compute unit a workgroup, else 128)
-    const double t3 = wgs8 >= 256 ? 3.0 + (wgs8 + 255) / 256 * 1.3 * n : 3.0 + (wgs4 + 255) / 256 * 0.95 * n;
-    if (tiles_per_seq >= 16 && (a.fresh == 0 || a.tiles_per_unit % 2 == 0) && t3 <= t1 && t3 <= t2) {
+    const AttentionChoice c = attention_choice(a.dh, a.H, a.L, a.fresh > 0, a.units, a.units_per_seq, a.tiles_per_unit);
+    if (c.way == 3) {
         if (a.dh == 128) {
-            if (wgs8 >= 256) launch_rows<128, 8, 2, 8>(a, sc, s);
+            if (c.rows8) launch_rows<128, 8, 2, 8>(a, sc, s);
             else launch_rows<128, 4, 2, 6>(a, sc, s);
         } else {
-            if (wgs8 >= 256) launch_rows<64, 8, 2, 8>(a, sc, s);
+            if (c.rows8) launch_rows<64, 8, 2, 8>(a, sc, s);
             else launch_rows<64, 4, 2, 6>(a, sc, s);
         }
-    } else if (t1 <= t2) {
-        launch_split<1, 8>(a, sc, items1, s);
+    } else if (c.way == 1) {
+        launch_split<1, 8>(a, sc, a.units * a.tiles_per_unit, s);
     } else {
-        launch_split<2, 4>(a, sc, items2, s);
+        launch_split<2, 4>(a, sc, a.units * ((a.tiles_per_unit + 1) / 2), s);
     }
 }
 
