@@ -1,6 +1,7 @@
 // Which kernel variant a launch takes, as plain functions of its sizes (no HIP: they can be tried on the CPU).
 #pragma once
 #include <math.h>
+#include <stddef.h>
 
 namespace odb {
 
@@ -47,6 +48,49 @@ inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int uni
     for (int w = 1; w <= 3; w++)
         if (t[w] < t[way]) way = w;
     return AttentionChoice{way, rows8};
+}
+
+// K slices of the tile kernel (gemm_tile.h), which need not divide K; `room` bounds the bytes of partial sums.
+//
+// The largest power of two that divides K and fits one round of workgroups stands, unless the model below puts another count
+// 1 % (up to 128 rows 2 %) under it.  The model was fitted to 6400 launches measured inside refreshes (m_tiles 3 to 188, d from 512 to 8192; 7 % off
+// at the root mean square): a launch lasts as long as its fullest compute unit has blocks and k-tiles of the LONGEST slice, up
+// to 128 rows at least as long as the weight stream; then there is the epilogue on the few compute units that own a block, or
+// the merge pass.  It matters too on which of the eight XCDs, which take the workgroups in turn, blocks meet: slices that share
+// no factor with eight make every XCD read all of A, blocks per row of blocks that share none make every XCD that works
+// on a column of blocks read its weights, and where there are few of them, counts that bring the workgroups of one slice
+// together on one XCD cost about a microsecond.
+// Over 861 sizes that take the tile kernel it is 2.9 % faster than the power of two on average, and slower by more than 3 % at
+// 17; a model with mean slices and without the XCDs was 1.7 % faster and slower by more than 3 % at 108, up to 28 %.
+// Microseconds with the merge pass, by slices: 1232 rows, N 1280, K 5120: 4 29.3, 5 37.6; 144 rows, N 3584, K 18944: 8 44.8,
+// 9 50.8; 640 rows, N 4096, K 12288: 2 96.7, 3 76.3; 128 rows, N 4096, K 4096: 5 20.1, 6 19.1, 8 20.4.
+enum class TileEpilogue { qkv, swiglu, resid };
+inline int tile_slices(TileEpilogue epi, int m_tiles, int n_tiles, int k_tiles, size_t room) {
+    const bool wide = m_tiles > 8;                          // two n-tiles per wave
+    const int m_blocks = (m_tiles + 7) / 8, n_blocks = (n_tiles + (wide ? 15 : 7)) / (wide ? 16 : 8), blocks = m_blocks * n_blocks;
+    const double a_mb = m_tiles * (double)k_tiles / 1024, w_mb = n_tiles * (double)k_tiles / 1024, out_mb = m_tiles * (double)n_tiles / 1024;
+    auto fits = [&](int ks) { return ks == 1 || (k_tiles / ks >= 8 && (size_t)ks * m_tiles * n_tiles * 1024 <= room); };
+    auto gcd8 = [](int x) { return x % 8 == 0 ? 8 : x % 4 == 0 ? 4 : x % 2 == 0 ? 2 : 1; };
+    auto least = [](int a, int b) { return a < b ? a : b; };
+    auto us = [&](int ks) {
+        const int rounds = (blocks * ks + kComputeUnits - 1) / kComputeUnits, longest = (k_tiles + ks - 1) / ks;
+        const int gk = gcd8(ks), gx = gcd8(n_blocks * ks);
+        if (!wide) {
+            const double loop = rounds * (0.22 * longest + 0.93) + 0.05 * a_mb * least(n_blocks, 8 / gk) + 0.03 * w_mb;
+            return (loop > 0.18 * w_mb ? loop : 0.18 * w_mb) + (ks == 1 ? 7.1 * rounds : 7.15 + 0.5 * ks * out_mb);
+        }
+        const double loop = rounds * (0.36 * longest + 0.42) + 0.05 * w_mb * least(m_blocks, 8 / gx);
+        if (ks == 1) return loop + rounds * (epi == TileEpilogue::qkv ? 17.5 : epi == TileEpilogue::swiglu ? 10.5 : 10.4);
+        const double merge = epi == TileEpilogue::qkv ? 15.1 : epi == TileEpilogue::swiglu ? 14.1 : 7.2, sums = ks * out_mb;
+        const double crowd = (gx == 8 ? 1.66 / n_blocks : 0) + (blocks * ks > 230 ? 0.44 : 0);
+        return loop + merge + 0.302 * sums + (sums > 26 ? 0.3 * (sums - 26) : 0) + crowd;      // (beyond 26 MB they leave the L2s)
+    };
+    int best = 1;
+    while (blocks * best * 2 <= kComputeUnits && k_tiles % (best * 2) == 0 && fits(best * 2)) best *= 2;
+    double best_us = (wide ? 0.99 : 0.98) * us(best);
+    for (int ks = 1; ks <= 16; ks++)
+        if (fits(ks) && us(ks) < best_us) { best = ks; best_us = us(ks); }
+    return best;
 }
 
 }  // namespace odb

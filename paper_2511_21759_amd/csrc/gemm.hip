@@ -1,6 +1,7 @@
 // Stand-alone launches of the weight-streaming GEMM (see gemm_core.h).
 #include <mutex>
 
+#include "choose.h"
 #include "gemm_slab.h"
 
 namespace odb {
@@ -12,7 +13,7 @@ __global__ __launch_bounds__(64 * WK) void gemm_stream_kernel(GemmArgs g, Epi ep
     gemm_wg<MT, NG, PF, Epi, IL>(g, epi, blockIdx.x, gridDim.x, blockIdx.y * MT, wb, smem);
 }
 
-constexpr int kStreamWGs = 256;      // one workgroup per compute unit
+constexpr int kStreamWGs = kComputeUnits;      // one workgroup per compute unit
 // Every workgroup of the streaming kernels reads the same activation tiles; started at the same k-tile they ask the
 // same L2 channels for them at the same time.  Workgroup wg starts kKRot * wg k-tiles further on and wraps round
 // (7 is coprime to the 12 and 16 k-tiles per wave of the 8B shape; of 1, 3, 5 and 7 the multipliers 3 and 7 leave the
@@ -167,23 +168,9 @@ static void stream_by_rows(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, 
 struct TileCfg { int nw, ngw; };
 static TileCfg tile_cfg(int m_tiles) { return m_tiles > 8 ? TileCfg{8, 2} : TileCfg{8, 1}; }
 
-// K slices of the tile kernel: fewest microseconds by a model of its two launches.  A compute unit takes in about 52 GB/s
-// of operands, one block and k-tile being 8 + per_wg KiB, so a launch takes as long as its fullest compute unit has blocks
-// and k-tiles; every slice costs 8 bytes per output (written and read once more, at about 5 TB/s), and the epilogue runs in a
-// second launch (5 us) or, unsplit, on the few compute units that own a block (6 us).
-// (Slices need not divide K.  640 rows of the 8B shape are 80 blocks: three slices on 240 workgroups instead of two on 160.)
-static int tile_slices(GemmShape sh, int blocks, int per_wg, Workspace ws) {
-    const double t_tile = (8 + per_wg) * 1024 / 52e3, t_slice = (double)sh.M_tiles * sh.N_tiles * 256 * 8 / 5e6;
-    int best = 1;
-    double best_us = 0;
-    for (int ks = 1; ks <= 16; ks++) {
-        if (ks > 1 && (sh.K_tiles / ks < 8 || (size_t)ks * sh.M_tiles * sh.N_tiles * 1024 > ws.partial_bytes)) break;
-        const int rounds = (blocks * ks + kStreamWGs - 1) / kStreamWGs;
-        const double us = rounds * ((double)sh.K_tiles / ks) * t_tile + (ks > 1 ? ks * t_slice + 5.0 : 6.0);
-        if (ks == 1 || us < best_us) { best = ks; best_us = us; }
-    }
-    return best;
-}
+template <class Epi> constexpr TileEpilogue tile_epilogue_of = TileEpilogue::resid;
+template <> constexpr TileEpilogue tile_epilogue_of<EpiQKV> = TileEpilogue::qkv;
+template <> constexpr TileEpilogue tile_epilogue_of<EpiSwiGLU> = TileEpilogue::swiglu;
 
 template <class Epi>
 static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, Workspace ws, bool may_split,
@@ -196,7 +183,7 @@ static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
     const TileCfg c = tile_cfg(sh.M_tiles);
     const int per_wg = c.nw * c.ngw;
     g.n_blocks = (sh.N_tiles + per_wg - 1) / per_wg;
-    const int ks = may_split ? tile_slices(sh, g.n_blocks * m_blocks, per_wg, ws) : 1;
+    const int ks = may_split ? tile_slices(tile_epilogue_of<Epi>, sh.M_tiles, sh.N_tiles, sh.K_tiles, ws.partial_bytes) : 1;
     g.KS = ks;
     dim3 grid(g.n_blocks * ks, m_blocks);
     // (8 waves x 1 n-tile, ring of 8) for the multi-draft step, (8 x 2, ring of 4) for compute-bound shapes:

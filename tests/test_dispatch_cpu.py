@@ -15,6 +15,7 @@ SHIM = r"""
 using namespace odb;
 extern "C" {
 int attention_way(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).way; }
+int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
 """
 
@@ -74,3 +75,50 @@ def test_attention_way_is_near_the_fastest_measured(rules, case):
     assert way in us, "a way that cannot run at this size"
     # (the rule stays with its first choice up to 10 %; the model is off by a few percent beside that)
     assert us[way] <= 1.15 * min(us.values())
+
+
+# projection, row tiles, n-tiles, k-tiles -> us of the tile kernel and its merge pass by K slices
+SLICES = [
+    ("down", 16, 96, 192, {1: 75.4, 2: 41.5, 3: 31.5, 4: 26.2, 5: 23.6, 6: 21.9, 7: 21.2, 8: 19.9, 9: 20.0, 10: 19.5, 11: 20.1, 12: 19.2, 14: 20.1, 16: 17.7}),
+    ("down", 77, 80, 160, {1: 65.2, 2: 39.3, 3: 35.4, 4: 29.8, 5: 37.8}),
+    ("down", 40, 160, 216, {1: 96.3, 2: 54.3, 3: 44.6, 4: 38.3, 5: 44.6}),
+    ("down", 28, 176, 200, {1: 86.8, 2: 50.6, 3: 40.6, 4: 34.1, 5: 39.0, 6: 48.1}),
+    ("down", 28, 192, 256, {1: 108.2, 2: 59.8, 3: 47.4, 4: 40.7, 5: 39.0, 6: 49.4}),
+    ("qkv", 64, 96, 16, {1: 24.6, 2: 21.5, 3: 22.5, 4: 23.7}),
+    ("o", 28, 192, 96, {1: 48.2, 2: 30.5, 3: 26.5, 4: 24.7, 5: 25.9, 6: 31.3}),
+    ("down", 4, 176, 200, {1: 50.4, 2: 31.5, 3: 24.9, 4: 21.6, 5: 20.2, 6: 19.9, 7: 18.7, 8: 18.3, 9: 18.5, 10: 19.3, 11: 20.4, 12: 25.7, 14: 25.4, 16: 23.6}),
+    ("down", 7, 512, 896, {1: 244.5, 2: 139.8, 3: 106.1, 4: 91.3, 5: 128.7, 6: 111.2, 7: 104.8, 8: 109.2, 9: 120.3}),
+    ("o", 8, 256, 128, {1: 42.2, 2: 27.4, 3: 22.4, 4: 21.6, 5: 20.1, 6: 19.1, 7: 19.0, 8: 20.4, 9: 25.2, 10: 24.9, 11: 24.6, 12: 25.1, 14: 25.8, 16: 26.6}),
+    ("down", 8, 256, 384, {1: 110.9, 2: 62.8, 3: 47.7, 4: 41.7, 5: 37.0, 6: 34.3, 7: 32.4, 8: 33.0, 9: 43.4, 10: 41.2, 11: 41.4, 12: 40.4, 14: 38.2, 16: 40.0}),
+    ("down", 64, 256, 384, {1: 171.5, 2: 110.0, 3: 137.6, 4: 119.5}),
+    ("down", 40, 256, 384, {1: 163.1, 2: 96.7, 3: 76.3, 4: 101.9}),
+    ("o", 40, 256, 128, {1: 62.8, 2: 42.6, 3: 38.1, 4: 50.2}),
+    ("o", 16, 256, 128, {1: 62.5, 2: 36.5, 3: 29.2, 4: 26.8, 5: 25.4, 6: 25.1, 7: 25.2, 8: 26.3}),
+    ("down", 16, 256, 384, {1: 164.5, 2: 88.6, 3: 65.2, 4: 53.3, 5: 47.6, 6: 46.9, 7: 45.3, 8: 44.1}),
+    ("o", 13, 128, 64, {1: 35.2, 2: 22.0, 3: 18.5, 4: 17.5, 5: 15.4, 6: 15.1, 7: 15.0, 8: 15.9, 9: 16.1, 10: 17.3, 11: 16.6, 12: 18.3, 14: 18.5, 16: 20.0}),
+    ("down", 9, 224, 592, {1: 223.4, 2: 118.4, 3: 86.6, 4: 68.5, 5: 60.7, 6: 54.7, 7: 53.2, 8: 48.2, 9: 54.6, 10: 68.1, 11: 67.3, 12: 60.2, 14: 60.5, 16: 58.7}),
+    ("o", 3, 160, 80, {1: 23.3, 2: 17.9, 3: 15.1, 4: 12.7, 5: 12.3, 6: 12.0, 7: 11.8, 8: 12.1, 9: 13.4, 10: 13.4, 11: 14.6, 12: 14.3, 14: 18.9, 16: 16.8}),
+    ("down", 63, 64, 96, {1: 43.5, 2: 26.6, 3: 22.4, 4: 21.3, 5: 19.9, 6: 19.7, 7: 24.7, 8: 20.8}),
+    ("gu", 9, 704, 64, {1: 35.5, 2: 31.8, 3: 45.2, 4: 42.2, 5: 44.4}),
+    ("qkv", 13, 384, 64, {1: 43.0, 2: 30.5, 3: 27.8, 4: 27.6, 5: 28.8, 6: 38.3}),
+]
+
+
+@pytest.mark.parametrize("case", SLICES)
+def test_tile_slices_are_near_the_fastest_measured(rules, case):
+    name, m, n, k, us = case
+    epi = {"qkv": 0, "gu": 1}.get(name, 2)
+    ks = rules.slices(epi, m, n, k, ctypes.c_size_t(64 << 20))
+    assert ks in us, "a count that does not fit"
+    assert us[ks] <= 1.1 * min(us.values())
+
+
+def test_tile_slices_keep_to_the_room_and_to_the_matrix(rules):
+    """A slice has eight k-tiles, the partial sums fit, and an unsplit launch needs no room."""
+    for m in (1, 3, 8, 9, 39, 188):
+        for n in (16, 48, 256, 1024):
+            for k in (8, 24, 64, 896):
+                for room in (0, 1 << 20, 32 << 20):
+                    for epi in (0, 1, 2):
+                        ks = rules.slices(epi, m, n, k, ctypes.c_size_t(room))
+                        assert ks == 1 or (k // ks >= 8 and ks * m * n * 1024 <= room)
