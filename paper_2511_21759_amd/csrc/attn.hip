@@ -38,11 +38,10 @@ static void launch_rows(AttnArgs a, float sc, hipStream_t s) {
     attn_rows_kernel<DH, NW, QTW, NS><<<grid, 64 * NW, attn_rows_smem_bytes<DH, NS>(), s>>>(a, sc);
 }
 
-// QT row tiles of one unit per workgroup, its NW waves split the keys.  The work items of a head are kept on one XCD where the heads
-// allow it (8.7 -> 8.4 us at 32 rows; 11.8 -> 11.3 us at four drafts, a quarter of the K/V fetches).
+// QT row tiles of one unit per workgroup, its NW waves split the keys.
 template <int QT, int NW, bool SHARED = false>
-static void launch_split(AttnArgs a, float sc, int items, hipStream_t s) {
-    if (a.dh == 128 && a.H % 8 == 0 && items > 1) attn_xcd_kernel<128, QT, NW, SHARED><<<dim3(items * a.H), 64 * NW, 0, s>>>(a, sc, items);
+static void launch_split(AttnArgs a, float sc, int items, bool one_xcd, hipStream_t s) {
+    if (one_xcd) attn_xcd_kernel<128, QT, NW, SHARED><<<dim3(items * a.H), 64 * NW, 0, s>>>(a, sc, items);
     else if (a.dh == 128) attn_kernel<128, QT, NW, SHARED><<<dim3(items, a.H), 64 * NW, 0, s>>>(a, sc);
     else attn_kernel<64, QT, NW, SHARED><<<dim3(items, a.H), 64 * NW, 0, s>>>(a, sc);
 }
@@ -51,7 +50,7 @@ void launch_attention(AttnArgs a, hipStream_t s) {
     const float sc = 1.4426950408889634f / sqrtf((float)a.dh);
     if (a.split_tile > 0) {
         // decoded-share step: one row tile per workgroup, block_0 tiles first, then the speculative units'
-        launch_split<1, 8, true>(a, sc, a.mt_total, s);
+        launch_split<1, 8, true>(a, sc, a.mt_total, a.dh == 128 && a.H % 8 == 0 && a.mt_total > 1, s);
         return;
     }
     const AttentionChoice c = attention_choice(a.dh, a.H, a.L, a.fresh > 0, a.units, a.units_per_seq, a.tiles_per_unit);
@@ -64,9 +63,9 @@ void launch_attention(AttnArgs a, hipStream_t s) {
             else launch_rows<64, 4, 2, 6>(a, sc, s);
         }
     } else if (c.way == 1) {
-        launch_split<1, 8>(a, sc, a.units * a.tiles_per_unit, s);
+        launch_split<1, 8>(a, sc, a.units * a.tiles_per_unit, c.one_xcd, s);
     } else {
-        launch_split<2, 4>(a, sc, a.units * ((a.tiles_per_unit + 1) / 2), s);
+        launch_split<2, 4>(a, sc, a.units * ((a.tiles_per_unit + 1) / 2), c.one_xcd, s);
     }
 }
 

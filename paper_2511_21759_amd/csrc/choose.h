@@ -22,7 +22,11 @@ constexpr int kComputeUnits = 256;
 //   32 heads of 128, L 544: 4 x 32 rows 7.6 / 10.3 / -, 6 x 32 13.0 / 10.6 / -, 8 x 32 13.5 / 10.8 / 18.1
 //   12 heads of 128, L 1056, 4 x (4 x 32) rows 33.8 / 19.7 / -; 8 heads of 128, L 544, 8 x 32 rows 7.1 / 10.6 / 17.8
 //   28 heads of 128, L 3040, 2 x (5 x 64) rows 128 / 123 / 78; 16 heads of 64, L 1056, 2 x (8 x 64) rows 19.8 / 15.9 / 26.2
-struct AttentionChoice { int way; bool rows8; };
+//
+// one_xcd: the workgroups of a head go to one XCD, which then fetches that head's K/V alone (8.7 -> 8.4 us at 32 rows of 32
+// heads; 11.8 -> 11.3 at four drafts).  Not in a refresh: the O projection behind it, whose K slices lie on other XCDs than
+// the heads that wrote them, loses more (200 rows of 16 heads: attention 8.0 -> 7.1 us, O 10.0 -> 12.7).
+struct AttentionChoice { int way; bool rows8, one_xcd; };
 inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int units, int units_per_seq, int tiles_per_unit) {
     const int per_seq = units_per_seq * tiles_per_unit, seqs = units / units_per_seq;
     const int items1 = units * tiles_per_unit, items2 = units * ((tiles_per_unit + 1) / 2);
@@ -30,7 +34,6 @@ inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int uni
     const bool wide = dh == 128, heads8 = H % 8 == 0, may_rows = per_seq >= 16 && (!step || tiles_per_unit % 2 == 0);
     const bool rows8 = wgs8 >= kComputeUnits;       // 256 rows per workgroup when that still gives every compute unit one, else 128
     const double n = (L + 31) / 32, kv_us = n * 32 * dh * 4 * seqs * H / 6.6e6;
-    // (one_xcd: the launch keeps the workgroups of a head on one XCD)
     auto us = [&](int wgs, int wgs_per_head, bool one_xcd, double base, double round, double tile) {
         const double walk = base + (wgs + kComputeUnits - 1) / kComputeUnits * (round + tile * n);
         const double fetch = kv_us * (one_xcd ? 1 : wgs_per_head < 8 ? wgs_per_head : 8);
@@ -38,7 +41,7 @@ inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int uni
     };
     double t[4] = {0, 1e30, 1e30, 1e30};
     if (step) t[1] = wide ? us(items1 * H, per_seq, heads8 && items1 > 1, 0.9, 3.7, 0.173) : us(items1 * H, per_seq, false, 3.6, 1.0, 0.076);
-    t[2] = wide ? us(items2 * H, items2 / seqs, heads8 && items2 > 1, step ? 0.5 : 1.7, step ? 5.2 : 3.9, step ? 0.28 : 0.27)
+    t[2] = wide ? us(items2 * H, items2 / seqs, step && heads8 && items2 > 1, step ? 0.5 : 1.7, step ? 5.2 : 3.9, step ? 0.28 : 0.27)
                 : us(items2 * H, items2 / seqs, false, step ? 4.5 : 4.4, step ? 0.8 : 0.7, step ? 0.166 : 0.14);
     if (may_rows)
         t[3] = rows8 ? us(wgs8, (per_seq + 15) / 16, heads8, wide ? 5.8 : 4.1, wide ? 6.9 : 3.0, wide ? 1.12 : 0.81)
@@ -47,7 +50,7 @@ inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int uni
     t[way] *= step ? 0.9 : 0.8;
     for (int w = 1; w <= 3; w++)
         if (t[w] < t[way]) way = w;
-    return AttentionChoice{way, rows8};
+    return AttentionChoice{way, rows8, step && wide && heads8 && (way == 1 ? items1 : items2) > 1};
 }
 
 // K slices of the tile kernel (gemm_tile.h), which need not divide K; `room` bounds the bytes of partial sums.

@@ -15,6 +15,7 @@ SHIM = r"""
 using namespace odb;
 extern "C" {
 int attention_way(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).way; }
+int attention_one_xcd(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).one_xcd; }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
 """
@@ -75,6 +76,19 @@ def test_attention_way_is_near_the_fastest_measured(rules, case):
     assert way in us, "a way that cannot run at this size"
     # (the rule stays with its first choice up to 10 %; the model is off by a few percent beside that)
     assert us[way] <= 1.15 * min(us.values())
+
+
+def test_heads_stay_on_one_xcd_in_steps_only(rules):
+    """A refresh leaves the heads spread (the O projection behind it is faster), and only heads of 128 channels in eights can be
+    mapped."""
+    for H in (8, 12, 16, 32):
+        for dh in (64, 128):
+            for units, tpu in ((1, 1), (1, 2), (4, 2), (8, 4)):
+                got = rules.attention_one_xcd(dh, H, 544, 1, units, units, tpu)
+                way = rules.attention_way(dh, H, 544, 1, units, units, tpu)
+                items = units * (tpu if way == 1 else (tpu + 1) // 2)
+                assert got == (dh == 128 and H % 8 == 0 and items > 1)
+                assert not rules.attention_one_xcd(dh, H, 16 * tpu * units, 0, 1, 1, tpu * units)
 
 
 # projection, row tiles, n-tiles, k-tiles -> us of the tile kernel and its merge pass by K slices
