@@ -96,4 +96,17 @@ inline int tile_slices(TileEpilogue epi, int m_tiles, int n_tiles, int k_tiles, 
     return best;
 }
 
+// Gate/up of 129 to 256 rows: n-tiles per group of the streaming kernel in blocks of 64 rows, or 0 where the LDS-ring or tile kernel
+// runs.  Up to 512 n-tiles (d_ff 4096) the streaming kernel wins as long as its groups and row blocks make one round of
+// workgroups, or K is short; a second round costs it a whole pass over K.  us at 144 / 256 rows, streaming against tile kernel:
+// d 1024, d_ff 3072 (one round) 10.8 / 11.1 and 22.5 / 23.9; d 3072, d_ff 3072 (one) 21.9 / 21.9 and 27.1 / 29.6; d 1280,
+// d_ff 4096 (two) 20.2 / 26.6 and 24.1 / 26.7; d 2048, d_ff 4096 (two) 28.5 / 35.6 and 28.6 / 31.4; d 4096, d_ff 4096 (two)
+// 48.9 / 63.4 and 35.4 / 42.8; with groups of three d 2048, d_ff 2048 (two) 17.1 / 22.7 and 23.9 / 26.3, d 3072 23.1 / 31.4
+// and 25.1 / 27.8.
+inline int swiglu_row_block_group(int m_tiles, int n_tiles, int k_tiles) {
+    if (m_tiles <= 8 || m_tiles > 16 || n_tiles > 2 * kComputeUnits) return 0;
+    const int group = n_tiles <= kComputeUnits ? 3 : 6, wgs = (n_tiles + group - 1) / group * ((m_tiles + 3) / 4);
+    return wgs <= kComputeUnits || k_tiles <= (group == 3 ? 80 : 40) ? group : 0;
+}
+
 }  // namespace odb

@@ -343,10 +343,10 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
 void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u16 *act, unsigned *status, Workspace ws,
                         hipStream_t s) {
     EpiSwiGLU e{act, sh.M_tiles, status};
-    const int ng = stream_ng(sh.N_tiles, 6, true);
+    const int ng = stream_ng(sh.N_tiles, 6, true), rb = swiglu_row_block_group(sh.M_tiles, sh.N_tiles, sh.K_tiles);
     if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 2) launch_stream<4, 3, 2, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles > 8 && sh.M_tiles <= 16 && ng == 2) launch_stream<4, 6, 2, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles > 8 && sh.M_tiles <= 16 && ng == 1) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
+    else if (rb == 6) launch_stream<4, 6, 2, true>(xa, w, sh, ni, e, s);
+    else if (rb == 3) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 2) stream_by_rows<2, 2>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8 && ng == 3) stream_by_rows<3, 1>(xa, w, sh, ni, e, s);

@@ -16,6 +16,7 @@ using namespace odb;
 extern "C" {
 int attention_way(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).way; }
 int attention_one_xcd(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).one_xcd; }
+int swiglu_group(int m, int n, int k) { return swiglu_row_block_group(m, n, k); }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
 """
@@ -136,3 +137,18 @@ def test_tile_slices_keep_to_the_room_and_to_the_matrix(rules):
                     for epi in (0, 1, 2):
                         ks = rules.slices(epi, m, n, k, ctypes.c_size_t(room))
                         assert ks == 1 or (k // ks >= 8 and ks * m * n * 1024 <= room)
+
+
+# row tiles, n-tiles, k-tiles -> us of gate/up on the streaming kernel in row blocks and on the tile kernel
+SWIGLU = [
+    (9, 192, 16, 6.3, 18.2), (16, 256, 24, 11.9, 21.5), (9, 384, 32, 10.8, 22.5), (16, 384, 32, 11.1, 23.9), (16, 512, 32, 22.1, 26.5),
+    (9, 512, 40, 20.2, 24.1), (16, 512, 40, 26.6, 26.7), (9, 384, 64, 16.0, 24.9), (16, 384, 96, 21.9, 29.6), (16, 512, 64, 35.6, 31.4),
+    (9, 256, 64, 17.1, 23.9), (16, 256, 64, 22.7, 26.3), (13, 256, 80, 25.0, 24.4), (13, 256, 96, 30.2, 25.2), (16, 512, 96, 49.5, 37.4), (16, 256, 128, 40.2, 31.2), (9, 512, 128, 48.9, 35.4), (16, 512, 128, 63.4, 42.8),
+]
+
+
+@pytest.mark.parametrize("m,n,k,stream,tile", SWIGLU)
+def test_swiglu_takes_row_blocks_where_they_are_faster(rules, m, n, k, stream, tile):
+    us = stream if rules.swiglu_group(m, n, k) else tile
+    assert us <= 1.05 * min(stream, tile)
+    assert rules.swiglu_group(8, n, k) == 0 and rules.swiglu_group(17, n, k) == 0 and rules.swiglu_group(m, 513, k) == 0
