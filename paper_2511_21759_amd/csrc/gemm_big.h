@@ -17,14 +17,15 @@
 
 namespace odb {
 
-// k-tiles per stage and stages in the ring: one barrier interval covers a stage.  A 256-row block has 24 or 32 MFMAs per
-// wave and k-tile, enough to hide the operand reads of the other group of waves; a 128-row block has 8 to 16, so its
-// stages are two k-tiles deep (measured on the loop alone at K = 4096: 128 x 128 blocks 43.3 -> 37.1 us at 1024 x 4096,
-// 128 x 192 blocks 56.1 -> 52.4 us at 256 x 24576; 256 x 256 blocks equal).
-constexpr int big_kp(int wn, int mbt) { return mbt == 8 && wn <= 4 ? 2 : 1; }
-constexpr int big_stages(int mbt) { return mbt == 8 ? 3 : 4; }
+// k-tiles per stage and stages in the ring: one barrier interval covers a stage.  A 256-row block of 192 or 256 columns has 24 or
+// 32 MFMAs per wave and k-tile, enough to hide the operand reads of the other group of waves; 256 x 128 and the 128-row blocks
+// have 8 to 16, so their stages are two k-tiles deep (measured on the loop alone at K = 4096: 128 x 128 blocks 43.3 -> 37.1 us
+// at 1024 x 4096, 128 x 192 blocks 56.1 -> 52.4 us at 256 x 24576; 256 x 256 blocks equal.  256 x 128 blocks, two layers of a
+// refresh of 4 x 512 positions, one k-tile with four stages -> two with three: O 167.9 -> 153.2 us, down 420.8 -> 387.8).
+constexpr int big_kp(int wn, int mbt) { return (mbt == 8 && wn <= 4) || wn == 2 ? 2 : 1; }
+constexpr int big_stages(int wn, int mbt) { return mbt == 8 || wn == 2 ? 3 : 4; }
 constexpr int big_stage_tiles(int wn, int mbt) { return big_kp(wn, mbt) * (mbt + 4 * wn); }
-constexpr int big_smem_bytes(int wn, int mbt) { return big_stages(mbt) * big_stage_tiles(wn, mbt) * 1024 + 256 * 4; }   // ring, row scales
+constexpr int big_smem_bytes(int wn, int mbt) { return big_stages(wn, mbt) * big_stage_tiles(wn, mbt) * 1024 + 256 * 4; }   // ring, row scales
 // per-wave scratch of the epilogues, in the ring's place once the k-loop is over
 constexpr int kBigScratch = 4096;
 
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
     constexpr int CW = 4;                       // waves side by side; two rows of them
     constexpr int WT = WN;                      // 16-column tiles per wave
     constexpr int MW = MBT / 2;                 // 16-row tiles per wave
-    constexpr int NS = big_stages(MBT), KP = big_kp(WN, MBT), TK = MBT + 4 * WN, ST = KP * TK;     // tiles per k-tile, per stage
+    constexpr int NS = big_stages(WN, MBT), KP = big_kp(WN, MBT), TK = MBT + 4 * WN, ST = KP * TK;     // tiles per k-tile, per stage
     extern __shared__ __attribute__((aligned(16))) char smem[];
     typedef frag_t stage_t[ST][64];                                          // per k-tile: MBT tiles of A, then 4 WN of W
     stage_t *ring = reinterpret_cast<stage_t *>(smem);

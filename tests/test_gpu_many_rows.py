@@ -103,6 +103,16 @@ def test_refresh_with_slices_that_do_not_divide_k(L):
         p.close()
 
 
+def test_refresh_in_256_by_128_blocks():
+    """2040 positions at d = 3072: the O and down projections in blocks of 256 x 128, two k-tiles per stage, the last one ragged."""
+    p = Pair(dict(_width(3072, 512), vocab=512, mask_id=511))
+    try:
+        wl = W.decode_workload(p.shape, 2000, 40, 16, 1, 995, batch=1)
+        run_prefill_case(p, wl.tokens, wl.resp_off, "2040 positions")
+    finally:
+        p.close()
+
+
 # ---- the fixed scratch area: the same bits as the growing one, up to its limit ------------------------------------------
 
 @pytest.mark.parametrize("d,f,vocab,b,S", [
