@@ -109,4 +109,45 @@ inline int swiglu_row_block_group(int m_tiles, int n_tiles, int k_tiles) {
     return wgs <= kComputeUnits || k_tiles <= (group == 3 ? 80 : 40) ? group : 0;
 }
 
+// Block shape for the LDS-ring kernel - mbt 16-row tiles by 64 * wn columns - or wn = 0 when the tile kernel
+// should run instead.  With T blocks on 256 compute units a launch takes ceil(T / 256) block-times, and a
+// block-time shrinks more slowly than the block (the k-step is bound by its barrier and operand delivery as
+// much as by its MFMAs).  In units of the 256 x 256 block at K = 4096: 256-row blocks of 192 / 128 columns 0.87 / 0.68;
+// 128-row blocks of 256 / 192 / 128 columns 0.66 / 0.60 / 0.46 (measured with one group of waves; with two, in us at 96 to
+// 190 blocks: 88 for the 256 x 256 block, 0.86 / 0.72 and 0.69 / 0.64 / 0.48).  The
+// shape with the smallest rounds x block-time wins among those whose block slots are at least `least` useful (a
+// ragged last block counts by its real rows); below that for every shape the 128-row tile kernel wins
+// (measured at 640 rows).  The 128-row blocks serve shapes that would leave compute units idle: QKV at 512 rows
+// (256 blocks of 128 x 192 instead of 192 of 256 x 128: 83 -> 69 us), every wide projection at 640 rows (five row
+// blocks that fit exactly: refresh 14.7 -> 13.0 ms), the 256-row step (7.6 -> 7.2 ms).  144 to 176 rows count as 192: both
+// kernels run two row blocks for them, gate/up at 160 rows takes 73.9 us on the tile kernel and 65 us in 128 x 192 blocks.
+//
+// per_xcd: the launch gives a column of blocks to one XCD, so a round is 32 blocks of the fullest XCD: 11 x 22 blocks of
+// 128 x 192 at 1300 rows of N = 4096 are 33 on six of the XCDs, two rounds and 97 us (the tile kernel: 61), while 10 x 22
+// at 1232 rows take 56 us (67 and 62 on the tile kernel).
+struct BigChoice { int mbt, wn; };
+inline BigChoice big_choice_by(int m, int n_tiles, bool per_xcd, double least) {
+    BigChoice best{16, 0};
+    if (m <= 8 || n_tiles < 32) return best;
+    const double m_tiles = m < 12 ? 12 : m;     // (see above)
+    const double rel16[5] = {0, 0, 0.68, 0.87, 1.0}, rel8[5] = {0, 0, 0.46, 0.60, 0.66};
+    double best_cost = 0;
+    for (int mbt = 16; mbt >= 8; mbt -= 8)
+        for (int wn = 4; wn >= 2; wn--) {
+            const int mb = (m + mbt - 1) / mbt, nb = (n_tiles + 4 * wn - 1) / (4 * wn);
+            const int rounds = per_xcd ? (mb * ((nb + 7) / 8) + kComputeUnits / 8 - 1) / (kComputeUnits / 8) : (mb * nb + kComputeUnits - 1) / kComputeUnits;
+            const double useful = (m_tiles / (double)mbt) * (n_tiles / (4.0 * wn)) / ((double)rounds * kComputeUnits);
+            const double cost = rounds * (mbt == 16 ? rel16[wn] : rel8[wn]);
+            // (a 128-row shape has to promise 5 % over the best 256-row one: the unit times are measurements)
+            if (useful >= least && (best.wn == 0 || cost < best_cost * (mbt == 8 && best.mbt == 16 ? 0.95 : 1.0) - 1e-9)) {
+                best = BigChoice{mbt, wn};
+                best_cost = cost;
+            }
+        }
+    return best;
+}
+inline BigChoice big_choice(int m, int n_tiles) { return big_choice_by(m, n_tiles, true, 0.65); }
+// The LM head by its own numbers: as many statistics per row as before, which decide with the rest whether a step fits the fixed area.
+inline BigChoice lm_block_choice(int m, int n_tiles) { return big_choice_by(m, n_tiles, false, 0.7); }
+
 }  // namespace odb

@@ -216,61 +216,27 @@ static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
     gemm_big_kernel<WN, Epi, MBT><<<grid, 512, big_smem_bytes(WN, MBT), s>>>(g, e);
 }
 
-// Block shape for the LDS-ring kernel - MBT 16-row tiles by 64 * WN columns - or wn = 0 when the tile kernel
-// should run instead.  With T blocks on 256 compute units a launch takes ceil(T / 256) block-times, and a
-// block-time shrinks more slowly than the block (the k-step is bound by its barrier and operand delivery as
-// much as by its MFMAs).  Measured on one GPU at K = 4096, in units of the 256 x 256 block (110 us): 256-row
-// blocks of 192 / 128 columns 0.87 / 0.68; 128-row blocks of 256 / 192 / 128 columns 0.66 / 0.60 / 0.46.  The
-// shape with the smallest rounds x block-time wins among those whose block slots are at least 70 % useful (a
-// ragged last block counts by its real rows); below 70 % for every shape the 128-row tile kernel wins
-// (measured at 640 rows).  The 128-row blocks serve shapes that would leave compute units idle: QKV at 512 rows
-// (256 blocks of 128 x 192 instead of 192 of 256 x 128: 83 -> 69 us), every wide projection at 640 rows (five row
-// blocks that fit exactly: refresh 14.7 -> 13.0 ms), the 256-row step (7.6 -> 7.2 ms).  144 to 176 rows count as 192: both
-// kernels run two row blocks for them, gate/up at 160 rows takes 73.9 us on the tile kernel and 65 us in 128 x 192 blocks.
-struct BigChoice { int mbt, wn; };
-static BigChoice big_choice(GemmShape sh, bool may_192 = true) {
-    BigChoice best{16, 0};
-    if (sh.M_tiles <= 8 || sh.N_tiles < 32) return best;
-    const double m_tiles = sh.M_tiles < 12 ? 12 : sh.M_tiles;     // (see above)
-    const double rel16[5] = {0, 0, 0.68, 0.87, 1.0}, rel8[5] = {0, 0, 0.46, 0.60, 0.66};
-    double best_cost = 0;
-    for (int mbt = 16; mbt >= 8; mbt -= 8)
-        for (int wn = 4; wn >= 2; wn--) {
-            if (wn == 3 && !may_192) continue;
-            const int blocks = ((sh.M_tiles + mbt - 1) / mbt) * ((sh.N_tiles + 4 * wn - 1) / (4 * wn));
-            const int rounds = (blocks + kStreamWGs - 1) / kStreamWGs;
-            const double useful = (m_tiles / (double)mbt) * (sh.N_tiles / (4.0 * wn)) / ((double)rounds * kStreamWGs);
-            const double cost = rounds * (mbt == 16 ? rel16[wn] : rel8[wn]);
-            // (a 128-row shape has to promise 5 % over the best 256-row one: the unit times are measurements)
-            if (useful >= 0.7 && (best.wn == 0 || cost < best_cost * (mbt == 8 && best.mbt == 16 ? 0.95 : 1.0) - 1e-9)) {
-                best = BigChoice{mbt, wn};
-                best_cost = cost;
-            }
-        }
-    return best;
-}
-static bool use_big(GemmShape sh, bool may_192 = true) { return big_choice(sh, may_192).wn != 0; }
+static BigChoice big_choice(GemmShape sh) { return big_choice(sh.M_tiles, sh.N_tiles); }
 
 template <class Epi>
 static void launch_big_as(BigChoice c, const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
-    if constexpr (!is_resid<Epi>::value) {
-        if (c.wn == 3) {
+    switch (c.wn) {
+        case 2:
+            if (c.mbt == 8) launch_big_wn<2, Epi, 8>(a, w, sh, ni, e, s);
+            else launch_big_wn<2, Epi, 16>(a, w, sh, ni, e, s);
+            break;
+        case 3:
             if (c.mbt == 8) launch_big_wn<3, Epi, 8>(a, w, sh, ni, e, s);
             else launch_big_wn<3, Epi, 16>(a, w, sh, ni, e, s);
-            return;
-        }
-    }
-    if (c.wn == 2) {
-        if (c.mbt == 8) launch_big_wn<2, Epi, 8>(a, w, sh, ni, e, s);
-        else launch_big_wn<2, Epi, 16>(a, w, sh, ni, e, s);
-    } else {
-        if (c.mbt == 8) launch_big_wn<4, Epi, 8>(a, w, sh, ni, e, s);
-        else launch_big_wn<4, Epi, 16>(a, w, sh, ni, e, s);
+            break;
+        default:
+            if (c.mbt == 8) launch_big_wn<4, Epi, 8>(a, w, sh, ni, e, s);
+            else launch_big_wn<4, Epi, 16>(a, w, sh, ni, e, s);
     }
 }
 template <class Epi>
 static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
-    launch_big_as(big_choice(sh, !is_resid<Epi>::value), a, w, sh, ni, e, s);
+    launch_big_as(big_choice(sh), a, w, sh, ni, e, s);
 }
 
 // The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles.
@@ -308,7 +274,7 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     // two row blocks on 130 to 256 compute units: 44 us at 160 to 256 rows of the 8B shape, against 54 to 58 us on the tile
     // kernel and its merge pass and 50 us in 192 blocks of 128 x 128
     else if (sh.M_tiles <= 16 && sh.N_tiles > 384 && sh.N_tiles <= 768) launch_slab<6>(xa, w, sh, ni, e, s);
-    else if (use_big(sh)) launch_big(xa, w, sh, ni, e, s);
+    else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }
 void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int ldh, NormOut no, Workspace ws,
@@ -335,8 +301,7 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
     else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
     // (128-row blocks only for the O projection: at 1024 rows 256 blocks of 128 x 128 take 57 us against 64 us for the
     // tile kernel and its reduction pass; the down projection, three times as long in K, measured 4 % slower that way)
-    // (no 192-column blocks here: N is a multiple of 256, and the sums of squares are left per 64 columns)
-    else if (use_big(sh, false) && (big_choice(sh, false).mbt == 16 || sh.K_tiles <= sh.N_tiles))
+    else if (big_choice(sh).wn && (big_choice(sh).mbt == 16 || sh.K_tiles <= sh.N_tiles))
         launch_big(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
     else launch_tile(a, w, sh, NormIn{nullptr, 0, 0.f}, e, ws, true, s);
 }
@@ -354,7 +319,7 @@ void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u1
     else if (sh.M_tiles <= 4) launch_stream<4, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 6) launch_stream<6, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8) launch_slab<6>(xa, w, sh, ni, e, s);
-    else if (use_big(sh)) launch_big(xa, w, sh, ni, e, s);
+    else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }
 
@@ -375,7 +340,7 @@ static int lm_ng(int n_tiles, int m_tiles) {
 // At 144 to 176 rows blocks narrower than that serve vocabularies whose 256-column blocks leave compute units idle, up to 65536;
 // beyond, their statistics (twice as many, over 1 MiB) would not fit the room that lm_stats_excess counts on.
 static BigChoice lm_big(GemmShape sh) {
-    const BigChoice c = big_choice(sh);
+    const BigChoice c = lm_block_choice(sh.M_tiles, sh.N_tiles);
     if (sh.N_tiles < 32 || (c.wn && (sh.M_tiles >= 12 || sh.N_tiles <= 16 * kStreamWGs))) return c;
     return BigChoice{16, 4};
 }
@@ -424,7 +389,7 @@ void launch_gemm_store(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, flo
     if (sh.M_tiles <= 2) launch_stream<2, 3, 8, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8) launch_stream<8, 3, 2, false>(xa, w, sh, ni, e, s);
-    else if (use_big(sh)) launch_big(xa, w, sh, ni, e, s);
+    else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, false, s);
 }
 

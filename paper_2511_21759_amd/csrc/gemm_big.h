@@ -143,27 +143,35 @@ __device__ __forceinline__ void big_epilogue(const EpiSwiGLU &e, f32x4 (&acc)[MW
     if (bad && e.status) atomicOr(e.status, kStatusSaturated);
 }
 
-// (N is a multiple of 256 here, and WN = 4 or 2: the wave's columns are one partial sum of squares, or half of one)
+// Sums of squares go out per 64 columns.  WT = 4: the wave's columns are one such sum.  WT = 2 or 3: the wave leaves what it has per row
+// and 32 or 16 columns in its scratch, [parts][MW * 16 rows], and the workgroup adds them up.  (N is a multiple of 256, so only
+// a block of 192 columns can reach beyond it, and then by whole sums.)
+template <int WT> constexpr int resid_parts() { return WT == 3 ? 3 : 1; }
 template <int MW, int WT>
 __device__ __forceinline__ void big_epilogue(const EpiResid &e, f32x4 (&acc)[MW][WT], int mtw, int ntw, const BigArgs &g,
                                              const float *, char *scr, int lane) {
     const NormOut &no = e.no;
     const int mi = lane & 15, gq = lane >> 4;
     float *s_q = reinterpret_cast<float *>(scr);
+    static_assert(resid_parts<WT>() * MW * 16 * 4 <= kBigScratch, "sums of a wave");
     f32x4 gn[WT], hv[WT];
     float *hp = e.h + (size_t)(mtw * 16 + mi) * e.ld + ntw * 16 + 4 * gq;
     u16 *xp[WT];
+    bool in[WT];
+    int col[WT];
 #pragma unroll
     for (int j = 0; j < WT; j++) {
-        gn[j] = no.hb ? *reinterpret_cast<const f32x4 *>(no.gain + (ntw + j) * 16 + 4 * gq) : f32x4{0.f, 0.f, 0.f, 0.f};
+        in[j] = WT != 3 || ntw + j < g.NT;
+        col[j] = (in[j] ? ntw + j : g.NT - 1) * 16 + 4 * gq;
+        gn[j] = no.hb ? *reinterpret_cast<const f32x4 *>(no.gain + col[j]) : f32x4{0.f, 0.f, 0.f, 0.f};
         const int kk = ((ntw + j) & 1) * 16 + 4 * gq;
         xp[j] = no.hb + ((size_t)((ntw + j) >> 1) * e.mt_total + mtw) * kTileElems + ((kk >> 3) * 16 + mi) * 8 + (kk & 7);
     }
     auto fetch = [&](int m) __attribute__((always_inline)) {
         const int mt = mtw + m < g.MT_total ? mtw + m : g.MT_total - 1;
-        const float *p = e.h + (size_t)(mt * 16 + mi) * e.ld + ntw * 16 + 4 * gq;
+        const float *p = e.h + (size_t)(mt * 16 + mi) * e.ld;
 #pragma unroll
-        for (int j = 0; j < WT; j++) hv[j] = *reinterpret_cast<const f32x4 *>(p + j * 16);
+        for (int j = 0; j < WT; j++) hv[j] = *reinterpret_cast<const f32x4 *>(p + col[j]);
     };
     bool bad = false;
     fetch(0);
@@ -174,22 +182,35 @@ __device__ __forceinline__ void big_epilogue(const EpiResid &e, f32x4 (&acc)[MW]
         for (int j = 0; j < WT; j++) v[j] = hv[j] + acc[m][j];
         if (mtw + m >= g.MT_total) break;
         if (m + 1 < MW) fetch(m + 1);
-        float q = 0.f;
+        float q[WT];
 #pragma unroll
         for (int j = 0; j < WT; j++) {
+            q[j] = 0.f;
+            if (!in[j]) continue;
             *reinterpret_cast<f32x4 *>(hp + (size_t)m * 16 * e.ld + j * 16) = v[j];
             if (no.hb) {
                 const f32x4 y = v[j] * gn[j];
                 bad |= out_of_f16(y[0], y[1], y[2], y[3]);
                 st_f16x4(xp[j] + m * kTileElems, y[0], y[1], y[2], y[3]);
-                q += v[j][0] * v[j][0] + v[j][1] * v[j][1] + v[j][2] * v[j][2] + v[j][3] * v[j][3];
+                q[j] = v[j][0] * v[j][0] + v[j][1] * v[j][1] + v[j][2] * v[j][2] + v[j][3] * v[j][3];
             }
         }
         if (no.hb) {
-            q = EpiResid::over_row(q);
-            if (lane < 16) {
-                if constexpr (WT == 4) no.ssq[(size_t)((mtw + m) * 16 + lane) * no.n_ssq + (ntw >> 2)] = q;
-                else s_q[m * 16 + lane] = q;
+            if constexpr (WT == 3) {
+#pragma unroll
+                for (int j = 0; j < WT; j++) {
+                    const float t = EpiResid::over_row(q[j]);
+                    if (lane < 16) s_q[j * MW * 16 + m * 16 + lane] = t;
+                }
+            } else {
+                float t = q[0];
+#pragma unroll
+                for (int j = 1; j < WT; j++) t += q[j];
+                t = EpiResid::over_row(t);
+                if (lane < 16) {
+                    if constexpr (WT == 4) no.ssq[(size_t)((mtw + m) * 16 + lane) * no.n_ssq + (ntw >> 2)] = t;
+                    else s_q[m * 16 + lane] = t;
+                }
             }
         }
     }
@@ -213,7 +234,6 @@ template <int WN, class Epi, int MBT = 16>
 __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
     static_assert((WN >= 2 && WN <= 4) || (WN == 8 && MBT == 8), "block width in units of 64 columns");
     static_assert(MBT == 16 || MBT == 8, "rows per block");
-    static_assert(!is_resid<Epi>::value || WN != 3, "partial sums of squares cover 64 columns");
     constexpr int CW = 4;                       // waves side by side; two rows of them
     constexpr int WT = WN;                      // 16-column tiles per wave
     constexpr int MW = MBT / 2;                 // 16-row tiles per wave
@@ -406,14 +426,22 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
         }
     } else {
         big_epilogue<MW, WT>(epi, acc, mt0 + wm * MW, nt0 + wn * WT, g, s_rstd + wm * MW * 16, smem + w * kBigScratch, lane);
-        if constexpr (is_resid<Epi>::value && WT == 2) {
-            if (epi.no.hb) {        // two waves side by side make one partial sum of 64 columns
+        if constexpr (is_resid<Epi>::value && (WT == 2 || WT == 3)) {
+            if (epi.no.hb) {        // the waves side by side make WN partial sums of 64 columns
                 __syncthreads();
-                for (int i = threadIdx.x; i < 2 * MBT * 16; i += 512) {
+                constexpr int P = 4 / (WT == 2 ? 2 : 1);         // parts of a sum
+                for (int i = threadIdx.x; i < WN * MBT * 16; i += 512) {
                     const int r = i % (MBT * 16), c = i / (MBT * 16), row = mt0 * 16 + r, wr = r / (MW * 16), rr = r % (MW * 16);
-                    const float *q0 = reinterpret_cast<const float *>(smem + (wr * CW + 2 * c) * kBigScratch);
-                    const float *q1 = reinterpret_cast<const float *>(smem + (wr * CW + 2 * c + 1) * kBigScratch);
-                    if (row < g.MT_total * 16) epi.no.ssq[(size_t)row * epi.no.n_ssq + nb * 2 + c] = q0[rr] + q1[rr];
+                    float q[P];
+#pragma unroll
+                    for (int x = 0; x < P; x++) {
+                        const int part = c * P + x, wv = part / resid_parts<WT>(), in = part % resid_parts<WT>();
+                        q[x] = reinterpret_cast<const float *>(smem + (wr * CW + wv) * kBigScratch)[in * MW * 16 + rr];
+                    }
+                    float t;
+                    if constexpr (P == 4) t = (q[0] + q[1]) + (q[2] + q[3]);
+                    else t = q[0] + q[1];
+                    if (row < g.MT_total * 16 && (nb * WN + c) * 4 < g.NT) epi.no.ssq[(size_t)row * epi.no.n_ssq + nb * WN + c] = t;
                 }
             }
         }

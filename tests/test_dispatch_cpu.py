@@ -17,6 +17,7 @@ extern "C" {
 int attention_way(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).way; }
 int attention_one_xcd(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).one_xcd; }
 int swiglu_group(int m, int n, int k) { return swiglu_row_block_group(m, n, k); }
+int big_block(int m, int n) { const BigChoice c = big_choice(m, n); return c.wn ? c.mbt * 10 + c.wn : 0; }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
 """
@@ -152,3 +153,47 @@ def test_swiglu_takes_row_blocks_where_they_are_faster(rules, m, n, k, stream, t
     us = stream if rules.swiglu_group(m, n, k) else tile
     assert us <= 1.05 * min(stream, tile)
     assert rules.swiglu_group(8, n, k) == 0 and rules.swiglu_group(17, n, k) == 0 and rules.swiglu_group(m, 513, k) == 0
+
+
+# n-tiles, rows -> us of the O projection (first table), QKV and gate/up (second) by block (16-row tiles * 10 + units of 64 columns;
+# 0: tile kernel and merge pass)
+BLOCKS = [
+    (96, 3008, {0: 33.4, 162: 33.3, 163: 40.0, 164: 46.8, 82: 40.2, 83: 28.5, 84: 33.1}),
+    (160, 2048, {0: 47.4, 162: 45.3, 163: 55.6, 164: 63.7, 82: 60.9, 83: 40.3, 84: 48.1}),
+    (176, 2048, {0: 53.0, 162: 48.4, 163: 57.9, 164: 67.4, 82: 65.7, 83: 43.7, 84: 52.0}),
+    (192, 1536, {0: 51.8, 162: 51.0, 163: 61.6, 164: 72.1, 82: 62.2, 83: 42.7, 84: 50.8}),
+    (192, 2048, {0: 54.1, 162: 52.3, 163: 62.1, 164: 73.0, 82: 70.6, 83: 46.5, 84: 56.6}),
+    (192, 3008, {0: 97.4, 162: 101.1, 163: 67.3, 164: 79.2, 82: 98.2, 83: 83.7, 84: 99.9}),
+    (224, 1232, {0: 62.6, 162: 56.8, 163: 68.7, 164: 79.8, 82: 70.7, 83: 49.9, 84: 55.4}),
+    (256, 1008, {0: 49.5, 162: 63.0, 163: 74.7, 164: 87.0, 82: 46.4, 83: 56.1, 84: 60.8}),
+    (256, 1232, {0: 67.4, 162: 63.9, 163: 75.1, 164: 87.1, 82: 80.2, 83: 56.8, 84: 62.4}),
+    (256, 1536, {0: 66.5, 162: 64.3, 163: 75.6, 164: 87.8, 82: 88.7, 83: 100.2, 84: 64.0}),
+    (256, 2048, {0: 79.0, 162: 78.3, 163: 87.0, 164: 95.5, 82: 96.9, 83: 108.7, 84: 73.6}),
+    (320, 1008, {0: 85.2, 162: 75.3, 163: 90.7, 164: 105.4, 82: 103.5, 83: 69.4, 84: 73.8}),
+    (320, 2048, {0: 157.5, 162: 165.1, 163: 122.0, 164: 129.4, 82: 168.4, 83: 142.6, 84: 159.0}),
+    (384, 768, {0: 102.7, 162: 94.1, 163: 109.0, 164: 127.9, 82: 117.2, 83: 75.4, 84: 90.4}),
+    (384, 1536, {0: 162.8, 162: 185.8, 163: 119.9, 164: 140.8, 82: 189.5, 83: 152.5, 84: 177.0}),
+    (512, 608, {0: 114.6, 162: 122.6, 163: 139.3, 164: 163.4, 82: 159.0, 83: 104.4, 84: 118.4}),
+    (512, 1232, {0: 217.5, 162: 250.8, 163: 174.1, 164: 185.0, 82: 246.7, 83: 206.5, 84: 232.6}),
+    (256, 1312, {0: 61.5, 83: 97.0}),           # 11 x 22 blocks: 33 on six of the XCDs
+    (1024, 512, {0: 41.6, 162: 37.8, 163: 41.4, 164: 45.4, 82: 46.3, 83: 54.6, 84: 35.4}),
+    (864, 512, {0: 52.4, 162: 43.6, 163: 48.5, 164: 54.4, 82: 54.5, 83: 65.8, 84: 40.8}),
+    (480, 1008, {0: 54.9, 162: 51.1, 163: 56.7, 164: 62.7, 82: 60.5, 83: 72.3, 84: 46.5}),
+    (576, 768, {0: 60.1, 162: 54.6, 163: 63.6, 164: 71.2, 82: 67.0, 83: 79.7, 84: 52.2}),
+    (672, 608, {0: 71.0, 162: 108.4, 163: 73.3, 164: 79.9, 82: 78.4, 83: 89.7, 84: 58.9}),
+    (512, 768, {0: 63.7, 162: 58.1, 163: 68.1, 164: 77.0, 82: 76.4, 83: 94.3, 84: 55.3}),
+    (768, 512, {0: 74.0, 162: 67.5, 163: 80.8, 164: 89.2, 82: 86.5, 83: 58.2, 84: 62.6}),
+    (1536, 512, {0: 128.2, 162: 119.3, 163: 86.0, 164: 87.8, 82: 118.7, 83: 101.5, 84: 114.0}),
+    (768, 640, {0: 75.4, 162: 124.5, 163: 81.2, 164: 88.0, 82: 87.6, 83: 104.7, 84: 66.0}),
+    (1536, 640, {0: 134.9, 162: 175.1, 163: 147.2, 164: 172.2, 82: 154.2, 83: 146.1, 84: 117.0}),
+    (768, 1024, {0: 136.1, 162: 131.8, 163: 93.2, 164: 96.1, 82: 134.8, 83: 115.6, 84: 122.9}),
+    (1536, 1024, {0: 200.2, 162: 188.0, 163: 165.3, 164: 176.7, 82: 240.3, 83: 204.0, 84: 179.4}),
+    (960, 512, {0: 90.8, 162: 85.9, 163: 97.5, 164: 108.9, 82: 107.7, 83: 125.8, 84: 81.5}),
+    (1536, 608, {0: 292.6, 162: 356.9, 163: 304.1, 164: 342.9, 82: 311.3, 83: 297.5, 84: 233.0}),
+]
+
+
+@pytest.mark.parametrize("n,rows,us", BLOCKS)
+def test_blocks_are_near_the_fastest_measured(rules, n, rows, us):
+    block = rules.big_block(rows // 16, n)
+    assert block in us and us[block] <= 1.15 * min(us.values())

@@ -103,14 +103,34 @@ def test_refresh_with_slices_that_do_not_divide_k(L):
         p.close()
 
 
-def test_refresh_in_256_by_128_blocks():
-    """2040 positions at d = 3072: the O and down projections in blocks of 256 x 128, two k-tiles per stage, the last one ragged."""
-    p = Pair(dict(_width(3072, 512), vocab=512, mask_id=511))
+@pytest.mark.parametrize("d,batch", [
+    (4096, 4),         # 2048 rows: O and down in blocks of 256 x 128, two k-tiles per stage
+    (3072, 4),         # O in blocks of 128 x 192: sums of squares of 64 columns from waves of 48
+    (5120, 4),         # blocks of 256 x 192, the last one two thirds full
+    (5120, 2),         # 1024 rows: O in blocks of 128 x 192
+])
+def test_batched_refresh_equals_its_sequences_one_by_one(d, batch):
+    """Wide residual projections in the blocks that many rows take, against the same sequences alone (512 rows, other blocks and
+    kernels): logits within the parity bar.  500 positions: the last row tile of every sequence is ragged."""
+    import torch
+    from paper_2511_21759_amd import binding as B
+    shape = dict(_width(d, 512), vocab=512, mask_id=511)
+    model = B.odb_model_create(shape)
     try:
-        wl = W.decode_workload(p.shape, 2000, 40, 16, 1, 995, batch=1)
-        run_prefill_case(p, wl.tokens, wl.resp_off, "2040 positions")
+        B.odb_model_init_random(model, W.WEIGHT_SEED, W.WEIGHT_STD)
+        tok = torch.randint(0, 511, (batch, 500), generator=torch.Generator().manual_seed(d), dtype=torch.int32).cuda()
+        many = B.odb_cache_create(model, batch, 500)
+        one = B.odb_cache_create(model, 1, 500)
+        got = B.odb_prefill_logits(model, many, tok, 300, shape["vocab"])
+        for i in range(batch):
+            ref = B.odb_prefill_logits(model, one, tok[i:i + 1].contiguous(), 300, shape["vocab"])
+            assert (got[i] - ref[0]).abs().max().item() <= 2e-2 * ref.abs().max().item()
+            assert not torch.equal(got[i], ref[0])          # another order of sums: the other kernels ran
+        B.odb_model_status(model)
+        B.odb_cache_destroy(many)
+        B.odb_cache_destroy(one)
     finally:
-        p.close()
+        B.odb_model_destroy(model)
 
 
 # ---- the fixed scratch area: the same bits as the growing one, up to its limit ------------------------------------------
