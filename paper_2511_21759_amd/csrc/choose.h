@@ -124,7 +124,9 @@ inline int swiglu_row_block_group(int m_tiles, int n_tiles, int k_tiles) {
 //
 // per_xcd: the launch gives a column of blocks to one XCD, so a round is 32 blocks of the fullest XCD: 11 x 22 blocks of
 // 128 x 192 at 1300 rows of N = 4096 are 33 on six of the XCDs, two rounds and 97 us (the tile kernel: 61), while 10 x 22
-// at 1232 rows take 56 us (67 and 62 on the tile kernel).
+// at 1232 rows take 56 us (67 and 62 on the tile kernel).  Up to K = 1024 a shape needs to be 45 % useful only: the block-times are
+// short and the tile kernel pays its merge pass all the same (K 768, N 2304: 15.1 us in 128 x 128 blocks at 1008 rows and 20.6
+// in 128 x 192 at 1536, 28.8 and 29.1 on the tile kernel; K 768, N 4096, 512 rows: 11.2 and 21.7).
 struct BigChoice { int mbt, wn; };
 inline BigChoice big_choice_by(int m, int n_tiles, bool per_xcd, double least) {
     BigChoice best{16, 0};
@@ -146,7 +148,7 @@ inline BigChoice big_choice_by(int m, int n_tiles, bool per_xcd, double least) {
         }
     return best;
 }
-inline BigChoice big_choice(int m, int n_tiles) { return big_choice_by(m, n_tiles, true, 0.65); }
+inline BigChoice big_choice(int m, int n_tiles, int k_tiles) { return big_choice_by(m, n_tiles, true, k_tiles <= 32 ? 0.45 : 0.65); }
 // The LM head by its own numbers: as many statistics per row as before, which decide with the rest whether a step fits the fixed area.
 inline BigChoice lm_block_choice(int m, int n_tiles) { return big_choice_by(m, n_tiles, false, 0.7); }
 

@@ -216,7 +216,7 @@ static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
     gemm_big_kernel<WN, Epi, MBT><<<grid, 512, big_smem_bytes(WN, MBT), s>>>(g, e);
 }
 
-static BigChoice big_choice(GemmShape sh) { return big_choice(sh.M_tiles, sh.N_tiles); }
+static BigChoice big_choice(GemmShape sh) { return big_choice(sh.M_tiles, sh.N_tiles, sh.K_tiles); }
 
 template <class Epi>
 static void launch_big_as(BigChoice c, const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
