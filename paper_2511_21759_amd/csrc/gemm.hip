@@ -259,7 +259,7 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     // with one group of tiles each in flight keep the HBM stream full, and fewer outstanding weight loads per
     // compute unit leave the activation loads less to queue behind: 1.9 % per step at 32 rows for this and the
     // gate/up projection together, 1.5 % at 64 rows, 0.5 % at 96.)
-    const int ng = stream_ng(sh.N_tiles, 3, false);
+    const int ng = stream_ng(sh.N_tiles, 3, false), slab = qkv_slab_group(sh.M_tiles, sh.N_tiles);
     // (a narrow model's 97 to 128 rows: blocks of 32 rows and three n-tiles read 160 instead of 288 KB per compute unit at
     // d = 1024: 10.4 -> 7.2 us; gate/up below: 64 rows and three n-tiles, 10.9 -> 8.5 us.  129 to 256 rows: blocks of 64 rows,
     // QKV 22.7 -> 9.8 us and gate/up 22.9 -> 10.6 us at 192 rows against the split tile kernel and its merge pass)
@@ -270,10 +270,8 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     else if (sh.M_tiles <= 2) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
     else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);          // 65..96 rows
-    else if (sh.M_tiles <= 8) launch_slab<3>(xa, w, sh, ni, e, s);
-    // two row blocks on 130 to 256 compute units: 44 us at 160 to 256 rows of the 8B shape, against 54 to 58 us on the tile
-    // kernel and its merge pass and 50 us in 192 blocks of 128 x 128
-    else if (sh.M_tiles <= 16 && sh.N_tiles > 384 && sh.N_tiles <= 768) launch_slab<6>(xa, w, sh, ni, e, s);
+    else if (slab == 3) launch_slab<3>(xa, w, sh, ni, e, s);
+    else if (slab == 6) launch_slab<6>(xa, w, sh, ni, e, s);
     else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }

@@ -17,6 +17,7 @@ extern "C" {
 int attention_way(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).way; }
 int attention_one_xcd(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).one_xcd; }
 int swiglu_group(int m, int n, int k) { return swiglu_row_block_group(m, n, k); }
+int qkv_slab(int m, int n) { return qkv_slab_group(m, n); }
 int big_block(int m, int n, int k) { const BigChoice c = big_choice(m, n, k); return c.wn ? c.mbt * 10 + c.wn : 0; }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
@@ -154,6 +155,21 @@ def test_swiglu_takes_row_blocks_where_they_are_faster(rules, m, n, k, stream, t
     us = stream if rules.swiglu_group(m, n, k) else tile
     assert us <= 1.05 * min(stream, tile)
     assert rules.swiglu_group(8, n, k) == 0 and rules.swiglu_group(17, n, k) == 0 and rules.swiglu_group(m, 513, k) == 0
+
+
+# n-tiles -> us of QKV at 128 rows in blocks of 3 and 6 n-tiles and on the streaming kernel (0)
+QKV_SLAB = [
+    (528, {3: 22.7, 6: 30.3, 0: 24.5}), (672, {3: 28.3, 6: 36.8, 0: 30.9}), (768, {3: 31.1, 6: 40.2, 0: 31.8}), (864, {3: 61.4, 6: 45.6, 0: 66.2}),
+    (960, {3: 68.7, 6: 51.1, 0: 73.4}), (1152, {3: 81.7, 6: 60.1, 0: 84.5}), (1344, {3: 96.0, 6: 72.7, 0: 102.7}), (1536, {3: 112.5, 6: 83.7, 0: 105.3}),
+]
+
+
+@pytest.mark.parametrize("n,us", QKV_SLAB)
+def test_qkv_of_97_to_128_rows_takes_the_fastest_width(rules, n, us):
+    for m in (7, 8):
+        assert us[rules.qkv_slab(m, n)] <= 1.02 * min(us.values())
+    assert rules.qkv_slab(6, n) == 0 and rules.qkv_slab(17, n) == 0
+    assert rules.qkv_slab(9, n) == (6 if n <= 768 else 0)
 
 
 # n-tiles, rows -> us of the O projection (first table), QKV and gate/up (second) by block (16-row tiles * 10 + units of 64 columns;
