@@ -113,10 +113,11 @@ inline int swiglu_row_block_group(int m_tiles, int n_tiles, int k_tiles) {
 // QKV on the slab kernel (gemm_slab.h): n-tiles per workgroup, or 0 where another kernel runs.  One row block (97 to 128 rows): three
 // while that is one round of workgroups, beyond it six, which is one round up to twice as far and half as many reads of A
 // (us at 128 rows with three and with six: d 4096 31.1 and 40.2, d 5120 68.7 and 51.1, d 8192 112.5 and 83.7, where the
-// streaming kernel took 105.3).  Two row blocks: 44 us at 160 to 256 rows of the 8B shape on 2 x 128 workgroups, against 54 to 58 us
+// streaming kernel took 105.3); 20.7 at d 2560 against 22.6 in groups of two there.  Up to 384 n-tiles the streaming kernel in blocks of
+// 64 rows and three n-tiles makes one round (d 2048: 13.4 us against 17.1).  Two row blocks: 44 us at 160 to 256 rows of the 8B shape on 2 x 128 workgroups, against 54 to 58 us
 // on the tile kernel and its merge pass and 50 us in 192 blocks of 128 x 128.
 inline int qkv_slab_group(int m_tiles, int n_tiles) {
-    if (m_tiles > 6 && m_tiles <= 8 && n_tiles > 512) return n_tiles <= 3 * kComputeUnits ? 3 : 6;
+    if (m_tiles > 6 && m_tiles <= 8 && n_tiles > 384) return n_tiles <= 3 * kComputeUnits ? 3 : 6;
     return m_tiles > 8 && m_tiles <= 16 && n_tiles > 384 && n_tiles <= 768 ? 6 : 0;
 }
 

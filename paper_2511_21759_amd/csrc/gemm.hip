@@ -156,12 +156,12 @@ static int stream_ng(int n_tiles, int widest, bool has3) {
     if (has3 && n_tiles <= 3 * kStreamWGs) return 3;
     return widest;
 }
-template <int NG, int PF, class Epi>
+template <int NG, int PF, int MAX, class Epi>
 static void stream_by_rows(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
     if (sh.M_tiles <= 2) launch_stream<2, NG, PF, true>(a, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, NG, PF, true>(a, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 6) launch_stream<6, NG, PF, true>(a, w, sh, ni, e, s);
-    else launch_stream<8, NG, PF, true>(a, w, sh, ni, e, s);
+    else if (MAX == 6 || sh.M_tiles <= 6) launch_stream<6, NG, PF, true>(a, w, sh, ni, e, s);
+    else if constexpr (MAX == 8) launch_stream<8, NG, PF, true>(a, w, sh, ni, e, s);
 }
 
 // workgroup shapes of the tile kernel: (waves, n-tiles per wave, ring depth)
@@ -261,12 +261,14 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     // gate/up projection together, 1.5 % at 64 rows, 0.5 % at 96.)
     const int ng = stream_ng(sh.N_tiles, 3, false), slab = qkv_slab_group(sh.M_tiles, sh.N_tiles);
     // (a narrow model's 97 to 128 rows: blocks of 32 rows and three n-tiles read 160 instead of 288 KB per compute unit at
-    // d = 1024: 10.4 -> 7.2 us; gate/up below: 64 rows and three n-tiles, 10.9 -> 8.5 us.  129 to 256 rows: blocks of 64 rows,
+    // d = 1024: 10.4 -> 7.2 us; with 257 to 384 n-tiles blocks of 64 rows, 16.0 -> 11.3 us at d = 1536, where 128 rows and groups of
+    // two spilled; gate/up below: 64 rows and three n-tiles, 10.9 -> 8.5 us.  129 to 256 rows: blocks of 64 rows,
     // QKV 22.7 -> 9.8 us and gate/up 22.9 -> 10.6 us at 192 rows against the split tile kernel and its merge pass)
     if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 1) launch_stream<2, 3, 4, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles > 6 && sh.M_tiles <= 8 && slab == 0) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles > 8 && sh.M_tiles <= 16 && ng == 1) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8 && ng == 2) stream_by_rows<2, 2>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 6 && ng == 1) stream_by_rows<1, 4, 6>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 6 && ng == 2) stream_by_rows<2, 2, 6>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
     else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);          // 65..96 rows
@@ -310,9 +312,9 @@ void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u1
     if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 2) launch_stream<4, 3, 2, true>(xa, w, sh, ni, e, s);
     else if (rb == 6) launch_stream<4, 6, 2, true>(xa, w, sh, ni, e, s);
     else if (rb == 3) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8 && ng == 2) stream_by_rows<2, 2>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8 && ng == 3) stream_by_rows<3, 1>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4, 8>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 6 && ng == 2) stream_by_rows<2, 2, 6>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 3) stream_by_rows<3, 1, 8>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 6) launch_stream<6, 6, 1, true>(xa, w, sh, ni, e, s);

@@ -159,6 +159,7 @@ def test_swiglu_takes_row_blocks_where_they_are_faster(rules, m, n, k, stream, t
 
 # n-tiles -> us of QKV at 128 rows in blocks of 3 and 6 n-tiles and on the streaming kernel (0)
 QKV_SLAB = [
+    (480, {3: 20.7, 6: 28.0, 0: 22.6}),
     (528, {3: 22.7, 6: 30.3, 0: 24.5}), (672, {3: 28.3, 6: 36.8, 0: 30.9}), (768, {3: 31.1, 6: 40.2, 0: 31.8}), (864, {3: 61.4, 6: 45.6, 0: 66.2}),
     (960, {3: 68.7, 6: 51.1, 0: 73.4}), (1152, {3: 81.7, 6: 60.1, 0: 84.5}), (1344, {3: 96.0, 6: 72.7, 0: 102.7}), (1536, {3: 112.5, 6: 83.7, 0: 105.3}),
 ]
@@ -169,6 +170,7 @@ def test_qkv_of_97_to_128_rows_takes_the_fastest_width(rules, n, us):
     for m in (7, 8):
         assert us[rules.qkv_slab(m, n)] <= 1.02 * min(us.values())
     assert rules.qkv_slab(6, n) == 0 and rules.qkv_slab(17, n) == 0
+    assert rules.qkv_slab(7, 384) == 0
     assert rules.qkv_slab(9, n) == (6 if n <= 768 else 0)
 
 

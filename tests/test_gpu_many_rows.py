@@ -53,6 +53,8 @@ def _width(d, f, layers=1):
     (1024, 3072, [(3, 16), (4, 16), (5, 16), (7, 16), (4, 32)]),   # K split over 64-row blocks, one and two n-tiles per group
     (1024, 5120, [(1, 16), (5, 16), (8, 16)]),                     # gate/up in groups of three
     (2048, 2048, [(3, 16), (7, 16)]),                              # K split with two and four n-tiles per block
+    (1536, 512, [(7, 16), (4, 32)]),                               # QKV from 97 rows on: blocks of 64 rows and three n-tiles
+    (2560, 512, [(7, 16), (4, 32)]),                               # and through LDS
     (2816, 6400, [(7, 16), (4, 32), (9, 16), (16, 16)]),           # all rows through LDS; from 9 row tiles two row blocks for QKV
     (4352, 512, [(7, 16), (4, 32)]),                               # QKV of 816 n-tiles: six per workgroup from 97 rows on
 ])
