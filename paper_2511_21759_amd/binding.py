@@ -132,9 +132,10 @@ def _check(rc: int) -> None:
 
 def _stream() -> int:
     # the handle of torch.cuda.current_stream() without building the Stream object (a call of the jump controller is
-    # bound by its host side: 15.3 us a call, of which the kernel takes 7)
+    # bound by its host side: 15.3 us a call, of which the kernel takes 7); the function is not public, so the public way stays
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _dev_i32(t):

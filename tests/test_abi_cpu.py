@@ -104,3 +104,16 @@ def test_bench_reads_the_gate_up_row_of_every_tracked_profile():
         avg_us, traffic, rel = bench.profile_figures(name)
         assert avg_us is not None and lo_us < avg_us < hi_us, (name, avg_us, rel)
         assert traffic is not None and 1.9e8 < traffic < 2e9, (name, traffic, rel)
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_stream_handle_with_and_without_the_private_function(monkeypatch, private):
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    if private:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 70 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert binding._stream() == (73 if private else 77)
