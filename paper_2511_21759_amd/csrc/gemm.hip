@@ -239,18 +239,18 @@ static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi 
     launch_big_as(big_choice(sh), a, w, sh, ni, e, s);
 }
 
-// The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles.
-template <int NTB, class Epi>
+// The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles; NTW where there is one such block.
+template <int NTB, bool NTW, class Epi>
 static void launch_slab(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
     SlabArgs g;
     g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
     g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
     static std::once_flag attr_once;
     std::call_once(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_slab_kernel<NTB, Epi>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_slab_kernel<NTB, Epi, NTW>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, slab_smem_bytes(NTB));
     });
-    gemm_slab_kernel<NTB, Epi><<<dim3((g.NT + NTB - 1) / NTB, (g.MT_total + 7) / 8), 512, slab_smem_bytes(NTB), s>>>(g, e);
+    gemm_slab_kernel<NTB, Epi, NTW><<<dim3((g.NT + NTB - 1) / NTB, (g.MT_total + 7) / 8), 512, slab_smem_bytes(NTB), s>>>(g, e);
 }
 
 void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOut out, Workspace ws, hipStream_t s) {
@@ -272,8 +272,9 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     else if (sh.M_tiles <= 2) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
     else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);          // 65..96 rows
-    else if (slab == 3) launch_slab<3>(xa, w, sh, ni, e, s);
-    else if (slab == 6) launch_slab<6>(xa, w, sh, ni, e, s);
+    else if (slab == 3) launch_slab<3, true>(xa, w, sh, ni, e, s);
+    else if (slab == 6 && sh.M_tiles <= 8) launch_slab<6, true>(xa, w, sh, ni, e, s);
+    else if (slab == 6) launch_slab<6, false>(xa, w, sh, ni, e, s);
     else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }
@@ -318,7 +319,7 @@ void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u1
     else if (sh.M_tiles <= 2) launch_stream<2, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 6) launch_stream<6, 6, 1, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8) launch_slab<6>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8) launch_slab<6, true>(xa, w, sh, ni, e, s);
     else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }

@@ -27,7 +27,8 @@ constexpr int kSlabKP = 2;                                                    //
 constexpr int slab_stages(int ntb) { return 150 / (kSlabKP * (8 + ntb)); }
 constexpr int slab_smem_bytes(int ntb) { return slab_stages(ntb) * kSlabKP * (8 + ntb) * 1024 + 128 * 4; }
 
-template <int NTB, class Epi>
+// NTW: the weight tiles are loaded non-temporally.
+template <int NTB, class Epi, bool NTW>
 __global__ __launch_bounds__(512) void gemm_slab_kernel(SlabArgs g, Epi epi) {
     constexpr int CS = NTB % 2 == 0 ? 2 : 1, RS = 4 / CS;       // the four waves of a group over columns and rows
     constexpr int WT = NTB / CS, MW = 8 / RS;                   // tiles per wave
@@ -42,8 +43,9 @@ __global__ __launch_bounds__(512) void gemm_slab_kernel(SlabArgs g, Epi epi) {
     const int ns = g.KT / kSlabKP;                              // stages (k-tiles come in eights)
 
     // Of a stage's kSlabKP x NTB tiles of W wave w copies those numbered w, w + 8, .., of its 16 tiles of A those numbered
-    // 7 - w and 15 - w.  W is read once (by every row block), non-temporally: gate/up 44.7 -> 42.5 us at 128 rows.  The
-    // workgroups walk K from different places, so that they do not ask the same L2 channels for the same tiles of A at once.
+    // 7 - w and 15 - w.  A single row block reads W once, non-temporally (gate/up 44.7 -> 42.5 us at 128 rows); two of them leave
+    // it to the L2s for each other (QKV of d 3072: 30.4 -> 27.8 us at 144 rows, 31.0 -> 31.6 at 256).  The workgroups
+    // walk K from different places, so that they do not ask the same L2 channels for the same tiles of A at once.
     constexpr int PW = (kSlabKP * NTB + 7) / 8, RW = (kSlabKP * NTB - 1) % 8 + 1, PA = kSlabKP;
     const bool fw = w < RW;                                     // whether this wave has PW tiles of W to copy or one less
     const char *srcw[PW], *srca[PA];
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(512) void gemm_slab_kernel(SlabArgs g, Epi epi) {
             const int t = i * 8 + w;
             if (i < PW - 1 || fw)
                 __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(srcw[i] + ow + lane_off),
-                                                 (__attribute__((address_space(3))) void *)(smem + (slot * ST + t / NTB * TK + 8 + t % NTB) * 1024), 16, 0, 2);
+                                                 (__attribute__((address_space(3))) void *)(smem + (slot * ST + t / NTB * TK + 8 + t % NTB) * 1024), 16, 0, NTW ? 2 : 0);
         }
 #pragma unroll
         for (int i = 0; i < PA; i++)
