@@ -1,8 +1,10 @@
 """GPU parity of the GEMM kernels beyond 128 rows at shapes where their row blocks end raggedly: 128- and 256-row blocks
 of the LDS-ring kernel, the tile kernel with and without its K split, and the partial sums of squares of 64 columns that
 all of them leave for the next RMSNorm.  Element by element against the oracle, with the bars of test_gpu_parity."""
+import numpy as np
 import pytest
 
+from oracle import odb_oracle as o
 from paper_2511_21759_amd import workloads as W
 from test_gpu_parity import Pair, run_prefill_case, run_step_case
 
@@ -196,3 +198,22 @@ def test_scratch_that_cannot_grow_past_the_least_room():
         out.append(a)
     for i in (0, 2):
         assert torch.allclose(torch.log(out[0][i]), torch.log(out[1][i]), atol=2e-2)
+
+
+@pytest.mark.parametrize("vocab", [50000, 70000])
+def test_lm_head_of_one_row_block_with_a_ragged_last_block(vocab):
+    """33 to 128 rows against vocabularies that take blocks of 256 (up to 65536 columns) and 512 columns and fill the last one in part;
+    most winning tokens are in that block."""
+    assert vocab % (512 if vocab > 65536 else 256) != 0
+    p = Pair(dict(n_layers=1, d_model=256, n_heads=2, head_dim=128, d_ff=256, vocab=vocab, rope_base=10000.0, rms_eps=1e-5, mask_id=5))
+    try:
+        lm = np.random.default_rng(vocab).normal(0, 0.02, (vocab, 256)).astype(np.float32)
+        lm[-24:] *= 6
+        p.set(o.T_LM, 0, lm)
+        for S, b in ((3, 16), (8, 16)):
+            wl = W.decode_workload(p.shape, 20, 30, b, S, 40 + S)
+            cache, oc = run_prefill_case(p, wl.tokens, wl.resp_off, "set-up")
+            _, am, _, _ = run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "vocab %d, %d x %d" % (vocab, S, b))
+            assert (am >= vocab - 24).mean() > 0.5
+    finally:
+        p.close()
