@@ -164,9 +164,8 @@ static void stream_by_rows(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, 
     else if constexpr (MAX == 8) launch_stream<8, NG, PF, true>(a, w, sh, ni, e, s);
 }
 
-// workgroup shapes of the tile kernel: (waves, n-tiles per wave, ring depth)
-struct TileCfg { int nw, ngw; };
-static TileCfg tile_cfg(int m_tiles) { return m_tiles > 8 ? TileCfg{8, 2} : TileCfg{8, 1}; }
+// n-tiles of a workgroup of the tile kernel
+static int tile_columns(int m_tiles) { return m_tiles > 8 ? 16 : 8; }
 
 template <class Epi> constexpr TileEpilogue tile_epilogue_of = TileEpilogue::resid;
 template <> constexpr TileEpilogue tile_epilogue_of<EpiQKV> = TileEpilogue::qkv;
@@ -180,8 +179,7 @@ static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
     g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
     g.partial = ws.partial;
     const int m_blocks = (sh.M_tiles + 7) / 8;
-    const TileCfg c = tile_cfg(sh.M_tiles);
-    const int per_wg = c.nw * c.ngw;
+    const int per_wg = tile_columns(sh.M_tiles);
     g.n_blocks = (sh.N_tiles + per_wg - 1) / per_wg;
     const int ks = may_split ? tile_slices(tile_epilogue_of<Epi>, sh.M_tiles, sh.N_tiles, sh.K_tiles, ws.partial_bytes) : 1;
     g.KS = ks;
@@ -189,10 +187,12 @@ static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
     // (8 waves x 1 n-tile, ring of 8) for the multi-draft step, (8 x 2, ring of 4) for compute-bound shapes:
     // the best of the shapes tried on MI355X (4-wave workgroups of 1, 2 or 4 n-tiles per wave, 8 x 2 with a ring of 8
     // and 2 or 4 k-tiles per barrier were all slower or equal - occupancy beats wider tiles here; 8 x 4 spills)
-    // (a single block of rows: every weight tile is read once, non-temporally)
-    if (c.ngw == 1 && m_blocks == 1) gemm_tile_kernel<8, 1, 8, Epi, true><<<grid, 512, 0, s>>>(g, e);
-    else if (c.ngw == 1) gemm_tile_kernel<8, 1, 8, Epi><<<grid, 512, 0, s>>>(g, e);
-    else gemm_tile_kernel<8, 2, 4, Epi><<<grid, 512, 0, s>>>(g, e);
+    // (a single block of rows, which O and down alone bring here: every weight tile is read once, non-temporally)
+    if (is_resid<Epi>::value && m_blocks == 1) {
+        if constexpr (is_resid<Epi>::value) gemm_tile_kernel<1, 8, Epi, true><<<grid, 512, 0, s>>>(g, e);
+    } else {
+        gemm_tile_kernel<2, 4, Epi><<<grid, 512, 0, s>>>(g, e);
+    }
     if (ks > 1) {
         if constexpr (!is_row_stats<Epi>::value)
             tile_epilogue_kernel<Epi><<<dim3((sh.N_tiles + 7) / 8, sh.M_tiles), 512, 0, s>>>(g, e);
@@ -330,8 +330,7 @@ constexpr int kLmNG = 6;      // n-tiles per group of the LM head at up to 32 ro
 // Up to 32 rows the group is four n-tiles wide where that leaves fewer padded slots in a workgroup's last group
 // (126464 columns: 31 n-tiles per workgroup = eight groups of four with one slot idle, against six groups of six
 // with five; measured 166 -> 159 us).
-static int lm_ng(int n_tiles, int m_tiles) {
-    if (m_tiles > 2) return kLmNG;
+static int lm_ng(int n_tiles) {
     const int per = (n_tiles + kStreamWGs - 1) / kStreamWGs;
     return (per + 3) / 4 * 4 < (per + kLmNG - 1) / kLmNG * kLmNG ? 4 : kLmNG;
 }
@@ -351,20 +350,19 @@ static bool lm_one_block(int m_tiles) { return m_tiles > 2 && m_tiles <= 8; }
 static int lm_one_wn(int n_tiles) { return n_tiles <= 8 * kStreamWGs ? 2 : n_tiles <= 16 * kStreamWGs ? 4 : 8; }
 int lm_stats_parts(int n_tiles, int m_tiles) {
     if (lm_one_block(m_tiles)) return (n_tiles + 4 * lm_one_wn(n_tiles) - 1) / (4 * lm_one_wn(n_tiles));
-    if (m_tiles <= 8) {
-        const int ng = lm_ng(n_tiles, m_tiles);
+    if (m_tiles <= 2) {
+        const int ng = lm_ng(n_tiles);
         const int groups = (n_tiles + ng - 1) / ng;
         return (groups < kStreamWGs ? groups : kStreamWGs) * ng;
     }
     if (const int wn = lm_big(GemmShape{m_tiles, n_tiles, 0}).wn) return (n_tiles + 4 * wn - 1) / (4 * wn);
-    const TileCfg c = tile_cfg(m_tiles);
-    return (n_tiles + c.nw * c.ngw - 1) / (c.nw * c.ngw);
+    return (n_tiles + tile_columns(m_tiles) - 1) / tile_columns(m_tiles);
 }
 
 void launch_gemm_lmstats(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, float *stats, Workspace ws,
                          hipStream_t s) {
     const int parts = lm_stats_parts(sh.N_tiles, sh.M_tiles);
-    if (sh.M_tiles <= 2 && lm_ng(sh.N_tiles, sh.M_tiles) == 4) launch_stream<2, 4, 4, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
+    if (sh.M_tiles <= 2 && lm_ng(sh.N_tiles) == 4) launch_stream<2, 4, 4, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
     else if (sh.M_tiles <= 2) launch_stream<2, kLmNG, 4, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
     else if (lm_one_block(sh.M_tiles)) {
         // 33..128 rows.  A streaming workgroup reads all activation rows once per group of six n-tiles, and with 31

@@ -1,5 +1,5 @@
-// binary16 MFMA GEMM  C[M,N] = A[M,K] * W[N,K]^T  for 33 rows and more (the multi-draft step,
-// the prefill, the long-context step).  Same operand layouts and epilogues as gemm_core.h.
+// binary16 MFMA GEMM  C[M,N] = A[M,K] * W[N,K]^T  where neither the streaming nor the
+// LDS-ring kernels take the shape (from 33 rows on).  Same operand layouts and epilogues as gemm_core.h.
 //
 // A workgroup computes a 128-row block x (8*NGW n-tiles) x one slice of K.  Its eight waves split
 // the n-tiles; the 128 x 32 slab of A that a k-step needs is shared through LDS: every wave fetches
@@ -44,17 +44,16 @@ __device__ __forceinline__ void merge_stat(float &m, float &s, int &a, float om,
     m = nm;
 }
 
-// NW waves per workgroup, each NGW n-tiles wide: the workgroup covers NW*NGW n-tiles.  One k-tile per barrier; every
-// wave keeps PF k-tiles (its share of the A slab and its own weight tiles) in flight.  The A slab goes through a ring
+// Eight waves per workgroup, each NGW (one or two) n-tiles wide: the workgroup covers 8 * NGW n-tiles.  One k-tile per barrier;
+// every wave keeps PF k-tiles (its tile of the A slab and its own weight tiles) in flight.  The A slab goes through a ring
 // of kTileSlots LDS slots (a slot is rewritten four barriers after its last reader asked for it).
 constexpr int kTileSlots = 4;
 constexpr int tile_smem_bytes() { return kTileSlots * 8 * 1024 + 8 * 1024 + 128 * 4; }
 
 // SW: the weight tiles are read by one workgroup only (a single block of rows), so they are loaded non-temporally.
-template <int NW, int NGW, int PF, class Epi, bool SW = false>
-__global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi) {
-    constexpr int AW = 8 / NW;                 // A tiles (per k-tile) of the slab each wave fetches
-    static_assert(NW == 4 || NW == 8, "waves per workgroup");
+template <int NGW, int PF, class Epi, bool SW = false>
+__global__ __launch_bounds__(512) void gemm_tile_kernel(TileArgs g, Epi epi) {
+    static_assert(NGW <= 2, "two sets of slab registers");
     static_assert(PF % kTileSlots == 0, "ring slots and register buffers are indexed by the unrolled step");
     __shared__ __attribute__((aligned(16))) char smem[tile_smem_bytes()];
     frag_t (*a_lds)[8][64] = reinterpret_cast<frag_t (*)[8][64]>(smem);                    // [slots][8 m-tiles][64 lanes]
@@ -68,7 +67,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
     const int mt0 = blockIdx.y * 8;
     const int k_lo = (int)((unsigned)ks * (unsigned)g.KT / (unsigned)g.KS), k_hi = (int)((unsigned)(ks + 1) * (unsigned)g.KT / (unsigned)g.KS);
     const int nk = k_hi - k_lo;                 // k-tiles of this slice
-    const int nt0 = (nb * NW + w) * NGW;
+    const int nt0 = (nb * 8 + w) * NGW;
 
     const u16 *wp[NGW];
 #pragma unroll
@@ -76,45 +75,38 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
         int nt = nt0 + j < g.NT ? nt0 + j : g.NT - 1;
         wp[j] = g.W + ((size_t)nt * g.KT + k_lo) * kTileElems + lane * 8;
     }
-    const u16 *ap[AW];                                                             // the A tiles this wave fetches
-#pragma unroll
-    for (int i = 0; i < AW; i++) {
-        int mt = mt0 + w * AW + i < g.MT_total ? mt0 + w * AW + i : g.MT_total - 1;
-        ap[i] = g.A + ((size_t)k_lo * g.MT_total + mt) * kTileElems + lane * 8;
-    }
+    const int mt_a = mt0 + w < g.MT_total ? mt0 + w : g.MT_total - 1;             // the row tile of A that this wave fetches
+    const u16 *ap = g.A + ((size_t)k_lo * g.MT_total + mt_a) * kTileElems + lane * 8;
     const size_t a_step = (size_t)g.MT_total * kTileElems;
 
-    // row scales of the fused RMSNorm: 128 / NW rows per wave; a row's partial sums (up to 256) are one
+    // row scales of the fused RMSNorm: 16 rows per wave; a row's partial sums (up to 256) are one
     // 16-byte load per lane, and the loads of 16 rows are issued back to back
     if (g.ssq) {
         const int si = 4 * lane;
+        f32x4 sv[16];
+        float q[16];
 #pragma unroll
-        for (int r0 = 0; r0 < 16 * AW; r0 += 16) {
-            f32x4 sv[16];
-            float q[16];
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-                int row = (mt0 + w * AW) * 16 + r0 + r;
-                row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
-                const float *p = g.ssq + (size_t)row * g.n_ssq;
-                q[r] = 0.f;
-                for (int i0 = 256; i0 < g.n_ssq; i0 += 256) {       // rows wider than 4096 only
-                    const int i = i0 + si, ic = i < g.n_ssq - 4 ? i : g.n_ssq - 4;
-                    f32x4 v = *reinterpret_cast<const f32x4 *>(p + ic);
-                    q[r] += i < g.n_ssq ? (v[0] + v[1]) + (v[2] + v[3]) : 0.f;
-                }
-                sv[r] = *reinterpret_cast<const f32x4 *>(p + (si < g.n_ssq - 4 ? si : g.n_ssq - 4));
+        for (int r = 0; r < 16; r++) {
+            int row = (mt0 + w) * 16 + r;
+            row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
+            const float *p = g.ssq + (size_t)row * g.n_ssq;
+            q[r] = 0.f;
+            for (int i0 = 256; i0 < g.n_ssq; i0 += 256) {       // rows wider than 4096 only
+                const int i = i0 + si, ic = i < g.n_ssq - 4 ? i : g.n_ssq - 4;
+                f32x4 v = *reinterpret_cast<const f32x4 *>(p + ic);
+                q[r] += i < g.n_ssq ? (v[0] + v[1]) + (v[2] + v[3]) : 0.f;
             }
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-                float t = q[r] + (si < g.n_ssq ? (sv[r][0] + sv[r][1]) + (sv[r][2] + sv[r][3]) : 0.f);
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-                if (lane == 0) s_rstd[w * 16 * AW + r0 + r] = 1.0f / sqrtf(t * g.inv_d + g.eps);
-            }
+            sv[r] = *reinterpret_cast<const f32x4 *>(p + (si < g.n_ssq - 4 ? si : g.n_ssq - 4));
         }
-    } else if (lane < 16 * AW) {
-        s_rstd[w * 16 * AW + lane] = 1.0f;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            float t = q[r] + (si < g.n_ssq ? (sv[r][0] + sv[r][1]) + (sv[r][2] + sv[r][3]) : 0.f);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+            if (lane == 0) s_rstd[w * 16 + r] = 1.0f / sqrtf(t * g.inv_d + g.eps);
+        }
+    } else if (lane < 16) {
+        s_rstd[w * 16 + lane] = 1.0f;
     }
 
     f32x4 acc[8][NGW];
@@ -125,11 +117,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
 
     // Loads past the end of the slice fetch its last tile again and are never used: the refills of the main loop
     // are unconditional, so the order of the outstanding loads is fixed and every wait counts exactly.
-    frag_t wr[PF][NGW], ar[PF][AW];
+    frag_t wr[PF][NGW], ar[PF];
     auto load_step = [&](int slot, int c) __attribute__((always_inline)) {
         const int k = c < nk ? c : nk - 1;
-#pragma unroll
-        for (int i = 0; i < AW; i++) ar[slot][i] = ld_frag(ap[i] + k * a_step);
+        ar[slot] = ld_frag(ap + k * a_step);
 #pragma unroll
         for (int j = 0; j < NGW; j++)
             wr[slot][j] = SW ? ld_frag_stream(wp[j] + (size_t)k * kTileElems) : ld_frag(wp[j] + (size_t)k * kTileElems);
@@ -137,29 +128,22 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
 #pragma unroll
     for (int s = 0; s < PF; s++) load_step(s, s);
 
-    // PIPE (up to two n-tiles per wave): step c stores the slab of step c+1, and after the barrier reads it into a second
-    // set of registers while the MFMAs of step c run on the set read one step earlier.  Wider waves have no registers
-    // for the second set: they store, wait and read the slab of step c itself.
-    constexpr bool PIPE = NGW <= 2;
-    frag_t a[PIPE ? 2 : 1][8];
-    if constexpr (PIPE) {
+    // Step c stores the slab of step c+1, and after the barrier reads it into a second set of registers while the MFMAs
+    // of step c run on the set read one step earlier.
+    frag_t a[2][8];
+    a_lds[0][w][lane] = ar[0];
+    __syncthreads();
 #pragma unroll
-        for (int i = 0; i < AW; i++) a_lds[0][w * AW + i][lane] = ar[0][i];
-        __syncthreads();
-#pragma unroll
-        for (int m = 0; m < 8; m++) a[0][m] = a_lds[0][m][lane];
-    }
+    for (int m = 0; m < 8; m++) a[0][m] = a_lds[0][m][lane];
     auto step = [&](int s, int c) __attribute__((always_inline)) {
-        constexpr int nxt = PIPE ? 1 : 0;
-#pragma unroll
-        for (int i = 0; i < AW; i++) a_lds[(s + nxt) % kTileSlots][w * AW + i][lane] = ar[(s + nxt) % PF][i];
+        a_lds[(s + 1) % kTileSlots][w][lane] = ar[(s + 1) % PF];
         __syncthreads();
 #pragma unroll
-        for (int m = 0; m < 8; m++) a[(s + nxt) & nxt][m] = a_lds[(s + nxt) % kTileSlots][m][lane];
+        for (int m = 0; m < 8; m++) a[(s + 1) & 1][m] = a_lds[(s + 1) % kTileSlots][m][lane];
 #pragma unroll
         for (int m = 0; m < 8; m++)
 #pragma unroll
-            for (int j = 0; j < NGW; j++) acc[m][j] = mfma16(wr[s][j], a[s & nxt][m], acc[m][j]);
+            for (int j = 0; j < NGW; j++) acc[m][j] = mfma16(wr[s][j], a[s & 1][m], acc[m][j]);
         load_step(s, c + PF);
     };
     int cb = 0;
@@ -193,9 +177,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
     if constexpr (is_row_stats<Epi>::value) {
         // softmax statistics per row over this workgroup's n-tiles: lane-local, across the four lane
         // groups, across the wave's NGW tiles, then across the eight waves through LDS
-        float *st_m = reinterpret_cast<float *>(smem);               // the A slots are free now: [NW waves][128 rows]
-        float *st_s = st_m + NW * 128;
-        int *st_a = reinterpret_cast<int *>(st_s + NW * 128);
+        float *st_m = reinterpret_cast<float *>(smem);               // the A slots are free now: [8 waves][128 rows]
+        float *st_s = st_m + 8 * 128;
+        int *st_a = reinterpret_cast<int *>(st_s + 8 * 128);
         const int mi = lane & 15, gq = lane >> 4;
 #pragma unroll
         for (int m = 0; m < 8; m++) {
@@ -234,7 +218,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
             float rm = st_m[r], rs = st_s[r];
             int ra = st_a[r];
 #pragma unroll
-            for (int x = 1; x < NW; x++) merge_stat(rm, rs, ra, st_m[x * 128 + r], st_s[x * 128 + r], st_a[x * 128 + r]);
+            for (int x = 1; x < 8; x++) merge_stat(rm, rs, ra, st_m[x * 128 + r], st_s[x * 128 + r], st_a[x * 128 + r]);
             if (row < g.MT_total * 16) {
                 float *p = epi.stats + ((size_t)row * epi.n_part + nb) * 3;
                 p[0] = rm;
@@ -259,7 +243,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(TileArgs g, Epi epi)
                     if (lane < 16) s_q[w * 128 + m * 16 + lane] = q;
                 }
                 __syncthreads();
-                for (int i = threadIdx.x; i < 4 * 128; i += 64 * NW) {
+                for (int i = threadIdx.x; i < 4 * 128; i += 512) {
                     const int r = i & 127, c4 = i >> 7, row = mt0 * 16 + r;     // 64 columns = two waves
                     if (row < g.MT_total * 16) epi.no.ssq[(size_t)row * epi.no.n_ssq + nb * 4 + c4] = s_q[2 * c4 * 128 + r] + s_q[(2 * c4 + 1) * 128 + r];
                 }
