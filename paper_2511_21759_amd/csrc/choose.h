@@ -55,16 +55,16 @@ inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int uni
 
 // K slices of the tile kernel (gemm_tile.h), which need not divide K; `room` bounds the bytes of partial sums.
 //
-// The largest power of two that divides K and fits one round of workgroups stands, unless the model below puts another count
-// 5 % (up to 128 rows 2 %) under it.  The model was fitted to 6400 launches measured inside refreshes (m_tiles 3 to 188, d from 512 to 8192; 7 % off
+// The count with the smallest time by the model below; up to 128 rows it has to lie 2 % under the largest power of two that divides
+// K and fits one round of workgroups.  The model was fitted to 6400 launches measured inside refreshes (m_tiles 3 to 188, d from 512 to 8192; 7 % off
 // at the root mean square): a launch lasts as long as its fullest compute unit has blocks and k-tiles of the LONGEST slice, up
 // to 128 rows at least as long as the weight stream; then there is the epilogue on the few compute units that own a block, or
 // the merge pass.  It matters too on which of the eight XCDs, which take the workgroups in turn, blocks meet: slices that share
 // no factor with eight make every XCD read all of A, blocks per row of blocks that share none make every XCD that works
 // on a column of blocks read its weights, and where there are few of them, counts that bring the workgroups of one slice
 // together on one XCD cost about a microsecond.
-// Over 858 sizes that take the tile kernel it is 2.3 % faster than the power of two on average and slower by more than 3 % at two, 5 % at
-// most; with 1 % for 5 it was 2.6 % faster and slower by more than 3 % at 13 (144 rows, N 2048, K 5632: 14 slices 20.0 us, 16 17.8);
+// Over 858 sizes that take the tile kernel it is 3 % faster than the power of two on average and slower by more than 3 % at
+// 15 (measured while the merge pass added nine to fifteen slices one after the other);
 // a model with mean slices and without the XCDs was 1.7 % faster and slower by more than 3 % at 108, up to 28 %.
 // Microseconds with the merge pass, by slices: 1232 rows, N 1280, K 5120: 4 29.3, 5 37.6; 144 rows, N 3584, K 18944: 8 44.8,
 // 9 50.8; 640 rows, N 4096, K 12288: 2 96.7, 3 76.3; 128 rows, N 4096, K 4096: 5 20.1, 6 19.1, 8 20.4.
@@ -91,7 +91,7 @@ inline int tile_slices(TileEpilogue epi, int m_tiles, int n_tiles, int k_tiles, 
     };
     int best = 1;
     while (blocks * best * 2 <= kComputeUnits && k_tiles % (best * 2) == 0 && fits(best * 2)) best *= 2;
-    double best_us = (wide ? 0.95 : 0.98) * us(best);
+    double best_us = (wide ? 1.0 : 0.98) * us(best);
     for (int ks = 1; ks <= 16; ks++)
         if (fits(ks) && us(ks) < best_us) { best = ks; best_us = us(ks); }
     return best;

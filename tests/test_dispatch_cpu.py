@@ -114,7 +114,7 @@ SLICES = [
     ("down", 16, 256, 384, {1: 164.5, 2: 88.6, 3: 65.2, 4: 53.3, 5: 47.6, 6: 46.9, 7: 45.3, 8: 44.1}),
     ("o", 13, 128, 64, {1: 35.2, 2: 22.0, 3: 18.5, 4: 17.5, 5: 15.4, 6: 15.1, 7: 15.0, 8: 15.9, 9: 16.1, 10: 17.3, 11: 16.6, 12: 18.3, 14: 18.5, 16: 20.0}),
     ("down", 9, 224, 592, {1: 223.4, 2: 118.4, 3: 86.6, 4: 68.5, 5: 60.7, 6: 54.7, 7: 53.2, 8: 48.2, 9: 54.6, 10: 68.1, 11: 67.3, 12: 60.2, 14: 60.5, 16: 58.7}),
-    ("down", 9, 128, 176, {1: 74.6, 2: 41.0, 3: 31.1, 4: 26.0, 5: 23.3, 6: 21.6, 7: 20.4, 8: 19.3, 9: 19.7, 10: 19.7, 11: 19.7, 12: 19.7, 14: 20.0, 16: 17.8}),
+    ("down", 9, 128, 176, {1: 74.6, 2: 41.0, 3: 31.1, 4: 26.0, 5: 23.3, 6: 21.6, 7: 19.9, 8: 19.3, 9: 18.9, 10: 18.2, 11: 18.0, 12: 18.1, 13: 17.9, 14: 17.9, 15: 18.2, 16: 17.7}),
     ("o", 3, 160, 80, {1: 23.3, 2: 17.9, 3: 15.1, 4: 12.7, 5: 12.3, 6: 12.0, 7: 11.8, 8: 12.1, 9: 13.4, 10: 13.4, 11: 14.6, 12: 14.3, 14: 18.9, 16: 16.8}),
     ("down", 63, 64, 96, {1: 43.5, 2: 26.6, 3: 22.4, 4: 21.3, 5: 19.9, 6: 19.7, 7: 24.7, 8: 20.8}),
     ("gu", 9, 704, 64, {1: 35.5, 2: 31.8, 3: 45.2, 4: 42.2, 5: 44.4}),
