@@ -21,7 +21,9 @@
  *     Calls with a stream argument are asynchronous on it unless they say
  *     otherwise (odb_generate is synchronous): outputs are valid once the caller
  *     has synchronised the stream.  Calls that use the same model must be issued
- *     on one stream at a time (they share scratch).
+ *     on one stream at a time (they share scratch).  A model's scratch grows with the largest call it has served
+ *     and is freed with the model; beside the activations of that call it holds 32 MiB of partial sums for split
+ *     projections, with many rows up to 96 MiB (16 bytes per row and channel; 32 MiB where more cannot be had).
  *   - Every function returns ODB_OK (0) or a negative ODB_E_* code; a message
  *     for the last failure on the calling thread is kept in odb_last_error().
  *     Arguments are validated on the host before any kernel is launched, so an
@@ -178,7 +180,7 @@ int odb_model_status(odb_model *m);
  * that they are added in the order of odb_block_step); the call itself allocates and frees nothing.
  * A step whose rows need more than that area is rejected with ODB_E_UNSUPPORTED before
  * anything is launched (at the 8B shape of the paper's models, d = 4096, d_ff = 12288,
- * vocab = 126464, the area holds steps of up to 128 rows).  All models on one GPU share the
+ * vocab = 126464, the area holds steps of up to 352 rows in blocks of 32).  All models on one GPU share the
  * area and every call overwrites what the last one left there: calls on one GPU that overlap
  * in time, on whatever streams or models, race; issue them one after the other on one
  * stream.  Other errors as odb_block_step. */

@@ -63,8 +63,7 @@ inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int uni
 // no factor with eight make every XCD read all of A, blocks per row of blocks that share none make every XCD that works
 // on a column of blocks read its weights, and where there are few of them, counts that bring the workgroups of one slice
 // together on one XCD cost about a microsecond.
-// Over 858 sizes that take the tile kernel it is 3 % faster than the power of two on average and slower by more than 3 % at
-// 15 (measured while the merge pass added nine to fifteen slices one after the other);
+// Over 858 sizes that take the tile kernel it is 2.8 % faster than the power of two on average and slower by more than 3 % at 12;
 // a model with mean slices and without the XCDs was 1.7 % faster and slower by more than 3 % at 108, up to 28 %.
 // Microseconds with the merge pass, by slices: 1232 rows, N 1280, K 5120: 4 29.3, 5 37.6; 144 rows, N 3584, K 18944: 8 44.8,
 // 9 50.8; 640 rows, N 4096, K 12288: 2 96.7, 3 76.3; 128 rows, N 4096, K 4096: 5 20.1, 6 19.1, 8 20.4.
@@ -87,7 +86,7 @@ inline int tile_slices(TileEpilogue epi, int m_tiles, int n_tiles, int k_tiles, 
         if (ks == 1) return loop + rounds * (epi == TileEpilogue::qkv ? 17.5 : epi == TileEpilogue::swiglu ? 10.5 : 10.4);
         const double merge = epi == TileEpilogue::qkv ? 15.1 : epi == TileEpilogue::swiglu ? 14.1 : 7.2, sums = ks * out_mb;
         const double crowd = (gx == 8 ? 1.66 / n_blocks : 0) + (blocks * ks > 230 ? 0.44 : 0);
-        return loop + merge + 0.302 * sums + (sums > 26 ? 0.3 * (sums - 26) : 0) + crowd;      // (beyond 26 MB they leave the L2s)
+        return loop + merge + 0.302 * sums + (sums > 26 ? 0.1 * (sums - 26) : 0) + crowd;      // (beyond 26 MB they leave the L2s)
     };
     int best = 1;
     while (blocks * best * 2 <= kComputeUnits && k_tiles % (best * 2) == 0 && fits(best * 2)) best *= 2;

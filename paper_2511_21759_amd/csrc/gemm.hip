@@ -199,7 +199,7 @@ static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
     }
 }
 
-// 256 rows and more: blocks of MBT x 16 rows through LDS (gemm_big.h), 64 * WN columns wide
+// blocks of MBT x 16 rows through LDS (gemm_big.h), 64 * WN columns wide
 template <int WN, class Epi, int MBT = 16>
 static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
     BigArgs g;
@@ -239,7 +239,7 @@ static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi 
     launch_big_as(big_choice(sh), a, w, sh, ni, e, s);
 }
 
-// The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles; NTW where there is one such block.
+// The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles.
 template <int NTB, bool NTW, class Epi>
 static void launch_slab(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
     SlabArgs g;
@@ -273,7 +273,7 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
     else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);          // 65..96 rows
     else if (slab == 3) launch_slab<3, true>(xa, w, sh, ni, e, s);
-    else if (slab == 6 && sh.M_tiles <= 8) launch_slab<6, true>(xa, w, sh, ni, e, s);
+    else if (slab == 6 && (sh.M_tiles <= 8 || sh.M_tiles >= 12)) launch_slab<6, true>(xa, w, sh, ni, e, s);
     else if (slab == 6) launch_slab<6, false>(xa, w, sh, ni, e, s);
     else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
@@ -300,8 +300,8 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
     }
     else if (sh.M_tiles <= 6 && (long_k || sh.M_tiles > 2) && ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
-    // (128-row blocks only for the O projection: at 1024 rows 256 blocks of 128 x 128 take 57 us against 64 us for the
-    // tile kernel and its reduction pass; the down projection, three times as long in K, measured 4 % slower that way)
+    // (128-row blocks only for the O projection: at 1024 rows of the 8B shape 256 blocks of 128 x 128 take 47.7 us against 50.4 for
+    // the tile kernel and its merge pass; the down projection, three times as long in K, takes 126 us against 105)
     else if (big_choice(sh).wn && (big_choice(sh).mbt == 16 || sh.K_tiles <= sh.N_tiles))
         launch_big(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
     else launch_tile(a, w, sh, NormIn{nullptr, 0, 0.f}, e, ws, true, s);

@@ -1,6 +1,6 @@
-// binary16 MFMA GEMM  C[M,N] = A[M,K] * W[N,K]^T  for the compute-bound shapes (256 rows and more:
-// the cache-refresh prefill, the batched long-context step).  Same operand layouts and epilogues
-// as gemm_core.h / gemm_tile.h.
+// binary16 MFMA GEMM  C[M,N] = A[M,K] * W[N,K]^T  for the compute-bound shapes (the cache-refresh
+// prefill, the batched long-context step: from 129 rows on where its blocks fill the chip) and the LM head from 33 rows on.
+// Same operand layouts and epilogues as gemm_core.h / gemm_tile.h.
 //
 // A workgroup of eight waves computes a 256 x (64 WN) block of C over all of K, WN = 4, 3 or 2 (256, 192 or
 // 128 columns: the narrower blocks exist for shapes whose count of 256-wide blocks fills the compute units

@@ -111,7 +111,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
     constexpr int RPW = MT * 16 / WK;                      // rows per wave
     float q[RPW];
     f32x4 sv[RPW];
-    const int si = 4 * lane, sic = si < g.n_ssq - 4 ? si : g.n_ssq - 4;     // n_ssq is a multiple of 16
+    const int si = 4 * lane, sic = si < g.n_ssq - 4 ? si : g.n_ssq - 4;     // n_ssq is a multiple of 4
 #pragma unroll
     for (int j = 0; j < RPW; j++) {
         q[j] = 0.f;

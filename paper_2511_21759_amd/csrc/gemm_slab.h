@@ -43,9 +43,10 @@ __global__ __launch_bounds__(512) void gemm_slab_kernel(SlabArgs g, Epi epi) {
     const int ns = g.KT / kSlabKP;                              // stages (k-tiles come in eights)
 
     // Of a stage's kSlabKP x NTB tiles of W wave w copies those numbered w, w + 8, .., of its 16 tiles of A those numbered
-    // 7 - w and 15 - w.  A single row block reads W once, non-temporally (gate/up 44.7 -> 42.5 us at 128 rows); two of them leave
-    // it to the L2s for each other (QKV of d 3072: 30.4 -> 27.8 us at 144 rows, 31.0 -> 31.6 at 256).  The workgroups
-    // walk K from different places, so that they do not ask the same L2 channels for the same tiles of A at once.
+    // 7 - w and 15 - w.  A single row block reads W once, non-temporally (gate/up 44.7 -> 42.5 us at 128 rows).  Of two row
+    // blocks the second finds the tiles in L2 or not, but only a nearly empty one gains by their being kept there (QKV of d 3072 at 144
+    // rows 30.4 -> 27.8 us, at 256 31.0 -> 31.6; over all widths 4 % faster at 144 rows, equal at 176, 1.5 % slower at 256).  The
+    // workgroups walk K from different places, so that they do not ask the same L2 channels for the same tiles of A at once.
     constexpr int PW = (kSlabKP * NTB + 7) / 8, RW = (kSlabKP * NTB - 1) % 8 + 1, PA = kSlabKP;
     const bool fw = w < RW;                                     // whether this wave has PW tiles of W to copy or one less
     const char *srcw[PW], *srca[PA];
