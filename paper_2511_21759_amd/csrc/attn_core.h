@@ -52,12 +52,12 @@ struct KeyVis {
     unsigned long long visible;
     int m, row0;
 };
-template <int DH, int QT, bool MASK, bool POOL = false>
+template <int DH, int QT, bool MASK, bool POOL = false, int DV>
 __device__ __forceinline__ void attn_scores(const AttnArgs &a, float sc, int key0, int mode, const KeyVis &kv,
                                             const frag_t (&kf)[2][DH / 32], const frag_t (&q)[QT][DH / 32],
-                                            f32x4 (&o)[QT][DH / 16], float (&mrun)[QT], float (&lrun)[QT],
+                                            f32x4 (&o)[QT][DV], float (&mrun)[QT], float (&lrun)[QT],
                                             frag_t (&pf)[QT], int lane) {
-    constexpr int DT32 = DH / 32, DT16 = DH / 16;
+    constexpr int DT32 = DH / 32;
     const int g = lane >> 4;
     bool ok[2][4];
     if (MASK) {
@@ -118,7 +118,7 @@ __device__ __forceinline__ void attn_scores(const AttnArgs &a, float sc, int key
             const float alpha = __builtin_amdgcn_exp2f(mrun[t] - (mnew == -INFINITY ? 0.f : mnew));
             lrun[t] *= alpha;
 #pragma unroll
-            for (int dt = 0; dt < DT16; dt++) o[t][dt] *= alpha;
+            for (int dt = 0; dt < DV; dt++) o[t][dt] *= alpha;
             mrun[t] = mnew;
         }
         const float mref = mrun[t] == -INFINITY ? 0.f : mrun[t];
@@ -216,13 +216,13 @@ __device__ __forceinline__ void attn_softmax_qk(const AttnArgs &a, float sc, int
     attn_qk<DH, QT>(kf_next, q, st_next);
 }
 
-// O^T += V^T P^T for QT row tiles
-template <int DH, int QT>
-__device__ __forceinline__ void attn_pv(const frag_t (&vf)[DH / 16], const frag_t (&pf)[QT], f32x4 (&o)[QT][DH / 16]) {
+// O^T += V^T P^T for QT row tiles and DV 16-channel tiles
+template <int QT, int DV>
+__device__ __forceinline__ void attn_pv(const frag_t (&vf)[DV], const frag_t (&pf)[QT], f32x4 (&o)[QT][DV]) {
 #pragma unroll
     for (int t = 0; t < QT; t++)
 #pragma unroll
-        for (int dt = 0; dt < DH / 16; dt++) o[t][dt] = mfma16(vf[dt], pf[t], o[t][dt]);
+        for (int dt = 0; dt < DV; dt++) o[t][dt] = mfma16(vf[dt], pf[t], o[t][dt]);
 }
 
 // true if some key of the 32-key tile at key0 may be invisible (see attn_scores)
@@ -232,30 +232,31 @@ __device__ __forceinline__ bool attn_tile_masked(const AttnArgs &a, int key0, in
 }
 
 // One 32-key tile (K fragments kf, V^T fragments vf) against QT row tiles: scores, online softmax, O update.
-template <int DH, int QT, bool POOL = false>
+template <int DH, int QT, bool POOL = false, int DV>
 __device__ __forceinline__ void attn_tile_update(const AttnArgs &a, float sc, int key0, int mode, const KeyVis &kv,
-                                                 const frag_t (&kf)[2][DH / 32], const frag_t (&vf)[DH / 16],
-                                                 const frag_t (&q)[QT][DH / 32], f32x4 (&o)[QT][DH / 16],
+                                                 const frag_t (&kf)[2][DH / 32], const frag_t (&vf)[DV],
+                                                 const frag_t (&q)[QT][DH / 32], f32x4 (&o)[QT][DV],
                                                  float (&mrun)[QT], float (&lrun)[QT], int lane) {
     frag_t pf[QT];
     if (attn_tile_masked(a, key0, mode, kv.fresh_n)) attn_scores<DH, QT, true, POOL>(a, sc, key0, mode, kv, kf, q, o, mrun, lrun, pf, lane);
     else attn_scores<DH, QT, false, POOL>(a, sc, key0, mode, kv, kf, q, o, mrun, lrun, pf, lane);
-    attn_pv<DH, QT>(vf, pf, o);
+    attn_pv(vf, pf, o);
 }
 
-template <int QT, int NW>
-constexpr int attn_smem_bytes() { return NW * 4 * 1024 + 2 * NW * QT * 16 * 4; }
+// the waves' unscaled sums of one row tile, and their (max, sum) of QT row tiles
+template <int DH, int QT, int NW, int VS>
+constexpr int attn_smem_bytes() { return NW * (DH / 16 / VS) * 1024 + 2 * NW * QT * 16 * 4; }
 
 // One work item: QT row tiles (chunk `item` of the units' tiles) of head hd.  sc = log2(e)/sqrt(dh).
 // SHARED (decoded-share step, QT = 1): item is the m-tile; tiles from a.split_tile on belong to the pooled
 // speculative unit of a sequence (the rows of its speculative blocks one after the other), whose rows see the
 // cache, the pooled fresh keys of their own block and block_0's fresh keys at the decoded positions.
-template <int DH, int QT, int NW, bool SHARED = false>
-__device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, int hd, char *smem) {
-    constexpr int DT32 = DH / 32, DT16 = DH / 16;
-    constexpr int DC = DT16 < 4 ? DT16 : 4;          // channel tiles merged per pass through LDS
+// VS: the item's output channels are dealt to VS workgroups (this one: part `part`), each of which computes all scores.
+template <int DH, int QT, int NW, bool SHARED = false, int VS = 1>
+__device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, int hd, int part, char *smem) {
+    constexpr int DT32 = DH / 32, DT16 = DH / 16, DV = DT16 / VS;
     static_assert(!SHARED || QT == 1, "the decoded-share step works on single row tiles");
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, mi = lane & 15, g = lane >> 4;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, mi = lane & 15, g = lane >> 4, dv0 = part * DV;
     const bool spec = SHARED && item >= a.split_tile;                     // a speculative unit's tile
     const int tpu = spec ? a.tiles_per_unit_b : a.tiles_per_unit;
     const int chunks = (tpu + QT - 1) / QT;
@@ -263,8 +264,8 @@ __device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, i
     const int unit = item_u / chunks, tu0 = (item_u % chunks) * QT;
     const int seq = spec ? unit : unit / a.units_per_seq;              // one pooled speculative unit per sequence
     const int mt_base = (spec ? a.split_tile : 0) + unit * tpu;           // first m-tile of the unit
-    f32x4 (*s_o)[DC][64] = reinterpret_cast<f32x4 (*)[DC][64]>(smem);
-    float (*s_m)[QT][16] = reinterpret_cast<float (*)[QT][16]>(smem + NW * 4 * 1024);
+    f32x4 (*s_o)[DV][64] = reinterpret_cast<f32x4 (*)[DV][64]>(smem);
+    float (*s_m)[QT][16] = reinterpret_cast<float (*)[QT][16]>(smem + NW * DV * 1024);
     float (*s_l)[QT][16] = s_m + NW;
 
     frag_t q[QT][DT32];
@@ -276,14 +277,14 @@ __device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, i
         for (int dt = 0; dt < DT32; dt++)
             q[t][dt] = ld_frag(a.q + (((size_t)hd * a.mt_total + mt) * DT32 + dt) * kTileElems + lane * 8);
     }
-    f32x4 o[QT][DT16];
+    f32x4 o[QT][DV];
     float mrun[QT], lrun[QT];
 #pragma unroll
     for (int t = 0; t < QT; t++) {
         mrun[t] = -INFINITY;
         lrun[t] = 0.f;
 #pragma unroll
-        for (int dt = 0; dt < DT16; dt++) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int dt = 0; dt < DV; dt++) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
     // visibility of the unit's own fresh keys and (speculative unit) of block_0's
@@ -291,16 +292,16 @@ __device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, i
     const int fresh_n = spec ? a.spec_blocks * a.mcount[seq] : a.fresh;
     const KeyVis kv{fresh_n, spec ? a.dmask[seq] : 0ull, m_seq, tu0 * 16};
     struct TileRef { const u16 *kp, *vp; int key0, mode; bool live; };
-    auto load_tile = [&](const TileRef &r, frag_t (&kf)[2][DT32], frag_t (&vf)[DT16]) __attribute__((always_inline)) {
+    auto load_tile = [&](const TileRef &r, frag_t (&kf)[2][DT32], frag_t (&vf)[DV]) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < 2; s++)
 #pragma unroll
             for (int dt = 0; dt < DT32; dt++)
                 kf[s][dt] = ld_frag(r.kp + (size_t)(s * DT32 + dt) * kTileElems + lane * 8);
 #pragma unroll
-        for (int dt = 0; dt < DT16; dt++) vf[dt] = ld_frag(r.vp + (size_t)dt * kTileElems + lane * 8);
+        for (int dt = 0; dt < DV; dt++) vf[dt] = ld_frag(r.vp + (size_t)dt * kTileElems + lane * 8);
     };
-    auto compute_tile = [&](const TileRef &r, const frag_t (&kf)[2][DT32], const frag_t (&vf)[DT16])
+    auto compute_tile = [&](const TileRef &r, const frag_t (&kf)[2][DT32], const frag_t (&vf)[DV])
                             __attribute__((always_inline)) {
         attn_tile_update<DH, QT, SHARED>(a, sc, r.key0, r.mode, kv, kf, vf, q, o, mrun, lrun, lane);
     };
@@ -326,21 +327,21 @@ __device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, i
         const int gi = w + i * NW;
         if (gi < n32) {
             r.kp = kc + (size_t)gi * 2 * DT32 * kTileElems;
-            r.vp = vc + (size_t)gi * DT16 * kTileElems;
+            r.vp = vc + ((size_t)gi * DT16 + dv0) * kTileElems;
             r.key0 = gi * 32;
             r.mode = kKeysCached;
             r.live = !(gi * 32 >= a.blk_lo && gi * 32 + 32 <= a.blk_hi);
         } else if (gi < n32 + nf32) {
             const int T = gi - n32;
             r.kp = kfr + (size_t)T * 2 * DT32 * kTileElems;
-            r.vp = vfr + (size_t)T * DT16 * kTileElems;
+            r.vp = vfr + ((size_t)T * DT16 + dv0) * kTileElems;
             r.key0 = T * 32;
             r.mode = spec ? kKeysPooled : kKeysFresh;
             r.live = true;
         } else {
             const int T = gi - n32 - nf32;
             r.kp = ksh + (size_t)T * 2 * DT32 * kTileElems;
-            r.vp = vsh + (size_t)T * DT16 * kTileElems;
+            r.vp = vsh + ((size_t)T * DT16 + dv0) * kTileElems;
             r.key0 = T * 32;
             r.mode = kKeysShared;
             r.live = true;
@@ -348,7 +349,7 @@ __device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, i
         return r;
     };
     if (total > 0) {
-        frag_t kf_c[2][DT32], vf_c[DT16], kf_n[2][DT32], vf_n[DT16];
+        frag_t kf_c[2][DT32], vf_c[DV], kf_n[2][DT32], vf_n[DV];
         TileRef cur = get(0);
         if (cur.live) load_tile(cur, kf_c, vf_c);
         for (int i = 0; i < total; i++) {
@@ -366,53 +367,56 @@ __device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, i
 #pragma unroll
                     for (int dt = 0; dt < DT32; dt++) kf_c[s][dt] = kf_n[s][dt];
 #pragma unroll
-                for (int dt = 0; dt < DT16; dt++) vf_c[dt] = vf_n[dt];
+                for (int dt = 0; dt < DV; dt++) vf_c[dt] = vf_n[dt];
             }
         }
     }
 
-    // merge the waves
+    // Merge the waves: each leaves its unscaled sums and its (max, sum); behind one barrier every wave has all it needs for the
+    // channel tiles that it finishes.  (Scaled sums of four tiles per pass, with five barriers, were 2.4 of the 8 us of this kernel at
+    // 32 heads, 512 keys.)
 #pragma unroll
     for (int t = 0; t < QT; t++) {
         float l = lrun[t];
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
-        lrun[t] = l;
         if (g == 0) {
             s_m[w][t][mi] = mrun[t];
             s_l[w][t][mi] = l;
         }
     }
-    __syncthreads();
 #pragma unroll
     for (int t = 0; t < QT; t++) {
+        if (t > 0) __syncthreads();              // the sums of the tile before have been read
+#pragma unroll
+        for (int dt = 0; dt < DV; dt++) s_o[w][dt][lane] = o[t][dt];
+        __syncthreads();
         float mall = -INFINITY;
 #pragma unroll
         for (int x = 0; x < NW; x++) mall = fmaxf(mall, s_m[x][t][mi]);
-        float ltot = 0.f, fown = 0.f;
+        float ltot = 0.f, f[NW];
 #pragma unroll
         for (int x = 0; x < NW; x++) {
-            float mx = s_m[x][t][mi];
-            float f = mx == -INFINITY ? 0.f : exp2f(mx - mall);
-            ltot += s_l[x][t][mi] * f;
-            if (x == w) fown = f;
+            const float mx = s_m[x][t][mi];
+            f[x] = mx == -INFINITY ? 0.f : exp2f(mx - mall);
+            ltot += s_l[x][t][mi] * f[x];
         }
-        const int tu = tu0 + t;
-        const int mt = mt_base + tu;
+        const float inv = 1.0f / ltot;
+        // (rounded products, then sums: what is added does not depend on how the channels are dealt out)
+        auto scaled = [](f32x4 x, float y) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+            return x * y;
+        };
+        if (tu0 + t < tpu) {
 #pragma unroll
-        for (int d0 = 0; d0 < DT16; d0 += DC) {
+            for (int d0 = 0; d0 < DV; d0 += NW) {
+                const int dt = d0 + w;
+                if (dt >= DV) break;
+                f32x4 v = scaled(s_o[0][dt][lane], f[0]);
 #pragma unroll
-            for (int dt = 0; dt < DC; dt++) s_o[w][dt][lane] = o[t][d0 + dt] * fown;
-            __syncthreads();
-            if (tu < tpu) {
-                for (int dt = w; dt < DC; dt += NW) {
-                    f32x4 v = s_o[0][dt][lane];
-#pragma unroll
-                    for (int x = 1; x < NW; x++) v += s_o[x][dt][lane];
-                    store_out_tile<DH>(a, mt, hd, d0 + dt, lane, v * (1.0f / ltot));
-                }
+                for (int x = 1; x < NW; x++) v += scaled(s_o[x][dt][lane], f[x]);
+                store_out_tile<DH>(a, mt_base + tu0 + t, hd, dv0 + dt, lane, v * inv);
             }
-            __syncthreads();
         }
     }
 }

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(AttnArgs a, float sc
             attn_softmax_qk<DH, QTW>(a, sc, key0, attn_tile_masked(a, key0, kKeysCached, 0), sc_t[p], kf, q, sc_t[1 - p], o,
                                      mrun, lrun, pf, lane);
             read_k(i2);
-            attn_pv<DH, QTW>(vf, pf, o);
+            attn_pv(vf, pf, o);
         }
     };
     {
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(AttnArgs a, float sc
 #pragma unroll
         for (int dt = 0; dt < DT16; dt++) vf[dt] = ld_frag(vfr + ((size_t)T * DT16 + dt) * kTileElems);
         attn_scores<DH, QTW, true>(a, sc, T * 32, kKeysFresh, kv, kf, q, o, mrun, lrun, pf, lane);
-        attn_pv<DH, QTW>(vf, pf, o);
+        attn_pv(vf, pf, o);
     }
 
 #pragma unroll

@@ -1,16 +1,14 @@
 // Stand-alone launches of the weight-streaming GEMM (see gemm_core.h).
-#include <mutex>
-
 #include "choose.h"
 #include "gemm_slab.h"
+#include "launch.h"
 
 namespace odb {
 
 template <int MT, int NG, int PF, class Epi, bool IL = false>
 __global__ __launch_bounds__(64 * WK) void gemm_stream_kernel(GemmArgs g, Epi epi) {
-    __shared__ __attribute__((aligned(16))) char smem[kGemmSmemBytes];
-    frag_t wb[PF][NG];
-    gemm_wg<MT, NG, PF, Epi, IL>(g, epi, blockIdx.x, gridDim.x, blockIdx.y * MT, wb, smem);
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    gemm_wg<MT, NG, PF, Epi, IL>(g, epi, blockIdx.x, blockIdx.y * MT, smem);
 }
 
 constexpr int kStreamWGs = kComputeUnits;      // one workgroup per compute unit
@@ -30,47 +28,63 @@ constexpr int kKRot = 7;
 // device-coherent accesses, ordered by a wait for the stores' completion before the counter is touched; cache-wide
 // fences (a release / acquire pair) were measured to stall the weight streams of every workgroup on the chip
 // (108 us instead of 20 us in a traffic model of this kernel).  The counter is back at zero when the kernel ends.
+// What follows the k-loop is a chain of latencies - sums through LDS, stores out, counter, sums back in: 16-byte accesses, one
+// pass through LDS and all of a wave's tiles requested at once took O and down of 64 rows at d 4096 from 20.4 to 19.9 us on average,
+// down of 32 rows from 20.6 to 20.2, and at d 1024, 128 rows O from 7.2 to 6.6 and down from 8.5 to 7.9.
 // (RB: blockIdx.y numbers blocks of MT row tiles.  SPAN64: sums of squares over 64 columns, NormOut::span; with NG = 4 and N a
 // multiple of 64 a block is one such sum.)
 template <int MT, int NG, int PF, int KS, bool RB = false, bool SPAN64 = false>
 __global__ __launch_bounds__(64 * WK) void gemm_stream_ksplit_kernel(GemmArgs g, EpiResid epi, float *partial, unsigned *arrive) {
-    __shared__ __attribute__((aligned(16))) char smem[kGemmSmemBytes];
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     static_assert(!SPAN64 || NG == 4, "one sum per block");
     float *s_q = reinterpret_cast<float *>(smem);            // (SPAN64) [MT * NG][16], in the finishing workgroup
     __shared__ unsigned s_old;
-    const int ks = blockIdx.x % KS, nb = blockIdx.x / KS, nblocks = gridDim.x / KS;
-    const int kl = g.KT / KS;
+    const int ks = blockIdx.x % KS, nb = blockIdx.x / KS, nblocks = g.nwg;
     GemmArgs gs = g;
-    gs.k_len = kl;
-    gs.A += (size_t)ks * kl * g.MT_total * kTileElems;
-    gs.W += (size_t)ks * kl * kTileElems;
+    gs.A += (size_t)ks * g.k_len * g.MT_total * kTileElems;
+    gs.W += (size_t)ks * g.k_len * kTileElems;
     const size_t slice = (size_t)g.MT_total * g.NT * 256;
-    frag_t wb[PF][NG];
     const int mt0 = RB ? blockIdx.y * MT : 0, mt1 = RB && mt0 + MT < g.MT_total ? mt0 + MT : g.MT_total;
-    gemm_wg<MT, NG, PF, EpiPartial, false>(gs, EpiPartial{partial + ks * slice, g.NT}, nb, nblocks, mt0, wb, smem);
+    gemm_wg<MT, NG, PF, EpiPartial, false>(gs, EpiPartial{partial + ks * slice, g.NT, g.MT_total}, nb, mt0, smem);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's partial sums have been written
     __syncthreads();
     arrive += RB ? blockIdx.y * nblocks + nb : nb;
     if (threadIdx.x == 0) s_old = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_old != KS - 1) return;
+    // The slices of all tiles of a wave are requested together with what the epilogue reads.
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int n_lo = (int)((unsigned)nb * (unsigned)g.NT / (unsigned)nblocks), n_hi = (int)((unsigned)(nb + 1) * (unsigned)g.NT / (unsigned)nblocks);
-    const int nn = n_hi - n_lo;
-    for (int t = wv; t < (mt1 - mt0) * nn; t += WK) {
-        const int mt = mt0 + t / nn, nt = n_lo + t % nn;
-        const float *q = partial + ((size_t)mt * g.NT + nt) * 256 + lane;
-        const auto pre = epi_preload(epi, mt, nt, lane);
-        f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < KS; s++)
+    constexpr int TW = (MT * NG + WK - 1) / WK;             // tiles of a wave
+    u32x4 v[TW][KS];
+    ResidPre pre[TW];
+    auto tile_of = [&](int u, int &mt, int &nt) __attribute__((always_inline)) {      // (every block has NG n-tiles: set at the launch)
+        const int t = wv + u * WK;
+        mt = mt0 + t / NG;
+        nt = nb * NG + t % NG;
+        return t < MT * NG && mt < mt1;
+    };
 #pragma unroll
-            for (int r = 0; r < 4; r++)
-                c[r] += __hip_atomic_load(q + s * slice + r * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int u = 0; u < TW; u++) {
+        int mt, nt;
+        if (!tile_of(u, mt, nt)) continue;
+        const unsigned at = ((unsigned)mt * g.NT + nt) * 1024 + lane * 16;
+#pragma unroll
+        for (int s = 0; s < KS; s++)
+            v[u][s] = __builtin_amdgcn_raw_buffer_load_b128(sums_rsrc(partial + s * slice, slice * 4), at, 0, kDeviceScope);
+        pre[u] = epi_preload(epi, mt, nt, lane);
+    }
+#pragma unroll
+    for (int u = 0; u < TW; u++) {
+        int mt, nt;
+        if (!tile_of(u, mt, nt)) continue;
+        f32x4 c = __builtin_bit_cast(f32x4, v[u][0]);
+#pragma unroll
+        for (int s = 1; s < KS; s++) c += __builtin_bit_cast(f32x4, v[u][s]);
         if constexpr (SPAN64) {                     // the block's four n-tiles make one partial sum of squares
-            const float sq = EpiResid::over_row(epi.put(mt, nt, c, lane, pre));
-            if (lane < 16) s_q[t * 16 + lane] = sq;
+            const float sq = EpiResid::over_row(epi.put(mt, nt, c, lane, pre[u]));
+            if (lane < 16) s_q[(wv + u * WK) * 16 + lane] = sq;
         } else {
-            epi_apply(epi, mt, nt, c, lane, 0, pre);
+            epi_apply(epi, mt, nt, c, lane, 0, pre[u]);
         }
     }
     if constexpr (SPAN64) {
@@ -94,25 +108,33 @@ static bool ksplit_ok(GemmShape sh, Workspace ws) {
     return sh.M_tiles <= 6 && sh.K_tiles % (kSplitKS * WK * kSplitPF) == 0 &&
            ksplit_fits(sh, (sh.N_tiles + kSplitNG - 1) / kSplitNG, ws);
 }
-static GemmArgs ksplit_args(const u16 *a, const u16 *w, GemmShape sh) {
+static GemmArgs stream_args(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, int k_len, int nwg) {
     GemmArgs g;
     g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
-    g.ssq = nullptr; g.n_ssq = 0; g.eps = 0.f; g.inv_d = 0.f; g.k_len = 0; g.k_rot = kKRot;
+    g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
+    g.k_len = k_len; g.k_rot = kKRot;
+    set_shares(g, nwg);
     return g;
 }
+template <int MT, int NG, int PF, int KS, bool RB = false, bool SPAN64 = false>
+static void launch_ksplit_as(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, Workspace ws, hipStream_t s) {
+    // (N is a multiple of 256, so the blocks have NG n-tiles each)
+    const GemmArgs g = stream_args(a, w, sh, NormIn{nullptr, 0, 0.f}, sh.K_tiles / KS, sh.N_tiles / NG);
+    const dim3 grid(g.nwg * KS, RB ? (sh.M_tiles + MT - 1) / MT : 1);
+    constexpr int lds = gemm_smem_bytes(MT, NG);
+    allow_lds<gemm_stream_ksplit_kernel<MT, NG, PF, KS, RB, SPAN64>>(lds);
+    gemm_stream_ksplit_kernel<MT, NG, PF, KS, RB, SPAN64><<<grid, 64 * WK, lds, s>>>(g, e, ws.partial, ws.arrive);
+}
 static void launch_stream_ksplit(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, Workspace ws, hipStream_t s) {
-    const GemmArgs g = ksplit_args(a, w, sh);
-    const int nblocks = (sh.N_tiles + kSplitNG - 1) / kSplitNG;
-    const dim3 grid(nblocks * kSplitKS);
-    if (sh.M_tiles <= 2) gemm_stream_ksplit_kernel<2, kSplitNG, kSplitPF, kSplitKS><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else if (sh.M_tiles <= 4) gemm_stream_ksplit_kernel<4, kSplitNG, 4, kSplitKS><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else gemm_stream_ksplit_kernel<6, kSplitNG, 2, kSplitKS><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    if (sh.M_tiles <= 2) launch_ksplit_as<2, kSplitNG, kSplitPF, kSplitKS>(a, w, sh, e, ws, s);
+    else if (sh.M_tiles <= 4) launch_ksplit_as<4, kSplitNG, 4, kSplitKS>(a, w, sh, e, ws, s);
+    else launch_ksplit_as<6, kSplitNG, 2, kSplitKS>(a, w, sh, e, ws, s);
 }
 
 // The same kernel for narrow models (N up to 2048 from 33 to 128 rows, up to 1024 from 129 to 256): blocks of 64 rows and one, two or four n-tiles, so
 // that four k-slices of every block make up to 256 workgroups, and as many ring stages as a wave has k-tiles where that is two
 // or three.  At d = 1024, d_ff = 3072 and 128 rows it replaces the tile kernel on 32 and 64 workgroups and its merge pass:
-// O 6.7 + 3.7, down 9.0 + 3.7 us before, 7.3 and 8.5 now (blocks of all 128 rows and one n-tile: 7.4 and 9.7 us); at 192 rows
+// O 6.7 + 3.7, down 9.0 + 3.7 us before, 6.6 and 7.9 now (blocks of all 128 rows and one n-tile: 7.4 and 9.7 us); at 192 rows
 // 7.6 + 4.4 and 11.6 + 4.4 before, 9.3 and 11.7 now.
 static int ksplit_narrow_ng(GemmShape sh, Workspace ws) {
     if (sh.M_tiles <= 2 || sh.M_tiles > 16 || sh.K_tiles % (kSplitKS * WK) != 0) return 0;
@@ -121,12 +143,10 @@ static int ksplit_narrow_ng(GemmShape sh, Workspace ws) {
 }
 template <int NG, bool SPAN64 = false>
 static void launch_ksplit_narrow(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, Workspace ws, hipStream_t s) {
-    const GemmArgs g = ksplit_args(a, w, sh);
-    const dim3 grid((sh.N_tiles + NG - 1) / NG * kSplitKS, (sh.M_tiles + 3) / 4);
     const int kw = sh.K_tiles / (kSplitKS * WK);
-    if (kw % 3 == 0) gemm_stream_ksplit_kernel<4, NG, 3, kSplitKS, true, SPAN64><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else if (kw % 2 == 0) gemm_stream_ksplit_kernel<4, NG, 2, kSplitKS, true, SPAN64><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
-    else gemm_stream_ksplit_kernel<4, NG, 1, kSplitKS, true, SPAN64><<<grid, 64 * WK, 0, s>>>(g, e, ws.partial, ws.arrive);
+    if (kw % 3 == 0) launch_ksplit_as<4, NG, 3, kSplitKS, true, SPAN64>(a, w, sh, e, ws, s);
+    else if (kw % 2 == 0) launch_ksplit_as<4, NG, 2, kSplitKS, true, SPAN64>(a, w, sh, e, ws, s);
+    else launch_ksplit_as<4, NG, 1, kSplitKS, true, SPAN64>(a, w, sh, e, ws, s);
 }
 
 // The persistent streaming kernel for up to 128 rows: MT row tiles per wave (2, 4, 6 or 8: 32-row steps),
@@ -135,15 +155,18 @@ static void launch_ksplit_narrow(const u16 *a, const u16 *w, GemmShape sh, EpiRe
 // divide fall back to a ring of one.
 template <int MT, int NG, int PF, bool IL, class Epi>
 static void launch_stream(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
-    GemmArgs g;
-    g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
-    g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
-    g.k_len = 0; g.k_rot = kKRot;
     const int kw = sh.K_tiles / WK;                // K_tiles is a multiple of 8 (checked at model creation)
     const int groups = (sh.N_tiles + NG - 1) / NG;
     dim3 grid(groups < kStreamWGs ? groups : kStreamWGs, (sh.M_tiles + MT - 1) / MT);
-    if (kw % PF == 0) gemm_stream_kernel<MT, NG, PF, Epi, IL><<<grid, 64 * WK, 0, s>>>(g, e);
-    else gemm_stream_kernel<MT, NG, 1, Epi, IL><<<grid, 64 * WK, 0, s>>>(g, e);
+    const GemmArgs g = stream_args(a, w, sh, ni, sh.K_tiles, grid.x);
+    constexpr int lds = gemm_smem_bytes(MT, NG);
+    if (kw % PF == 0) {
+        allow_lds<gemm_stream_kernel<MT, NG, PF, Epi, IL>>(lds);
+        gemm_stream_kernel<MT, NG, PF, Epi, IL><<<grid, 64 * WK, lds, s>>>(g, e);
+    } else {
+        allow_lds<gemm_stream_kernel<MT, NG, 1, Epi, IL>>(lds);
+        gemm_stream_kernel<MT, NG, 1, Epi, IL><<<grid, 64 * WK, lds, s>>>(g, e);
+    }
 }
 
 // Narrow models: a projection whose n-tiles give fewer than 256 groups of the usual width takes smaller groups, the
@@ -207,11 +230,7 @@ static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
     g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
     g.m_blocks = (sh.M_tiles + MBT - 1) / MBT;
     g.n_blocks = (sh.N_tiles + 4 * WN - 1) / (4 * WN);
-    static std::once_flag attr_once;        // once per instantiation: the ring needs more than the default 64 KiB
-    std::call_once(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_big_kernel<WN, Epi, MBT>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, big_smem_bytes(WN, MBT));
-    });
+    allow_lds<gemm_big_kernel<WN, Epi, MBT>>(big_smem_bytes(WN, MBT));
     dim3 grid(8 * g.m_blocks * ((g.n_blocks + 7) / 8));
     gemm_big_kernel<WN, Epi, MBT><<<grid, 512, big_smem_bytes(WN, MBT), s>>>(g, e);
 }
@@ -245,11 +264,7 @@ static void launch_slab(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
     SlabArgs g;
     g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
     g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
-    static std::once_flag attr_once;
-    std::call_once(attr_once, [] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_slab_kernel<NTB, Epi, NTW>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, slab_smem_bytes(NTB));
-    });
+    allow_lds<gemm_slab_kernel<NTB, Epi, NTW>>(slab_smem_bytes(NTB));
     gemm_slab_kernel<NTB, Epi, NTW><<<dim3((g.NT + NTB - 1) / NTB, (g.MT_total + 7) / 8), 512, slab_smem_bytes(NTB), s>>>(g, e);
 }
 
@@ -362,8 +377,8 @@ int lm_stats_parts(int n_tiles, int m_tiles) {
 void launch_gemm_lmstats(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, float *stats, Workspace ws,
                          hipStream_t s) {
     const int parts = lm_stats_parts(sh.N_tiles, sh.M_tiles);
-    if (sh.M_tiles <= 2 && lm_ng(sh.N_tiles) == 4) launch_stream<2, 4, 4, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
-    else if (sh.M_tiles <= 2) launch_stream<2, kLmNG, 4, true>(xa, w, sh, ni, EpiLMStats<2>(stats, parts), s);
+    if (sh.M_tiles <= 2 && lm_ng(sh.N_tiles) == 4) launch_stream<2, 4, 4, true>(xa, w, sh, ni, EpiLMStats<gemm_slots(2, 4)>(stats, parts), s);
+    else if (sh.M_tiles <= 2) launch_stream<2, kLmNG, 4, true>(xa, w, sh, ni, EpiLMStats<gemm_slots(2, kLmNG)>(stats, parts), s);
     else if (lm_one_block(sh.M_tiles)) {
         // 33..128 rows.  A streaming workgroup reads all activation rows once per group of six n-tiles, and with 31
         // n-tiles per workgroup that is five to six times [rows x d] through each compute unit's vector-memory path,

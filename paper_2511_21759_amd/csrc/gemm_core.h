@@ -29,26 +29,41 @@ constexpr int WK = 8;    // waves per workgroup = K slices
 
 struct GemmArgs {
     const u16 *A, *W;
-    int KT, MT_total, NT;
     // fused RMSNorm of the input rows: A holds binary16(x * gain) and ssq[row][0..n_ssq) partial sums
     // of x^2; the result rows are scaled by 1/sqrt(sum/d + eps).  ssq == nullptr: A is used as is.
     const float *ssq;
-    int n_ssq;
+    int KT, MT_total, NT, n_ssq;
     float eps, inv_d;
-    // k-tiles this call covers (0: all KT).  A and W then point at the first k-tile of the slice; KT stays the
+    // k-tiles this call covers (KT, or a slice of it).  A and W then point at the first k-tile of the slice; KT stays the
     // distance between the n-tiles of W.
     int k_len;
     // > 0: workgroup wg walks its k-tiles starting at (wg * k_rot) % (k-tiles per wave) and wraps round, so that the
     // workgroups, which all read the same activation tiles, do not ask the same L2 channels for them at the same time
     int k_rot;
+    // workgroups that share the n-tiles, n-tiles of each where that divides them (else 0), divisor for k_rot: a workgroup
+    // has nothing to request before it knows its tiles, and three divisions are 0.2 us
+    int nwg, per;
+    FastDiv fd_kw;
 };
-
-// m-tiles per reduction pass: at most six 1 KiB tiles per wave go through LDS at a time
-constexpr int gemm_mc(int mt, int ng) {
-    return (ng >= 4 ? 1 : (ng >= 3 ? 2 : ng == 2 ? (mt == 6 ? 3 : 2) : (mt < 4 ? mt : (mt % 4 == 0 ? 4 : 3))));
+// (host) the fields that follow from the others
+inline void set_shares(GemmArgs &g, int nwg) {
+    g.nwg = nwg;
+    g.per = g.NT % nwg == 0 ? g.NT / nwg : 0;
+    g.fd_kw = FastDiv::make(g.k_len / WK);
 }
 
-constexpr int kGemmSmemBytes = WK * 6 * 1024 + 8 * 16 * 4;    // LDS one workgroup needs (red + row scales)
+// m-tiles per reduction pass: the sums of up to eighteen tiles per wave (144 KiB) go through LDS at a time.  A pass costs two
+// barriers and a chain of LDS latencies whatever its size: with six tiles (48 KiB) the tail of a 64-row workgroup of 4 x 4
+// tiles was four passes and 3.9 us.
+constexpr int gemm_mc(int mt, int ng) {
+    int mc = mt;
+    while (mt % mc != 0 || mc * ng > 18) mc--;
+    return mc;
+}
+// output tiles that a wave finishes: (m-chunk, tile) pairs, see gemm_wg
+constexpr int gemm_slots(int mt, int ng) { return mt / gemm_mc(mt, ng) * ((gemm_mc(mt, ng) * ng + WK - 1) / WK); }
+constexpr int gemm_red_bytes(int mt, int ng) { return WK * gemm_mc(mt, ng) * ng * 1024; }
+constexpr int gemm_smem_bytes(int mt, int ng) { return gemm_red_bytes(mt, ng) + mt * 16 * 4; }    // red + row scales
 
 // Hooks for epilogues that read global memory (the residual tile, the RoPE table): epi_preload issues those loads
 // before the partial sums go through LDS, epi_apply hands their result to the epilogue, so that their latency runs
@@ -63,22 +78,53 @@ __device__ __forceinline__ void epi_apply(Epi &epi, int mt, int nt, f32x4 c, int
 // The epilogue is called as epi(mt, nt, c, lane, slot): slot numbers the (m-chunk, tile) pairs that
 // this wave serves, the same in every group of n-tiles, so a stateful epilogue can keep one
 // accumulator per slot; epi.finish(mt, part, lane, slot) follows once per slot at the end.
+// smem: gemm_smem_bytes(MT, NG) bytes.
 template <int MT, int NG, int PF, class Epi, bool IL = false>
-__device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int nwg, int mt0,
-                                        frag_t (&wb)[PF][NG], char *smem) {
-    constexpr int MC = gemm_mc(MT, NG);                // m-tiles reduced per pass through LDS (<= 48 KiB)
+__device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int mt0, char *smem) {
+    constexpr int MC = gemm_mc(MT, NG);                // m-tiles reduced per pass through LDS
     constexpr int SPW = (MC * NG + WK - 1) / WK;          // reduced tiles a wave serves per m-chunk
-    static_assert(MT % MC == 0 && MC * NG * WK <= 6 * WK && MT <= 8, "m chunking");
+    static_assert(MT % MC == 0 && MT <= 8, "m chunking");
     f32x4 (*red)[MC * NG][64] = reinterpret_cast<f32x4 (*)[MC * NG][64]>(smem);
-    float *s_rstd = reinterpret_cast<float *>(smem + WK * 6 * 1024);
+    float *s_rstd = reinterpret_cast<float *>(smem + gemm_red_bytes(MT, NG));
 
+    // (all arguments in one go: read where they are first used they are a chain of scalar-cache misses)
+    asm volatile("" ::"s"(g.A), "s"(g.W), "s"(g.ssq), "s"(g.KT), "s"(g.MT_total), "s"(g.NT), "s"(g.n_ssq), "s"(g.k_len), "s"(g.k_rot),
+                 "s"(g.nwg), "s"(g.per), "s"(g.fd_kw.mul), "s"(g.fd_kw.div));
     const int lane = threadIdx.x & 63, wk = threadIdx.x >> 6;
-    const int n_lo = (int)((unsigned)wg * (unsigned)g.NT / (unsigned)nwg);      // (32-bit: wg * NT stays far below 2^32)
-    const int n_hi = (int)((unsigned)(wg + 1) * (unsigned)g.NT / (unsigned)nwg);
+    const int n_lo = g.per ? wg * g.per : (int)((unsigned)wg * (unsigned)g.NT / (unsigned)g.nwg);      // (32-bit: wg * NT stays far below 2^32)
+    const int n_hi = g.per ? n_lo + g.per : (int)((unsigned)(wg + 1) * (unsigned)g.NT / (unsigned)g.nwg);
     if (n_lo >= n_hi) return;
-    const int KW = (g.k_len ? g.k_len : g.KT) / WK;
+    const int KW = g.k_len / WK;
     const int ngroups = (n_hi - n_lo + NG - 1) / NG;
     const int k0 = IL ? wk : wk * KW, kst = IL ? WK : 1;      // first k-tile of this wave and its stride
+
+    // Row scales of the fused RMSNorm.  A row's partial sums (up to 256 of them) are one 16-byte
+    // load per lane; the loads of all RPW rows of this wave are issued back to back and BEFORE the
+    // first stage, so that waiting for them does not wait for the weight stream (loads return in
+    // order), and they are only reduced after the ring has been filled.
+    constexpr int RPW = MT * 16 / WK;                      // rows per wave
+    float q[RPW];
+    f32x4 sv[RPW];
+    const int si = 4 * lane, sic = si < g.n_ssq - 4 ? si : g.n_ssq - 4;     // n_ssq is a multiple of 4
+    if (g.ssq) {
+#pragma unroll
+        for (int j = 0; j < RPW; j++) {
+            int row = mt0 * 16 + wk + j * WK;
+            row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
+            sv[j] = *reinterpret_cast<const f32x4 *>(g.ssq + (size_t)row * g.n_ssq + sic);
+            q[j] = 0.f;
+        }
+        for (int i0 = 256; i0 < g.n_ssq; i0 += 256) {   // rows wider than 4096 only
+            const int i = i0 + si, ic = i < g.n_ssq - 4 ? i : g.n_ssq - 4;
+#pragma unroll
+            for (int j = 0; j < RPW; j++) {
+                int row = mt0 * 16 + wk + j * WK;
+                row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(g.ssq + (size_t)row * g.n_ssq + ic);
+                q[j] += i < g.n_ssq ? (v[0] + v[1]) + (v[2] + v[3]) : 0.f;
+            }
+        }
+    }
 
     const u16 *wbase = g.W + (size_t)k0 * kTileElems + lane * 8;
     const u16 *ap[MT];
@@ -89,8 +135,12 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
     }
     const size_t a_step = (size_t)g.MT_total * kTileElems * kst;
 
-    frag_t ab[PF][MT];
-    const int rot = g.k_rot > 0 ? (int)(((unsigned)wg * (unsigned)g.k_rot) % (unsigned)KW) : 0;
+    frag_t wb[PF][NG], ab[PF][MT];
+    int rot = 0;
+    if (g.k_rot > 0) {
+        const int x = wg * g.k_rot;                     // below 2^16
+        rot = x - g.fd_kw.quot(x) * KW;
+    }
     auto load_stage = [&](int slot, int grp, int k_seq) __attribute__((always_inline)) {
         int kk = k_seq + rot;
         kk = kk >= KW ? kk - KW : kk;
@@ -103,42 +153,18 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
 #pragma unroll
         for (int m = 0; m < MT; m++) ab[slot][m] = ld_frag(ap[m] + kk * a_step);
     };
-
-    // Row scales of the fused RMSNorm.  A row's partial sums (up to 256 of them) are one 16-byte
-    // load per lane; the loads of all RPW rows of this wave are issued back to back and BEFORE the
-    // first stage, so that waiting for them does not wait for the weight stream (loads return in
-    // order), and they are only reduced after the ring has been filled.
-    constexpr int RPW = MT * 16 / WK;                      // rows per wave
-    float q[RPW];
-    f32x4 sv[RPW];
-    const int si = 4 * lane, sic = si < g.n_ssq - 4 ? si : g.n_ssq - 4;     // n_ssq is a multiple of 4
-#pragma unroll
-    for (int j = 0; j < RPW; j++) {
-        q[j] = 0.f;
-        sv[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (g.ssq) {
-            int row = mt0 * 16 + wk + j * WK;
-            row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
-            const float *p = g.ssq + (size_t)row * g.n_ssq;
-            for (int i0 = 256; i0 < g.n_ssq; i0 += 256) {   // rows wider than 4096 only
-                const int i = i0 + si, ic = i < g.n_ssq - 4 ? i : g.n_ssq - 4;
-                f32x4 v = *reinterpret_cast<const f32x4 *>(p + ic);
-                q[j] += i < g.n_ssq ? (v[0] + v[1]) + (v[2] + v[3]) : 0.f;
-            }
-            sv[j] = *reinterpret_cast<const f32x4 *>(p + sic);
-        }
-    }
 #pragma unroll
     for (int s = 0; s < PF; s++) load_stage(s, 0, s);
     if (g.ssq) {
         // 64 lane-partials per row -> one sum per row: transposed through LDS (row stride 65 floats keeps
         // the gather conflict-free), then lane l adds RPW of the partials of row l % RPW and the 64 / RPW
-        // lanes of a row finish with shuffles.  A wave only touches its own part of the buffer.
+        // lanes of a row finish with shuffles.  A wave only touches its own part of the reduction buffer: no barrier before
+        // the one in front of the first sums, which publishes the scales too.
         // (RP: RPW rounded up to a power of two - six row tiles over eight waves give twelve rows per wave;
         // the lanes of the rows beyond RPW add stale scratch and are dropped)
-        constexpr int RP = RPW <= 1 ? 1 : RPW <= 2 ? 2 : RPW <= 4 ? 4 : RPW <= 8 ? 8 : RPW <= 16 ? 16 : RPW <= 32 ? 32 : 64;
-        static_assert(RPW <= 64 && WK * RP * 65 * 4 <= WK * 6 * 1024, "rows per wave");
-        float *tmp = reinterpret_cast<float *>(smem) + wk * (RP * 65);
+        constexpr int RP = RPW <= 4 ? 4 : RPW <= 8 ? 8 : 16;
+        static_assert(RPW <= 16 && RP * 65 * 4 <= MC * NG * 1024, "a wave's part of the buffer");
+        float *tmp = reinterpret_cast<float *>(&red[wk][0][0]);
 #pragma unroll
         for (int j = 0; j < RPW; j++)
             tmp[j * 65 + lane] = q[j] + (si < g.n_ssq ? (sv[j][0] + sv[j][1]) + (sv[j][2] + sv[j][3]) : 0.f);
@@ -149,7 +175,6 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
 #pragma unroll
         for (int o = RP; o < 64; o <<= 1) t += __shfl_xor(t, o);
         if (lane < RPW) s_rstd[wk + lane * WK] = 1.0f / sqrtf(t * g.inv_d + g.eps);
-        __syncthreads();                        // the buffer is reused by the K reduction below
     } else if (lane < RPW) {
         s_rstd[wk + lane * WK] = 1.0f;
     }
@@ -220,7 +245,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
                     epi_apply(epi, mt, nt, c, lane, (mc / MC) * SPW + u, pre[u]);
                 }
             }
-            __syncthreads();
+            if (mc + MC < MT || grp + 1 < ngroups) __syncthreads();         // (the buffer is written again)
         }
     }
     // epilogues that accumulate over the n-tiles of the workgroup write their result now
@@ -245,12 +270,14 @@ __device__ inline void st_f16x4(u16 *p, float a, float b, float c, float d) { *r
 template <class T>
 __device__ __forceinline__ T pick(bool c, T a, T b) { return c ? a : b; }
 
+struct QkvPre { f32x4 cs; u16 *dst; bool rotate; };
 struct EpiQKV {
     QkvOut o;
     int mt_total;
     __device__ bool transposed(int nt) const { return nt * 16 >= 2 * o.d; }
     __device__ void finish(int, int, int, int) const {}
-    __device__ void operator()(int mt, int nt, f32x4 c, int lane, int) const {
+    // where a tile goes, and the (cos, sin) of the lane's two channel pairs: requested before the sums are there
+    __device__ QkvPre preload(int mt, int nt, int lane) const {
         const int mi = lane & 15, g = lane >> 4;
         // unit and tile inside the unit; in the decoded-share step the speculative units have their own size and K/V area
         const bool spec = o.split_tile > 0 && mt >= o.split_tile;
@@ -259,33 +286,36 @@ struct EpiQKV {
         u16 *kdst = pick(spec, o.k_b, o.k) + unit * pick(spec, o.k_b_unit_stride, o.k_unit_stride);
         u16 *vdst = pick(spec, o.v_b, o.v) + unit * pick(spec, o.v_b_unit_stride, o.v_unit_stride);
         const size_t khs = pick(spec, o.k_b_head_stride, o.k_head_stride), vhs = pick(spec, o.v_b_head_stride, o.v_head_stride);
-        // (index arithmetic on tiles with precomputed multipliers: it sits in the serial tail of the kernel)
+        // (index arithmetic on tiles with precomputed multipliers)
         const int sec = o.fd_d.quot(nt), rt = nt - sec * (o.d >> 4);
         const int hd = o.fd_dh.quot(rt), p0 = (rt - hd * (o.dh >> 4)) * 16;            // p0 is a multiple of 16
+        QkvPre p;
+        p.rotate = sec < 2;
         if (sec < 2) {
             // physical channel 2j is logical j, 2j+1 is j + dh/2: each adjacent pair is a RoPE pair
             const int pos = o.rowpos ? o.rowpos[mt * 16 + mi] : o.pos_off + tu * 16 + mi;
-            const float2 *tab = reinterpret_cast<const float2 *>(o.rope) + (size_t)pos * (o.dh / 2);
-            u16 *dst = sec == 0
-                ? o.q + (((size_t)hd * mt_total + mt) * (o.dh / 32) + p0 / 32) * kTileElems
-                : kdst + hd * khs + ((size_t)tu * (o.dh / 32) + p0 / 32) * kTileElems;
-            const int j = (p0 + 4 * g) >> 1;
-            float2 cs0 = tab[j], cs1 = tab[j + 1];
-            float y0 = c[0] * cs0.x - c[1] * cs0.y;
-            float y1 = c[1] * cs0.x + c[0] * cs0.y;
-            float y2 = c[2] * cs1.x - c[3] * cs1.y;
-            float y3 = c[3] * cs1.x + c[2] * cs1.y;
-            const int kk = (p0 & 16) + 4 * g;                 // k-element of y0 inside the 32-wide tile
-            note_saturation(o.status, y0, y1, y2, y3);
-            st_f16x4(dst + ((kk >> 3) * 16 + mi) * 8 + (kk & 7), y0, y1, y2, y3);
+            p.cs = *reinterpret_cast<const f32x4 *>(o.rope + (size_t)pos * o.dh + p0 + 4 * g);
+            const int kk = (p0 & 16) + 4 * g;                 // k-element of the lane's first channel inside the 32-wide tile
+            p.dst = (sec == 0 ? o.q + (((size_t)hd * mt_total + mt) * (o.dh / 32) + p0 / 32) * kTileElems
+                              : kdst + hd * khs + ((size_t)tu * (o.dh / 32) + p0 / 32) * kTileElems) + ((kk >> 3) * 16 + mi) * 8 + (kk & 7);
         } else {
             // V^T tile: row = channel, the 32 keys of a tile sit in k-slot 8*g + 4*half + r
-            u16 *dst = vdst + hd * vhs + ((size_t)(tu >> 1) * (o.dh / 16) + p0 / 16) * kTileElems + lane * 8 + 4 * (tu & 1);
-            note_saturation(o.status, c[0], c[1], c[2], c[3]);
-            st_f16x4(dst, c[0], c[1], c[2], c[3]);
+            p.cs = f32x4{1.f, 0.f, 1.f, 0.f};
+            p.dst = vdst + hd * vhs + ((size_t)(tu >> 1) * (o.dh / 16) + p0 / 16) * kTileElems + lane * 8 + 4 * (tu & 1);
         }
+        return p;
     }
+    __device__ void apply(f32x4 c, const QkvPre &p) const {
+        if (p.rotate)
+            c = f32x4{c[0] * p.cs[0] - c[1] * p.cs[1], c[1] * p.cs[0] + c[0] * p.cs[1],
+                      c[2] * p.cs[2] - c[3] * p.cs[3], c[3] * p.cs[2] + c[2] * p.cs[3]};
+        note_saturation(o.status, c[0], c[1], c[2], c[3]);
+        st_f16x4(p.dst, c[0], c[1], c[2], c[3]);
+    }
+    __device__ void operator()(int mt, int nt, f32x4 c, int lane, int) const { apply(c, preload(mt, nt, lane)); }
 };
+__device__ __forceinline__ QkvPre epi_preload(const EpiQKV &e, int mt, int nt, int lane) { return e.preload(mt, nt, lane); }
+__device__ __forceinline__ void epi_apply(EpiQKV &e, int, int, f32x4 c, int, int, const QkvPre &pre) { e.apply(c, pre); }
 
 // h += C.  With a NormOut it also prepares the next RMSNorm: hb = binary16(h * gain) in the
 // operand layout and the sum of squares of this tile's 16 columns per row.
@@ -432,17 +462,21 @@ struct EpiStore {
 };
 
 // One K slice's sums, left for the workgroup that finishes the tile (gemm.hip: gemm_stream_ksplit_kernel):
-// p[m_tile][n_tile][r][lane] holds element r of the lane's fragment.  Written with device-coherent stores so
-// that a workgroup on another XCD reads them without any cache-wide fence.
+// p[m_tile][n_tile][lane] holds the lane's fragment.  Written with device-coherent stores (sc1) so that a workgroup on
+// another XCD reads them without any cache-wide fence.
+constexpr int kDeviceScope = 16;            // sc1 in the cache policy operand of a buffer load or store
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t sums_rsrc(const float *p, size_t bytes) {     // p: the same in all lanes
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, (int)(unsigned)bytes, 0x00027000);
+}
 struct EpiPartial {
     float *p;
-    int nt_total;
+    int nt_total, mt_total;
     __device__ bool transposed(int) const { return false; }
     __device__ void finish(int, int, int, int) const {}
     __device__ void operator()(int mt, int nt, f32x4 c, int lane, int) const {
-        float *q = p + ((size_t)mt * nt_total + nt) * 256 + lane;
-#pragma unroll
-        for (int r = 0; r < 4; r++) __hip_atomic_store(q + r * 64, c[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned at = ((unsigned)mt * nt_total + nt) * 1024 + lane * 16;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, c), sums_rsrc(p, (size_t)mt_total * nt_total * 1024), at, 0, kDeviceScope);
     }
 };
 

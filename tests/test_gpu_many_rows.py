@@ -88,6 +88,25 @@ def test_step_attention_by_size(heads, b, S):
         p.close()
 
 
+@pytest.mark.parametrize("heads,dh,b,S", [
+    (32, 128, 32, 1),      # 64 workgroups: the channels of an item go to four
+    (32, 128, 16, 3),      # 96, and two drafts with padded rows below: two workgroups each
+    (32, 128, 23, 2),
+    (32, 128, 16, 5),      # 160: one
+    (8, 64, 16, 8),        # heads of 64 channels, four workgroups
+    (8, 64, 16, 9),        # and two
+])
+def test_step_attention_channels_dealt_out(heads, dh, b, S):
+    """One-tile attention with the output channels of an item on one, two and four workgroups."""
+    p = Pair(dict(_width(heads * dh, 512), n_heads=heads, head_dim=dh, vocab=512, mask_id=511))
+    try:
+        wl = W.decode_workload(p.shape, 150, 107, b, S, 920 + S)
+        cache, oc = run_prefill_case(p, wl.tokens, wl.resp_off, "set-up with %d heads" % heads)
+        run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "%d heads, %d x %d" % (heads, S, b))
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("rows", [(9, 16), (3, 64), (13, 16), (8, 32)])
 def test_narrow_step_beyond_128_rows(mid, rows):
     """129 to 256 rows at d = 1024: row blocks of 64 in the streaming kernels, 64-column sums from the K-split kernel."""
