@@ -109,6 +109,71 @@ inline int swiglu_row_block_group(int m_tiles, int n_tiles, int k_tiles) {
     return wgs <= kComputeUnits || k_tiles <= (group == 3 ? 80 : 40) ? group : 0;
 }
 
+// QKV and gate/up from 33 rows on in small blocks of rows on the streaming kernel: row tiles (2 or 4) and n-tiles of a workgroup, or
+// mt = 0 where another kernel runs.  `else_tile`: the tile kernel and its merge pass would take the call, not a streaming kernel of
+// wider row blocks.
+//
+// 32 rows and the fewest n-tiles that make one round of workgroups.  Beyond four of them: at 65 to 128 rows 64 rows and three or four
+// n-tiles while that is one round, else 32 rows and four, two workgroups to a compute unit, as long as those of a
+// compute unit together take in little enough (KiB: (2 row + 4 n-tiles) x K each; it takes in about 80 GB/s): a wider row block
+// needs fewer reads, but the small ones hide each other's prologue and epilogue.  A streaming kernel of one round of wide row blocks wins
+// as soon as the small ones do not fit the chip together.  Fitted over eleven widths, 48 to 1024 rows, models of up to 600 MB so that the weights come
+// from HBM.  Microseconds a layer:
+//   QKV, d 256, 512 rows: 4.8, tile kernel 21.2; d 1024, 320 rows 9.2, tile 24.6; d 1536, 144 rows 10.7, tile 25.7; d 2048, 320 rows
+//   23.3, tile 31.2; d 1024, 96 rows 6.0, 96-row blocks 9.0; d 2560, 128 rows 16.4, slab kernel 20.8
+//   gate/up, d 1024, d_ff 3072, 112 rows 7.5, the same in 32-row blocks 8.3; d 1536, d_ff 4096, 128 rows 10.7, two rounds of three
+//   n-tiles 20.0; d 2560, d_ff 6912, 192 rows 52.4 (2430 KiB), tile 41.2
+struct RowBlock { int mt, ng; };
+inline RowBlock row_block(int m_tiles, int n_tiles, int k_tiles, bool else_tile) {
+    const int blocks = (m_tiles + 1) / 2;
+    for (int ng = 1; ng <= 3; ng++)
+        if ((n_tiles + ng - 1) / ng * blocks <= kComputeUnits) return RowBlock{2, ng};
+    if (m_tiles > 4 && (n_tiles + 3) / 4 * blocks <= kComputeUnits) return RowBlock{2, 4};
+    if (m_tiles > 4 && m_tiles <= 8)
+        for (int ng = 3; ng <= 4; ng++)
+            if ((n_tiles + ng - 1) / ng * 2 <= kComputeUnits) return RowBlock{4, ng};
+    const int wgs = (n_tiles + 3) / 4 * blocks;
+    const double kib = wgs * 6.0 * k_tiles / kComputeUnits;
+    const bool small = m_tiles <= 4 ? kib <= 460 : m_tiles <= 8 ? kib <= 600 : else_tile ? kib <= 1800 : wgs <= 2 * kComputeUnits;
+    return small ? RowBlock{2, 4} : RowBlock{0, 0};
+}
+
+// Gate/up beyond 128 rows in blocks of 96 rows and six n-tiles on the streaming kernel: one round of workgroups instead of the tile
+// kernel, where the small blocks above would take in more than 1200 KiB (us: d 2048, d_ff 5632, 192 rows 20.5, small blocks 31.0, tile
+// 34.0; d 3072, d_ff 3072, 384 rows 23.1, 38.1, 36.0; d 1536, d_ff 4096, 144 rows 15.4, 15.0, 25.3), and instead of the LDS-ring
+// kernel over a short K (d 1024, d_ff 3072, 320 to 384 rows 11.9, 13.7).
+inline bool swiglu_wide_block(int m_tiles, int n_tiles, int k_tiles, bool else_tile) {
+    if (m_tiles <= 8 || (n_tiles + 5) / 6 * ((m_tiles + 5) / 6) > kComputeUnits) return false;
+    return else_tile ? (n_tiles + 3) / 4 * ((m_tiles + 1) / 2) * 6.0 * k_tiles / kComputeUnits > 1200 : m_tiles > 16 && m_tiles <= 24 && k_tiles <= 32;
+}
+
+// O and down from 33 rows on in blocks with all of K in a workgroup: row tiles (2 or 4) and n-tiles, or mt = 0 where K is split.
+//
+// Up to 128 rows the smallest of 32 x 16, 32 x 32 and 64 x 32 that makes one round, beyond 64 columns (the sums of squares cover as
+// many) and 32 rows, else 64, counted per XCD, which takes whole columns of blocks.  A second and third round still pay over a
+// short K.  Splitting K costs an exchange or a merge pass, about 5 us; blocks of all of K take in (mt + ng) x K KiB each, which
+// is what they lose by beyond the limits.  Measured as above, us a layer:
+//   d 1024: O of 128 rows 4.4, K split 6.5; of 333 rows 5.5, 11.3; of 1008 rows 8.2, 14.5; down (d_ff 3072) of 128 rows 7.9, 8.1; of 64
+//   rows 8.2, 7.3 with K split in the kernel; of 192 rows 12.0, 11.5; of 333 rows 9.5, 14.3;
+//   d 4096: O of 128 rows 17.1, 18.9, of 256 rows 22.5, 26.3, of 48 rows 12.2, 11.8 with K split in the kernel;
+//   down, d 1024, d_ff 8192, 144 rows 17.4, 14.1; d 1280, d_ff 5120, 192 rows 17.4, 15.7; d 2560, d_ff 6912, 192 rows 23.4, 22.3
+inline RowBlock resid_block(int m_tiles, int n_tiles, int k_tiles) {
+    if (m_tiles <= 2 || (m_tiles <= 16 && n_tiles <= 64 && k_tiles > (m_tiles <= 8 ? 96 : 64))) return RowBlock{0, 0};      // (the K-split kernel takes these)
+    if (m_tiles <= 8) {
+        const RowBlock shapes[3] = {{2, 1}, {2, 2}, {4, 2}};
+        for (const RowBlock &b : shapes)
+            if ((n_tiles + b.ng - 1) / b.ng * ((m_tiles + b.mt - 1) / b.mt) <= kComputeUnits)
+                return (b.mt + b.ng) * k_tiles <= (m_tiles > 4 ? 800 : b.ng == 1 ? 240 : 400) ? b : RowBlock{0, 0};
+        return RowBlock{0, 0};
+    }
+    const int columns = (n_tiles / 4 + 7) / 8, two = (m_tiles + 1) / 2 * columns, four = (m_tiles + 3) / 4 * columns, round = kComputeUnits / 8;
+    if (two <= round && k_tiles <= 128) return RowBlock{2, 4};
+    if (four <= round && k_tiles <= 128) return RowBlock{4, 4};
+    if (k_tiles <= 64 && two <= 3 * round) return RowBlock{2, 4};
+    if (k_tiles <= 64 && four <= 2 * round) return RowBlock{4, 4};
+    return RowBlock{0, 0};
+}
+
 // QKV on the slab kernel (gemm_slab.h): n-tiles per workgroup, or 0 where another kernel runs.  One row block (97 to 128 rows): three
 // while that is one round of workgroups, beyond it six, which is one round up to twice as far and half as many reads of A
 // (us at 128 rows with three and with six: d 4096 31.1 and 40.2, d 5120 68.7 and 51.1, d 8192 112.5 and 83.7, where the

@@ -5,10 +5,10 @@
 
 namespace odb {
 
-template <int MT, int NG, int PF, class Epi, bool IL = false>
+template <int MT, int NG, int PF, class Epi, bool IL = false, bool NTW = true>
 __global__ __launch_bounds__(64 * WK) void gemm_stream_kernel(GemmArgs g, Epi epi) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    gemm_wg<MT, NG, PF, Epi, IL>(g, epi, blockIdx.x, blockIdx.y * MT, smem);
+    gemm_wg<MT, NG, PF, Epi, IL, NTW>(g, epi, blockIdx.x, blockIdx.y * MT, smem);
 }
 
 constexpr int kStreamWGs = kComputeUnits;      // one workgroup per compute unit
@@ -153,7 +153,7 @@ static void launch_ksplit_narrow(const u16 *a, const u16 *w, GemmShape sh, EpiRe
 // NG n-tiles per group, a PF-deep ring.
 // The per-projection choices below are the fastest measured on MI355X; K_tiles that the ring depth does not
 // divide fall back to a ring of one.
-template <int MT, int NG, int PF, bool IL, class Epi>
+template <int MT, int NG, int PF, bool IL, bool NTW = true, class Epi>
 static void launch_stream(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
     const int kw = sh.K_tiles / WK;                // K_tiles is a multiple of 8 (checked at model creation)
     const int groups = (sh.N_tiles + NG - 1) / NG;
@@ -161,12 +161,40 @@ static void launch_stream(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
     const GemmArgs g = stream_args(a, w, sh, ni, sh.K_tiles, grid.x);
     constexpr int lds = gemm_smem_bytes(MT, NG);
     if (kw % PF == 0) {
-        allow_lds<gemm_stream_kernel<MT, NG, PF, Epi, IL>>(lds);
-        gemm_stream_kernel<MT, NG, PF, Epi, IL><<<grid, 64 * WK, lds, s>>>(g, e);
+        allow_lds<gemm_stream_kernel<MT, NG, PF, Epi, IL, NTW>>(lds);
+        gemm_stream_kernel<MT, NG, PF, Epi, IL, NTW><<<grid, 64 * WK, lds, s>>>(g, e);
     } else {
-        allow_lds<gemm_stream_kernel<MT, NG, 1, Epi, IL>>(lds);
-        gemm_stream_kernel<MT, NG, 1, Epi, IL><<<grid, 64 * WK, lds, s>>>(g, e);
+        allow_lds<gemm_stream_kernel<MT, NG, 1, Epi, IL, NTW>>(lds);
+        gemm_stream_kernel<MT, NG, 1, Epi, IL, NTW><<<grid, 64 * WK, lds, s>>>(g, e);
     }
+}
+
+// O and down beyond 128 rows, whose sums of squares cover 64 columns: blocks of 32 or 64 rows (MT) and 64 columns with all of K in a
+// workgroup, so that nothing is exchanged and no merge pass follows.  Where they are taken: choose.h.
+constexpr int kBlockNG = 4;
+template <int MT>
+__global__ __launch_bounds__(64 * WK) void gemm_block_kernel(GemmArgs g, EpiResid epi) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    constexpr int NG = kBlockNG;
+    float *s_q = reinterpret_cast<float *>(smem + gemm_smem_bytes(MT, NG));
+    // ids go round-robin over the XCDs: the row blocks of a column of blocks meet on one, which then fetches its weights once
+    const int rb = (g.MT_total + MT - 1) / MT, j = blockIdx.x >> 3, nb = (j / rb) * 8 + (blockIdx.x & 7), mt0 = (j % rb) * MT;
+    if (nb >= g.nwg) return;
+    gemm_wg<MT, NG, 1, EpiResidSums<NG>, true, false>(g, EpiResidSums<NG>{epi, s_q, mt0, nb * NG}, nb, mt0, smem);
+    __syncthreads();
+    if (epi.no.hb && threadIdx.x < MT * 16 && mt0 * 16 + threadIdx.x < g.MT_total * 16) {
+        const float *p = s_q + (threadIdx.x >> 4) * (NG * 16) + (threadIdx.x & 15);
+        epi.no.ssq[(size_t)(mt0 * 16 + threadIdx.x) * epi.no.n_ssq + nb] = (p[0] + p[16]) + (p[32] + p[48]);
+    }
+}
+template <int MT>
+static void launch_block(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, hipStream_t s) {
+    // (N is a multiple of 256: every block has four n-tiles)
+    const GemmArgs g = stream_args(a, w, sh, NormIn{nullptr, 0, 0.f}, sh.K_tiles, sh.N_tiles / kBlockNG);
+    const int rb = (sh.M_tiles + MT - 1) / MT, grid = 8 * rb * ((g.nwg + 7) / 8);
+    constexpr int lds = gemm_smem_bytes(MT, kBlockNG) + MT * kBlockNG * 16 * 4;
+    allow_lds<gemm_block_kernel<MT>>(lds);
+    gemm_block_kernel<MT><<<grid, 64 * WK, lds, s>>>(g, e);
 }
 
 // Narrow models: a projection whose n-tiles give fewer than 256 groups of the usual width takes smaller groups, the
@@ -179,12 +207,16 @@ static int stream_ng(int n_tiles, int widest, bool has3) {
     if (has3 && n_tiles <= 3 * kStreamWGs) return 3;
     return widest;
 }
-template <int NG, int PF, int MAX, class Epi>
-static void stream_by_rows(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
-    if (sh.M_tiles <= 2) launch_stream<2, NG, PF, true>(a, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 4) launch_stream<4, NG, PF, true>(a, w, sh, ni, e, s);
-    else if (MAX == 6 || sh.M_tiles <= 6) launch_stream<6, NG, PF, true>(a, w, sh, ni, e, s);
-    else if constexpr (MAX == 8) launch_stream<8, NG, PF, true>(a, w, sh, ni, e, s);
+// QKV and gate/up in small blocks of rows (choose.h: row_block).  Several row blocks read a weight tile: ordinary loads, through L2.
+// With 32 rows and four n-tiles the ring has one stage, so that two workgroups share a compute unit.
+template <class Epi>
+static void launch_row_blocks(RowBlock b, const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
+    if (b.mt == 4 && b.ng == 3) launch_stream<4, 3, 2, true, false>(a, w, sh, ni, e, s);
+    else if (b.mt == 4) launch_stream<4, 4, 2, true, false>(a, w, sh, ni, e, s);
+    else if (b.ng == 1) launch_stream<2, 1, 1, true, false>(a, w, sh, ni, e, s);
+    else if (b.ng == 2) launch_stream<2, 2, 2, true, false>(a, w, sh, ni, e, s);
+    else if (b.ng == 3) launch_stream<2, 3, 4, true, false>(a, w, sh, ni, e, s);
+    else launch_stream<2, 4, 1, true, false>(a, w, sh, ni, e, s);
 }
 
 // n-tiles of a workgroup of the tile kernel
@@ -275,15 +307,15 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     // compute unit leave the activation loads less to queue behind: 1.9 % per step at 32 rows for this and the
     // gate/up projection together, 1.5 % at 64 rows, 0.5 % at 96.)
     const int ng = stream_ng(sh.N_tiles, 3, false), slab = qkv_slab_group(sh.M_tiles, sh.N_tiles);
-    // (a narrow model's 97 to 128 rows: blocks of 32 rows and three n-tiles read 160 instead of 288 KB per compute unit at
-    // d = 1024: 10.4 -> 7.2 us; with 257 to 384 n-tiles blocks of 64 rows, 16.0 -> 11.3 us at d = 1536, where 128 rows and groups of
-    // two spilled; gate/up below: 64 rows and three n-tiles, 10.9 -> 8.5 us.  129 to 256 rows: blocks of 64 rows,
-    // QKV 22.7 -> 9.8 us and gate/up 22.9 -> 10.6 us at 192 rows against the split tile kernel and its merge pass)
-    if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 1) launch_stream<2, 3, 4, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles > 6 && sh.M_tiles <= 8 && slab == 0) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles > 8 && sh.M_tiles <= 16 && ng == 1) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 6 && ng == 1) stream_by_rows<1, 4, 6>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 6 && ng == 2) stream_by_rows<2, 2, 6>(xa, w, sh, ni, e, s);
+    // (blocks of 64 rows and four n-tiles before the slab kernel: one round up to 512 n-tiles)
+    RowBlock rows{0, 0};
+    if (sh.M_tiles > 2 && sh.M_tiles <= 8 && (slab == 0 || sh.N_tiles <= 512)) rows = row_block(sh.M_tiles, sh.N_tiles, sh.K_tiles, false);
+    else if (sh.M_tiles > 8 && slab == 0 && (ng == 1 && sh.M_tiles <= 16 ? true : !big_choice(sh).wn))
+        rows = row_block(sh.M_tiles, sh.N_tiles, sh.K_tiles, sh.M_tiles > 16 || ng != 1);
+    if (rows.mt) launch_row_blocks(rows, xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 2 && ng == 1) launch_stream<2, 1, 4, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 2 && ng == 2) launch_stream<2, 2, 2, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 4 && ng == 2) launch_stream<4, 2, 2, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
     else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);          // 65..96 rows
@@ -306,14 +338,25 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
     // Otherwise, more than 32 rows: the tile kernel, whose K split over workgroups also splits the activation
     // reads, with a separate pass that adds the partial sums.  From 2048 rows the 256 x 128 blocks of the 256-row
     // kernel fill the chip (8 x 32 blocks for N = 4096).
-    const bool long_k = sh.K_tiles > sh.N_tiles;
-    if (const int ng = ksplit_narrow_ng(sh, ws)) {
+    // Blocks with all of K in a workgroup, where they are short enough (choose.h): d 1024 at 128 rows, O 6.5 -> 4.4 us.
+    const RowBlock rows = resid_block(sh.M_tiles, sh.N_tiles, sh.K_tiles);
+    const NormIn none{nullptr, 0, 0.f};
+    if (rows.mt && no.span == 64) {
+        if (rows.mt == 2) launch_block<2>(a, w, sh, e, s);
+        else launch_block<4>(a, w, sh, e, s);
+    }
+    else if (rows.mt) {
+        if (rows.mt == 4) launch_stream<4, 2, 4, true, false>(a, w, sh, none, e, s);
+        else if (rows.ng == 2) launch_stream<2, 2, 4, true, false>(a, w, sh, none, e, s);
+        else launch_stream<2, 1, 4, true, false>(a, w, sh, none, e, s);
+    }
+    else if (const int ng = ksplit_narrow_ng(sh, ws)) {
         if (ng == 1) launch_ksplit_narrow<1>(a, w, sh, e, ws, s);
         else if (ng == 2) launch_ksplit_narrow<2>(a, w, sh, e, ws, s);
         else if (no.span == 64) launch_ksplit_narrow<4, true>(a, w, sh, e, ws, s);
         else launch_ksplit_narrow<4>(a, w, sh, e, ws, s);
     }
-    else if (sh.M_tiles <= 6 && (long_k || sh.M_tiles > 2) && ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
+    else if (ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
     // (128-row blocks only for the O projection: at 1024 rows of the 8B shape 256 blocks of 128 x 128 take 47.7 us against 50.4 for
     // the tile kernel and its merge pass; the down projection, three times as long in K, takes 126 us against 105)
@@ -325,16 +368,25 @@ void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u1
                         hipStream_t s) {
     EpiSwiGLU e{act, sh.M_tiles, status};
     const int ng = stream_ng(sh.N_tiles, 6, true), rb = swiglu_row_block_group(sh.M_tiles, sh.N_tiles, sh.K_tiles);
-    if (sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 2) launch_stream<4, 3, 2, true>(xa, w, sh, ni, e, s);
+    const bool slab = sh.M_tiles > 6 && sh.M_tiles <= 8 && ng == 6, big = sh.M_tiles > 8 && !rb && big_choice(sh).wn;
+    RowBlock rows{0, 0};
+    if (sh.M_tiles > 2 && !slab && !big) rows = row_block(sh.M_tiles, sh.N_tiles, sh.K_tiles, sh.M_tiles > 8 && !rb);
+    if (!rb && swiglu_wide_block(sh.M_tiles, sh.N_tiles, sh.K_tiles, !big)) launch_stream<6, 6, 1, true, false>(xa, w, sh, ni, e, s);
+    else if (rows.mt) launch_row_blocks(rows, xa, w, sh, ni, e, s);
     else if (rb == 6) launch_stream<4, 6, 2, true>(xa, w, sh, ni, e, s);
-    else if (rb == 3) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8 && ng == 1) stream_by_rows<1, 4, 8>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 6 && ng == 2) stream_by_rows<2, 2, 6>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8 && ng == 3) stream_by_rows<3, 1, 8>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 2 && ng == 1) launch_stream<2, 1, 4, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 2 && ng == 2) launch_stream<2, 2, 2, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 4 && ng == 2) launch_stream<4, 2, 2, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 2 && ng == 3) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 4 && ng == 3) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 6 && ng == 3) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);
+    else if (sh.M_tiles <= 8 && ng == 3) launch_stream<8, 3, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 6, 1, true>(xa, w, sh, ni, e, s);
+    // (33 to 64 rows, up to 1024 n-tiles: groups of four leave fewer compute units idle - d 2560, d_ff 6912 20.0 -> 15.9 us)
+    else if (sh.M_tiles <= 4 && sh.N_tiles <= 4 * kStreamWGs) launch_stream<4, 4, 2, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 6) launch_stream<6, 6, 1, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 8) launch_slab<6, true>(xa, w, sh, ni, e, s);
+    else if (slab) launch_slab<6, true>(xa, w, sh, ni, e, s);
     else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, true, s);
 }

@@ -74,12 +74,19 @@ __device__ __forceinline__ NoPre epi_preload(const Epi &, int, int, int) { retur
 template <class Epi>
 __device__ __forceinline__ void epi_apply(Epi &epi, int mt, int nt, f32x4 c, int lane, int slot, NoPre) { epi(mt, nt, c, lane, slot); }
 
+// the sum of the eight waves' values: a chain of three additions, not of seven, and the smaller error
+template <class F>
+__device__ __forceinline__ auto pairwise(F f) {
+    static_assert(WK == 8, "three levels");
+    return ((f(0) + f(1)) + (f(2) + f(3))) + ((f(4) + f(5)) + (f(6) + f(7)));
+}
+
 // One workgroup's share of the GEMM: n-tiles [wg*NT/nwg, (wg+1)*NT/nwg), m-tiles mt0 .. mt0+MT-1.
 // The epilogue is called as epi(mt, nt, c, lane, slot): slot numbers the (m-chunk, tile) pairs that
 // this wave serves, the same in every group of n-tiles, so a stateful epilogue can keep one
 // accumulator per slot; epi.finish(mt, part, lane, slot) follows once per slot at the end.
-// smem: gemm_smem_bytes(MT, NG) bytes.
-template <int MT, int NG, int PF, class Epi, bool IL = false>
+// smem: gemm_smem_bytes(MT, NG) bytes.  NTW: the weight tiles are read by this workgroup only, non-temporally.
+template <int MT, int NG, int PF, class Epi, bool IL = false, bool NTW = true>
 __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int mt0, char *smem) {
     constexpr int MC = gemm_mc(MT, NG);                // m-tiles reduced per pass through LDS
     constexpr int SPW = (MC * NG + WK - 1) / WK;          // reduced tiles a wave serves per m-chunk
@@ -148,7 +155,8 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
         for (int n = 0; n < NG; n++) {
             int nt = n_lo + grp * NG + n;
             nt = nt < n_hi ? nt : n_hi - 1;
-            wb[slot][n] = ld_frag_stream(wbase + ((size_t)nt * g.KT + kk * kst) * kTileElems);
+            const u16 *p = wbase + ((size_t)nt * g.KT + kk * kst) * kTileElems;
+            wb[slot][n] = NTW ? ld_frag_stream(p) : ld_frag(p);
         }
 #pragma unroll
         for (int m = 0; m < MT; m++) ab[slot][m] = ld_frag(ap[m] + kk * a_step);
@@ -224,9 +232,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
                 if (mt < g.MT_total && nt < n_hi) {
                     f32x4 c;
                     if (!epi.transposed(nt)) {
-                        c = red[0][t][lane];
-#pragma unroll
-                        for (int w = 1; w < WK; w++) c += red[w][t][lane];
+                        c = pairwise([&](int w) { return red[w][t][lane]; });
                         c *= s_rstd[(mc + m) * 16 + (lane & 15)];
                     } else {
                         // hand lane (g, ni) the four rows 4g..4g+3 of column ni instead of four columns of one row
@@ -236,9 +242,7 @@ __device__ __forceinline__ void gemm_wg(const GemmArgs &g, Epi epi, int wg, int 
 #pragma unroll
                         for (int r = 0; r < 4; r++) {
                             const int src = ((ni >> 2) * 16 + 4 * gq + r) * 4 + (ni & 3);
-                            float v = base[src];
-#pragma unroll
-                            for (int w = 1; w < WK; w++) v += base[w * stride + src];
+                            const float v = pairwise([&](int w) { return base[w * stride + src]; });
                             c[r] = v * s_rstd[(mc + m) * 16 + 4 * gq + r];
                         }
                     }
@@ -363,6 +367,23 @@ struct EpiResid {
 
 __device__ __forceinline__ ResidPre epi_preload(const EpiResid &e, int mt, int nt, int lane) { return e.preload(mt, nt, lane); }
 __device__ __forceinline__ void epi_apply(EpiResid &e, int mt, int nt, f32x4 c, int lane, int, const ResidPre &pre) { e.apply(mt, nt, c, lane, pre); }
+
+// The same with the sums of squares left in LDS, s_q[row tile][n-tile][16 rows] of the workgroup's block, for sums over 64 columns.
+template <int NG>
+struct EpiResidSums {
+    EpiResid r;
+    float *s_q;
+    int mt0, nt0;
+    __device__ bool transposed(int) const { return false; }
+    __device__ void finish(int, int, int, int) const {}
+};
+template <int NG>
+__device__ __forceinline__ ResidPre epi_preload(const EpiResidSums<NG> &e, int mt, int nt, int lane) { return e.r.preload(mt, nt, lane); }
+template <int NG>
+__device__ __forceinline__ void epi_apply(EpiResidSums<NG> &e, int mt, int nt, f32x4 c, int lane, int, const ResidPre &pre) {
+    const float q = EpiResid::over_row(e.r.put(mt, nt, c, lane, pre));
+    if (lane < 16) e.s_q[((mt - e.mt0) * NG + nt - e.nt0) * 16 + lane] = q;
+}
 
 // W_gu interleaves the rows of W_gate and W_up (physical row 2j = gate j, 2j+1 = up j)
 struct EpiSwiGLU {

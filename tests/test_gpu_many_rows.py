@@ -107,6 +107,31 @@ def test_step_attention_channels_dealt_out(heads, dh, b, S):
         p.close()
 
 
+@pytest.mark.parametrize("d,f,steps,refresh", [
+    (256, 768, [(3, 16), (9, 23)], [(1, 630), (3, 333)]),     # one to four n-tiles per workgroup, O / down in blocks of 32 rows
+    (768, 2048, [(5, 16), (3, 43)], [(1, 333)]),              # K of three k-tiles a wave: rings of one stage
+    (1024, 3072, [(3, 16), (4, 29)], [(1, 333), (1, 650)]),   # O / down in blocks of 32 x 16, 32 x 64 and 64 x 64
+    (1280, 512, [], [(3, 333)]),                              # O in three rounds of blocks
+    (1536, 512, [(5, 16), (9, 16)], [(1, 333)]),              # O in blocks of 32 x 32
+    (2048, 512, [(3, 16)], [(1, 333), (1, 500)]),             # two rounds of blocks of 64 x 64
+    (4096, 512, [(5, 16), (9, 16)], []),                      # O in blocks of 64 x 32 and 64 x 64
+    (4096, 4096, [(1, 32), (7, 16)], []),                     # O of 32 rows with K split; gate/up in groups of four
+])
+def test_row_blocks_by_width(d, f, steps, refresh):
+    """QKV, gate/up, O and down in small blocks of rows (33 rows and more), the last block and the drafts ragged."""
+    p = Pair(dict(_width(d, f), vocab=512, mask_id=511))
+    try:
+        for S, b in steps:
+            wl = W.decode_workload(p.shape, 40, 60, b, S, 760 + S)
+            cache, oc = run_prefill_case(p, wl.tokens, wl.resp_off, "set-up at d = %d" % d)
+            run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "d = %d, %d x %d" % (d, S, b))
+        for Bn, L in refresh:
+            wl = W.decode_workload(p.shape, L - 60, 60, 16, 1, 770 + L, batch=Bn)
+            run_prefill_case(p, wl.tokens, wl.resp_off, "d = %d, %d x %d" % (d, Bn, L))
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("rows", [(9, 16), (3, 64), (13, 16), (8, 32)])
 def test_narrow_step_beyond_128_rows(mid, rows):
     """129 to 256 rows at d = 1024: row blocks of 64 in the streaming kernels, 64-column sums from the K-split kernel."""
