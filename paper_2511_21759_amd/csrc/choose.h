@@ -68,7 +68,7 @@ inline AttentionChoice attention_choice(int dh, int H, int L, bool step, int uni
 // Microseconds with the merge pass, by slices: 1232 rows, N 1280, K 5120: 4 29.3, 5 37.6; 144 rows, N 3584, K 18944: 8 44.8,
 // 9 50.8; 640 rows, N 4096, K 12288: 2 96.7, 3 76.3; 128 rows, N 4096, K 4096: 5 20.1, 6 19.1, 8 20.4.
 enum class TileEpilogue { qkv, swiglu, resid };
-inline int tile_slices(TileEpilogue epi, int m_tiles, int n_tiles, int k_tiles, size_t room) {
+inline int tile_slices(TileEpilogue epi, int m_tiles, int n_tiles, int k_tiles, size_t room, double *time = nullptr) {
     const bool wide = m_tiles > 8;                          // two n-tiles per wave
     const int m_blocks = (m_tiles + 7) / 8, n_blocks = (n_tiles + (wide ? 15 : 7)) / (wide ? 16 : 8), blocks = m_blocks * n_blocks;
     const double a_mb = m_tiles * (double)k_tiles / 1024, w_mb = n_tiles * (double)k_tiles / 1024, out_mb = m_tiles * (double)n_tiles / 1024;
@@ -93,6 +93,7 @@ inline int tile_slices(TileEpilogue epi, int m_tiles, int n_tiles, int k_tiles, 
     double best_us = (wide ? 1.0 : 0.98) * us(best);
     for (int ks = 1; ks <= 16; ks++)
         if (fits(ks) && us(ks) < best_us) { best = ks; best_us = us(ks); }
+    if (time) *time = us(best);
     return best;
 }
 
@@ -227,5 +228,54 @@ inline BigChoice big_choice_by(int m, int n_tiles, bool per_xcd, double least) {
 inline BigChoice big_choice(int m, int n_tiles, int k_tiles) { return big_choice_by(m, n_tiles, true, k_tiles <= 32 ? 0.45 : 0.65); }
 // The LM head by its own numbers: as many statistics per row as before, which decide with the rest whether a step fits the fixed area.
 inline BigChoice lm_block_choice(int m, int n_tiles) { return big_choice_by(m, n_tiles, false, 0.7); }
+
+// What runs where big_choice decided until the blocks below were measured: a block shape of the LDS-ring kernel - mbt x 16 rows by
+// 64 * wn columns, its last round split over `ks` workgroups a block - or the tile kernel (wn = 0).
+//
+// `now` stands - the shape big_choice picks, or the tile kernel - unless another block promises 4 % by the model of big_us, 6 % with
+// its last round split.  Blocks of 192 and 320 rows serve counts of rows that 128 and 256 divide badly (8B shape: gate/up of 608 rows in
+// 256 blocks of 320 x 192 135 -> 111 us, of 320 rows in 192 x 192 124 -> 69, QKV of 1408 rows in 320 x 256 194 -> 151, down of 3008
+// rows in 192 x 256 311 -> 281).  Splitting K in the blocks of the last, half empty round fills it (256 x 256 blocks: down of 2048 rows
+// 128 blocks on 256 compute units 240 -> 202 us; QKV of 2048 rows one and a half rounds 220 -> 207).  The gain is less than the
+// idle units suggest, as the others run at a lower clock the more of them multiply; the exchange costs 7 us a block of 256 x 256.
+// Over 222 measured sizes (d 1024 to 4096, 176 to 3008 rows) the launches take 0.956 of the time on average, 0.951 with the best of
+// these blocks everywhere; three are slower by more than 2 %, up to 5 %.  Splits of other shapes would add 0.4 %.
+struct BigPlan { int mbt, wn, ks; };
+constexpr int kSplitMbt = 16, kSplitWn = 4;                     // the shape whose last round may be split
+// blocks of the fullest XCD, which takes whole columns of blocks and runs kXcdUnits of them at a time
+constexpr int kXcdUnits = kComputeUnits / 8;
+inline int big_per_xcd(int mbt, int wn, int m, int n) { return (m + mbt - 1) / mbt * (((n + 4 * wn - 1) / (4 * wn) + 7) / 8); }
+// Microseconds of a launch, fitted to 4180 measured (6 % off at the root mean square): a block's time by shape and K when all
+// compute units work; the last round between 0.57 and 1 of that by its fill; 3.4 a round, the epilogue (under the next round by half), the
+// exchange of a split block.
+inline double big_us(TileEpilogue epi, int mbt, int wn, int ks, int m, int n, int k) {
+    const double at4096[4][3] = {{43.9, 59.6, 70.9}, {76.0, 71.5, 93.8}, {74.6, 98.9, 112.1}, {98.5, 114.1, 143.3}};    // mbt 8 .. 20, wn 2 .. 4
+    const int per = big_per_xcd(mbt, wn, m, n), all = (m + mbt - 1) / mbt * ((n + 4 * wn - 1) / (4 * wn));
+    const double area = mbt * wn / 64.0, full = at4096[mbt / 4 - 2][wn - 2] * k / 128;
+    const double out = (epi == TileEpilogue::swiglu ? 0 : epi == TileEpilogue::qkv ? 13.2 : 14.3) * area;
+    const int whole = ks > 1 ? per / kXcdUnits : (per + kXcdUnits - 1) / kXcdUnits - 1;
+    const int rounds = ((per - whole * kXcdUnits) * ks + kXcdUnits - 1) / kXcdUnits;
+    double fill = (all - whole * (double)kComputeUnits) * ks / kComputeUnits - (rounds - 1);
+    fill = fill < 0.02 ? 0.02 : fill > 1 ? 1 : fill;
+    return out * (1 + 0.5 * whole) + 3.4 * (whole + rounds) + full * whole + full / ks * (rounds - 1 + 0.57 + 0.43 * fill) +
+           (ks > 1 ? 0.9 + 6.8 * area * (ks - 1) : 0);
+}
+// room: bytes for partial sums; may_exchange: workgroups of a launch may exchange them
+inline BigPlan big_plan(TileEpilogue epi, BigChoice now, int m, int n, int k, size_t room, bool may_exchange) {
+    BigPlan best{now.mbt, now.wn, 1};
+    double now_us = 0;
+    if (now.wn) now_us = big_us(epi, now.mbt, now.wn, 1, m, n, k);
+    else (void)tile_slices(epi, m, n, k, room, &now_us);
+    double best_us = 1e30;
+    auto consider = [&](int mbt, int wn, int ks) {
+        const double us = big_us(epi, mbt, wn, ks, m, n, k);
+        if (us < best_us && us < (ks > 1 ? 0.94 : 0.96) * now_us) { best = BigPlan{mbt, wn, ks}; best_us = us; }
+    };
+    for (int mbt = 8; mbt <= 20; mbt += 4)
+        for (int wn = mbt % 8 == 4 ? 3 : 2; wn <= 4; wn++) consider(mbt, wn, 1);         // (no narrow blocks of 192 and 320 rows)
+    const int left = big_per_xcd(kSplitMbt, kSplitWn, m, n) % kXcdUnits;
+    if (may_exchange && left > 0 && (size_t)left * 8 * kSplitMbt * kSplitWn * 4096 <= room) consider(kSplitMbt, kSplitWn, 2);
+    return best;
+}
 
 }  // namespace odb

@@ -255,16 +255,19 @@ static void launch_tile(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
 }
 
 // blocks of MBT x 16 rows through LDS (gemm_big.h), 64 * WN columns wide
-template <int WN, class Epi, int MBT = 16>
-static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
+template <int WN, class Epi, int MBT = 16, int KS = 1>
+static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s, Workspace ws = Workspace{}) {
     BigArgs g;
     g.A = a; g.W = w; g.KT = sh.K_tiles; g.MT_total = sh.M_tiles; g.NT = sh.N_tiles;
     g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
     g.m_blocks = (sh.M_tiles + MBT - 1) / MBT;
     g.n_blocks = (sh.N_tiles + 4 * WN - 1) / (4 * WN);
-    allow_lds<gemm_big_kernel<WN, Epi, MBT>>(big_smem_bytes(WN, MBT));
-    dim3 grid(8 * g.m_blocks * ((g.n_blocks + 7) / 8));
-    gemm_big_kernel<WN, Epi, MBT><<<grid, 512, big_smem_bytes(WN, MBT), s>>>(g, e);
+    g.partial = ws.partial; g.arrive = ws.arrive;
+    const int per_xcd = big_per_xcd(MBT, WN, sh.M_tiles, sh.N_tiles);
+    g.whole = KS > 1 ? per_xcd / kXcdUnits * kXcdUnits : per_xcd;
+    allow_lds<gemm_big_kernel<WN, Epi, MBT, KS>>(big_smem_bytes(WN, MBT));
+    dim3 grid(8 * (g.whole + (per_xcd - g.whole) * KS));
+    gemm_big_kernel<WN, Epi, MBT, KS><<<grid, 512, big_smem_bytes(WN, MBT), s>>>(g, e);
 }
 
 static BigChoice big_choice(GemmShape sh) { return big_choice(sh.M_tiles, sh.N_tiles, sh.K_tiles); }
@@ -285,9 +288,18 @@ static void launch_big_as(BigChoice c, const u16 *a, const u16 *w, GemmShape sh,
             else launch_big_wn<4, Epi, 16>(a, w, sh, ni, e, s);
     }
 }
+// QKV, gate/up, O and down beyond 128 rows in the blocks that big_plan picks, `now` being the choice it starts from
 template <class Epi>
-static void launch_big(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, hipStream_t s) {
-    launch_big_as(big_choice(sh), a, w, sh, ni, e, s);
+static void launch_big_or_tile(BigChoice now, const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, Workspace ws, hipStream_t s) {
+    static_assert(2 * 8 * (kXcdUnits - 1) <= 1024, "two counters for every split block");
+    const BigPlan p = big_plan(tile_epilogue_of<Epi>, now, sh.M_tiles, sh.N_tiles, sh.K_tiles, ws.partial_bytes, ws.arrive != nullptr);
+    if (p.wn == 0) launch_tile(a, w, sh, ni, e, ws, true, s);
+    else if (p.ks == 2) launch_big_wn<kSplitWn, Epi, kSplitMbt, 2>(a, w, sh, ni, e, s, ws);
+    else if (p.mbt == 12 && p.wn == 3) launch_big_wn<3, Epi, 12>(a, w, sh, ni, e, s);
+    else if (p.mbt == 12) launch_big_wn<4, Epi, 12>(a, w, sh, ni, e, s);
+    else if (p.mbt == 20 && p.wn == 3) launch_big_wn<3, Epi, 20>(a, w, sh, ni, e, s);
+    else if (p.mbt == 20) launch_big_wn<4, Epi, 20>(a, w, sh, ni, e, s);
+    else launch_big_as(BigChoice{p.mbt, p.wn}, a, w, sh, ni, e, s);
 }
 
 // The slab kernel (gemm_slab.h): blocks of 128 rows against NTB n-tiles.
@@ -322,8 +334,7 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     else if (slab == 3) launch_slab<3, true>(xa, w, sh, ni, e, s);
     else if (slab == 6 && (sh.M_tiles <= 8 || sh.M_tiles >= 12)) launch_slab<6, true>(xa, w, sh, ni, e, s);
     else if (slab == 6) launch_slab<6, false>(xa, w, sh, ni, e, s);
-    else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
-    else launch_tile(xa, w, sh, ni, e, ws, true, s);
+    else launch_big_or_tile(big_choice(sh), xa, w, sh, ni, e, ws, s);
 }
 void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int ldh, NormOut no, Workspace ws,
                        hipStream_t s) {
@@ -358,11 +369,13 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
     }
     else if (ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
-    // (128-row blocks only for the O projection: at 1024 rows of the 8B shape 256 blocks of 128 x 128 take 47.7 us against 50.4 for
-    // the tile kernel and its merge pass; the down projection, three times as long in K, takes 126 us against 105)
-    else if (big_choice(sh).wn && (big_choice(sh).mbt == 16 || sh.K_tiles <= sh.N_tiles))
-        launch_big(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
-    else launch_tile(a, w, sh, NormIn{nullptr, 0, 0.f}, e, ws, true, s);
+    else if (sh.M_tiles <= 8) launch_tile(a, w, sh, none, e, ws, true, s);
+    else {
+        // (128-row blocks only for the O projection: at 1024 rows of the 8B shape 256 blocks of 128 x 128 take 47.7 us against 50.4 for
+        // the tile kernel and its merge pass; the down projection, three times as long in K, takes 126 us against 105)
+        const BigChoice now = big_choice(sh);
+        launch_big_or_tile(now.mbt == 16 || sh.K_tiles <= sh.N_tiles ? now : BigChoice{16, 0}, a, w, sh, none, e, ws, s);
+    }
 }
 void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u16 *act, unsigned *status, Workspace ws,
                         hipStream_t s) {
@@ -387,8 +400,7 @@ void launch_gemm_swiglu(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, u1
     else if (sh.M_tiles <= 4) launch_stream<4, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 6) launch_stream<6, 6, 1, true>(xa, w, sh, ni, e, s);
     else if (slab) launch_slab<6, true>(xa, w, sh, ni, e, s);
-    else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
-    else launch_tile(xa, w, sh, ni, e, ws, true, s);
+    else launch_big_or_tile(big_choice(sh), xa, w, sh, ni, e, ws, s);
 }
 
 constexpr int kLmNG = 6;      // n-tiles per group of the LM head at up to 32 rows
@@ -455,7 +467,7 @@ void launch_gemm_store(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, flo
     if (sh.M_tiles <= 2) launch_stream<2, 3, 8, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 4, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 8) launch_stream<8, 3, 2, false>(xa, w, sh, ni, e, s);
-    else if (big_choice(sh).wn) launch_big(xa, w, sh, ni, e, s);
+    else if (big_choice(sh).wn) launch_big_as(big_choice(sh), xa, w, sh, ni, e, s);
     else launch_tile(xa, w, sh, ni, e, ws, false, s);
 }
 

@@ -22,10 +22,10 @@ namespace odb {
 // have 8 to 16, so their stages are two k-tiles deep (measured on the loop alone at K = 4096: 128 x 128 blocks 43.3 -> 37.1 us
 // at 1024 x 4096, 128 x 192 blocks 56.1 -> 52.4 us at 256 x 24576; 256 x 256 blocks equal.  256 x 128 blocks, two layers of a
 // refresh of 4 x 512 positions, one k-tile with four stages -> two with three: O 167.9 -> 153.2 us, down 420.8 -> 387.8).
-constexpr int big_kp(int wn, int mbt) { return (mbt == 8 && wn <= 4) || wn == 2 ? 2 : 1; }
-constexpr int big_stages(int wn, int mbt) { return mbt == 8 || wn == 2 ? 3 : 4; }
+constexpr int big_kp(int wn, int mbt) { return (mbt == 8 && wn <= 4) || (mbt == 12 && wn <= 3) || (mbt == 16 && wn == 2) ? 2 : 1; }
+constexpr int big_stages(int wn, int mbt) { return mbt == 8 || big_kp(wn, mbt) == 2 ? 3 : 4; }
 constexpr int big_stage_tiles(int wn, int mbt) { return big_kp(wn, mbt) * (mbt + 4 * wn); }
-constexpr int big_smem_bytes(int wn, int mbt) { return big_stages(wn, mbt) * big_stage_tiles(wn, mbt) * 1024 + 256 * 4; }   // ring, row scales
+constexpr int big_smem_bytes(int wn, int mbt) { return big_stages(wn, mbt) * big_stage_tiles(wn, mbt) * 1024 + 320 * 4; }   // ring, row scales
 // per-wave scratch of the epilogues, in the ring's place once the k-loop is over
 constexpr int kBigScratch = 4096;
 
@@ -36,6 +36,10 @@ struct BigArgs {
     const float *ssq;          // fused RMSNorm of the input rows (see GemmArgs)
     int n_ssq;
     float eps, inv_d;
+    // (KS > 1) an XCD's blocks from number `whole` on are split over KS workgroups each, which add their sums up (big_exchange)
+    int whole;
+    float *partial;
+    unsigned *arrive;
 };
 
 // ---- epilogues of a wave's MW x WT output tiles ------------------------------------------------------------------
@@ -129,15 +133,16 @@ __device__ __forceinline__ void big_epilogue(const EpiSwiGLU &e, f32x4 (&acc)[MW
     bool bad = false;
 #pragma unroll
     for (int m = 0; m < MW; m++) {
-        if (mtw + m >= g.MT_total) break;
-        const float rs = rstd[m * 16 + mi];
+        if (mtw + m < g.MT_total) {
+            const float rs = rstd[m * 16 + mi];
 #pragma unroll
-        for (int j = 0; j < WT; j++) {
-            if (ntw + j >= g.NT) break;
-            const f32x4 c = acc[m][j] * rs;
-            const float y0 = EpiSwiGLU::act2(c[0], c[1]), y1 = EpiSwiGLU::act2(c[2], c[3]);
-            bad |= out_of_f16(y0, y1, 0.f, 0.f);
-            *reinterpret_cast<uint32_t *>(dst[j] + m * kTileElems) = pack4(y0, y1, 0.f, 0.f).x;
+            for (int j = 0; j < WT; j++) {
+                if (ntw + j >= g.NT) break;
+                const f32x4 c = acc[m][j] * rs;
+                const float y0 = EpiSwiGLU::act2(c[0], c[1]), y1 = EpiSwiGLU::act2(c[2], c[3]);
+                bad |= out_of_f16(y0, y1, 0.f, 0.f);
+                *reinterpret_cast<uint32_t *>(dst[j] + m * kTileElems) = pack4(y0, y1, 0.f, 0.f).x;
+            }
         }
     }
     if (bad && e.status) atomicOr(e.status, kStatusSaturated);
@@ -227,13 +232,76 @@ __device__ __forceinline__ void big_epilogue(const EpiStore &e, f32x4 (&acc)[MW]
             if (mtw + m < g.MT_total && ntw + j < g.NT) e(mtw + m, ntw + j, acc[m][j] * rstd[m * 16 + (lane & 15)], lane, 0);
 }
 
+// Adds the sums of the KS workgroups of a split block (number `at` of the launch's split ones).  All but the one that arrives last
+// leave theirs in the workspace, wait for the stores and count themselves ready; the last waits for those - they have arrived, so
+// they run and wait for nobody - adds them up in slice order with its own and goes on to the epilogue (returns true).
+// Stores, loads and counters are device-scope accesses without cache-wide fences, as in gemm_stream_ksplit_kernel.  With two slices
+// one of them is ever stored; more have a place each.  The counters are back at zero when the kernel ends.
+template <int KS, int MW, int WT>
+__device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs &g, int at, int ks, int w, int lane, unsigned *s_old) {
+    constexpr unsigned bytes = 8 * MW * WT * 1024;
+    constexpr int P = KS == 2 ? 1 : KS;
+    unsigned *arrive = g.arrive + 2 * at;
+    float *base = g.partial + (size_t)at * P * (bytes / 4);
+    if (threadIdx.x == 0) *s_old = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const bool last = *s_old == (unsigned)KS - 1;
+    const unsigned off = w * (MW * WT * 1024) + lane * 16;
+    if (!last) {
+        float *p = base + (KS == 2 ? 0 : ks) * (size_t)(bytes / 4);
+#pragma unroll
+        for (int m = 0; m < MW; m++)
+#pragma unroll
+            for (int j = 0; j < WT; j++)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[m][j]), sums_rsrc(p, bytes), off + (m * WT + j) * 1024, 0, kDeviceScope);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(arrive + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+    }
+    if (threadIdx.x == 0)
+        while (__hip_atomic_load(arrive + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)KS - 1) __builtin_amdgcn_s_sleep(1);
+    __syncthreads();
+    constexpr int B = 16 / P;                   // tiles requested together
+#pragma unroll
+    for (int t0 = 0; t0 < MW * WT; t0 += B) {
+        u32x4 v[B][P];
+#pragma unroll
+        for (int t = 0; t < B; t++)
+            if (t0 + t < MW * WT)
+#pragma unroll
+                for (int s = 0; s < P; s++)      // (a last slice's own place holds nothing; what is read there is not used)
+                    v[t][s] = __builtin_amdgcn_raw_buffer_load_b128(sums_rsrc(base + s * (size_t)(bytes / 4), bytes), off + (t0 + t) * 1024, 0, kDeviceScope);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < B; t++)
+            if (t0 + t < MW * WT) {
+                f32x4 &own = acc[(t0 + t) / WT][(t0 + t) % WT];
+                if constexpr (KS == 2) {
+                    own += __builtin_bit_cast(f32x4, v[t][0]);
+                } else {
+                    f32x4 c = ks == 0 ? own : __builtin_bit_cast(f32x4, v[t][0]);
+#pragma unroll
+                    for (int s = 1; s < P; s++) c += ks == s ? own : __builtin_bit_cast(f32x4, v[t][s]);
+                    own = c;
+                }
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(arrive + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return true;
+}
+
 // MBT: 16-row tiles per block, 16 (256 rows) or 8 (128 rows: twice the blocks for shapes that leave compute
 // units idle otherwise; per flop it needs 1.4 x the operand bytes of the 256-row block).  WN = 8: a single block of 128 rows
 // against 512 columns, for the LM head at 33 to 128 rows; W is then read once, non-temporally.
-template <int WN, class Epi, int MBT = 16>
+template <int WN, class Epi, int MBT = 16, int KS = 1>
 __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
     static_assert((WN >= 2 && WN <= 4) || (WN == 8 && MBT == 8), "block width in units of 64 columns");
-    static_assert(MBT == 16 || MBT == 8, "rows per block");
+    static_assert(MBT % 4 == 0 && MBT >= 8 && MBT <= 20, "rows per block");
     constexpr int CW = 4;                       // waves side by side; two rows of them
     constexpr int WT = WN;                      // 16-column tiles per wave
     constexpr int MW = MBT / 2;                 // 16-row tiles per wave
@@ -249,8 +317,12 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
     // blocks of a column of blocks before they move to that XCD's next column, so concurrently
     // resident workgroups of an XCD share weight panels (and all of them the rows of A) in its L2.
     const int xcd = blockIdx.x % 8, jx = blockIdx.x / 8;
-    const int nb = (jx / g.m_blocks) * 8 + xcd, mb = jx % g.m_blocks;
+    const bool split = KS > 1 && jx >= g.whole;
+    const int blk = split ? g.whole + (jx - g.whole) / KS : jx, ks = split ? (jx - g.whole) % KS : 0;
+    const int nb = (blk / g.m_blocks) * 8 + xcd, mb = blk % g.m_blocks;
     if (nb >= g.n_blocks) return;
+    const int ns_all = g.KT / KP;               // stages (K is a multiple of 256: k-tiles come in eights)
+    const int s_lo = split ? ks * ns_all / KS : 0, ns = (split ? (ks + 1) * ns_all / KS : ns_all) - s_lo;
     const int mt0 = mb * MBT, nt0 = nb * 4 * WN;
 
     // the first half of the waves copies the MBT tiles of A of every k-tile, the second half the 4 WN of W
@@ -263,7 +335,7 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
         for (int i = 0; i < PMAX; i++) {
             int mt = mt0 + PA * w + (i < PA ? i : PA - 1);
             mt = mt < g.MT_total ? mt : g.MT_total - 1;
-            src[i] = g.A + (size_t)mt * kTileElems;
+            src[i] = g.A + ((size_t)s_lo * KP * g.MT_total + mt) * kTileElems;
         }
         kstride = (size_t)g.MT_total * kTileElems;
     } else {
@@ -271,7 +343,7 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
         for (int i = 0; i < PMAX; i++) {
             int nt = nt0 + PW * (w - CW) + (i < PW ? i : PW - 1);
             nt = nt < g.NT ? nt : g.NT - 1;
-            src[i] = g.W + (size_t)nt * g.KT * kTileElems;
+            src[i] = g.W + ((size_t)nt * g.KT + s_lo * KP) * kTileElems;
         }
         kstride = kTileElems;
     }
@@ -290,17 +362,16 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
                 }
     };
 
-    const int ns = g.KT / KP;                   // stages (K is a multiple of 256: k-tiles come in eights)
 #pragma unroll
     for (int j = 0; j < NS - 1; j++)
         if (j < ns) issue(j, j);
 
-    // row scales of the fused RMSNorm: two (256 rows) or four threads per row, behind the ring's first copies
+    // row scales of the fused RMSNorm: one to four threads per row, behind the ring's first copies
     {
         constexpr int TR = 512 / (MBT * 16);
         const int r = threadIdx.x / TR, part = threadIdx.x % TR;
         float t = 1.f;
-        if (g.ssq) {
+        if (g.ssq && r < MBT * 16) {
             int row = mt0 * 16 + r;
             row = row < g.MT_total * 16 ? row : g.MT_total * 16 - 1;
             const float *p = g.ssq + (size_t)row * g.n_ssq;
@@ -313,7 +384,7 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
             for (int o = 1; o < TR; o <<= 1) t += __shfl_xor(t, o);
             t = 1.0f / sqrtf(t * g.inv_d + g.eps);
         }
-        if (part == 0) s_rstd[r] = t;
+        if (part == 0 && r < MBT * 16) s_rstd[r] = t;
     }
 
     f32x4 acc[MW][WT];
@@ -362,13 +433,19 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
 #pragma unroll
             for (int m = 0; m < MW; m++)
 #pragma unroll
-                for (int j = 0; j < WT; j++) acc[m][j] = mfma16(b[q][j], a[q][m], acc[m][j]);
+                for (int i = 0; i < WT; i++) {
+                    const int j = m & 1 ? WT - 1 - i : i;       // to and fro: one operand changes from MFMA to MFMA, never both
+                    acc[m][j] = mfma16(b[q][j], a[q][m], acc[m][j]);
+                }
         if (wm == 0) wait_stage(more);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();
     }
     if (wm == 0) __builtin_amdgcn_s_barrier();
     __syncthreads();            // the ring is reused below
+
+    if constexpr (KS > 1)
+        if (split && !big_exchange<KS, MW, WT>(acc, g, (blk - g.whole) * 8 + xcd, ks, w, lane, reinterpret_cast<unsigned *>(smem))) return;
 
     if constexpr (is_row_stats<Epi>::value) {
         // softmax statistics per row over this workgroup's columns: lane-local, across the four lane

@@ -19,6 +19,10 @@ int attention_one_xcd(int dh, int H, int L, int step, int units, int ups, int tp
 int swiglu_group(int m, int n, int k) { return swiglu_row_block_group(m, n, k); }
 int qkv_slab(int m, int n) { return qkv_slab_group(m, n); }
 int big_block(int m, int n, int k) { const BigChoice c = big_choice(m, n, k); return c.wn ? c.mbt * 10 + c.wn : 0; }
+int plan(int epi, int now_mbt, int now_wn, int m, int n, int k, size_t room, int may) {
+    const BigPlan p = big_plan((TileEpilogue)epi, BigChoice{now_mbt, now_wn}, m, n, k, room, may != 0);
+    return p.wn ? p.mbt * 100 + p.wn * 10 + p.ks : 0;
+}
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
 """
@@ -236,3 +240,39 @@ SHORT_K = [
 def test_blocks_over_a_short_k(rules, n, rows, k, us):
     block = rules.big_block(rows // 16, n, k)
     assert block in us and us[block] <= 1.15 * min(us.values())
+
+
+# projection (0 QKV, 1 gate/up, 2 O and down), rows, n-tiles, k-tiles, block before the rule (0: tile kernel) -> us by block (16-row
+# tiles * 100 + units of 64 columns * 10 + workgroups that share a block of the last round)
+PLANS = [
+    (1, 320, 1536, 128, 0, {0: 123.7, 1231: 69.3, 1241: 83.1, 1631: 87.6, 2031: 90.8, 2041: 107.4}),
+    (1, 608, 1536, 128, 841, {841: 135.4, 2031: 112.9, 2041: 125.5, 1231: 139.2, 1241: 166.6, 1642: 157.3}),
+    (1, 704, 1536, 128, 1641, {1641: 171.9, 1231: 141.1, 1642: 159.6, 1241: 167.1, 2031: 199.4}),
+    (0, 768, 768, 128, 841, {841: 95.9, 1231: 78.4, 1241: 92.7, 2031: 114.4, 1642: 120.5}),
+    (1, 1024, 1536, 128, 1631, {1631: 197.2, 1642: 188.9, 1231: 219.3, 2031: 226.9, 1241: 264.1}),
+    (0, 1408, 768, 128, 1641, {1641: 194.0, 2041: 151.3, 1231: 162.8, 1642: 173.6, 1241: 183.1}),
+    (2, 1536, 256, 384, 1621, {1621: 211.2, 1642: 177.9, 1231: 190.9, 1241: 241.5, 2031: 277.1}),
+    (0, 2048, 768, 128, 1631, {1631: 220.1, 1642: 207.1, 1231: 243.0, 2031: 248.6, 1241: 279.5}),
+    (2, 2048, 256, 384, 1621, {1621: 240.4, 1642: 202.3, 1241: 268.0, 2031: 302.8, 1231: 355.0}),
+    (2, 3008, 256, 384, 1631, {1631: 311.4, 1241: 280.9, 2031: 323.9, 1642: 348.1, 2041: 372.3}),
+    (2, 3008, 256, 128, 1631, {1631: 128.8, 1241: 114.7, 2031: 132.9, 2041: 154.8, 1231: 155.1}),
+]
+
+
+@pytest.mark.parametrize("epi,rows,n,k,now,us", PLANS)
+def test_plans_are_near_the_fastest_measured(rules, epi, rows, n, k, now, us):
+    rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
+    picked = rules.plan(epi, now // 100 if now else 16, now // 10 % 10, rows // 16, n, k, 96 << 20, 1)
+    assert picked in us and us[picked] <= 1.05 * min(us.values()) and us[picked] <= us[now]
+
+
+def test_plans_exchange_only_where_there_is_room_for_it(rules):
+    rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
+    split = lambda room, may: rules.plan(2, 16, 2, 128, 256, 384, room, may) == 1642
+    assert split(32 << 20, 1) and not split((32 << 20) - 1, 1) and not split(96 << 20, 0)      # 128 blocks of 256 KiB
+    for m in range(9, 190):
+        for n in (64, 96, 160, 256, 480, 768, 1536):
+            p = rules.plan(2, 16, 3, m, n, 128, 96 << 20, 1)
+            if p % 10 == 2:                    # two counters a split block; the whole rounds' blocks are not split
+                left = (m + 15) // 16 * ((n // 16 + (n % 16 > 0) + 7) // 8) % 32
+                assert p == 1642 and 0 < left and 2 * 8 * left <= 1024

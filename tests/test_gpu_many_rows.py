@@ -5,10 +5,12 @@ import numpy as np
 import pytest
 
 from oracle import odb_oracle as o
+from paper_2511_21759_amd import binding as B
 from paper_2511_21759_amd import workloads as W
 from test_gpu_parity import Pair, run_prefill_case, run_step_case
 
 pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
 
 SHAPE = dict(n_layers=2, d_model=1024, n_heads=8, head_dim=128, d_ff=3072, vocab=4096, rope_base=10000.0,
              rms_eps=1e-5, mask_id=4095)
@@ -259,5 +261,48 @@ def test_lm_head_of_one_row_block_with_a_ragged_last_block(vocab):
             cache, oc = run_prefill_case(p, wl.tokens, wl.resp_off, "set-up")
             _, am, _, _ = run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "vocab %d, %d x %d" % (vocab, S, b))
             assert (am >= vocab - 24).mean() > 0.5
+    finally:
+        p.close()
+
+
+# ---- blocks of 192 and 320 rows, and a last round split over two workgroups a block, each at the smallest sizes that take it -------
+
+@pytest.mark.parametrize("d,f,rows", [
+    (256, 8192, 267),      # gate/up in 192 x 192: a row block of 75 rows behind a whole one
+    (256, 5120, 779),      # 192 x 256
+    (256, 12288, 523),     # 320 x 192
+    (256, 6144, 1291),     # 320 x 256
+    (1024, 256, 2059),     # QKV in 192 x 192: the heads' boundaries inside a wave's columns
+])
+def test_refresh_in_blocks_of_192_and_320_rows(d, f, rows):
+    p = Pair(_width(d, f))
+    try:
+        wl = W.decode_workload(p.shape, rows - 40, 40, 8, 1, 900 + d)
+        run_prefill_case(p, wl.tokens, wl.resp_off, "d %d, d_ff %d, %d rows" % (d, f, rows))
+    finally:
+        p.close()
+
+
+def test_split_last_round_repeats_and_agrees_with_whole_blocks():
+    """Gate/up of 395 rows at d 2560, d_ff 8192: 128 blocks of 256 x 256, each split over two workgroups.  The same bits whichever of the
+    two arrives last, the counters back at zero for the next launch, and the whole blocks' values up to the order of two fp32 sums (their
+    other projections run unsplit kernels, and a confidence moves by 1.3e-4 between two orders over 8 layers: four times that)."""
+    p = Pair(_width(2560, 8192, layers=2))
+    try:
+        wl = W.decode_workload(p.shape, 300, 95, 8, 1, 77)
+        tokens, cache = torch.from_numpy(wl.tokens).cuda(), p.cache(1, wl.tokens.shape[1])
+        first = [x.clone() for x in B.odb_prefill(p.model, cache, tokens, wl.resp_off)]
+        kv = B.odb_cache_read(cache, 1, 0, 0, 0, 395, 20, 128)
+        for _ in range(8):
+            again = B.odb_prefill(p.model, cache, tokens, wl.resp_off)
+            assert torch.equal(first[0], again[0]) and torch.equal(first[1], again[1])
+        assert np.array_equal(kv, B.odb_cache_read(cache, 1, 0, 0, 0, 395, 20, 128))
+        B.odb_set_option(p.model, B.OPT_KSPLIT_REDUCE, 0)
+        whole = B.odb_prefill(p.model, cache, tokens, wl.resp_off)
+        assert float((whole[0].double() - first[0].double()).norm() / whole[0].double().norm()) <= 6e-4
+        kv_whole = B.odb_cache_read(cache, 1, 0, 0, 0, 395, 20, 128)
+        # (a key is rounded to binary16: half a unit in the last place of the largest, twice as one of each side)
+        assert np.abs(kv - kv_whole).max() <= 2 * 2.0 ** -11 * np.abs(kv_whole).max()
+        B.odb_model_status(p.model)
     finally:
         p.close()
