@@ -175,6 +175,14 @@ inline RowBlock resid_block(int m_tiles, int n_tiles, int k_tiles) {
     return RowBlock{0, 0};
 }
 
+// O and down of up to 32 rows whose K is split over four workgroups: n-tiles of a block, or 0 where a workgroup has all of K (3 KiB a
+// k-tile for each of its rows and columns; the same line as for more rows above) or K cannot be split.  As many blocks as make one round:
+// down at d 1024, d_ff 3072 on 64 workgroups with all of K 10.4 us, on 256 with a quarter 7.1.
+inline int few_rows_split(int m_tiles, int n_tiles, int k_tiles) {
+    if (m_tiles > 2 || 3 * k_tiles <= 240 || k_tiles % 32 != 0 || n_tiles > kComputeUnits) return 0;
+    return n_tiles <= kComputeUnits / 4 ? 1 : n_tiles <= kComputeUnits / 2 ? 2 : 4;
+}
+
 // QKV on the slab kernel (gemm_slab.h): n-tiles per workgroup, or 0 where another kernel runs.  One row block (97 to 128 rows): three
 // while that is one round of workgroups, beyond it six, which is one round up to twice as far and half as many reads of A
 // (us at 128 rows with three and with six: d 4096 31.1 and 40.2, d 5120 68.7 and 51.1, d 8192 112.5 and 83.7, where the

@@ -102,10 +102,10 @@ static bool ksplit_fits(GemmShape sh, int nblocks, Workspace ws) {       // nblo
     return ws.arrive && nblocks * kSplitKS <= kStreamWGs && nblocks <= 1024 &&
            (size_t)kSplitKS * sh.M_tiles * sh.N_tiles * 1024 <= ws.partial_bytes;
 }
-// shapes the K-split kernel takes: up to 96 rows without a fused norm, n-blocks x KS workgroups within the chip,
+// shapes the K-split kernel takes: 33 to 96 rows without a fused norm, n-blocks x KS workgroups within the chip,
 // k-slices that the waves and the ring divide, room for the partial sums
 static bool ksplit_ok(GemmShape sh, Workspace ws) {
-    return sh.M_tiles <= 6 && sh.K_tiles % (kSplitKS * WK * kSplitPF) == 0 &&
+    return sh.M_tiles > 2 && sh.M_tiles <= 6 && sh.K_tiles % (kSplitKS * WK * kSplitPF) == 0 &&
            ksplit_fits(sh, (sh.N_tiles + kSplitNG - 1) / kSplitNG, ws);
 }
 static GemmArgs stream_args(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, int k_len, int nwg) {
@@ -125,9 +125,16 @@ static void launch_ksplit_as(const u16 *a, const u16 *w, GemmShape sh, EpiResid 
     allow_lds<gemm_stream_ksplit_kernel<MT, NG, PF, KS, RB, SPAN64>>(lds);
     gemm_stream_ksplit_kernel<MT, NG, PF, KS, RB, SPAN64><<<grid, 64 * WK, lds, s>>>(g, e, ws.partial, ws.arrive);
 }
+template <int NG>
+static void launch_ksplit_few(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, Workspace ws, hipStream_t s) {
+    const int kw = sh.K_tiles / (kSplitKS * WK);
+    if (kw % 4 == 0) launch_ksplit_as<2, NG, 4, kSplitKS>(a, w, sh, e, ws, s);
+    else if (kw % 3 == 0) launch_ksplit_as<2, NG, 3, kSplitKS>(a, w, sh, e, ws, s);
+    else if (kw % 2 == 0) launch_ksplit_as<2, NG, 2, kSplitKS>(a, w, sh, e, ws, s);
+    else launch_ksplit_as<2, NG, 1, kSplitKS>(a, w, sh, e, ws, s);
+}
 static void launch_stream_ksplit(const u16 *a, const u16 *w, GemmShape sh, EpiResid e, Workspace ws, hipStream_t s) {
-    if (sh.M_tiles <= 2) launch_ksplit_as<2, kSplitNG, kSplitPF, kSplitKS>(a, w, sh, e, ws, s);
-    else if (sh.M_tiles <= 4) launch_ksplit_as<4, kSplitNG, 4, kSplitKS>(a, w, sh, e, ws, s);
+    if (sh.M_tiles <= 4) launch_ksplit_as<4, kSplitNG, 4, kSplitKS>(a, w, sh, e, ws, s);
     else launch_ksplit_as<6, kSplitNG, 2, kSplitKS>(a, w, sh, e, ws, s);
 }
 
@@ -367,8 +374,20 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
         else if (no.span == 64) launch_ksplit_narrow<4, true>(a, w, sh, e, ws, s);
         else launch_ksplit_narrow<4>(a, w, sh, e, ws, s);
     }
+    else if (const int few = few_rows_split(sh.M_tiles, sh.N_tiles, sh.K_tiles); few && ksplit_fits(sh, sh.N_tiles / few, ws)) {
+        if (few == 1) launch_ksplit_few<1>(a, w, sh, e, ws, s);
+        else if (few == 2) launch_ksplit_few<2>(a, w, sh, e, ws, s);
+        else launch_ksplit_few<4>(a, w, sh, e, ws, s);
+    }
     else if (ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
-    else if (sh.M_tiles <= 2) launch_stream<2, 1, 8, false>(a, w, sh, NormIn{nullptr, 0, 0.f}, e, s);
+    else if (sh.M_tiles <= 2) {
+        // (as many ring stages as divide a wave's k-tiles: with one O of 32 rows at d 1024 took 5.0 us)
+        const int kw = sh.K_tiles / WK;
+        if (kw % 8 == 0) launch_stream<2, 1, 8, false>(a, w, sh, none, e, s);
+        else if (kw % 4 == 0) launch_stream<2, 1, 4, false>(a, w, sh, none, e, s);
+        else if (kw % 3 == 0) launch_stream<2, 1, 3, false>(a, w, sh, none, e, s);
+        else launch_stream<2, 1, 2, false>(a, w, sh, none, e, s);
+    }
     else if (sh.M_tiles <= 8) launch_tile(a, w, sh, none, e, ws, true, s);
     else {
         // (128-row blocks only for the O projection: at 1024 rows of the 8B shape 256 blocks of 128 x 128 take 47.7 us against 50.4 for

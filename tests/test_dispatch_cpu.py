@@ -23,6 +23,7 @@ int plan(int epi, int now_mbt, int now_wn, int m, int n, int k, size_t room, int
     const BigPlan p = big_plan((TileEpilogue)epi, BigChoice{now_mbt, now_wn}, m, n, k, room, may != 0);
     return p.wn ? p.mbt * 100 + p.wn * 10 + p.ks : 0;
 }
+int few_split(int m, int n, int k) { return few_rows_split(m, n, k); }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
 """
@@ -276,3 +277,13 @@ def test_plans_exchange_only_where_there_is_room_for_it(rules):
             if p % 10 == 2:                    # two counters a split block; the whole rounds' blocks are not split
                 left = (m + 15) // 16 * ((n // 16 + (n % 16 > 0) + 7) // 8) % 32
                 assert p == 1642 and 0 < left and 2 * 8 * left <= 1024
+
+
+@pytest.mark.parametrize("m,n,k,blocks_of", [
+    (2, 64, 96, 1), (1, 64, 96, 1), (2, 128, 256, 2), (2, 256, 128, 4), (2, 256, 384, 4),      # O and down, a round of 256 workgroups at most
+    (2, 64, 32, 0), (2, 64, 80, 0),        # a short K stays whole
+    (2, 128, 176, 0), (2, 64, 88, 0),      # four slices of eight waves do not divide it
+    (2, 272, 384, 0), (3, 64, 96, 0),      # too many blocks; more than 32 rows have rules of their own
+])
+def test_few_rows_split_k_where_it_fits(rules, m, n, k, blocks_of):
+    assert rules.few_split(m, n, k) == blocks_of

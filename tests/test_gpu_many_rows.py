@@ -57,6 +57,11 @@ def _width(d, f, layers=1):
     (1024, 3072, [(3, 16), (4, 16), (5, 16), (7, 16), (4, 32)]),   # K split over 64-row blocks, one and two n-tiles per group
     (1024, 5120, [(1, 16), (5, 16), (8, 16)]),                     # gate/up in groups of three
     (2048, 2048, [(3, 16), (7, 16)]),                              # K split with two and four n-tiles per block
+    (1024, 3072, [(1, 9), (2, 16)]),                               # up to 32 rows: down split over K, one n-tile and a ring of three
+    (512, 5120, [(1, 16), (1, 32)]),                               # a ring of one
+    (2048, 4096, [(2, 16)]),                                       # two n-tiles, a ring of four
+    (2304, 2816, [(2, 16)]),                                       # K that four slices do not divide: all of it, a ring of one (O: of three)
+    (2304, 4096, [(2, 16)]),                                       # four n-tiles
     (1536, 512, [(7, 16), (4, 32)]),                               # QKV from 97 rows on: blocks of 64 rows and three n-tiles
     (2560, 512, [(7, 16), (4, 32)]),                               # and through LDS
     (2816, 6400, [(7, 16), (4, 32), (9, 16), (16, 16)]),           # all rows through LDS; from 9 row tiles two row blocks for QKV
