@@ -8,6 +8,7 @@
 #include <mutex>
 #include <new>
 
+#include "choose.h"
 #include "model.h"
 
 using namespace odb;
@@ -63,7 +64,8 @@ struct Plan {
 };
 
 // part_bytes: room for K-split partial sums (the GEMM launchers split K only as far as it allows)
-Plan make_plan(const odb_config &c, int rows_pad, int fresh_rows, int lm_rows_pad, bool need_stats, size_t extra_bytes,
+// q_rows: rows of Q, those of the units (rows_pad, or more where the rows are dense)
+Plan make_plan(const odb_config &c, int rows_pad, int q_rows, int fresh_rows, int lm_rows_pad, bool need_stats, size_t extra_bytes,
                size_t part_bytes) {
     Plan p;
     if (part_bytes == kPartialByRows) {
@@ -75,8 +77,8 @@ Plan make_plan(const odb_config &c, int rows_pad, int fresh_rows, int lm_rows_pa
     size_t d = c.d_model;
     p.h = take((size_t)rows_pad * d * 4);
     p.xa = take((size_t)rows_pad * d * 2);
-    p.q = take((size_t)rows_pad * d * 2);
     p.kf = take((size_t)fresh_rows * d * 2);
+    p.q = take((size_t)q_rows * d * 2);         // (q, vf and ao one behind the other: cleared together)
     p.vf = take((size_t)fresh_rows * d * 2);
     p.ao = take((size_t)rows_pad * d * 2);
     p.act = take((size_t)rows_pad * c.d_ff * 2);
@@ -196,7 +198,9 @@ struct ProfScope {
 // per-tile sums of squares, the consuming GEMM turns them into row scales (both calls run this way).
 // Otherwise a separate RMSNorm kernel writes the GEMM input.
 struct StackIO {
-    RowMap rm;
+    RowMap rm;          // the rows that the projections work on
+    RowMap units;       // and the units that attention works on: rm, or with padded rows of their own (dense: rm is then one unit)
+    bool dense;
     int pos_off;
     bool to_cache;      // prefill: K/V are written into the cache
     int blk_lo, blk_hi, fresh, units_per_seq;
@@ -224,12 +228,13 @@ int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackI
         *vf = (u16 *)(base + pl.vf), *ao = (u16 *)(base + pl.ao), *act = (u16 *)(base + pl.act);
     const int d = cfg.d_model, H = cfg.n_heads, dh = cfg.head_dim, F = cfg.d_ff;
     const SharedMap *sm = io.shared;
-    const int rows_pad = sm ? sm->rows() : io.rm.units * io.rm.rpu_pad, mt = rows_pad / 16, tpu = io.rm.rpu_pad / 16;
+    const int rows_pad = sm ? sm->rows() : io.rm.units * io.rm.rpu_pad, mt = rows_pad / 16;
+    const int tpu = io.units.rpu_pad / 16, unit_mt = io.dense ? io.units.units * tpu : mt;
     // decoded-share step: fresh K/V of the batch block_0 units (bp32 rows each) first, then of the pooled speculative units (mp32 rows each)
     const int mp32 = sm ? ru(sm->mp, 32) : 0;
     const size_t spec_off = sm ? (size_t)sm->batch * H * ru(sm->bp, 32) * dh : 0;
     const size_t seq_elems = (size_t)H * c.lmax32 * dh;
-    const int fresh32 = ru(io.rm.rpu_pad, 32);
+    const int fresh32 = ru(io.units.rpu_pad, 32);
     const Workspace ws = workspace(m, base, pl);
     unsigned *status = m.counters;
     const NormIn ni = io.fused_norm ? norm_in(m, base, pl, mt) : NormIn{nullptr, 0, 0.f};
@@ -244,6 +249,9 @@ int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackI
         qo.q = q;
         qo.rope = c.rope;
         qo.status = status;
+        qo.q_mt = unit_mt;
+        qo.dense_rows = io.dense ? io.rm.valid : 0;
+        qo.valid = io.units.valid;
         qo.tiles_per_unit = tpu; qo.pos_off = io.pos_off; qo.H = H; qo.dh = dh; qo.d = d;
         u16 *kc = c.k + (size_t)l * c.layer_elems, *vc = c.v + (size_t)l * c.layer_elems;
         if (io.to_cache) {
@@ -274,7 +282,8 @@ int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackI
         a.kf_unit_stride = qo.k_unit_stride; a.kf_head_stride = qo.k_head_stride;
         a.vf_unit_stride = qo.v_unit_stride; a.vf_head_stride = qo.v_head_stride;
         a.out = ao;
-        a.H = H; a.dh = dh; a.mt_total = mt; a.tiles_per_unit = tpu; a.units = io.rm.units;
+        a.H = H; a.dh = dh; a.mt_total = unit_mt; a.tiles_per_unit = tpu; a.units = io.units.units;
+        a.out_mt = mt; a.valid = io.dense ? io.units.valid : 0;
         a.units_per_seq = io.units_per_seq; a.L = c.length; a.blk_lo = io.blk_lo; a.blk_hi = io.blk_hi;
         a.fresh = io.fresh;
         if (sm) {
@@ -342,6 +351,7 @@ int run_head(Model &m, char *base, const Plan &pl, RowMap rm, int skip, bool fus
             ProfScope ps(m, ODB_K_GEMM_LM_HEAD, s);
             launch_gemm_lmstats(xa, m.w[PK_LM], sh, ni, stats, ws, s);
         }
+        if (fused_norm && rm.valid != rpu_out) rpu_pad = rpu_out;          // dense rows: the drafts follow each other
         launch_lm_finish(stats, lm_stats_parts(cfg.vocab / 16, lm_mt), rows, rpu_out, rpu_pad, tokens, cfg.mask_id, tau, conf, argmax, unmask,
                          s);
     }
@@ -362,13 +372,13 @@ int prefill_impl(odb_model *mh, odb_cache *ch, const int32_t *tokens, int L, int
     HIP_TRY(hipSetDevice(m.device));
     const int lp = ru(L, 16), rows_pad = c.batch * lp, lm_rows = c.batch * (L - resp_off);
     Plan pl;
-    int rc = plan_scratch(m, [&](size_t room) { return make_plan(m.cfg, rows_pad, 0, ru(lm_rows, 16), logits == nullptr, 0, room); }, pl, s);
+    int rc = plan_scratch(m, [&](size_t room) { return make_plan(m.cfg, rows_pad, rows_pad, 0, ru(lm_rows, 16), logits == nullptr, 0, room); }, pl, s);
     if (rc) return rc;
     RowMap rm{c.batch, lp, L};
     c.length = L;
     char *base = (char *)m.scratch;
     launch_embed(m, tokens, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), nullptr, 0, s);
-    StackIO io{rm, 0, true, 0, 0, 0, 1, true};
+    StackIO io{rm, rm, false, 0, true, 0, 0, 0, 1, true};
     rc = run_stack(m, c, base, pl, io, s);
     if (rc) return rc;
     return run_head(m, base, pl, rm, resp_off, false, nullptr, 64, 0.f, conf, argmax, nullptr, logits, s);
@@ -402,32 +412,41 @@ int step_impl(odb_model *mh, const odb_cache *ch, const int32_t *drafts, int blo
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(m.device));
     const odb_config &cfg = m.cfg;
-    const int bp = ru(b, 16), bp32 = ru(b, 32), units = c.batch * S, rows_pad = units * bp;
+    const int bp = ru(b, 16), bp32 = ru(b, 32), units = c.batch * S, unit_rows = units * bp, fresh_rows = units * bp32;
     Plan pl;
     char *base;
     // What the call needs beside K-split partial sums decides whether the fixed area holds it.  A call that it holds gets the same
     // room for partial sums there as in the model's own scratch: their number of slices, and with it the order of the
     // additions, follows from that room, and both entry points promise the same results.
-    const size_t need = make_plan(cfg, rows_pad, units * bp32, rows_pad, true, 0, 0).total + (1u << 20) - lm_stats_excess(cfg, rows_pad);
+    const size_t padded = make_plan(cfg, unit_rows, unit_rows, fresh_rows, unit_rows, true, 0, 0).total;
+    const size_t need = padded + (1u << 20) - lm_stats_excess(cfg, unit_rows);
     const size_t part = need <= kStaticScratchBytes ? kPartialBytes : kPartialByRows;
+    // Drafts whose rows do not fill their tiles are packed one behind the other for the projections, norms and the LM head; attention
+    // keeps a draft's rows in tiles of its own.  (The buffers must not outgrow those that decide about the fixed area.)
+    const int dense_rows = ru(units * b, 16);
+    // (row numbers are divided by a multiplication that holds below 2^16)
+    const bool dense = unit_rows <= 65536 && dense_rows_pay(dense_rows / 16, unit_rows / 16) && make_plan(cfg, dense_rows, unit_rows, fresh_rows, dense_rows, true, 0, 0).total <= padded;
+    const int rows_pad = dense ? dense_rows : unit_rows;
     if (scratch_base) {
         if (need > kStaticScratchBytes)
             return fail(ODB_E_UNSUPPORTED, "block_step_static: %d rows of this model need %zu bytes of scratch, the fixed "
-                        "area holds %zu", rows_pad, need, kStaticScratchBytes);
-        pl = make_plan(cfg, rows_pad, units * bp32, rows_pad, true, 0, part);
+                        "area holds %zu", unit_rows, need, kStaticScratchBytes);
+        pl = make_plan(cfg, rows_pad, unit_rows, fresh_rows, rows_pad, true, 0, part);
         base = scratch_base;
     } else {
         int rc = plan_scratch(m, [&](size_t room) {
-            return make_plan(cfg, rows_pad, units * bp32, rows_pad, logits == nullptr, 0, part == kPartialBytes ? part : room);
+            return make_plan(cfg, rows_pad, unit_rows, fresh_rows, rows_pad, logits == nullptr, 0, part == kPartialBytes ? part : room);
         }, pl, s);
         if (rc) return rc;
         base = (char *)m.scratch;
     }
-    RowMap rm{units, bp, b};
-    // (slots of padded keys must hold finite values: they meet zero probabilities in the P*V product)
-    launch_embed(m, drafts, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), base + pl.vf,
-                 b % 32 ? (size_t)units * bp32 * cfg.d_model * 2 : 0, s);
-    StackIO io{rm, block_off, false, block_off, block_off + b, b, S, true};
+    const RowMap um{units, bp, b}, rm = dense ? RowMap{1, dense_rows, units * b} : um;
+    // Slots of padded keys must hold finite values: they meet zero probabilities in the P*V product.  Dense rows leave the padded rows
+    // of Q alone, which must not differ from call to call (a raised reference in one row is one in its tile), and the last rows of the
+    // attention's output, which the projections work on and report if they are out of range.
+    const size_t from = dense ? pl.q : pl.vf, to = dense ? pl.ao + (size_t)rows_pad * cfg.d_model * 2 : pl.vf + (size_t)fresh_rows * cfg.d_model * 2;
+    launch_embed(m, drafts, rm, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16), base + from, b % 32 ? to - from : 0, s);
+    StackIO io{rm, um, dense, block_off, false, block_off, block_off + b, b, S, true};
     int rc = run_stack(m, c, base, pl, io, s);
     if (rc) return rc;
     return run_head(m, base, pl, rm, 0, true, drafts, b, tau, conf, argmax, unmask, logits, s);
@@ -698,7 +717,7 @@ static int step_shared_impl(odb_model *mh, const odb_cache *ch, const int32_t *d
                           align_up((size_t)c.batch * 8, 256);
     Plan pl;
     int rc = plan_scratch(m, [&](size_t room) {
-        return make_plan(cfg, rows_pad, fresh_rows, rows_pad, logits == nullptr, tables, room);
+        return make_plan(cfg, rows_pad, rows_pad, fresh_rows, rows_pad, logits == nullptr, tables, room);
     }, pl, s);
     if (rc) return rc;
     char *base = (char *)m.scratch, *t = base + pl.extra;
@@ -713,7 +732,7 @@ static int step_shared_impl(odb_model *mh, const odb_cache *ch, const int32_t *d
     launch_embed(m, sm.rowtok, RowMap{rows_pad, 1, 1}, (float *)(base + pl.h), norm_out(m, base, pl, m.g1, rows_pad / 16),
                  base + pl.vf, (size_t)fresh_rows * cfg.d_model * 2, s);
     RowMap rm{c.batch, sm.bp, b};
-    StackIO io{rm, block_off, false, block_off, block_off + b, b, 1, true, &sm};
+    StackIO io{rm, rm, false, block_off, false, block_off, block_off + b, b, 1, true, &sm};
     rc = run_stack(m, c, base, pl, io, s);
     if (rc) return rc;
     // final norm (fused) + LM head on all rows, then the per-unit finish

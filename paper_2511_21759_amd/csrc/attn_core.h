@@ -20,11 +20,19 @@
 
 namespace odb {
 
+// (mt: the row tile, tile tu of its unit)
 template <int DH>
-__device__ inline void store_out_tile(const AttnArgs &a, int mt, int hd, int dt16, int lane, f32x4 v) {
-    const int mi = lane & 15, g = lane >> 4;
+__device__ inline void store_out_tile(const AttnArgs &a, int mt, int unit, int tu, int hd, int dt16, int lane, f32x4 v) {
+    int mi = lane & 15;
+    const int g = lane >> 4;
     const int kt = hd * (DH / 32) + (dt16 >> 1);
-    u16 *dst = a.out + ((size_t)kt * a.mt_total + mt) * kTileElems + (((dt16 & 1) * 2 + (g >> 1)) * 16 + mi) * 8 +
+    if (a.valid > 0) {
+        const int i = tu * 16 + mi, row = unit * a.valid + i;
+        if (i >= a.valid) return;
+        mt = row >> 4;
+        mi = row & 15;
+    }
+    u16 *dst = a.out + ((size_t)kt * a.out_mt + mt) * kTileElems + (((dt16 & 1) * 2 + (g >> 1)) * 16 + mi) * 8 +
                (g & 1) * 4;
     uint2 p;
     p.x = pack2(v[0], v[1]);
@@ -415,7 +423,7 @@ __device__ __forceinline__ void attn_wg(const AttnArgs &a, float sc, int item, i
                 f32x4 v = scaled(s_o[0][dt][lane], f[0]);
 #pragma unroll
                 for (int x = 1; x < NW; x++) v += scaled(s_o[x][dt][lane], f[x]);
-                store_out_tile<DH>(a, mt_base + tu0 + t, hd, dv0 + dt, lane, v * inv);
+                store_out_tile<DH>(a, mt_base + tu0 + t, unit, tu0 + t, hd, dv0 + dt, lane, v * inv);
             }
         }
     }

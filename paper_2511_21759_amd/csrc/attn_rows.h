@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(AttnArgs a, float sc
             const float inv = 1.0f / l;
             const int mt = seq * tiles_per_seq + ts0 + t;
 #pragma unroll
-            for (int dt = 0; dt < DT16; dt++) store_out_tile<DH>(a, mt, hd, dt, lane, o[t][dt] * inv);
+            for (int dt = 0; dt < DT16; dt++) store_out_tile<DH>(a, mt, unit, ts0 + t - (unit - seq * a.units_per_seq) * a.tiles_per_unit, hd, dt, lane, o[t][dt] * inv);
         }
     }
 }

@@ -183,6 +183,17 @@ inline int few_rows_split(int m_tiles, int n_tiles, int k_tiles) {
     return n_tiles <= kComputeUnits / 4 ? 1 : n_tiles <= kComputeUnits / 2 ? 2 : 4;
 }
 
+// Whether a step packs its drafts' rows densely (api.hip): row tiles packed, and with every draft in tiles of its own.  Two tiles fewer at
+// least, as the kernels of few rows take two at a time, and enough of them to pay for the places looked up row by row and for
+// V written key by key.
+// Microseconds a step, padded and packed: 8B shape, 8 layers, 4 -> 2 tiles 1015 and 882, 8 -> 6 1250 and 1164, 10 -> 8 1642 and 1277,
+// 16 -> 13 1718 and 1677, 32 -> 14 2735 and 1850; 1k-wide model 8 -> 6 299 and 298, 12 -> 10 355 and 328; before this line 10 -> 9
+// 1578 and 1562 (1k 322 and 323), 128 -> 120 7738 and 7723.
+inline bool dense_rows_pay(int dense, int padded) {
+    if ((dense + 1) / 2 >= (padded + 1) / 2) return false;
+    return padded > 8 ? dense <= 8 || 20 * dense <= 17 * padded : 4 * dense <= 3 * padded;
+}
+
 // QKV on the slab kernel (gemm_slab.h): n-tiles per workgroup, or 0 where another kernel runs.  One row block (97 to 128 rows): three
 // while that is one round of workgroups, beyond it six, which is one round up to twice as far and half as many reads of A
 // (us at 128 rows with three and with six: d 4096 31.1 and 40.2, d 5120 68.7 and 51.1, d 8192 112.5 and 83.7, where the

@@ -231,6 +231,7 @@ static int tile_columns(int m_tiles) { return m_tiles > 8 ? 16 : 8; }
 
 template <class Epi> constexpr TileEpilogue tile_epilogue_of = TileEpilogue::resid;
 template <> constexpr TileEpilogue tile_epilogue_of<EpiQKV> = TileEpilogue::qkv;
+template <> constexpr TileEpilogue tile_epilogue_of<EpiQKVDense> = TileEpilogue::qkv;
 template <> constexpr TileEpilogue tile_epilogue_of<EpiSwiGLU> = TileEpilogue::swiglu;
 
 template <class Epi>
@@ -319,8 +320,8 @@ static void launch_slab(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi
     gemm_slab_kernel<NTB, Epi, NTW><<<dim3((g.NT + NTB - 1) / NTB, (g.MT_total + 7) / 8), 512, slab_smem_bytes(NTB), s>>>(g, e);
 }
 
-void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOut out, Workspace ws, hipStream_t s) {
-    EpiQKV e{out, sh.M_tiles};
+template <class Epi>
+static void launch_qkv_as(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, Epi e, Workspace ws, hipStream_t s) {
     // (Up to 96 rows a ring of ONE stage is the fastest since the weight tiles are loaded non-temporally - 2048 waves
     // with one group of tiles each in flight keep the HBM stream full, and fewer outstanding weight loads per
     // compute unit leave the activation loads less to queue behind: 1.9 % per step at 32 rows for this and the
@@ -342,6 +343,10 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
     else if (slab == 6 && (sh.M_tiles <= 8 || sh.M_tiles >= 12)) launch_slab<6, true>(xa, w, sh, ni, e, s);
     else if (slab == 6) launch_slab<6, false>(xa, w, sh, ni, e, s);
     else launch_big_or_tile(big_choice(sh), xa, w, sh, ni, e, ws, s);
+}
+void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOut out, Workspace ws, hipStream_t s) {
+    if (out.dense_rows > 0) launch_qkv_as(xa, w, sh, ni, EpiQKVDense{out}, ws, s);
+    else launch_qkv_as(xa, w, sh, ni, EpiQKV{out}, ws, s);
 }
 void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int ldh, NormOut no, Workspace ws,
                        hipStream_t s) {

@@ -103,7 +103,7 @@ __device__ __forceinline__ void big_epilogue(const EpiQKV &e, f32x4 (&acc)[MW][W
                 const f32x4 c = acc[m][j] * rs, cs = r.cs[j];
                 const float y0 = c[0] * cs[0] - c[1] * cs[1], y1 = c[1] * cs[0] + c[0] * cs[1];
                 const float y2 = c[2] * cs[2] - c[3] * cs[3], y3 = c[3] * cs[2] + c[2] * cs[3];
-                u16 *dst = (sec[j] == 0 ? o.q + ((size_t)hd[j] * e.mt_total + mt) * (o.dh / 32) * kTileElems : kdst + hd[j] * khs) +
+                u16 *dst = (sec[j] == 0 ? o.q + ((size_t)hd[j] * o.q_mt + mt) * (o.dh / 32) * kTileElems : kdst + hd[j] * khs) +
                            (p0[j] >> 5) * kTileElems;
                 const int kk = (p0[j] & 16) + 4 * gq;
                 bad |= out_of_f16(y0, y1, y2, y3);
@@ -113,6 +113,74 @@ __device__ __forceinline__ void big_epilogue(const EpiQKV &e, f32x4 (&acc)[MW][W
                 const float y0 = base[0] * rs4[0], y1 = base[4] * rs4[1], y2 = base[8] * rs4[2], y3 = base[12] * rs4[3];
                 bad |= out_of_f16(y0, y1, y2, y3);
                 st_f16x4(vdst + hd[j] * vhs + (p0[j] >> 4) * kTileElems, y0, y1, y2, y3);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // reads before the next row's stores
+    }
+    if (bad && o.status) atomicOr(o.status, kStatusSaturated);
+}
+
+// The same for dense rows (QkvOut); what depends on the row alone is found once per row of tiles.
+template <int MW, int WT>
+__device__ __forceinline__ void big_epilogue(const EpiQKVDense &e, f32x4 (&acc)[MW][WT], int mtw, int ntw, const BigArgs &g,
+                                             const float *rstd, char *scr, int lane) {
+    const QkvOut &o = e.o;
+    const int mi = lane & 15, gq = lane >> 4;
+    int sec[WT], hd[WT], p0[WT];
+#pragma unroll
+    for (int j = 0; j < WT; j++) {
+        const int nt = ntw + j < g.NT ? ntw + j : g.NT - 1;
+        sec[j] = o.fd_d.quot(nt);
+        const int rt = nt - sec[j] * (o.d >> 4);
+        hd[j] = o.fd_dh.quot(rt);
+        p0[j] = (rt - hd[j] * (o.dh >> 4)) * 16;
+    }
+    f32x4 (*tr)[64] = reinterpret_cast<f32x4 (*)[64]>(scr);
+    bool bad = false;
+#pragma unroll
+    for (int m = 0; m < MW; m++) {
+        const int mt = mtw + m < g.MT_total ? mtw + m : g.MT_total - 1;
+        const bool live = mtw + m < g.MT_total;
+        const int row = mt * 16 + mi, unit = o.fd_valid.quot(row), i = row - unit * o.valid;
+        const bool in = live && row < o.dense_rows;
+        f32x4 cs[WT];
+#pragma unroll
+        for (int j = 0; j < WT; j++) {
+            cs[j] = sec[j] < 2 ? *reinterpret_cast<const f32x4 *>(o.rope + (size_t)(o.pos_off + i) * o.dh + p0[j] + 4 * gq) : f32x4{0.f, 0.f, 0.f, 0.f};
+            if (sec[j] == 2) tr[j][lane] = acc[m][j];
+        }
+        u16 *qd = o.q + ((size_t)unit * o.tiles_per_unit + (i >> 4)) * (o.dh / 32) * kTileElems + (i & 15) * 8;
+        u16 *kd = o.k + unit * o.k_unit_stride + (size_t)(i >> 4) * (o.dh / 32) * kTileElems + (i & 15) * 8;
+        u16 *vd[4];
+        bool vin[4];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int vrow = mt * 16 + 4 * gq + r, vu = o.fd_valid.quot(vrow), vi = vrow - vu * o.valid;
+            vin[r] = live && vrow < o.dense_rows;
+            vd[r] = o.v + vu * o.v_unit_stride + (size_t)(vi >> 5) * (o.dh / 16) * kTileElems + ((vi & 15) >> 2) * 128 + mi * 8 + 4 * ((vi >> 4) & 1) + (vi & 3);
+        }
+        const float rs = rstd[m * 16 + mi];
+        const f32x4 rs4 = *reinterpret_cast<const f32x4 *>(rstd + m * 16 + 4 * gq);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // stores before the transposed reads
+#pragma unroll
+        for (int j = 0; j < WT; j++) {
+            if (ntw + j >= g.NT) break;
+            if (sec[j] < 2) {
+                const f32x4 c = acc[m][j] * rs;
+                const float y0 = c[0] * cs[j][0] - c[1] * cs[j][1], y1 = c[1] * cs[j][0] + c[0] * cs[j][1];
+                const float y2 = c[2] * cs[j][2] - c[3] * cs[j][3], y3 = c[3] * cs[j][2] + c[2] * cs[j][3];
+                const int kk = (p0[j] & 16) + 4 * gq;
+                bad |= live && out_of_f16(y0, y1, y2, y3);
+                u16 *dst = (sec[j] == 0 ? qd + (size_t)hd[j] * o.q_mt * (o.dh / 32) * kTileElems : kd + hd[j] * o.k_head_stride) +
+                           (p0[j] >> 5) * kTileElems + (kk >> 3) * 128 + (kk & 7);
+                if (in) st_f16x4(dst, y0, y1, y2, y3);
+            } else {
+                const float *base = reinterpret_cast<const float *>(&tr[j][0]) + ((mi >> 2) * 16 + 4 * gq) * 4 + (mi & 3);
+                const f32x4 y = f32x4{base[0], base[4], base[8], base[12]} * rs4;
+                bad |= live && out_of_f16(y[0], y[1], y[2], y[3]);
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                    if (vin[r]) vd[r][hd[j] * o.v_head_stride + (p0[j] >> 4) * kTileElems] = f2h(y[r]);
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // reads before the next row's stores

@@ -277,7 +277,6 @@ __device__ __forceinline__ T pick(bool c, T a, T b) { return c ? a : b; }
 struct QkvPre { f32x4 cs; u16 *dst; bool rotate; };
 struct EpiQKV {
     QkvOut o;
-    int mt_total;
     __device__ bool transposed(int nt) const { return nt * 16 >= 2 * o.d; }
     __device__ void finish(int, int, int, int) const {}
     // where a tile goes, and the (cos, sin) of the lane's two channel pairs: requested before the sums are there
@@ -300,7 +299,7 @@ struct EpiQKV {
             const int pos = o.rowpos ? o.rowpos[mt * 16 + mi] : o.pos_off + tu * 16 + mi;
             p.cs = *reinterpret_cast<const f32x4 *>(o.rope + (size_t)pos * o.dh + p0 + 4 * g);
             const int kk = (p0 & 16) + 4 * g;                 // k-element of the lane's first channel inside the 32-wide tile
-            p.dst = (sec == 0 ? o.q + (((size_t)hd * mt_total + mt) * (o.dh / 32) + p0 / 32) * kTileElems
+            p.dst = (sec == 0 ? o.q + (((size_t)hd * o.q_mt + mt) * (o.dh / 32) + p0 / 32) * kTileElems
                               : kdst + hd * khs + ((size_t)tu * (o.dh / 32) + p0 / 32) * kTileElems) + ((kk >> 3) * 16 + mi) * 8 + (kk & 7);
         } else {
             // V^T tile: row = channel, the 32 keys of a tile sit in k-slot 8*g + 4*half + r
@@ -320,6 +319,53 @@ struct EpiQKV {
 };
 __device__ __forceinline__ QkvPre epi_preload(const EpiQKV &e, int mt, int nt, int lane) { return e.preload(mt, nt, lane); }
 __device__ __forceinline__ void epi_apply(EpiQKV &e, int, int, f32x4 c, int, int, const QkvPre &pre) { e.apply(c, pre); }
+
+// The same for dense rows (QkvOut), as kernels of their own: the index arithmetic would cost the others registers.  A lane's row of
+// Q and K has a unit of its own, and the four rows of V that a lane holds may lie in two units, so they are stored one by one.
+struct EpiQKVDense {
+    QkvOut o;
+    __device__ bool transposed(int nt) const { return nt * 16 >= 2 * o.d; }
+    __device__ void finish(int, int, int, int) const {}
+    struct Col { int sec, hd, p0; };           // Q, K or V, head, first physical channel of an n-tile
+    __device__ Col column(int nt) const {
+        const int sec = o.fd_d.quot(nt), rt = nt - sec * (o.d >> 4), hd = o.fd_dh.quot(rt);
+        return Col{sec, hd, (rt - hd * (o.dh >> 4)) * 16};
+    }
+    // the (cos, sin) of the lane's two channel pairs: requested before the sums are there
+    __device__ f32x4 preload(int mt, int nt, int lane) const {
+        asm volatile("" : "+v"(lane));          // (the rows' places are found where they are used: kept over the k-loop they spill)
+        const Col n = column(nt);
+        if (n.sec == 2) return f32x4{1.f, 0.f, 1.f, 0.f};
+        const int row = mt * 16 + (lane & 15), i = row - o.fd_valid.quot(row) * o.valid;
+        return *reinterpret_cast<const f32x4 *>(o.rope + (size_t)(o.pos_off + i) * o.dh + n.p0 + 4 * (lane >> 4));
+    }
+    __device__ void apply(int mt, int nt, f32x4 c, int lane, f32x4 cs) const {
+        asm volatile("" : "+v"(lane));
+        const Col n = column(nt);
+        const int mi = lane & 15, g = lane >> 4;
+        if (n.sec < 2) {
+            c = f32x4{c[0] * cs[0] - c[1] * cs[1], c[1] * cs[0] + c[0] * cs[1], c[2] * cs[2] - c[3] * cs[3], c[3] * cs[2] + c[2] * cs[3]};
+            note_saturation(o.status, c[0], c[1], c[2], c[3]);
+            const int row = mt * 16 + mi, unit = o.fd_valid.quot(row), i = row - unit * o.valid, kk = (n.p0 & 16) + 4 * g;
+            u16 *base = n.sec == 0 ? o.q + ((size_t)n.hd * o.q_mt + unit * o.tiles_per_unit) * (o.dh / 32) * kTileElems
+                                   : o.k + unit * o.k_unit_stride + n.hd * o.k_head_stride;
+            if (row < o.dense_rows)
+                st_f16x4(base + ((size_t)(i >> 4) * (o.dh / 32) + n.p0 / 32) * kTileElems + ((kk >> 3) * 16 + (i & 15)) * 8 + (kk & 7), c[0], c[1], c[2], c[3]);
+        } else {
+            note_saturation(o.status, c[0], c[1], c[2], c[3]);
+            u16 *base = o.v + n.hd * o.v_head_stride + (n.p0 / 16) * kTileElems + mi * 8;
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int row = mt * 16 + 4 * g + r, unit = o.fd_valid.quot(row), i = row - unit * o.valid;
+                if (row < o.dense_rows)
+                    base[unit * o.v_unit_stride + (size_t)(i >> 5) * (o.dh / 16) * kTileElems + ((i & 15) >> 2) * 128 + 4 * ((i >> 4) & 1) + (i & 3)] = f2h(c[r]);
+            }
+        }
+    }
+    __device__ void operator()(int mt, int nt, f32x4 c, int lane, int) const { apply(mt, nt, c, lane, preload(mt, nt, lane)); }
+};
+__device__ __forceinline__ f32x4 epi_preload(const EpiQKVDense &e, int mt, int nt, int lane) { return e.preload(mt, nt, lane); }
+__device__ __forceinline__ void epi_apply(EpiQKVDense &e, int mt, int nt, f32x4 c, int lane, int, f32x4 pre) { e.apply(mt, nt, c, lane, pre); }
 
 // h += C.  With a NormOut it also prepares the next RMSNorm: hb = binary16(h * gain) in the
 // operand layout and the sum of squares of this tile's 16 columns per row.

@@ -138,14 +138,20 @@ struct FastDiv {
 };
 
 struct QkvOut {
-    u16 *q;                    // [H][mt_total][dh/32][512]
+    u16 *q;                    // [H][q_mt][dh/32][512]
     u16 *k; size_t k_unit_stride, k_head_stride;   // tiles [pos/16][dh/32]
     u16 *v; size_t v_unit_stride, v_head_stride;   // tiles [pos/32][dh/16], keys permuted inside
     const float *rope;         // (cos,sin) table
     unsigned *status;          // the model's status word (saturation of a binary16 conversion), may be nullptr
     int tiles_per_unit, pos_off, H, dh, d;
+    int q_mt;                  // row tiles of q: those of the units
+    // Dense rows (dense_rows > 0; the GEMM then has fewer row tiles than the units): row r is row r % valid of unit r / valid, and goes
+    // to that unit's place in Q, K and V; rows from dense_rows on are padding and go nowhere.
+    int dense_rows, valid;
+    FastDiv fd_valid;
     FastDiv fd_d, fd_dh, fd_tpu, fd_tpu_b;     // by d / 16, dh / 16, tiles_per_unit, tiles_per_unit_b: set_divisors()
     void set_divisors() {
+        fd_valid = FastDiv::make(valid);
         fd_d = FastDiv::make(d / 16); fd_dh = FastDiv::make(dh / 16);
         fd_tpu = FastDiv::make(tiles_per_unit); fd_tpu_b = FastDiv::make(tiles_per_unit_b);
     }
@@ -179,8 +185,10 @@ struct AttnArgs {
     size_t kc_seq_stride, kc_head_stride, vc_seq_stride, vc_head_stride;
     const u16 *kf, *vf;        // fresh K/V of the units (step only)
     size_t kf_unit_stride, kf_head_stride, vf_unit_stride, vf_head_stride;
-    u16 *out;                  // [d/32][mt_total][512]
+    u16 *out;                  // [d/32][out_mt][512]
     int H, dh, mt_total, tiles_per_unit, units, units_per_seq;
+    // row tiles of out; valid > 0: its rows are dense, row i < valid of a unit is row unit * valid + i (see QkvOut)
+    int out_mt, valid;
     int L;                     // cached length
     int blk_lo, blk_hi;        // cached keys in [blk_lo, blk_hi) are ignored
     int fresh;                 // number of fresh keys per unit (0 in the prefill)

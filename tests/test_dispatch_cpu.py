@@ -23,6 +23,7 @@ int plan(int epi, int now_mbt, int now_wn, int m, int n, int k, size_t room, int
     const BigPlan p = big_plan((TileEpilogue)epi, BigChoice{now_mbt, now_wn}, m, n, k, room, may != 0);
     return p.wn ? p.mbt * 100 + p.wn * 10 + p.ks : 0;
 }
+int packed(int dense, int padded) { return dense_rows_pay(dense, padded); }
 int few_split(int m, int n, int k) { return few_rows_split(m, n, k); }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
@@ -287,3 +288,11 @@ def test_plans_exchange_only_where_there_is_room_for_it(rules):
 ])
 def test_few_rows_split_k_where_it_fits(rules, m, n, k, blocks_of):
     assert rules.few_split(m, n, k) == blocks_of
+
+
+@pytest.mark.parametrize("dense,padded,pays", [
+    (2, 4, 1), (1, 4, 1), (5, 8, 1), (6, 8, 1), (8, 10, 1), (10, 12, 1), (13, 16, 1), (14, 32, 1), (80, 96, 1),
+    (2, 2, 0), (1, 2, 0), (3, 4, 0), (7, 8, 0), (9, 10, 0), (120, 128, 0),
+])
+def test_drafts_are_packed_where_it_pays(rules, dense, padded, pays):
+    assert rules.packed(dense, padded) == pays

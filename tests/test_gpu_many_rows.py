@@ -311,3 +311,50 @@ def test_split_last_round_repeats_and_agrees_with_whole_blocks():
         B.odb_model_status(p.model)
     finally:
         p.close()
+
+
+# ---- drafts packed densely -------------------------------------------------------------------------------------------------------
+
+@pytest.mark.parametrize("d,dh,f,batch,b,S", [
+    (1024, 128, 512, 1, 7, 4),       # two row tiles; units that begin inside a tile, keys of two drafts in a lane's four rows
+    (256, 64, 512, 3, 5, 4),         # heads of 64, four row tiles
+    (1024, 128, 512, 1, 1, 40),      # drafts of one row
+    (1024, 128, 512, 1, 33, 2),      # three tiles a draft, two key tiles: five row tiles
+    (1024, 128, 512, 1, 11, 9),      # nine padded tiles, seven packed
+    (2816, 128, 512, 1, 24, 5),      # eight row tiles through LDS
+    (2816, 128, 512, 1, 20, 8),      # ten, two row blocks
+    (1024, 128, 512, 1, 20, 16),     # the many-row attention
+    (1024, 128, 512, 2, 9, 32),      # 36 row tiles, QKV in 128-row blocks
+    (2048, 128, 512, 1, 20, 80),     # 100 row tiles, QKV in 256-row blocks
+])
+def test_step_with_dense_rows(d, dh, f, batch, b, S):
+    p = Pair(dict(_width(d, f), n_heads=d // dh, head_dim=dh))
+    try:
+        wl = W.decode_workload(p.shape, 50, 60, b, S, 800 + b, batch=batch)
+        cache, oc = run_prefill_case(p, wl.tokens, wl.resp_off, "set-up at d = %d" % d)
+        run_step_case(p, cache, oc, wl.drafts, wl.block_off, 0.9, "d = %d, %d x %d x %d" % (d, batch, S, b))
+        # the same bits whatever the scratch held before: another step and another refresh between two of the same
+        dg, tokens = torch.from_numpy(wl.drafts).cuda(), torch.from_numpy(wl.tokens).cuda()
+        first = [x.clone() for x in B.odb_block_step(p.model, cache, dg, wl.block_off, 0.9)]
+        B.odb_block_step(p.model, cache, (dg + 1) % p.shape["vocab"], wl.block_off, 0.9)
+        B.odb_prefill(p.model, cache, tokens, wl.resp_off)
+        for x, y in zip(first, B.odb_block_step(p.model, cache, dg, wl.block_off, 0.9)):
+            assert torch.equal(x, y)
+        B.odb_model_status(p.model)
+    finally:
+        p.close()
+
+
+def test_dense_rows_in_the_fixed_area():
+    p = Pair(_width(1024, 512))
+    try:
+        wl = W.decode_workload(p.shape, 50, 60, 7, 4, 31)
+        cache = p.cache(1, wl.tokens.shape[1])
+        B.odb_prefill(p.model, cache, torch.from_numpy(wl.tokens).cuda(), wl.resp_off)
+        dg = torch.from_numpy(wl.drafts).cuda()
+        want = B.odb_block_step(p.model, cache, dg, wl.block_off, 0.9)
+        got = B.odb_block_step_static(p.model, cache, dg, wl.block_off, 0.9, *[torch.empty_like(x) for x in want])
+        for x, y in zip(want, got):
+            assert torch.equal(x, y)
+    finally:
+        p.close()
