@@ -351,16 +351,11 @@ void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOu
 void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int ldh, NormOut no, Workspace ws,
                        hipStream_t s) {
     EpiResid e{h, ldh, no, sh.M_tiles};
-    // K split over four workgroups with the in-kernel reduction (gemm_stream_ksplit_kernel) where it measured
-    // faster at the 8B shape: the down projection (more input than output channels) up to 96 rows and the O
-    // projection from 33 to 96 rows.  Per step: 3.55 -> 3.47 ms at 32 rows, 4.25 -> 4.03 at 64, 4.77 -> 4.71 at 96.
-    // (At 32 rows the O projection is 0.6 % slower that way than with the plain streaming kernel; at 96 rows either
-    // projection alone measured 1 % slower and only both together faster; at 128 rows, where the ring is down to
-    // two stages, every combination loses 1-1.5 % to the tile kernel, and a four-wave variant with a ring of
-    // four loses 4 %.)
-    // Otherwise, more than 32 rows: the tile kernel, whose K split over workgroups also splits the activation
-    // reads, with a separate pass that adds the partial sums.  From 2048 rows the 256 x 128 blocks of the 256-row
-    // kernel fill the chip (8 x 32 blocks for N = 4096).
+    // Up to 96 rows K is split over four workgroups that add up their sums in the kernel (gemm_stream_ksplit_kernel) unless it is
+    // short; a step of the 8B shape with down so took 3.55 -> 3.47 ms at 32 rows, with both 4.25 -> 4.03 at 64 and 4.77 -> 4.71 at 96.
+    // At 97 to 128 rows, where its ring is down to two stages, it loses to the tile kernel, whose K split over workgroups also splits
+    // the activation reads, with a separate pass that adds the partial sums.  Beyond, the blocks of the LDS-ring kernel where they fill
+    // the chip (choose.h: big_choice, big_plan).
     // Blocks with all of K in a workgroup, where they are short enough (choose.h): d 1024 at 128 rows, O 6.5 -> 4.4 us.
     const RowBlock rows = resid_block(sh.M_tiles, sh.N_tiles, sh.K_tiles);
     const NormIn none{nullptr, 0, 0.f};

@@ -4,7 +4,7 @@
 //
 // A workgroup of eight waves computes a 256 x (64 WN) block of C over all of K, WN = 4, 3 or 2 (256, 192 or
 // 128 columns: the narrower blocks exist for shapes whose count of 256-wide blocks fills the compute units
-// badly), or with MBT = 8 a 128 x (64 WN) block (each wave half as many row tiles).  Per k-tile it needs MBT 1 KiB
+// badly), or with MBT = 8, 12 or 20 a block of 128, 192 or 320 rows.  Per k-tile it needs MBT 1 KiB
 // tiles of A and 4 WN of W; they are copied from global memory straight into LDS (global_load ... lds, no registers in
 // between) into a ring of stages.  The waves form a 2 x 4 grid, each owning MBT/2 x WN output tiles.
 // Operand bytes per flop are half those of the 128-row tile kernel, which is what matters here:
@@ -22,6 +22,7 @@ namespace odb {
 // have 8 to 16, so their stages are two k-tiles deep (measured on the loop alone at K = 4096: 128 x 128 blocks 43.3 -> 37.1 us
 // at 1024 x 4096, 128 x 192 blocks 56.1 -> 52.4 us at 256 x 24576; 256 x 256 blocks equal.  256 x 128 blocks, two layers of a
 // refresh of 4 x 512 positions, one k-tile with four stages -> two with three: O 167.9 -> 153.2 us, down 420.8 -> 387.8).
+// (Blocks of 192 rows: two k-tiles up to 192 columns, 12 to 18 MFMAs a wave and k-tile; of 320 rows one, as 256 rows of these widths.)
 constexpr int big_kp(int wn, int mbt) { return (mbt == 8 && wn <= 4) || (mbt == 12 && wn <= 3) || (mbt == 16 && wn == 2) ? 2 : 1; }
 constexpr int big_stages(int wn, int mbt) { return mbt == 8 || big_kp(wn, mbt) == 2 ? 3 : 4; }
 constexpr int big_stage_tiles(int wn, int mbt) { return big_kp(wn, mbt) * (mbt + 4 * wn); }
@@ -36,7 +37,7 @@ struct BigArgs {
     const float *ssq;          // fused RMSNorm of the input rows (see GemmArgs)
     int n_ssq;
     float eps, inv_d;
-    // (KS > 1) an XCD's blocks from number `whole` on are split over KS workgroups each, which add their sums up (big_exchange)
+    // an XCD's blocks from number `whole` on are split over KS workgroups each, which add their sums up (big_exchange)
     int whole;
     float *partial;
     unsigned *arrive;
@@ -364,7 +365,8 @@ __device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs
 }
 
 // MBT: 16-row tiles per block, 16 (256 rows) or 8 (128 rows: twice the blocks for shapes that leave compute
-// units idle otherwise; per flop it needs 1.4 x the operand bytes of the 256-row block).  WN = 8: a single block of 128 rows
+// units idle otherwise; per flop it needs 1.4 x the operand bytes of the 256-row block), or 12 and 20 for counts of rows that those divide
+// badly (choose.h: big_plan).  KS: workgroups for a block of the last round, 1, or 2 in blocks of 256 x 256.  WN = 8: a single block of 128 rows
 // against 512 columns, for the LM head at 33 to 128 rows; W is then read once, non-temporally.
 template <int WN, class Epi, int MBT = 16, int KS = 1>
 __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
@@ -502,7 +504,9 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
             for (int m = 0; m < MW; m++)
 #pragma unroll
                 for (int i = 0; i < WT; i++) {
-                    const int j = m & 1 ? WT - 1 - i : i;       // to and fro: one operand changes from MFMA to MFMA, never both
+                    // to and fro: one operand changes from MFMA to MFMA, never both (MFMAs alone, normal values: 1.884 PFLOP/s; 1.845 when
+                    // both change at the end of a row - the clock under them hangs on the power they take)
+                    const int j = m & 1 ? WT - 1 - i : i;
                     acc[m][j] = mfma16(b[q][j], a[q][m], acc[m][j]);
                 }
         if (wm == 0) wait_stage(more);
