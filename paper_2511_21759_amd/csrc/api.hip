@@ -52,7 +52,7 @@ void dev_free(const Model &m, void *p) {
     else (void)hipFree(p);
 }
 
-constexpr int kCounters = 1 << 12;     // status word and arrival counters
+constexpr int kCounters = 1 << 12;     // status word and the counters of a Workspace
 // Room for the K-split partial sums: 32 MiB, and with more rows four slices of a [rows, d] projection up to 96 MiB (three slices
 // of 1264 rows at d = 4096 are 62 MB).
 constexpr size_t kPartialBytes = 32u << 20, kPartialMax = 96u << 20, kPartialByRows = ~(size_t)0;
@@ -218,7 +218,7 @@ NormIn norm_in(const Model &m, char *base, const Plan &pl, int m_tiles) {
 }
 
 Workspace workspace(const Model &m, char *base, const Plan &pl) {
-    return Workspace{(float *)(base + pl.part), pl.part_bytes, m.ksplit_reduce ? m.counters + 1024 : nullptr};
+    return Workspace{(float *)(base + pl.part), pl.part_bytes, m.ksplit_reduce ? m.counters + 1024 : nullptr, m.ksplit_reduce ? m.counters + 2048 : nullptr};
 }
 
 int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackIO &io, hipStream_t s) {

@@ -279,6 +279,15 @@ inline double big_us(TileEpilogue epi, int mbt, int wn, int ks, int m, int n, in
     return out * (1 + 0.5 * whole) + 3.4 * (whole + rounds) + full * whole + full / ks * (rounds - 1 + 0.57 + 0.43 * fill) +
            (ks > 1 ? 0.9 + 6.8 * area * (ks - 1) : 0);
 }
+// Two workgroups add up a split block's sums (gemm_big.h: big_exchange).  Each first takes a number from the block's arrival counter.  Even:
+// it leaves its sums, then adds two to the ready counter.  Odd: it waits until the ready counter has passed its number, that is, until
+// as many have left their sums as took even numbers before it.  Neither counter is ever reset, so a wait ends whatever else runs:
+// every even number below an odd one belongs to a workgroup that runs and waits for nobody.  (With counters set back to zero by
+// whoever waited, launches that overlap - two streams on one model, which the interface forbids - lost counts: a workgroup then waited
+// for ever, or every later launch of the block was out of step.)  Both counters wrap round at 2^32, in step.
+constexpr bool exchange_waits(unsigned number) { return number % 2 == 1; }
+constexpr bool exchange_ready(unsigned number, unsigned ready) { return (int)(ready - (number + 1)) >= 0; }
+
 // room: bytes for partial sums; may_exchange: workgroups of a launch may exchange them
 inline BigPlan big_plan(TileEpilogue epi, BigChoice now, int m, int n, int k, size_t room, bool may_exchange) {
     BigPlan best{now.mbt, now.wn, 1};

@@ -270,7 +270,7 @@ static void launch_big_wn(const u16 *a, const u16 *w, GemmShape sh, NormIn ni, E
     g.ssq = ni.ssq; g.n_ssq = ni.n_ssq; g.eps = ni.eps; g.inv_d = 1.0f / (float)(sh.K_tiles * 32);
     g.m_blocks = (sh.M_tiles + MBT - 1) / MBT;
     g.n_blocks = (sh.N_tiles + 4 * WN - 1) / (4 * WN);
-    g.partial = ws.partial; g.arrive = ws.arrive;
+    g.partial = ws.partial; g.exchange = ws.exchange;
     const int per_xcd = big_per_xcd(MBT, WN, sh.M_tiles, sh.N_tiles);
     g.whole = KS > 1 ? per_xcd / kXcdUnits * kXcdUnits : per_xcd;
     allow_lds<gemm_big_kernel<WN, Epi, MBT, KS>>(big_smem_bytes(WN, MBT));
@@ -299,8 +299,8 @@ static void launch_big_as(BigChoice c, const u16 *a, const u16 *w, GemmShape sh,
 // QKV, gate/up, O and down beyond 128 rows in the blocks that big_plan picks, `now` being the choice it starts from
 template <class Epi>
 static void launch_big_or_tile(BigChoice now, const u16 *a, const u16 *w, GemmShape sh, NormIn ni, Epi e, Workspace ws, hipStream_t s) {
-    static_assert(2 * 8 * (kXcdUnits - 1) <= 1024, "two counters for every split block");
-    const BigPlan p = big_plan(tile_epilogue_of<Epi>, now, sh.M_tiles, sh.N_tiles, sh.K_tiles, ws.partial_bytes, ws.arrive != nullptr);
+    static_assert(2 * 8 * (kXcdUnits - 1) <= 1024, "two counters for every split block (Workspace::exchange)");
+    const BigPlan p = big_plan(tile_epilogue_of<Epi>, now, sh.M_tiles, sh.N_tiles, sh.K_tiles, ws.partial_bytes, ws.exchange != nullptr);
     if (p.wn == 0) launch_tile(a, w, sh, ni, e, ws, true, s);
     else if (p.ks == 2) launch_big_wn<kSplitWn, Epi, kSplitMbt, 2>(a, w, sh, ni, e, s, ws);
     else if (p.mbt == 12 && p.wn == 3) launch_big_wn<3, Epi, 12>(a, w, sh, ni, e, s);

@@ -13,6 +13,7 @@
 // such that the workgroups resident on one XCD share their weight panels and rows of A.
 #pragma once
 #include <type_traits>
+#include "choose.h"
 #include "gemm_tile.h"
 
 namespace odb {
@@ -40,7 +41,7 @@ struct BigArgs {
     // an XCD's blocks from number `whole` on are split over KS workgroups each, which add their sums up (big_exchange)
     int whole;
     float *partial;
-    unsigned *arrive;
+    unsigned *exchange;        // two counters a split block
 };
 
 // ---- epilogues of a wave's MW x WT output tiles ------------------------------------------------------------------
@@ -301,22 +302,22 @@ __device__ __forceinline__ void big_epilogue(const EpiStore &e, f32x4 (&acc)[MW]
             if (mtw + m < g.MT_total && ntw + j < g.NT) e(mtw + m, ntw + j, acc[m][j] * rstd[m * 16 + (lane & 15)], lane, 0);
 }
 
-// Adds the sums of the KS workgroups of a split block (number `at` of the launch's split ones).  All but the one that arrives last
-// leave theirs in the workspace, wait for the stores and count themselves ready; the last waits for those - they have arrived, so
-// they run and wait for nobody - adds them up in slice order with its own and goes on to the epilogue (returns true).
-// Stores, loads and counters are device-scope accesses without cache-wide fences, as in gemm_stream_ksplit_kernel.  With two slices
-// one of them is ever stored; more have a place each.  The counters are back at zero when the kernel ends.
+// Adds the sums of the two workgroups of a split block (number `at` of the launch's split ones).  The first to arrive leaves its sums in
+// the workspace, waits for the stores and counts itself ready; the second waits for that (choose.h: exchange_ready), adds them to its own
+// and goes on to the epilogue (returns true): one addition per element, the same bits whoever is second.
+// Stores, loads and counters are device-scope accesses without cache-wide fences, as in gemm_stream_ksplit_kernel.
 template <int KS, int MW, int WT>
 __device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs &g, int at, int ks, int w, int lane, unsigned *s_old) {
+    static_assert(KS == 2, "one stores, the other adds");
     constexpr unsigned bytes = 8 * MW * WT * 1024;
     constexpr int P = KS == 2 ? 1 : KS;
-    unsigned *arrive = g.arrive + 2 * at;
+    unsigned *arrive = g.exchange + 2 * at;
     float *base = g.partial + (size_t)at * P * (bytes / 4);
     if (threadIdx.x == 0) *s_old = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    const bool last = *s_old == (unsigned)KS - 1;
+    const unsigned number = *s_old;
     const unsigned off = w * (MW * WT * 1024) + lane * 16;
-    if (!last) {
+    if (!exchange_waits(number)) {
         float *p = base + (KS == 2 ? 0 : ks) * (size_t)(bytes / 4);
 #pragma unroll
         for (int m = 0; m < MW; m++)
@@ -325,11 +326,11 @@ __device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[m][j]), sums_rsrc(p, bytes), off + (m * WT + j) * 1024, 0, kDeviceScope);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(arrive + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(arrive + 1, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return false;
     }
     if (threadIdx.x == 0)
-        while (__hip_atomic_load(arrive + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)KS - 1) __builtin_amdgcn_s_sleep(1);
+        while (!exchange_ready(number, __hip_atomic_load(arrive + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) __builtin_amdgcn_s_sleep(1);
     __syncthreads();
     constexpr int B = 16 / P;                   // tiles requested together
 #pragma unroll
@@ -356,10 +357,6 @@ __device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs
                 }
             }
         __builtin_amdgcn_sched_barrier(0);
-    }
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(arrive + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return true;
 }

@@ -33,8 +33,8 @@ struct Model {
     void *scratch;
     size_t scratch_bytes;
     bool least_partials;       // no more room for K-split partial sums than every call has (see plan_scratch)
-    unsigned *counters;        // [0] status word (kStatus* bits), [1024..2048) arrival counters of the K-split GEMM
-    bool ksplit_reduce;        // the K-split streaming GEMM with its in-kernel reduction may be used (ODB_OPT_KSPLIT_REDUCE)
+    unsigned *counters;        // [0] status word (kStatus* bits), [1024..2048) Workspace::arrive, [2048..3072) Workspace::exchange
+    bool ksplit_reduce;        // workgroups of a launch may exchange partial sums (ODB_OPT_KSPLIT_REDUCE)
     int n_cu;
     u16 *staging;              // set/get tensor staging
     size_t staging_bytes;
@@ -163,8 +163,9 @@ struct QkvOut {
     u16 *v_b; size_t v_b_unit_stride, v_b_head_stride;
 };
 // fp32 workspace for K-split partial sums (multi-draft step)
-// partial: K-split partial sums; arrive: 1024 arrival counters of the K-split streaming kernel (zero between launches)
-struct Workspace { float *partial; size_t partial_bytes; unsigned *arrive; };
+// partial: K-split partial sums; arrive: 1024 arrival counters of the K-split streaming kernel (zero between launches); exchange: 1024
+// counters of blocks that two workgroups share (choose.h: exchange_ready; never reset).  Both null: nothing is exchanged inside a launch.
+struct Workspace { float *partial; size_t partial_bytes; unsigned *arrive, *exchange; };
 void launch_gemm_qkv(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, QkvOut out, Workspace ws, hipStream_t s);
 void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int ldh, NormOut no, Workspace ws,
                        hipStream_t s);

@@ -23,6 +23,8 @@ int plan(int epi, int now_mbt, int now_wn, int m, int n, int k, size_t room, int
     const BigPlan p = big_plan((TileEpilogue)epi, BigChoice{now_mbt, now_wn}, m, n, k, room, may != 0);
     return p.wn ? p.mbt * 100 + p.wn * 10 + p.ks : 0;
 }
+int waits(unsigned number) { return exchange_waits(number); }
+int ready(unsigned number, unsigned count) { return exchange_ready(number, count); }
 int packed(int dense, int padded) { return dense_rows_pay(dense, padded); }
 int few_split(int m, int n, int k) { return few_rows_split(m, n, k); }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
@@ -278,6 +280,72 @@ def test_plans_exchange_only_where_there_is_room_for_it(rules):
             if p % 10 == 2:                    # two counters a split block; the whole rounds' blocks are not split
                 left = (m + 15) // 16 * ((n // 16 + (n % 16 > 0) + 7) // 8) % 32
                 assert p == 1642 and 0 < left and 2 * 8 * left <= 1024
+
+
+# ---- the counters of a block that two workgroups share ---------------------------------------------------------------------------
+
+def _exchange(steps, launches, start):
+    """Every order in which the workgroups of `launches` overlapping launches (two each) can take their steps on one block's two
+    counters, from (start, start): the states in which somebody waits and nobody can go on, and whether a workgroup ever went on from its
+    wait before as many had counted themselves ready as that takes.  A workgroup is (place in its program, its number)."""
+    first = (start, start, ((0, 0),) * (2 * launches))
+    seen, todo, stuck, early = {first}, [first], [], False
+    while todo:
+        arrive, ready, groups = state = todo.pop()
+        moved = False
+        for i, (place, number) in enumerate(groups):
+            after = steps(arrive, ready, place, number)
+            if after is None:
+                continue
+            moved = True
+            if place == 1 and steps is not RESET and after[2] == DONE and number % 2 == 1:
+                done = sum(1 for g in groups if g[0] == DONE and g[1] % 2 == 0)
+                early = early or done < ((number - start) % 2 ** 32 + 1) // 2
+            nxt = (after[0], after[1], tuple(sorted(groups[:i] + ((after[2], after[3]),) + groups[i + 1:])))
+            if nxt not in seen:
+                seen.add(nxt)
+                todo.append(nxt)
+        if not moved and any(place != DONE for place, _ in groups):
+            stuck.append(state)
+    return stuck, early
+
+
+DONE = 9
+
+
+def RESET(arrive, ready, place, number):
+    """Counters that start at zero and that the second workgroup sets back: the form that overlapping launches break."""
+    if place == 0:
+        return arrive + 1, ready, 1, arrive
+    if place == 1 and number != 1:
+        return arrive, ready + 1, DONE, number
+    if place == 1:
+        return (arrive, ready, 2, number) if ready == 1 else None
+    if place == 2:
+        return 0, ready, 3, number
+    return (arrive, 0, DONE, number) if place == 3 else None
+
+
+@pytest.mark.parametrize("start", [0, 2, 2 ** 31 - 2, 2 ** 31, 2 ** 32 - 4, 2 ** 32 - 2])
+def test_a_shared_blocks_workgroups_never_wait_for_ever(rules, start):
+    rules.waits.argtypes = [ctypes.c_uint]
+    rules.ready.argtypes = [ctypes.c_uint] * 2
+    M = 2 ** 32
+
+    def steps(arrive, ready, place, number):
+        if place == 0:
+            return (arrive + 1) % M, ready, 1, arrive
+        if place == 1 and not rules.waits(number):
+            return arrive, (ready + 2) % M, DONE, number
+        if place == 1 and rules.ready(number, ready):
+            return arrive, ready, DONE, number
+        return None
+
+    for launches in (1, 2, 3):
+        stuck, early = _exchange(steps, launches, start)
+        assert not stuck and not early
+    # alone on the counters, launch after launch
+    assert _exchange(RESET, 1, 0)[0] == [] and _exchange(RESET, 2, 0)[0]
 
 
 @pytest.mark.parametrize("m,n,k,blocks_of", [
