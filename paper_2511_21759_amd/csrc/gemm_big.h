@@ -306,24 +306,21 @@ __device__ __forceinline__ void big_epilogue(const EpiStore &e, f32x4 (&acc)[MW]
 // the workspace, waits for the stores and counts itself ready; the second waits for that (choose.h: exchange_ready), adds them to its own
 // and goes on to the epilogue (returns true): one addition per element, the same bits whoever is second.
 // Stores, loads and counters are device-scope accesses without cache-wide fences, as in gemm_stream_ksplit_kernel.
-template <int KS, int MW, int WT>
-__device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs &g, int at, int ks, int w, int lane, unsigned *s_old) {
-    static_assert(KS == 2, "one stores, the other adds");
+template <int MW, int WT>
+__device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs &g, int at, int w, int lane, unsigned *s_old) {
     constexpr unsigned bytes = 8 * MW * WT * 1024;
-    constexpr int P = KS == 2 ? 1 : KS;
     unsigned *arrive = g.exchange + 2 * at;
-    float *base = g.partial + (size_t)at * P * (bytes / 4);
+    float *sums = g.partial + (size_t)at * (bytes / 4);
     if (threadIdx.x == 0) *s_old = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const unsigned number = *s_old;
     const unsigned off = w * (MW * WT * 1024) + lane * 16;
     if (!exchange_waits(number)) {
-        float *p = base + (KS == 2 ? 0 : ks) * (size_t)(bytes / 4);
 #pragma unroll
         for (int m = 0; m < MW; m++)
 #pragma unroll
             for (int j = 0; j < WT; j++)
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[m][j]), sums_rsrc(p, bytes), off + (m * WT + j) * 1024, 0, kDeviceScope);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[m][j]), sums_rsrc(sums, bytes), off + (m * WT + j) * 1024, 0, kDeviceScope);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(arrive + 1, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -332,30 +329,17 @@ __device__ __forceinline__ bool big_exchange(f32x4 (&acc)[MW][WT], const BigArgs
     if (threadIdx.x == 0)
         while (!exchange_ready(number, __hip_atomic_load(arrive + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) __builtin_amdgcn_s_sleep(1);
     __syncthreads();
-    constexpr int B = 16 / P;                   // tiles requested together
+    constexpr int B = 16;                       // tiles requested together
 #pragma unroll
     for (int t0 = 0; t0 < MW * WT; t0 += B) {
-        u32x4 v[B][P];
+        u32x4 v[B];
 #pragma unroll
         for (int t = 0; t < B; t++)
-            if (t0 + t < MW * WT)
-#pragma unroll
-                for (int s = 0; s < P; s++)      // (a last slice's own place holds nothing; what is read there is not used)
-                    v[t][s] = __builtin_amdgcn_raw_buffer_load_b128(sums_rsrc(base + s * (size_t)(bytes / 4), bytes), off + (t0 + t) * 1024, 0, kDeviceScope);
+            if (t0 + t < MW * WT) v[t] = __builtin_amdgcn_raw_buffer_load_b128(sums_rsrc(sums, bytes), off + (t0 + t) * 1024, 0, kDeviceScope);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < B; t++)
-            if (t0 + t < MW * WT) {
-                f32x4 &own = acc[(t0 + t) / WT][(t0 + t) % WT];
-                if constexpr (KS == 2) {
-                    own += __builtin_bit_cast(f32x4, v[t][0]);
-                } else {
-                    f32x4 c = ks == 0 ? own : __builtin_bit_cast(f32x4, v[t][0]);
-#pragma unroll
-                    for (int s = 1; s < P; s++) c += ks == s ? own : __builtin_bit_cast(f32x4, v[t][s]);
-                    own = c;
-                }
-            }
+            if (t0 + t < MW * WT) acc[(t0 + t) / WT][(t0 + t) % WT] += __builtin_bit_cast(f32x4, v[t]);
         __builtin_amdgcn_sched_barrier(0);
     }
     return true;
@@ -369,6 +353,7 @@ template <int WN, class Epi, int MBT = 16, int KS = 1>
 __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
     static_assert((WN >= 2 && WN <= 4) || (WN == 8 && MBT == 8), "block width in units of 64 columns");
     static_assert(MBT % 4 == 0 && MBT >= 8 && MBT <= 20, "rows per block");
+    static_assert(KS == 1 || KS == 2, "one workgroup stores, the other adds");
     constexpr int CW = 4;                       // waves side by side; two rows of them
     constexpr int WT = WN;                      // 16-column tiles per wave
     constexpr int MW = MBT / 2;                 // 16-row tiles per wave
@@ -514,7 +499,7 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(BigArgs g, Epi epi) {
     __syncthreads();            // the ring is reused below
 
     if constexpr (KS > 1)
-        if (split && !big_exchange<KS, MW, WT>(acc, g, (blk - g.whole) * 8 + xcd, ks, w, lane, reinterpret_cast<unsigned *>(smem))) return;
+        if (split && !big_exchange<MW, WT>(acc, g, (blk - g.whole) * 8 + xcd, w, lane, reinterpret_cast<unsigned *>(smem))) return;
 
     if constexpr (is_row_stats<Epi>::value) {
         // softmax statistics per row over this workgroup's columns: lane-local, across the four lane
