@@ -251,14 +251,16 @@ inline BigChoice lm_block_choice(int m, int n_tiles) { return big_choice_by(m, n
 // What runs where big_choice decided until the blocks below were measured: a block shape of the LDS-ring kernel - mbt x 16 rows by
 // 64 * wn columns, its last round split over `ks` workgroups a block - or the tile kernel (wn = 0).
 //
-// `now` stands - the shape big_choice picks, or the tile kernel - unless another block promises 4 % by the model of big_us, 6 % with
+// `now` stands - the shape big_choice picks, or the tile kernel - unless another block promises 4 % by the model of big_us, or more with
 // its last round split.  Blocks of 192 and 320 rows serve counts of rows that 128 and 256 divide badly (8B shape: gate/up of 608 rows in
 // 256 blocks of 320 x 192 135 -> 111 us, of 320 rows in 192 x 192 124 -> 69, QKV of 1408 rows in 320 x 256 194 -> 151, down of 3008
 // rows in 192 x 256 311 -> 281).  Splitting K in the blocks of the last, half empty round fills it (256 x 256 blocks: down of 2048 rows
 // 128 blocks on 256 compute units 240 -> 202 us; QKV of 2048 rows one and a half rounds 220 -> 207).  The gain is less than the
 // idle units suggest, as the others run at a lower clock the more of them multiply; the exchange costs 7 us a block of 256 x 256.
+// Launches timed one by one, the chip idle between them, flatter the split: inside a call, behind other kernels, it takes 5 to 20 % more
+// than the model against other blocks, most for gate/up.  What it has to promise there: split_margin.
 // Over 222 measured sizes (d 1024 to 4096, 176 to 3008 rows) the launches take 0.956 of the time on average, 0.951 with the best of
-// these blocks everywhere; three are slower by more than 2 %, up to 5 %.  Splits of other shapes would add 0.4 %.
+// these blocks everywhere.  Splits of other shapes would add 0.4 %.
 struct BigPlan { int mbt, wn, ks; };
 constexpr int kSplitMbt = 16, kSplitWn = 4;                     // the shape whose last round may be split
 // blocks of the fullest XCD, which takes whole columns of blocks and runs kXcdUnits of them at a time
@@ -288,6 +290,23 @@ inline double big_us(TileEpilogue epi, int mbt, int wn, int ks, int m, int n, in
 constexpr bool exchange_waits(unsigned number) { return number % 2 == 1; }
 constexpr bool exchange_ready(unsigned number, unsigned ready) { return (int)(ready - (number + 1)) >= 0; }
 
+// Share of `now`'s time by the model that a split last round may take at most.  From kernel traces of whole calls, split against
+// `now`, us (d, d_ff, rows; promised):
+//   the same blocks unsplit: gate/up 3072, 8192, 1536 136 / 144 (0.90), 5120, 13824, 2048 434 / 466 (0.94)
+//   O and down: down 2048, 5632, 3000 86 / 93 (0.92), 4096, 12288, 2048 183 / 203 (0.83); O 5120, 1168 rows 92 / 86 (0.935)
+//   256 x 192: QKV 4096, 2048 rows 190 / 197 (0.92), 3584, 2048 rows 165 / 163 (0.94); gate/up 4096, 12288, 896 169 / 172 (0.89),
+//     2560, 6912, 1408 106 / 104, 2304, 6144, 2048 111 / 104, 2048, 5632, 2048 96 / 90 (0.92 to 0.93)
+//   256 x 128: gate/up 3072, 8192, 512 56.7 / 53.7 (0.90), 5120, 13824, 256 87.4 / 86.7 (0.85); QKV 5120, 512 rows 93.9 / 92.6 (0.92)
+// And split_lead: how much more it has to promise than unsplit blocks.  Split against those: gate/up 3072, 8192, 1536 132 / 124 (192 x 256; 0.95
+// of their time promised), 4096, 12288, 960 167 / 161 (0.96), 5120, 13824, 1856 418 / 423 (320 x 256; 0.99); QKV 4096, 1856 rows 190 / 181
+// (0.98), 5120, 1536 rows 215 / 211 (0.96); down 2048, 5632, 2720 79 / 89 (192 x 192; 0.97).
+inline double split_margin(TileEpilogue epi, BigChoice now) {
+    if (epi == TileEpilogue::resid) return 0.93;
+    if (now.wn == 2) return 0;
+    if (now.wn == 4 && now.mbt == kSplitMbt) return 0.94;
+    return epi == TileEpilogue::qkv ? 0.93 : 0.905;
+}
+inline double split_lead(TileEpilogue epi) { return epi == TileEpilogue::resid ? 1 : 1.06; }
 // room: bytes for partial sums; may_exchange: workgroups of a launch may exchange them
 inline BigPlan big_plan(TileEpilogue epi, BigChoice now, int m, int n, int k, size_t room, bool may_exchange) {
     BigPlan best{now.mbt, now.wn, 1};
@@ -297,7 +316,7 @@ inline BigPlan big_plan(TileEpilogue epi, BigChoice now, int m, int n, int k, si
     double best_us = 1e30;
     auto consider = [&](int mbt, int wn, int ks) {
         const double us = big_us(epi, mbt, wn, ks, m, n, k);
-        if (us < best_us && us < (ks > 1 ? 0.94 : 0.96) * now_us) { best = BigPlan{mbt, wn, ks}; best_us = us; }
+        if (us * (ks > 1 ? split_lead(epi) : 1) < best_us && us < (ks > 1 ? split_margin(epi, now) : 0.96) * now_us) { best = BigPlan{mbt, wn, ks}; best_us = us; }
     };
     for (int mbt = 8; mbt <= 20; mbt += 4)
         for (int wn = mbt % 8 == 4 ? 3 : 2; wn <= 4; wn++) consider(mbt, wn, 1);         // (no narrow blocks of 192 and 320 rows)

@@ -270,6 +270,46 @@ def test_plans_are_near_the_fastest_measured(rules, epi, rows, n, k, now, us):
     assert picked in us and us[picked] <= 1.05 * min(us.values()) and us[picked] <= us[now]
 
 
+# the same from kernel traces of whole calls, where the launches follow each other: a split last round is not worth there what it is by itself
+PLANS_IN_CALLS = [
+    (1, 512, 864, 80, 1621, {1621: 42.9, 841: 40.7, 1642: 46.5}),
+    (1, 512, 1024, 96, 1621, {1621: 51.0, 841: 49.3, 1642: 56.0}),
+    (1, 960, 1536, 128, 1631, {1631: 174.0, 1241: 161.0, 1642: 166.9}),
+    (1, 1536, 864, 80, 1631, {1631: 102.4, 1241: 98.9, 1642: 104.8}),
+    (1, 1536, 1024, 96, 1641, {1641: 139.2, 1241: 124.0, 1642: 132.2}),
+    (1, 1856, 768, 72, 1631, {1631: 100.9, 1241: 93.2, 1642: 106.9}),
+    (1, 1856, 1728, 160, 1641, {1641: 454.3, 2041: 423.5, 1642: 418.0}),
+    (1, 2048, 704, 64, 1631, {1631: 87.4, 1642: 95.4}),
+    (1, 2048, 768, 72, 1631, {1631: 99.9, 1642: 104.8}),
+    (1, 2048, 1216, 112, 1641, {1641: 245.6, 1642: 229.2}),
+    (0, 512, 960, 160, 1621, {1621: 91.7, 841: 88.9, 1642: 94.3}),
+    (0, 1536, 960, 160, 1631, {1631: 223.4, 1241: 210.6, 1642: 214.8}),
+    (0, 1856, 768, 128, 1631, {1631: 193.1, 1241: 180.9, 1642: 189.8}),
+    (0, 2048, 672, 112, 1631, {1631: 161.9, 1642: 163.1}),
+    (0, 2048, 768, 128, 1631, {1631: 197.1, 1642: 190.1}),
+    (2, 1200, 320, 160, 1621, {1621: 86.0, 1231: 80.7, 1642: 92.2}),
+    (2, 1856, 256, 384, 1621, {1621: 197.7, 1642: 178.1}),
+    (2, 2720, 128, 176, 1621, {1621: 89.4, 1231: 88.6, 1642: 79.0}),
+]
+
+
+@pytest.mark.parametrize("epi,rows,n,k,now,us", PLANS_IN_CALLS)
+def test_plans_are_no_slower_inside_calls(rules, epi, rows, n, k, now, us):
+    rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
+    picked = rules.plan(epi, now // 100, now // 10 % 10, rows // 16, n, k, 96 << 20, 1)
+    assert picked in us and us[picked] <= 1.02 * min(us.values()) and us[picked] <= us[now]
+
+
+def test_sizes_of_the_gpu_test_of_the_split_take_it(rules):
+    from test_gpu_many_rows import SPLIT
+    rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
+    for d, f, rows, which in SPLIT:
+        m, room = (rows + 15) // 16, max(32 << 20, (rows + 15) // 16 * 16 * d * 16)
+        epi, n, k = {"qkv": (0, 3 * d // 16, d // 32), "gate/up": (1, 2 * f // 16, d // 32), "down": (2, d // 16, f // 32)}[which]
+        block = rules.big_block(m, n, k)
+        assert block and rules.plan(epi, block // 10, block % 10, m, n, k, room, 1) == 1642
+
+
 def test_plans_exchange_only_where_there_is_room_for_it(rules):
     rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
     split = lambda room, may: rules.plan(2, 16, 2, 128, 256, 384, room, may) == 1642
