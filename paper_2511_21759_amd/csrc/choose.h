@@ -268,11 +268,12 @@ constexpr int kXcdUnits = kComputeUnits / 8;
 inline int big_per_xcd(int mbt, int wn, int m, int n) { return (m + mbt - 1) / mbt * (((n + 4 * wn - 1) / (4 * wn) + 7) / 8); }
 // Microseconds of a launch, fitted to 4180 measured (6 % off at the root mean square): a block's time by shape and K when all
 // compute units work; the last round between 0.57 and 1 of that by its fill; 3.4 a round, the epilogue (under the next round by half), the
-// exchange of a split block.
+// exchange of a split block.  A single row block of 192 rows takes 8 % more: half as many workgroups as two of 128 stream the weights
+// (gate/up of 144 to 192 rows in calls, 192 x 192 and 128 x 192: d 4096, d_ff 12288 63.9 and 61.6 us, d 3584, d_ff 9728 53.0 and 49.2).
 inline double big_us(TileEpilogue epi, int mbt, int wn, int ks, int m, int n, int k) {
     const double at4096[4][3] = {{43.9, 59.6, 70.9}, {76.0, 71.5, 93.8}, {74.6, 98.9, 112.1}, {98.5, 114.1, 143.3}};    // mbt 8 .. 20, wn 2 .. 4
     const int per = big_per_xcd(mbt, wn, m, n), all = (m + mbt - 1) / mbt * ((n + 4 * wn - 1) / (4 * wn));
-    const double area = mbt * wn / 64.0, full = at4096[mbt / 4 - 2][wn - 2] * k / 128;
+    const double area = mbt * wn / 64.0, full = at4096[mbt / 4 - 2][wn - 2] * k / 128 * (mbt == 12 && m <= 12 ? 1.08 : 1);
     const double out = (epi == TileEpilogue::swiglu ? 0 : epi == TileEpilogue::qkv ? 13.2 : 14.3) * area;
     const int whole = ks > 1 ? per / kXcdUnits : (per + kXcdUnits - 1) / kXcdUnits - 1;
     const int rounds = ((per - whole * kXcdUnits) * ks + kXcdUnits - 1) / kXcdUnits;
@@ -321,7 +322,7 @@ inline BigPlan big_plan(TileEpilogue epi, BigChoice now, int m, int n, int k, si
     for (int mbt = 8; mbt <= 20; mbt += 4)
         for (int wn = mbt % 8 == 4 ? 3 : 2; wn <= 4; wn++) consider(mbt, wn, 1);         // (no narrow blocks of 192 and 320 rows)
     const int left = big_per_xcd(kSplitMbt, kSplitWn, m, n) % kXcdUnits;
-    if (may_exchange && left > 0 && (size_t)left * 8 * kSplitMbt * kSplitWn * 4096 <= room) consider(kSplitMbt, kSplitWn, 2);
+    if (may_exchange && m >= kSplitMbt && left > 0 && (size_t)left * 8 * kSplitMbt * kSplitWn * 4096 <= room) consider(kSplitMbt, kSplitWn, 2);
     return best;
 }
 

@@ -272,6 +272,11 @@ def test_plans_are_near_the_fastest_measured(rules, epi, rows, n, k, now, us):
 
 # the same from kernel traces of whole calls, where the launches follow each other: a split last round is not worth there what it is by itself
 PLANS_IN_CALLS = [
+    (1, 144, 1536, 128, 831, {831: 57.7, 1231: 61.7}),          # one row block of 192 rows
+    (1, 192, 1536, 128, 831, {831: 57.4, 1231: 62.7}),
+    (1, 192, 1216, 112, 0, {831: 46.9, 1231: 53.5, 0: 61.1}),
+    (1, 192, 1728, 160, 0, {1231: 82.7, 0: 92.9}),
+    (1, 704, 1728, 160, 1631, {1631: 200.1, 1241: 195.4, 1642: 189.5}),
     (1, 512, 864, 80, 1621, {1621: 42.9, 841: 40.7, 1642: 46.5}),
     (1, 512, 1024, 96, 1621, {1621: 51.0, 841: 49.3, 1642: 56.0}),
     (1, 960, 1536, 128, 1631, {1631: 174.0, 1241: 161.0, 1642: 166.9}),
@@ -296,7 +301,7 @@ PLANS_IN_CALLS = [
 @pytest.mark.parametrize("epi,rows,n,k,now,us", PLANS_IN_CALLS)
 def test_plans_are_no_slower_inside_calls(rules, epi, rows, n, k, now, us):
     rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
-    picked = rules.plan(epi, now // 100, now // 10 % 10, rows // 16, n, k, 96 << 20, 1)
+    picked = rules.plan(epi, now // 100 if now else 16, now // 10 % 10, rows // 16, n, k, 96 << 20, 1)
     assert picked in us and us[picked] <= 1.02 * min(us.values()) and us[picked] <= us[now]
 
 
