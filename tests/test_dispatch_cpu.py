@@ -292,6 +292,10 @@ PLANS_IN_CALLS = [
     (0, 1856, 768, 128, 1631, {1631: 193.1, 1241: 180.9, 1642: 189.8}),
     (0, 2048, 672, 112, 1631, {1631: 161.9, 1642: 163.1}),
     (0, 2048, 768, 128, 1631, {1631: 197.1, 1642: 190.1}),
+    (2, 1792, 224, 112, 1621, {1621: 62.7, 841: 59.5}),
+    (1, 256, 1728, 160, 1621, {1621: 84.5, 841: 85.8}),
+    (1, 1024, 512, 48, 1621, {1621: 28.9, 841: 27.9}),
+    (0, 1024, 480, 80, 1621, {1621: 51.8, 841: 47.6}),
     (2, 1200, 320, 160, 1621, {1621: 86.0, 1231: 80.7, 1642: 92.2}),
     (2, 1856, 256, 384, 1621, {1621: 197.7, 1642: 178.1}),
     (2, 2720, 128, 176, 1621, {1621: 89.4, 1231: 88.6, 1642: 79.0}),
@@ -302,7 +306,7 @@ PLANS_IN_CALLS = [
 def test_plans_are_no_slower_inside_calls(rules, epi, rows, n, k, now, us):
     rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
     picked = rules.plan(epi, now // 100 if now else 16, now // 10 % 10, rows // 16, n, k, 96 << 20, 1)
-    assert picked in us and us[picked] <= 1.02 * min(us.values()) and us[picked] <= us[now]
+    assert picked in us and us[picked] <= 1.015 * min(us.values()) and us[picked] <= us[now]
 
 
 def test_sizes_of_the_gpu_test_of_the_split_take_it(rules):
