@@ -25,6 +25,7 @@ int plan(int epi, int now_mbt, int now_wn, int m, int n, int k, size_t room, int
 }
 int waits(unsigned number) { return exchange_waits(number); }
 int ready(unsigned number, unsigned count) { return exchange_ready(number, count); }
+int resid_rows(int m, int n, int k) { const RowBlock b = resid_block(m, n, k); return b.mt * 10 + b.ng; }
 int packed(int dense, int padded) { return dense_rows_pay(dense, padded); }
 int few_split(int m, int n, int k) { return few_rows_split(m, n, k); }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
@@ -395,6 +396,16 @@ def test_a_shared_blocks_workgroups_never_wait_for_ever(rules, start):
         assert not stuck and not early
     # alone on the counters, launch after launch
     assert _exchange(RESET, 1, 0)[0] == [] and _exchange(RESET, 2, 0)[0]
+
+
+# O and down beyond 128 rows, rows, n-tiles, k-tiles -> us inside calls in blocks of 64 x 64 with all of K (44), on the tile kernel (0)
+@pytest.mark.parametrize("rows,n,k,us", [
+    (2048, 48, 64, {44: 26.8, 0: 22.3}), (1952, 48, 64, {44: 25.6, 0: 22.2}), (1792, 48, 64, {44: 22.8, 0: 21.8}),
+    (2048, 48, 24, {44: 14.9, 0: 17.7}), (1024, 48, 64, {44: 11.8, 0: 19.1}), (1024, 128, 64, {44: 23.7, 0: 25.3}),
+    (1296, 96, 48, {44: 19.7, 0: 24.2}), (1296, 80, 40, {44: 17.9, 0: 20.5}),
+])
+def test_resid_blocks_where_they_are_faster(rules, rows, n, k, us):
+    assert us[rules.resid_rows(rows // 16, n, k)] == min(us.values())
 
 
 @pytest.mark.parametrize("m,n,k,blocks_of", [
