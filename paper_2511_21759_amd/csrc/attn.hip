@@ -5,19 +5,13 @@
 
 namespace odb {
 
-// gx work items (QT row tiles of a unit) of H heads, VS workgroups each.  one_xcd (H a multiple of 8): ids are mapped so that the
-// workgroups of a head (they read the same cached K/V) run on one XCD (id % 8) and share its L2:
-// id = xcd + 8 * (work + gx * VS * (head / 8)), head = xcd + 8 * (head / 8).
+// gx work items (QT row tiles of a unit) of H heads, VS workgroups each (choose.h: attention_place)
 template <int DH, int QT, int NW, bool SHARED, int VS>
 __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a, float sc, int gx, int one_xcd) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    int work = blockIdx.x, hd = blockIdx.y;
-    if (one_xcd) {
-        const int j = blockIdx.x >> 3, per = gx * VS, q = j / per;
-        work = j - q * per;
-        hd = (blockIdx.x & 7) + 8 * q;
-    }
-    attn_wg<DH, QT, NW, SHARED, VS>(a, sc, work / VS, hd, work % VS, smem);
+    const AttentionPlace p = attention_place(blockIdx.x, gx, VS, one_xcd != 0);
+    if (p.head >= a.H) return;              // (the last eight units need not all exist)
+    attn_wg<DH, QT, NW, SHARED, VS>(a, sc, p.item, p.head, p.part, smem);
 }
 
 // Many rows per (sequence, head): K/V tiles shared through LDS by all rows of a workgroup (attn_rows.h)
@@ -37,8 +31,7 @@ template <int DH, int QT, int NW, bool SHARED, int VS>
 static void launch_split_as(AttnArgs a, float sc, int items, bool one_xcd, hipStream_t s) {
     constexpr int lds = attn_smem_bytes<DH, QT, NW, VS>();
     allow_lds<attn_kernel<DH, QT, NW, SHARED, VS>>(lds);
-    const dim3 grid = one_xcd ? dim3(items * VS * a.H) : dim3(items * VS, a.H);
-    attn_kernel<DH, QT, NW, SHARED, VS><<<grid, 64 * NW, lds, s>>>(a, sc, items, one_xcd);
+    attn_kernel<DH, QT, NW, SHARED, VS><<<attention_grid(items, a.H, VS), 64 * NW, lds, s>>>(a, sc, items, one_xcd);
 }
 template <int QT, int NW, bool SHARED, int VS>
 static void launch_split(AttnArgs a, float sc, int items, bool one_xcd, hipStream_t s) {

@@ -16,6 +16,11 @@ using namespace odb;
 extern "C" {
 int attention_way(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).way; }
 int attention_one_xcd(int dh, int H, int L, int step, int units, int ups, int tpu) { return attention_choice(dh, H, L, step != 0, units, ups, tpu).one_xcd; }
+void attention_at(int id, int gx, int parts, int one_xcd, int *out) {
+    const AttentionPlace p = attention_place(id, gx, parts, one_xcd != 0);
+    out[0] = p.item; out[1] = p.head; out[2] = p.part;
+}
+int attention_wgs(int gx, int H, int parts) { return attention_grid(gx, H, parts); }
 int swiglu_group(int m, int n, int k) { return swiglu_row_block_group(m, n, k); }
 int qkv_slab(int m, int n) { return qkv_slab_group(m, n); }
 int big_block(int m, int n, int k) { const BigChoice c = big_choice(m, n, k); return c.wn ? c.mbt * 10 + c.wn : 0; }
@@ -101,6 +106,26 @@ def test_heads_stay_on_one_xcd_in_steps_only(rules):
                 items = units * (tpu if way == 1 else (tpu + 1) // 2)
                 assert got == (dh == 128 and H % 8 == 0 and items > 1)
                 assert not rules.attention_one_xcd(dh, H, 16 * tpu * units, 0, 1, 1, tpu * units)
+
+
+@pytest.mark.parametrize("H,gx,parts,one_xcd", [
+    (28, 4, 2, 0), (28, 2, 4, 0), (28, 8, 1, 0), (20, 6, 2, 0), (6, 8, 4, 0), (1, 1, 4, 0), (5, 3, 1, 0),
+    (32, 1, 4, 0), (32, 2, 4, 1), (32, 4, 2, 1), (8, 5, 4, 1), (16, 3, 1, 1),
+])
+def test_workgroups_that_read_the_same_keys_share_an_xcd(rules, H, gx, parts, one_xcd):
+    at, wgs, out = {}, rules.attention_wgs(gx, H, parts), (ctypes.c_int * 3)()
+    for i in range(wgs):
+        rules.attention_at(i, gx, parts, one_xcd, out)
+        if out[1] < H:
+            assert tuple(out) not in at
+            at[tuple(out)] = i % 8
+    assert set(at) == {(x, h, p) for x in range(gx) for h in range(H) for p in range(parts)}
+    for h in range(H):
+        for x in range(gx):
+            assert len({at[x, h, p] for p in range(parts)}) == 1
+        assert not one_xcd or len({at[x, h, 0] for x in range(gx)}) == 1
+    units = [sum(v == x for (_, _, p), v in at.items() if p == 0) for x in range(8)]
+    assert max(units) - min(units) <= 1 or one_xcd
 
 
 # projection, row tiles, n-tiles, k-tiles -> us of the tile kernel and its merge pass by K slices
