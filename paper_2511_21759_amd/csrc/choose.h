@@ -189,6 +189,12 @@ inline RowBlock resid_block(int m_tiles, int n_tiles, int k_tiles) {
     return RowBlock{0, 0};
 }
 
+// O of 65 to 128 rows in two blocks of rows, both of which read the weights: past the memory-side cache (256 MB) all the same where a layer's
+// take more than 16 MiB, which would push out the K/V that the next step reads.  us a layer at d 4096, 8 layers, 128 rows, O's weights past
+// the cache and through it: 1024 keys O 17.1 and 16.7, attention 9.8 and 12.4; 512 keys 17.3 and 16.7, 7.0 and 8.4.  With 32 layers neither
+// finds anything there, and the step takes the same either way; at d 3072 it makes no difference yet.
+inline bool weights_stream_once(int n_tiles, int k_tiles) { return n_tiles * (size_t)k_tiles > 16384; }
+
 // O and down of up to 32 rows whose K is split over four workgroups: n-tiles of a block, or 0 where a workgroup has all of K (3 KiB a
 // k-tile for each of its rows and columns; the same line as for more rows above) or K cannot be split.  As many blocks as make one round:
 // down at d 1024, d_ff 3072 on 64 workgroups with all of K 10.4 us, on 256 with a quarter 7.1.

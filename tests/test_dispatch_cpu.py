@@ -33,6 +33,7 @@ int ready(unsigned number, unsigned count) { return exchange_ready(number, count
 int resid_rows(int m, int n, int k) { const RowBlock b = resid_block(m, n, k); return b.mt * 10 + b.ng; }
 int packed(int dense, int padded) { return dense_rows_pay(dense, padded); }
 int few_split(int m, int n, int k) { return few_rows_split(m, n, k); }
+int once(int n, int k) { return weights_stream_once(n, k); }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
 """
@@ -441,6 +442,15 @@ def test_resid_blocks_where_they_are_faster(rules, rows, n, k, us):
 ])
 def test_few_rows_split_k_where_it_fits(rules, m, n, k, blocks_of):
     assert rules.few_split(m, n, k) == blocks_of
+
+
+# O of 96 and 128 rows in two blocks of rows, 8 layers -> us a layer of O and the attention, O's weights past the memory-side cache (1) and through it
+@pytest.mark.parametrize("d,keys,us", [
+    (4096, 512, {1: 17.3 + 7.0, 0: 16.7 + 8.4}), (4096, 1024, {1: 17.1 + 9.8, 0: 16.7 + 12.4}), (4096, 2048, {1: 16.7 + 20.7, 0: 16.7 + 21.3}),
+    (3072, 512, {1: 13.0 + 7.9, 0: 12.5 + 8.3}), (3072, 1500, {1: 12.4 + 16.4, 0: 12.4 + 16.2}),
+])
+def test_wide_weights_do_not_displace_the_cache(rules, d, keys, us):
+    assert us[rules.once(d // 16, d // 32)] <= 1.01 * min(us.values())
 
 
 @pytest.mark.parametrize("dense,padded,pays", [
