@@ -203,6 +203,14 @@ inline int few_rows_split(int m_tiles, int n_tiles, int k_tiles) {
     return n_tiles <= kComputeUnits / 4 ? 1 : n_tiles <= kComputeUnits / 2 ? 2 : 4;
 }
 
+// Up to 32 rows whose K cannot be split so: where the n-tiles make a second round of workgroups, which is not full or over a longer K, the
+// tile kernel and its merge pass.  Packed drafts come here from three and more row tiles, which ran there before.  us, all of K in a workgroup
+// and tile kernel: down at d 5120, d_ff 13824 49.9, 31.2; d 4352, d_ff 11776 41.8, 26.1; d 8192, d_ff 22016 85.9, 71.2; O at d 4352 21.8,
+// 15.7; d 5120 21.2, 18.8; d 6144 25.2, 22.3; d 8192, two full rounds, 32.8, 35.4; one round: down at d 3584, d_ff 9728 20.4, 21.2.
+inline bool few_rows_tile(int n_tiles, int k_tiles) {
+    return n_tiles > kComputeUnits && (k_tiles > n_tiles || n_tiles < 2 * kComputeUnits);
+}
+
 // Whether a step packs its drafts' rows densely (api.hip): row tiles packed, and with every draft in tiles of its own.  Two tiles fewer at
 // least, as the kernels of few rows take two at a time, and enough of them to pay for the places looked up row by row and for
 // V written key by key.

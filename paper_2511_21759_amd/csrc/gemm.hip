@@ -381,6 +381,7 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
         else launch_ksplit_few<4>(a, w, sh, e, ws, s);
     }
     else if (ksplit_ok(sh, ws)) launch_stream_ksplit(a, w, sh, e, ws, s);
+    else if (sh.M_tiles <= 8 && (sh.M_tiles > 2 || few_rows_tile(sh.N_tiles, sh.K_tiles))) launch_tile(a, w, sh, none, e, ws, true, s);
     else if (sh.M_tiles <= 2) {
         // (as many ring stages as divide a wave's k-tiles: with one O of 32 rows at d 1024 took 5.0 us)
         const int kw = sh.K_tiles / WK;
@@ -389,7 +390,6 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
         else if (kw % 3 == 0) launch_stream<2, 1, 3, false>(a, w, sh, none, e, s);
         else launch_stream<2, 1, 2, false>(a, w, sh, none, e, s);
     }
-    else if (sh.M_tiles <= 8) launch_tile(a, w, sh, none, e, ws, true, s);
     else {
         // (128-row blocks only for the O projection: at 1024 rows of the 8B shape 256 blocks of 128 x 128 take 47.7 us against 50.4 for
         // the tile kernel and its merge pass; the down projection, three times as long in K, takes 126 us against 105)

@@ -33,6 +33,7 @@ int ready(unsigned number, unsigned count) { return exchange_ready(number, count
 int resid_rows(int m, int n, int k) { const RowBlock b = resid_block(m, n, k); return b.mt * 10 + b.ng; }
 int packed(int dense, int padded) { return dense_rows_pay(dense, padded); }
 int few_split(int m, int n, int k) { return few_rows_split(m, n, k); }
+int few_tile(int n, int k) { return few_rows_tile(n, k); }
 int once(int n, int k) { return weights_stream_once(n, k); }
 int slices(int epi, int m_tiles, int n_tiles, int k_tiles, size_t room) { return tile_slices((TileEpilogue)epi, m_tiles, n_tiles, k_tiles, room); }
 }
@@ -442,6 +443,15 @@ def test_resid_blocks_where_they_are_faster(rules, rows, n, k, us):
 ])
 def test_few_rows_split_k_where_it_fits(rules, m, n, k, blocks_of):
     assert rules.few_split(m, n, k) == blocks_of
+
+
+# 32 rows (three drafts of 10 packed take the same), n-tiles, k-tiles -> us with all of K in a workgroup, on the tile kernel with its merge pass
+@pytest.mark.parametrize("n,k,whole,tile", [
+    (320, 432, 49.9, 31.2), (272, 368, 41.8, 26.1), (512, 688, 85.9, 71.2), (272, 136, 21.8, 15.7), (320, 160, 21.2, 18.8), (384, 192, 25.2, 22.3),
+    (512, 256, 32.8, 35.4), (224, 304, 20.4, 21.2), (160, 216, 15.0, 16.1), (224, 112, 9.4, 13.5), (160, 80, 7.8, 11.3),
+])
+def test_few_rows_over_more_than_a_round_of_columns(rules, n, k, whole, tile):
+    assert rules.few_split(2, n, k) == 0 and rules.few_tile(n, k) == (tile < whole)
 
 
 # O of 96 and 128 rows in two blocks of rows, 8 layers -> us a layer of O and the attention, O's weights past the memory-side cache (1) and through it
