@@ -276,6 +276,16 @@ inline BigChoice big_choice(int m, int n_tiles, int k_tiles) { return big_choice
 // The LM head by its own numbers: as many statistics per row as before, which decide with the rest whether a step fits the fixed area.
 inline BigChoice lm_block_choice(int m, int n_tiles) { return big_choice_by(m, n_tiles, false, 0.7); }
 
+// QKV in small blocks of rows (row_block): from 33 rows on, up to 128 rows where the slab kernel does not run or 64 rows and four n-tiles
+// make one round (up to 512 n-tiles), beyond where no block of the LDS-ring kernel is chosen.
+inline RowBlock qkv_row_block(int m_tiles, int n_tiles, int k_tiles) {
+    const int slab = qkv_slab_group(m_tiles, n_tiles);
+    if (m_tiles <= 2) return RowBlock{0, 0};
+    if (m_tiles <= 8) return slab == 0 || n_tiles <= 512 ? row_block(m_tiles, n_tiles, k_tiles, false) : RowBlock{0, 0};
+    const bool narrow = n_tiles <= kComputeUnits && m_tiles <= 16;
+    return slab == 0 && (narrow || !big_choice(m_tiles, n_tiles, k_tiles).wn) ? row_block(m_tiles, n_tiles, k_tiles, !narrow) : RowBlock{0, 0};
+}
+
 // What runs where big_choice decided until the blocks below were measured: a block shape of the LDS-ring kernel - mbt x 16 rows by
 // 64 * wn columns, its last round split over `ks` workgroups a block - or the tile kernel (wn = 0).
 //

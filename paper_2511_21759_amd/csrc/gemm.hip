@@ -327,15 +327,10 @@ static void launch_qkv_as(const u16 *xa, const u16 *w, GemmShape sh, NormIn ni, 
     // compute unit leave the activation loads less to queue behind: 1.9 % per step at 32 rows for this and the
     // gate/up projection together, 1.5 % at 64 rows, 0.5 % at 96.)
     const int ng = stream_ng(sh.N_tiles, 3, false), slab = qkv_slab_group(sh.M_tiles, sh.N_tiles);
-    // (blocks of 64 rows and four n-tiles before the slab kernel: one round up to 512 n-tiles)
-    RowBlock rows{0, 0};
-    if (sh.M_tiles > 2 && sh.M_tiles <= 8 && (slab == 0 || sh.N_tiles <= 512)) rows = row_block(sh.M_tiles, sh.N_tiles, sh.K_tiles, false);
-    else if (sh.M_tiles > 8 && slab == 0 && (ng == 1 && sh.M_tiles <= 16 ? true : !big_choice(sh).wn))
-        rows = row_block(sh.M_tiles, sh.N_tiles, sh.K_tiles, sh.M_tiles > 16 || ng != 1);
+    const RowBlock rows = qkv_row_block(sh.M_tiles, sh.N_tiles, sh.K_tiles);
     if (rows.mt) launch_row_blocks(rows, xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2 && ng == 1) launch_stream<2, 1, 4, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2 && ng == 2) launch_stream<2, 2, 2, true>(xa, w, sh, ni, e, s);
-    else if (sh.M_tiles <= 4 && ng == 2) launch_stream<4, 2, 2, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 2) launch_stream<2, 3, 1, true>(xa, w, sh, ni, e, s);
     else if (sh.M_tiles <= 4) launch_stream<4, 3, 1, true>(xa, w, sh, ni, e, s);          // 33..64 rows: still eight waves
     else if (sh.M_tiles <= 6) launch_stream<6, 3, 1, true>(xa, w, sh, ni, e, s);          // 65..96 rows
