@@ -30,6 +30,7 @@ int plan(int epi, int now_mbt, int now_wn, int m, int n, int k, size_t room, int
 }
 int waits(unsigned number) { return exchange_waits(number); }
 int ready(unsigned number, unsigned count) { return exchange_ready(number, count); }
+int qkv_rows(int m, int n, int k) { const RowBlock b = qkv_row_block(m, n, k); return b.mt * 10 + b.ng; }
 int resid_rows(int m, int n, int k) { const RowBlock b = resid_block(m, n, k); return b.mt * 10 + b.ng; }
 int packed(int dense, int padded) { return dense_rows_pay(dense, padded); }
 int few_split(int m, int n, int k) { return few_rows_split(m, n, k); }
@@ -345,6 +346,46 @@ def test_sizes_of_the_gpu_test_of_the_split_take_it(rules):
         epi, n, k = {"qkv": (0, 3 * d // 16, d // 32), "gate/up": (1, 2 * f // 16, d // 32), "down": (2, d // 16, f // 32)}[which]
         block = rules.big_block(m, n, k)
         assert block and rules.plan(epi, block // 10, block % 10, m, n, k, room, 1) == 1642
+
+
+def _resid_plan(rules, m, n, k, room):
+    """O or down beyond 128 rows: the plan where no block with all of K is taken (128-row blocks only over a K up to the columns)."""
+    if rules.resid_rows(m, n, k):
+        return None
+    block = rules.big_block(m, n, k)
+    if block < 160 and k > n:
+        block = 0
+    return rules.plan(2, block // 10 if block else 16, block % 10, m, n, k, room, 1)
+
+
+def _qkv_kernel(rules, m, n, k, room):
+    rows, slab, block = rules.qkv_rows(m, n, k), rules.qkv_slab(m, n), rules.big_block(m, n, k)
+    if rows:
+        return "rows %d" % rows
+    if m <= 6:
+        return "few" if m <= 2 else "stream"
+    if slab:
+        return "slab %d" % slab
+    plan = rules.plan(0, block // 10 if block else 16, block % 10, m, n, k, room, 1)
+    return "big %d" % plan if plan else "tile"
+
+
+def test_sizes_of_the_gpu_test_of_tall_blocks_take_them(rules):
+    from test_gpu_many_rows import TALL, TALL_BATCH
+    rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
+    seen = set()
+    for d, f, rows, plans in TALL + [(d, f, 16 * n * tiles, plans) for d, f, n, tiles, plans in TALL_BATCH]:
+        m, room = (rows + 15) // 16, min(96 << 20, max(32 << 20, (rows + 15) // 16 * 16 * d * 16))
+        for which, plan in plans.items():
+            if which == "qkv":
+                assert _qkv_kernel(rules, m, 3 * d // 16, d // 32, room) == "big %d" % plan
+            elif which == "gate/up":
+                block = rules.big_block(m, f // 8, d // 32)
+                assert rules.plan(1, block // 10 if block else 16, block % 10, m, f // 8, d // 32, room, 1) == plan
+            else:
+                assert _resid_plan(rules, m, d // 16, (d if which == "O" else f) // 32, room) == plan
+            seen.add(("resid" if which in ("O", "down") else which, plan))
+    assert seen == {(w, p) for w in ("qkv", "gate/up", "resid") for p in (1231, 1241, 2031, 2041)}
 
 
 def test_plans_exchange_only_where_there_is_room_for_it(rules):

@@ -7,7 +7,7 @@ import pytest
 from oracle import odb_oracle as o
 from paper_2511_21759_amd import binding as B
 from paper_2511_21759_amd import workloads as W
-from test_gpu_parity import Pair, run_prefill_case, run_step_case
+from test_gpu_parity import KV_TOL, LOGIT_TOL, Pair, check_decisions, rel_err, run_prefill_case, run_step_case
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -272,18 +272,61 @@ def test_lm_head_of_one_row_block_with_a_ragged_last_block(vocab):
 
 # ---- blocks of 192 and 320 rows, and a last round split over two workgroups a block, each at the smallest sizes that take it -------
 
-@pytest.mark.parametrize("d,f,rows", [
-    (256, 8192, 267),      # gate/up in 192 x 192: a row block of 75 rows behind a whole one
-    (256, 5120, 779),      # 192 x 256
-    (256, 12288, 523),     # 320 x 192
-    (256, 6144, 1291),     # 320 x 256
-    (1024, 256, 2059),     # QKV in 192 x 192: the heads' boundaries inside a wave's columns
-])
-def test_refresh_in_blocks_of_192_and_320_rows(d, f, rows):
+# d, d_ff, rows, which projections run in which blocks (test_dispatch_cpu.py: the plans of these sizes)
+TALL = [
+    (256, 8192, 267, {"gate/up": 1231}),       # 192 x 192: a row block of 75 rows behind a whole one
+    (256, 5120, 779, {"gate/up": 1241}),
+    (256, 12288, 523, {"gate/up": 2031}),
+    (256, 6144, 1291, {"gate/up": 2041}),
+    (1024, 256, 2059, {"qkv": 1231}),          # the heads' boundaries inside a wave's columns
+]
+
+
+@pytest.mark.parametrize("d,f,rows,plans", TALL)
+def test_refresh_in_blocks_of_192_and_320_rows(d, f, rows, plans):
     p = Pair(_width(d, f))
     try:
         wl = W.decode_workload(p.shape, rows - 40, 40, 8, 1, 900 + d)
         run_prefill_case(p, wl.tokens, wl.resp_off, "d %d, d_ff %d, %d rows" % (d, f, rows))
+    finally:
+        p.close()
+
+
+# The same where it takes more rows: sequences of 16 * tiles - 5 positions, the last by the oracle, the others as they come out alone (in the
+# blocks of fewer rows): each is within the bar of the oracle, so twice that apart.
+# d, d_ff, sequences, row tiles of each, which projections run in which blocks
+TALL_BATCH = [
+    (1280, 256, 5, 29, {"qkv": 1241}),
+    (1536, 256, 7, 23, {"qkv": 2031}),
+    (1792, 256, 13, 13, {"qkv": 2041}),
+    (2304, 256, 7, 23, {"O": 1231, "down": 1231}),      # sums of squares over 64 columns from waves of 48
+    (3328, 256, 7, 23, {"O": 1241, "down": 1241}),
+    (4352, 1536, 7, 23, {"O": 2031, "down": 2031}),
+    (4864, 256, 7, 23, {"O": 2041}),
+]
+
+
+@pytest.mark.parametrize("d,f,batch,tiles,plans", TALL_BATCH)
+def test_refresh_of_a_batch_in_blocks_of_192_and_320_rows(d, f, batch, tiles, plans):
+    p, L, off, H = Pair(_width(d, f)), 16 * tiles - 5, 16, d // 128
+    try:
+        wl = W.decode_workload(p.shape, off, L - off, 8, 1, 900 + d, batch=batch)
+        tokens, cache = torch.from_numpy(wl.tokens).cuda(), p.cache(batch, L)
+        logits = B.odb_prefill_logits(p.model, cache, tokens, off, p.cfg.vocab).cpu().numpy()
+        conf, am = B.odb_prefill(p.model, cache, tokens, off)
+        c, conf_o, am_o, z = o.prefill(p.cfg, p.w, wl.tokens[-1], off, return_logits=True)
+        assert rel_err(logits[-1], z) <= LOGIT_TOL
+        check_decisions(conf[-1].cpu().numpy(), am[-1].cpu().numpy(), conf_o, am_o, z, np.abs(logits[-1] - z).max(), "last sequence")
+        for kv, ref in ((0, c.k[0]), (1, c.v[0])):
+            assert rel_err(B.odb_cache_read(cache, 0, kv, batch - 1, 0, L, H, 128), ref) <= KV_TOL
+        one = p.cache(1, L)
+        for i in range(batch):
+            alone = B.odb_prefill_logits(p.model, one, tokens[i:i + 1].contiguous(), off, p.cfg.vocab).cpu().numpy()
+            assert rel_err(logits[i], alone[0]) <= 2 * LOGIT_TOL, "sequence %d" % i
+            for kv in (0, 1):
+                got, ref = (B.odb_cache_read(x, 0, kv, j, 0, L, H, 128) for x, j in ((cache, i), (one, 0)))
+                assert rel_err(got, ref) <= 2 * KV_TOL, "sequence %d" % i
+        B.odb_model_status(p.model)
     finally:
         p.close()
 
@@ -322,6 +365,8 @@ def test_split_last_round_repeats_and_agrees_with_whole_blocks(d, f, rows, which
         B.odb_model_status(p.model)
         if which == "qkv":
             B.odb_set_option(p.model, B.OPT_KSPLIT_REDUCE, 1)
+            assert (rows + 15) // 16 == 11 * 11            # as many row tiles in eleven sequences
+            wl = W.decode_workload(p.shape, 100, 11 * 16 - 5 - 100, 8, 1, 78, batch=11)
             run_prefill_case(p, wl.tokens, wl.resp_off, "QKV in split blocks")
     finally:
         p.close()
