@@ -388,6 +388,18 @@ def test_sizes_of_the_gpu_test_of_tall_blocks_take_them(rules):
     assert seen == {(w, p) for w in ("qkv", "gate/up", "resid") for p in (1231, 1241, 2031, 2041)}
 
 
+def test_sizes_of_the_gpu_test_of_packed_drafts_are_packed(rules):
+    from test_gpu_many_rows import DENSE
+    rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
+    for d, dh, f, batch, b, S, kernel, way in DENSE:
+        m, tpu = (batch * S * b + 15) // 16, (b + 15) // 16
+        assert rules.packed(m, batch * S * tpu), (b, S, batch)
+        for room in (32 << 20, min(96 << 20, max(32 << 20, m * 16 * d * 16))):          # of the fixed area, of the model's own scratch
+            assert _qkv_kernel(rules, m, 3 * d // 16, d // 32, room) == kernel, (d, b, S)
+        assert rules.attention_way(dh, d // dh, 110, 1, batch * S, S, tpu) == way, (d, b, S)
+    assert not rules.packed(5, 6)
+
+
 def test_plans_exchange_only_where_there_is_room_for_it(rules):
     rules.plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_int]
     split = lambda room, may: rules.plan(2, 16, 2, 128, 256, 384, room, may) == 1642
