@@ -151,12 +151,15 @@ int odb_block_step(odb_model *m, const odb_cache *c, const int32_t *drafts_dev,
                    int32_t *argmax_dev, uint8_t *unmask_dev, void *stream);
 
 /* Run-time switches of a model.
- *   ODB_OPT_KSPLIT_REDUCE (default 1): projections with few rows and a long K may run on the
- *     streaming kernel that splits K over four workgroups, which exchange their partial sums
- *     through device-scope stores and an arrival counter inside the one launch (the last
- *     workgroup to arrive adds them in slice order, so results do not depend on timing).
- *     0 routes those projections to the kernels that exchange nothing inside a launch (the
- *     plain streaming kernel, or the tile kernel with a separate reduction pass).
+ *   ODB_OPT_KSPLIT_REDUCE (default 1): workgroups of one launch may exchange partial sums, through
+ *     device-scope stores and counters.  Projections with few rows and a long K split K over four
+ *     workgroups of the streaming kernel, the last of which to arrive adds all sums in slice order and
+ *     none of which waits.  Beyond 128 rows the blocks of a last round of workgroups may be shared by
+ *     two each, the second of which waits inside the kernel for the sums of the first, a workgroup that
+ *     already runs and waits for nobody.  Results do not depend on timing.
+ *     0 routes these projections to kernels that exchange nothing inside a launch: the plain streaming
+ *     kernel, the tile kernel with a separate reduction pass, or, beyond 128 rows, blocks of another
+ *     shape.  Sums are then added in another order, in refreshes and steps alike.
  * Errors: ODB_E_INVALID_ARG for a NULL model, an unknown option or a value outside its range. */
 enum { ODB_OPT_KSPLIT_REDUCE = 0 };
 int odb_set_option(odb_model *m, int option, int value);
