@@ -237,6 +237,8 @@ int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackI
     const int fresh32 = ru(io.units.rpu_pad, 32);
     const Workspace ws = workspace(m, base, pl);
     unsigned *status = m.counters;
+    const double o_bytes = (double)cfg.n_layers * d * d * 2, kv_bytes = (double)cfg.n_layers * c.batch * c.length * d * 4;
+    const bool o_past_cache = !io.to_cache && weights_past_cache(kv_bytes, o_bytes);
     const NormIn ni = io.fused_norm ? norm_in(m, base, pl, mt) : NormIn{nullptr, 0, 0.f};
 
     for (int l = 0; l < cfg.n_layers; l++) {
@@ -302,7 +304,7 @@ int run_stack(Model &m, const Cache &c, char *base, const Plan &pl, const StackI
         NormOut no_mlp = io.fused_norm ? norm_out(m, base, pl, g_after_mlp, mt) : NormOut{};
         {
             ProfScope ps(m, ODB_K_GEMM_O, s);
-            launch_gemm_resid(ao, w.o, GemmShape{mt, d / 16, d / 32}, h, d, no_attn, ws, s);
+            launch_gemm_resid(ao, w.o, GemmShape{mt, d / 16, d / 32, o_past_cache}, h, d, no_attn, ws, s);
         }
         if (!io.fused_norm) {
             ProfScope ps(m, ODB_K_RMSNORM, s);

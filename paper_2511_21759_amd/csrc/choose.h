@@ -189,11 +189,16 @@ inline RowBlock resid_block(int m_tiles, int n_tiles, int k_tiles) {
     return RowBlock{0, 0};
 }
 
-// O of 65 to 128 rows in two blocks of rows, both of which read the weights: past the memory-side cache (256 MB) all the same where a layer's
-// take more than 16 MiB, which would push out the K/V that the next step reads.  us a layer at d 4096, 8 layers, 128 rows, O's weights past
-// the cache and through it: 1024 keys O 17.1 and 16.7, attention 9.8 and 12.4; 512 keys 17.3 and 16.7, 7.0 and 8.4.  With 32 layers neither
-// finds anything there, and the step takes the same either way; at d 3072 it makes no difference yet.
-inline bool weights_stream_once(int n_tiles, int k_tiles) { return n_tiles * (size_t)k_tiles > 16384; }
+// O of a step of 65 to 128 rows in two blocks of rows, both of which read the weights, through ordinary loads unless that costs the
+// attention more: where the K/V that a step reads fit the memory-side cache but not with O's weights beside them, the weights
+// are read past it.  Steps at d 4096 of 128 and 96 rows, weights past the cache against through it: 12 layers, 1024 keys (201 MB of
+// K/V, 403 of O) 0.986 and 0.992; 8 layers, 1024 keys 0.991, 0.997; 24 layers, 512 keys 0.991, 1.003; 4 layers, 2048 keys 0.983, 0.987; where K/V do not
+// fit, 32 layers, 512 keys (268 MB) 1.003, 1.012, 16 layers, 2048 keys 1.008, 1.008; where both fit, 4 layers, 512 keys 1.03.
+// At 8 layers and 1024 keys the attention takes 9.8 us a layer so, 12.4 with the weights in its way; O itself 17.1 instead of 16.7.
+inline bool weights_past_cache(double kv_bytes, double weight_bytes) {
+    const double cache = 250e6;            // (256 MiB; activations and partial sums pass through it too)
+    return kv_bytes <= cache && kv_bytes + weight_bytes > cache;
+}
 
 // O and down of up to 32 rows whose K is split over four workgroups: n-tiles of a block, or 0 where a workgroup has all of K (3 KiB a
 // k-tile for each of its rows and columns; the same line as for more rows above) or K cannot be split.  As many blocks as make one round:

@@ -359,7 +359,7 @@ void launch_gemm_resid(const u16 *a, const u16 *w, GemmShape sh, float *h, int l
         else launch_block<4>(a, w, sh, e, s);
     }
     else if (rows.mt) {
-        if (rows.mt == 4 && weights_stream_once(sh.N_tiles, sh.K_tiles)) launch_stream<4, 2, 4, true, true>(a, w, sh, none, e, s);
+        if (rows.mt == 4 && sh.past_cache) launch_stream<4, 2, 4, true, true>(a, w, sh, none, e, s);
         else if (rows.mt == 4) launch_stream<4, 2, 4, true, false>(a, w, sh, none, e, s);
         else if (rows.ng == 2) launch_stream<2, 2, 4, true, false>(a, w, sh, none, e, s);
         else launch_stream<2, 1, 4, true, false>(a, w, sh, none, e, s);

@@ -123,7 +123,8 @@ void launch_lm_finish_shared(const float *stats, int n_part, SharedMap sm, int m
                              int32_t *argmax, uint8_t *unmask, hipStream_t s);
 
 // ---- gemm.hip ---------------------------------------------------------------
-struct GemmShape { int M_tiles, N_tiles, K_tiles; };
+// past_cache: the weights should not stay in the memory-side cache (choose.h: weights_past_cache)
+struct GemmShape { int M_tiles, N_tiles, K_tiles; bool past_cache = false; };
 // Division by a run-time constant below 2^16 for dividends below 2^16: q = (x * mul) >> 32 with
 // mul = floor(2^32 / div) + 1 is exact there (the error term x * (mul * div - 2^32) stays below 2^32).
 struct FastDiv {
