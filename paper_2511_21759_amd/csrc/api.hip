@@ -797,8 +797,7 @@ int odb_model_status(odb_model *mh) {
     unsigned host = 0;
     HIP_TRY(hipMemcpy(&host, m.counters, sizeof(host), hipMemcpyDeviceToHost));
     if (host != 0) {
-        // bring flags, epoch and status back to a clean state
-        // back to a clean state (only the status word: the arrival counters are zero between launches anyway)
+        // back to a clean state (only the status word: the counters behind it are the launches' own)
         HIP_TRY(hipMemset(m.counters, 0, sizeof(unsigned)));
         if (host & kStatusSaturated)
             return fail(ODB_E_UNSUPPORTED, "an activation left the binary16 range (|x| > 65504, or not a number) and was "
