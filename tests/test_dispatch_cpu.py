@@ -397,6 +397,9 @@ def test_sizes_of_the_gpu_test_of_packed_drafts_are_packed(rules):
         for room in (32 << 20, min(96 << 20, max(32 << 20, m * 16 * d * 16))):          # of the fixed area, of the model's own scratch
             assert _qkv_kernel(rules, m, 3 * d // 16, d // 32, room) == kernel, (d, b, S)
         assert rules.attention_way(dh, d // dh, 110, 1, batch * S, S, tpu) == way, (d, b, S)
+    blocks = ["rows 21", "rows 22", "rows 23", "rows 24", "rows 43", "rows 44", "slab 3", "slab 6"]
+    rings = ["big %d" % p for p in (821, 831, 841, 1231, 1241, 1621, 1631, 1641, 1642, 2031, 2041)]
+    assert {case[6] for case in DENSE} == {"few", "stream", "tile", *blocks, *rings}
     assert not rules.packed(5, 6)
 
 

@@ -377,11 +377,15 @@ def test_split_last_round_repeats_and_agrees_with_whole_blocks(d, f, rows, which
 # d, head_dim, d_ff, batch, b, S, QKV's kernel and the attention's way behind 110 cached positions (test_dispatch_cpu.py: that these sizes take them)
 DENSE = [
     (1024, 128, 512, 1, 7, 4, "few", 1),           # two row tiles; units that begin inside a tile, keys of two drafts in a lane's four rows
+    (1536, 128, 512, 1, 7, 4, "few", 1),           # two n-tiles a workgroup
+    (2816, 128, 512, 1, 7, 4, "few", 1),           # three
     (256, 64, 512, 3, 5, 4, "rows 21", 1),         # heads of 64, four row tiles
     (1024, 128, 512, 1, 1, 40, "rows 22", 1),      # drafts of one row
     (1024, 128, 512, 1, 33, 4, "rows 24", 1),      # three tiles and two key tiles a draft: nine row tiles
     (1024, 128, 512, 1, 11, 9, "rows 23", 1),      # nine padded tiles, seven packed
     (2304, 128, 512, 1, 5, 13, "rows 44", 1),
+    (1536, 128, 512, 1, 20, 6, "rows 43", 1),
+    (2816, 128, 512, 1, 9, 6, "stream", 1),        # four row tiles in the streaming kernel of 64 rows
     (2816, 128, 512, 1, 5, 13, "stream", 1),       # five row tiles in the streaming kernel of 96 rows
     (2816, 128, 512, 1, 24, 5, "slab 3", 1),       # eight row tiles through LDS
     (2816, 128, 512, 1, 20, 8, "slab 6", 2),       # ten, two row blocks
@@ -391,10 +395,14 @@ DENSE = [
     (3584, 128, 512, 1, 52, 5, "tile", 3),         # the tile kernel and its merge pass; the many-row attention, four tiles a draft
     (2048, 128, 512, 1, 51, 8, "big 821", 2),      # 128-row blocks: 26 row tiles of 32
     (512, 128, 512, 1, 50, 41, "big 831", 3),
+    (1280, 128, 512, 1, 7, 183, "big 841", 1),
     (768, 128, 512, 1, 50, 41, "big 1621", 3),     # 256-row blocks
+    (768, 128, 512, 1, 53, 58, "big 1631", 3),
     (1792, 128, 512, 1, 50, 41, "big 1641", 3),
-    (2048, 128, 512, 1, 20, 80, "big 1241", 3),    # 192-row blocks, 100 row tiles
+    (512, 128, 512, 1, 25, 164, "big 1231", 3),    # 192-row blocks, 257 row tiles
+    (2048, 128, 512, 1, 20, 80, "big 1241", 3),
     (1536, 128, 512, 2, 39, 33, "big 2031", 2),    # 320-row blocks
+    (1280, 128, 512, 2, 25, 82, "big 2041", 3),
     (3840, 128, 512, 1, 17, 113, "big 1642", 3),   # the last round split
 ]
 
