@@ -524,6 +524,16 @@ def test_wide_weights_do_not_displace_the_cache(rules, layers, keys, ratios):
         assert (ratio if past else 1.0) <= 1.006 * min(1.0, ratio)
 
 
+def test_sizes_of_the_gpu_test_of_weights_past_the_cache_take_that_path(rules):
+    from test_gpu_many_rows import PAST_CACHE
+    rules.past_cache.argtypes = [ctypes.c_double] * 2
+    d, layers, keys, tiles = PAST_CACHE
+    assert rules.resid_rows(tiles, d // 16, d // 32) == 42
+    kv, weights = 2 * layers * keys * d * 4, layers * d * d * 2
+    assert rules.past_cache(2 * kv, weights) and not rules.past_cache(kv, weights)
+    assert not rules.packed(tiles, tiles)
+
+
 @pytest.mark.parametrize("dense,padded,pays", [
     (2, 4, 1), (1, 4, 1), (5, 8, 1), (6, 8, 1), (8, 10, 1), (10, 12, 1), (13, 16, 1), (14, 32, 1), (80, 96, 1),
     (2, 2, 0), (1, 2, 0), (3, 4, 0), (7, 8, 0), (9, 10, 0), (120, 128, 0),

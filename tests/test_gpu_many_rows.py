@@ -139,6 +139,36 @@ def test_row_blocks_by_width(d, f, steps, refresh):
         p.close()
 
 
+# d, layers, cached positions, row tiles of a step of four sequences whose O reads its weights past the memory-side cache (test_dispatch_cpu.py)
+PAST_CACHE = (2304, 3, 2090, 8)
+
+
+@pytest.mark.parametrize("b", [32, 29])
+def test_step_whose_weights_are_read_past_the_cache(b):
+    """O in blocks of 64 rows with non-temporal weight loads, where the K/V of four sequences fill the memory-side cache, against the same
+    drafts as two sequences of two each, whose weights go through it: both are within the bar of the oracle, so twice that apart."""
+    d, layers, L, _ = PAST_CACHE
+    shape = dict(_width(d, 256, layers), vocab=512, mask_id=511)
+    wl = W.decode_workload(shape, L - 60, 60, b, 2, 780 + b, batch=2)
+    model = B.odb_model_create(shape)
+    B.odb_model_init_random(model, W.WEIGHT_SEED, W.WEIGHT_STD)
+    out = []
+    try:
+        for tokens, drafts in ((np.repeat(wl.tokens, 2, axis=0), wl.drafts.reshape(4, 1, b)), (wl.tokens, wl.drafts)):
+            cache = B.odb_cache_create(model, len(tokens), L)
+            B.odb_prefill(model, cache, torch.from_numpy(np.ascontiguousarray(tokens)).cuda(), wl.resp_off)
+            dg = torch.from_numpy(np.ascontiguousarray(drafts)).cuda()
+            z, again = (B.odb_block_step_logits(model, cache, dg, wl.block_off, 512).cpu().numpy() for _ in range(2))
+            assert np.array_equal(z, again)
+            out.append(z.reshape(4, b, 512))
+            B.odb_cache_destroy(cache)
+        B.odb_model_status(model)
+        for i in range(4):
+            assert rel_err(out[0][i], out[1][i]) <= 2 * LOGIT_TOL
+    finally:
+        B.odb_model_destroy(model)
+
+
 @pytest.mark.parametrize("rows", [(9, 16), (3, 64), (13, 16), (8, 32)])
 def test_narrow_step_beyond_128_rows(mid, rows):
     """129 to 256 rows at d = 1024: row blocks of 64 in the streaming kernels, 64-column sums from the K-split kernel."""
