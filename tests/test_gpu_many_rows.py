@@ -62,10 +62,16 @@ def _width(d, f, layers=1):
     (2048, 4096, [(2, 16)]),                                       # two n-tiles, a ring of four
     (2304, 2816, [(2, 16)]),                                       # K that four slices do not divide: all of it, a ring of one (O: of three)
     (2304, 4096, [(2, 16)]),                                       # four n-tiles
+    (1024, 10240, [(2, 9)]),                                       # and the other rings: one n-tile, two stages
+    (1280, 3072, [(2, 16)]),                                       # two n-tiles, three
+    (1280, 5120, [(1, 16)]),                                       # and one
+    (2304, 3072, [(1, 32)]),                                       # four n-tiles, three
+    (2304, 5120, [(2, 16)]),                                       # and one
     (1536, 512, [(7, 16), (4, 32)]),                               # QKV from 97 rows on: blocks of 64 rows and three n-tiles
     (2560, 512, [(7, 16), (4, 32)]),                               # and through LDS
     (2816, 6400, [(7, 16), (4, 32), (9, 16), (16, 16)]),           # all rows through LDS; from 9 row tiles two row blocks for QKV
-    (4352, 512, [(7, 16), (4, 32)]),                               # QKV of 816 n-tiles: six per workgroup from 97 rows on
+    (4352, 512, [(7, 16), (4, 32), (1, 16), (2, 16), (4, 7)]),     # QKV of 816 n-tiles: six per workgroup from 97 rows on; O of up to 32 rows,
+                                                                   # packed ones too, on the tile kernel
 ])
 def test_step_by_width(d, f, rows):
     p = Pair(_width(d, f))
