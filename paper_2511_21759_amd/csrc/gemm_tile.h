@@ -1,5 +1,6 @@
 // binary16 MFMA GEMM  C[M,N] = A[M,K] * W[N,K]^T  where neither the streaming nor the
-// LDS-ring kernels take the shape (from 33 rows on).  Same operand layouts and epilogues as gemm_core.h.
+// LDS-ring kernels take the shape (from 33 rows on; O and down of fewer rows where choose.h: few_rows_tile says so).  Same operand
+// layouts and epilogues as gemm_core.h.
 //
 // A workgroup computes a 128-row block x (8*NGW n-tiles) x one slice of K.  Its eight waves split
 // the n-tiles; the 128 x 32 slab of A that a k-step needs is shared through LDS: every wave fetches
