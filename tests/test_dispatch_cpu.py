@@ -527,11 +527,11 @@ def test_wide_weights_do_not_displace_the_cache(rules, layers, keys, ratios):
 def test_sizes_of_the_gpu_test_of_weights_past_the_cache_take_that_path(rules):
     from test_gpu_many_rows import PAST_CACHE
     rules.past_cache.argtypes = [ctypes.c_double] * 2
-    d, layers, keys, tiles = PAST_CACHE
-    assert rules.resid_rows(tiles, d // 16, d // 32) == 42
-    kv, weights = 2 * layers * keys * d * 4, layers * d * d * 2
-    assert rules.past_cache(2 * kv, weights) and not rules.past_cache(kv, weights)
-    assert not rules.packed(tiles, tiles)
+    for d, layers, keys in PAST_CACHE:
+        assert rules.resid_rows(8, d // 16, d // 32) == 42
+        kv, weights = 2 * layers * keys * d * 4, layers * d * d * 2
+        assert rules.past_cache(2 * kv, weights) and not rules.past_cache(kv, weights)
+    assert not rules.packed(8, 8)
 
 
 @pytest.mark.parametrize("dense,padded,pays", [

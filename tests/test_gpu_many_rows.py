@@ -63,6 +63,8 @@ def _width(d, f, layers=1):
     (2304, 2816, [(2, 16)]),                                       # K that four slices do not divide: all of it, a ring of one (O: of three)
     (2304, 4096, [(2, 16)]),                                       # four n-tiles
     (1024, 10240, [(2, 9)]),                                       # and the other rings: one n-tile, two stages
+    (1280, 10240, [(2, 16)]),                                      # two n-tiles, two
+    (2304, 10240, [(1, 16)]),                                      # four n-tiles, two
     (1280, 3072, [(2, 16)]),                                       # two n-tiles, three
     (1280, 5120, [(1, 16)]),                                       # and one
     (2304, 3072, [(1, 32)]),                                       # four n-tiles, three
@@ -108,9 +110,11 @@ def test_step_attention_by_size(heads, b, S):
     (32, 128, 16, 5),      # 160: one
     (8, 64, 16, 8),        # heads of 64 channels, four workgroups
     (8, 64, 16, 9),        # and two
+    (16, 64, 32, 32),      # many rows of heads of 64: 128 of them a workgroup
+    (16, 64, 32, 128),     # and 256
 ])
 def test_step_attention_channels_dealt_out(heads, dh, b, S):
-    """One-tile attention with the output channels of an item on one, two and four workgroups."""
+    """One-tile attention with the output channels of an item on one, two and four workgroups; many rows of heads of 64."""
     p = Pair(dict(_width(heads * dh, 512), n_heads=heads, head_dim=dh, vocab=512, mask_id=511))
     try:
         wl = W.decode_workload(p.shape, 150, 107, b, S, 920 + S)
@@ -129,6 +133,20 @@ def test_step_attention_channels_dealt_out(heads, dh, b, S):
     (2048, 512, [(3, 16)], [(1, 333), (1, 500)]),             # two rounds of blocks of 64 x 64
     (4096, 512, [(5, 16), (9, 16)], []),                      # O in blocks of 64 x 32 and 64 x 64
     (4096, 4096, [(1, 32), (7, 16)], []),                     # O of 32 rows with K split; gate/up in groups of four
+    (2560, 4096, [(3, 16)], []),                              # gate/up of 33 to 128 rows beyond the small blocks: groups of two,
+    (2816, 4096, [(4, 16)], []),                              # of two with a ring of one,
+    (1792, 6144, [(4, 16)], []),                              # of three,
+    (1280, 6144, [(7, 16)], []),                              # of three and eight row tiles,
+    (1536, 8192, [(4, 16), (5, 16)], []),                     # of four; down with K split, four n-tiles and a ring of two
+    (1280, 8192, [(3, 16)], []),                              # of four with a ring of one
+    (1536, 7168, [(5, 16)], []),                              # down with K split, four n-tiles: a ring of one
+    (1536, 9216, [(5, 16)], []),                              # and of three
+    (1280, 3072, [(3, 16)], []),                              # two n-tiles and a ring of three
+    (256, 5120, [(3, 16), (9, 16)], []),                      # one n-tile and a ring of one; sums over 64 columns and a ring of one
+    (256, 4096, [(9, 16)], []),                               # and of two
+    (256, 8448, [], [(1, 268)]),                              # gate/up in 128 x 256 blocks
+    (2560, 256, [], [(1, 268)]),                              # gate/up on the tile kernel with a merge pass
+    (3584, 512, [(17, 16)], []),                              # QKV so
 ])
 def test_row_blocks_by_width(d, f, steps, refresh):
     """QKV, gate/up, O and down in small blocks of rows (33 rows and more), the last block and the drafts ragged."""
@@ -145,15 +163,15 @@ def test_row_blocks_by_width(d, f, steps, refresh):
         p.close()
 
 
-# d, layers, cached positions, row tiles of a step of four sequences whose O reads its weights past the memory-side cache (test_dispatch_cpu.py)
-PAST_CACHE = (2304, 3, 2090, 8)
+# d, layers, cached positions of steps of four sequences in eight row tiles whose O reads its weights past the memory-side cache
+# (test_dispatch_cpu.py); rings of one and of four stages
+PAST_CACHE = [(2304, 3, 2090), (3072, 3, 1500)]
 
 
-@pytest.mark.parametrize("b", [32, 29])
-def test_step_whose_weights_are_read_past_the_cache(b):
+@pytest.mark.parametrize("b,d,layers,L", [(32, *PAST_CACHE[0]), (29, *PAST_CACHE[1])])
+def test_step_whose_weights_are_read_past_the_cache(b, d, layers, L):
     """O in blocks of 64 rows with non-temporal weight loads, where the K/V of four sequences fill the memory-side cache, against the same
     drafts as two sequences of two each, whose weights go through it: both are within the bar of the oracle, so twice that apart."""
-    d, layers, L, _ = PAST_CACHE
     shape = dict(_width(d, 256, layers), vocab=512, mask_id=511)
     wl = W.decode_workload(shape, L - 60, 60, b, 2, 780 + b, batch=2)
     model = B.odb_model_create(shape)
@@ -415,11 +433,15 @@ DENSE = [
     (1024, 128, 512, 1, 7, 4, "few", 1),           # two row tiles; units that begin inside a tile, keys of two drafts in a lane's four rows
     (1536, 128, 512, 1, 7, 4, "few", 1),           # two n-tiles a workgroup
     (2816, 128, 512, 1, 7, 4, "few", 1),           # three
+    (1792, 128, 512, 1, 7, 4, "few", 1),           # two, a ring of one
     (256, 64, 512, 3, 5, 4, "rows 21", 1),         # heads of 64, four row tiles
     (1024, 128, 512, 1, 1, 40, "rows 22", 1),      # drafts of one row
     (1024, 128, 512, 1, 33, 4, "rows 24", 1),      # three tiles and two key tiles a draft: nine row tiles
     (1024, 128, 512, 1, 11, 9, "rows 23", 1),      # nine padded tiles, seven packed
+    (1280, 128, 512, 1, 12, 8, "rows 23", 1),      # a ring of one
     (2304, 128, 512, 1, 5, 13, "rows 44", 1),
+    (2560, 128, 512, 1, 20, 6, "rows 44", 1),
+    (1792, 128, 512, 1, 20, 6, "rows 43", 1),
     (1536, 128, 512, 1, 20, 6, "rows 43", 1),
     (2816, 128, 512, 1, 9, 6, "stream", 1),        # four row tiles in the streaming kernel of 64 rows
     (2816, 128, 512, 1, 5, 13, "stream", 1),       # five row tiles in the streaming kernel of 96 rows
